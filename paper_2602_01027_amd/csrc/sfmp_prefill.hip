@@ -20,6 +20,8 @@
 //     16-byte units XOR-swizzled by row%16: conflict-free operand reads whose addresses differ by
 //     immediates).  A step is software-pipelined over its four k-steps and into the next step; one
 //     barrier per step.  The product leaves through LDS in whole 256-byte row segments.
+//     Launches with few workgroups take a 64-row form with two K groups per workgroup and the packed words in LDS
+//     rings (RING below).
 //  3. scatter_cols_kernel (only with a row permutation): the GEMM writes the product in reordered
 //     row order into the workspace, then Y[m, row_perm[i]] = Yt[m, i] is done one row through LDS.
 //     Scattering 2-byte results straight from the GEMM epilogue leaves half-written cache lines all
@@ -119,34 +121,40 @@ __global__ __launch_bounds__(256) void scatter_cols_kernel(const _Float16* __res
 
 // Y[m, row_perm[i]] (or Y[m, i]) = fp16( sum over the K ranges, in range order, of partial[ks][m][i] ): the second
 // half of a split-K product, one row through LDS per workgroup.
+template <int KS>  // K ranges: ksplit rounded up to 2, 4 or 8
 __global__ __launch_bounds__(1024) void reduce_split_kernel(const float* __restrict__ partial, int ksplit, int M,
                                                             const int32_t* __restrict__ row_perm,
                                                             _Float16* __restrict__ Y, int N) {
-  // (1024 threads and all loads of a thread's column group issued before the sum: with few rows there are few
-  // workgroups, and a chain of dependent round trips per thread made this pass longer than the GEMM)
+  // (1024 threads, and eight loads of a thread issued before the sums - the ranges of one column group, or of two or
+  // four: with few rows there are few workgroups, and a chain of dependent round trips per thread made this pass
+  // longer than the GEMM)
   extern __shared__ __align__(16) unsigned char lds_raw[];
   _Float16* row = reinterpret_cast<_Float16*>(lds_raw);
   const int64_t m = blockIdx.x;
-  for (int i = threadIdx.x; i < N / 4; i += 1024) {
-    floatx4 v[8];
+  constexpr int U = 8 / KS;
+  for (int i0 = threadIdx.x; i0 < N / 4; i0 += 1024 * U) {
+    floatx4 v[U][KS];
+    int4 c[U];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      v[ks] = ks < ksplit ? *reinterpret_cast<const floatx4*>(partial + ((int64_t)ks * M + m) * N + 4 * i)
-                          : floatx4{0.f, 0.f, 0.f, 0.f};
-    floatx4 s = v[0];
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + 1024 * u, N / 4 - 1);
+      c[u] = row_perm ? reinterpret_cast<const int4*>(row_perm)[i] : int4{4 * i, 4 * i + 1, 4 * i + 2, 4 * i + 3};
 #pragma unroll
-    for (int ks = 1; ks < 8; ++ks) s += v[ks];  // range order; the ranges past ksplit add zeros
-    if (row_perm) {
-      const int4 c = reinterpret_cast<const int4*>(row_perm)[i];
-      row[c.x] = (_Float16)s[0];
-      row[c.y] = (_Float16)s[1];
-      row[c.z] = (_Float16)s[2];
-      row[c.w] = (_Float16)s[3];
-    } else {
-      row[4 * i] = (_Float16)s[0];
-      row[4 * i + 1] = (_Float16)s[1];
-      row[4 * i + 2] = (_Float16)s[2];
-      row[4 * i + 3] = (_Float16)s[3];
+      for (int ks = 0; ks < KS; ++ks)
+        v[u][ks] = ks < ksplit ? *reinterpret_cast<const floatx4*>(partial + ((int64_t)ks * M + m) * N + 4 * i)
+                               : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      floatx4 s = v[u][0];
+#pragma unroll
+      for (int ks = 1; ks < KS; ++ks) s += v[u][ks];  // range order; the ranges past ksplit add zeros
+      if (i0 + 1024 * u < N / 4) {
+        row[c[u].x] = (_Float16)s[0];
+        row[c[u].y] = (_Float16)s[1];
+        row[c[u].z] = (_Float16)s[2];
+        row[c[u].w] = (_Float16)s[3];
+      }
     }
   }
   __syncthreads();
@@ -174,6 +182,7 @@ struct PrefillParams {
 };
 
 constexpr int kPrefillMaxTiles = 224 * 2;  // K <= 57344
+constexpr int kRingSlots = 3;
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -183,9 +192,39 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 // loads itself (they complete in issue order with the ordinary loads around them).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"  // m0 is named as clobbered on purpose
-__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t byte_offset, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(byte_offset), "s"(lds_base)
+__device__ __forceinline__ void load_to_lds_16(u32x4 rsrc, uint32_t soffset, uint32_t byte_offset, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %0, %2 offen lds" ::"s"(rsrc), "v"(byte_offset), "s"(soffset),
+               "s"(lds_base)
                : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+// The three copies of one wavefront's part of a tile in one statement: 32 parameter dwords (64 at group length 64: lanes
+// 32-63 bring the second pair) from a full address per lane to LDS byte lds_par, then the two slabs, 16 bytes per lane
+// (lanes 0-31 always, of lanes 32-63 those whose bit is set in hi_lanes), to lds_a and lds_b.  Only the upper half of
+// EXEC changes, and it is put back.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void lds_copy_tile(uint64_t par_vaddr, uint64_t src_a, uint64_t src_b, uint32_t lane_off,
+                                              uint32_t lds_par, uint32_t lds_a, uint32_t lds_b, uint32_t hi_lanes,
+                                              uint32_t par_hi_lanes) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 m0, %4\n\t"
+      "s_mov_b32 %0, exec_hi\n\t"
+      "s_mov_b32 exec_hi, %9\n\t"
+      "global_load_lds_dword %1, off\n\t"
+      "s_mov_b32 m0, %5\n\t"
+      "s_mov_b32 exec_hi, %7\n\t"
+      "global_load_lds_dwordx4 %8, %2\n\t"
+      "s_mov_b32 m0, %6\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %8, %3\n\t"
+      "s_mov_b32 exec_hi, %0"
+      : "=&s"(saved)
+      : "v"(par_vaddr), "s"(src_a), "s"(src_b), "s"(lds_par), "s"(lds_a), "s"(lds_b), "s"(hi_lanes), "v"(lane_off),
+        "s"(par_hi_lanes)
+      : "memory", "m0");
 }
 #pragma clang diagnostic pop
 
@@ -237,17 +276,41 @@ struct PrefillShape {
 };
 
 // G64: group length 64 - a tile column has two (scale, zero) pairs per row, one for its k-steps 0-1 and one for 2-3.
-template <int BM, int WM, int WN, int IL = 2, bool G64 = false>
-__global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) / 4)) void prefill_kernel(const PrefillParams p) {
+//
+// RING (BM = 64): for launches that give a CU one workgroup.  With four wavefronts, one per SIMD, a step of the plain
+// form is bound by what one wavefront cannot overlap with itself: the packed words are requested one step ahead, which
+// covers 1.0 of the 2.1 thousand cycles they take to arrive (a build without the activation copies, the operand reads
+// and the dequantisation still took 0.87 of 0.95 us per 128-row tile), and its 300 instructions per tile issue one after
+// the other.  Here a workgroup is two K groups of four wavefronts, each with half of the workgroup's tiles and its own
+// buffers, so that a SIMD has two wavefronts without a second block of fp32 partial sums going through memory (the
+// groups add their sums in LDS); the packed words arrive in a ring of three tiles per wavefront by direct copies, and
+// three activation blocks are in LDS or on their way, copied in four parts spread over a step.  All waits are counted by
+// hand (the loop has no load to a register), and the addresses of a tile's copies are computed once, when the tile
+// sequence is laid out.  Per 64-row step of both groups 2500 cycles.  512 x 4096 x 4096 47 -> 34 us, 300 x 2048 x 2048
+// 26 -> 19, 128 x 4096 x 14336 43 -> 33, 64 x 4096 x 14336 29 -> 24.5 (whole calls, same machine).
+template <int BM, bool RING, bool G64 = false>
+__global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const PrefillParams p) {
+  static_assert(!RING || BM == 64, "the buffers of two K groups fit in LDS with 64 rows");
+  constexpr int WM = 1, WN = 4, KG = RING ? 2 : 1;
   using S = PrefillShape<BM, WM, WN>;
+  constexpr int kAllThreads = S::kThreads * KG;
   constexpr int MI = S::kMI, NS = S::kNS;
   constexpr uint32_t kBufBytes = BM * 256;
-  __shared__ __align__(16) unsigned char Xs[2 * kBufBytes];  // activation block, double-buffered
-  __shared__ int32_t seq[kPrefillMaxTiles];                  // (slot << 9) | tc of this tile row, width-sorted
+  constexpr int NB = RING ? 3 : 2;  // activation buffers
+  __shared__ __align__(16) unsigned char Xs_all[KG * NB * kBufBytes];  // activation blocks, per K group
+  // (RING) packed weights: per wavefront a ring of slots [16 scale + 16 zero dwords (twice at group length 64) | 2 slabs]
+  constexpr int kWPar = G64 ? 256 : 128, kWSlot = kWPar + 2048;
+  __shared__ __align__(16) unsigned char Ws[RING ? KG * WM * WN * kRingSlots * kWSlot : 16];
+  // the tiles of this tile row, width-sorted: (slot << 9) | tc, or (RING) everything their copies need: address of the
+  // tile, byte offset of its parameters, (tc << 15) | width
+  __shared__ int32_t seq[RING ? 1 : kPrefillMaxTiles];
+  __shared__ uint4 tiles[RING ? kPrefillMaxTiles : 1];
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x % S::kThreads;  // within the K group
+  const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / S::kThreads)) : 0;
   const int lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  unsigned char* const Xs = Xs_all + kg * (NB * kBufBytes);
   // Work items (tile row, M block) are numbered with the M blocks innermost, and block b (which runs on XCD
   // b % 8) takes item b.  With a multiple of 8 M blocks an XCD always sees the same M blocks (their activation
   // rows stay in its L2), and in any case the blocks that run at the same time need the same weight tiles, so
@@ -257,9 +320,13 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
   const int mt = ((int)blockIdx.x / p.ksplit) % p.n_mtiles;
   const int tr = ((int)blockIdx.x / p.ksplit) / p.n_mtiles;
   const int m0 = mt * BM;
-  // this workgroup's share of the width-sorted tile sequence: positions [e_first, e_end)
-  const int e_first = (int)((int64_t)ks * p.ntc / p.ksplit), e_end = (int)((int64_t)(ks + 1) * p.ntc / p.ksplit);
+  // this K group's share of the width-sorted tile sequence: positions [e_first, e_end), at least one (the shares of the
+  // groups differ by at most one tile; longest = the largest of this workgroup)
+  const int range = ks * KG + kg, ranges = p.ksplit * KG;
+  const int e_first = (int)((uint32_t)(range * p.ntc) / (uint32_t)ranges);
+  const int e_end = (int)((uint32_t)((range + 1) * p.ntc) / (uint32_t)ranges);
   const int e_last = e_end - 1;
+  const int longest = KG > 1 ? (p.ntc + ranges - 1) / ranges : 0;
 
   // The K reduction runs over the tiles of this tile row sorted by width (first all 2-bit tiles, then
   // the 3-bit, then the 4-bit ones; the order of a sum is free): three loops, each with a straight-line
@@ -272,7 +339,7 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
   const int end2 = row_ptr[tr + 1] - first2;
   const int end3 = end2 + row_ptr[(p.ntr + 1) + tr + 1] - first3;
   const int32_t total2 = p.index[0], total3 = p.index[1];
-  for (int e = tid; e < p.ntc; e += S::kThreads) {
+  for (int e = threadIdx.x; e < p.ntc; e += kAllThreads) {
     // Position in its stream, and position of that stream's column list.  Each tile row walks its runs
     // from a slightly different starting point: the workgroups of one XCD all read the same activation rows,
     // and 256-byte pieces at the same tile column of rows K*2 bytes apart sit in the same L2 channel, so
@@ -287,7 +354,15 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
     const int32_t i = (e - lo + (tr * 5) % 8) % n;
     const int32_t slot = (e < end2 ? first2 : e < end3 ? first3 : first4) + i;
     const int32_t cols = e < end2 ? 0 : e < end3 ? total2 : total2 + total3;
-    seq[e] = (slot << 9) | col_idx[cols + slot];
+    const int32_t tc = col_idx[cols + slot];
+    if constexpr (RING) {
+      const uint32_t bw = e < end2 ? 2 : e < end3 ? 3 : 4;
+      const uint64_t src = (uint64_t)(bw == 2 ? p.s2 : bw == 3 ? p.s3 : p.s4) + (uint64_t)(uint32_t)slot * (2048 * bw);
+      const uint32_t par = (uint32_t)(G64 ? 2 * tc : tc >> p.gshift) * (uint32_t)(2 * p.N);
+      tiles[e] = uint4{(uint32_t)src, (uint32_t)(src >> 32), par, ((uint32_t)tc << 15) | bw};
+    } else {
+      seq[e] = (slot << 9) | tc;
+    }
   }
   __syncthreads();
 
@@ -316,16 +391,19 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
   // block (mt, tc) of the staged activations starts at (mt * ntc + tc) * 16384 elements; rows past M of the last
   // row block are never written and feed only output rows that are never stored
   const _Float16* xbase = p.Xp + (int64_t)(m0 / kTile) * p.ntc * (kTile * kTile) + (m0 % kTile) * kTile;
-  constexpr int xstep = kTile * kTile;  // elements between consecutive tile columns
+  const uint64_t xb64 = (uint64_t)xbase;
+  const u32x4 xrsrc = {(uint32_t)xb64, (uint32_t)(xb64 >> 32), (uint32_t)p.ntc * (uint32_t)(kTile * kTile * 2), 0x00020000u};
   const uint32_t xs_base = (uint32_t)(uintptr_t)(lptr_t)Xs;
+  // copies [first, last) of the block of tile position e into buffer `buf`
+  auto issue_x_part = [&](uint32_t soff, int buf, int first, int last) __attribute__((always_inline)) {
+    const uint32_t dst = xs_base + (uint32_t)buf * kBufBytes + wave * 1024;
+#pragma unroll
+    for (int i = first; i < last; ++i) load_to_lds_16(xrsrc, soff, xoff[i], dst + i * (S::kRowsPerPass * 256));
+  };
   // block of tile position e into the buffer that block `like` uses (like = e mod 2, except for the idle
   // loads past the end)
   auto issue_x = [&](int e, int like) __attribute__((always_inline)) {
-    const int tc = __builtin_amdgcn_readfirstlane(seq[e]) & 511;
-    const uint32_t dst = xs_base + (like & 1) * kBufBytes + wave * 1024;
-    const _Float16* src = xbase + (int64_t)tc * xstep;
-#pragma unroll
-    for (int i = 0; i < S::kPasses; ++i) load_to_lds_16(src, xoff[i], dst + i * (S::kRowsPerPass * 256));
+    issue_x_part((uint32_t)(__builtin_amdgcn_readfirstlane(seq[e]) & 511) << 15, like & 1, 0, S::kPasses);
   };
   // operand read addresses: row 16*(MI*wm + i) + i16, unit 4*kappa + kb -> byte offset aoff[kappa] + 4096*i
   uint32_t aoff[4];
@@ -391,6 +469,20 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
     issue_sz(d & 511, rsz);
   };
 
+  // (RING) tile of position e into ring slot `slot`: three copies, whatever the width
+  const uint32_t ws_base = (uint32_t)(uintptr_t)(lptr_t)Ws + (uint32_t)((kg * WM * WN + wave) * kRingSlots * kWSlot);
+  const unsigned char* ws = Ws + (kg * WM * WN + wave) * kRingSlots * kWSlot;
+  const uint64_t par_vbase = ((lane & 16) == 0 ? (uint64_t)p.scales : (uint64_t)p.zeros) +
+                             (uint64_t)(2 * (tr * 128 + 8 * (lane & 15) + NS * wn)) +
+                             (G64 && lane >= 32 ? (uint64_t)p.N * 2 : (uint64_t)0);
+  const uint32_t lane16 = lane * 16;
+  auto issue_w_ring = [&](const uint4& d, int slot) __attribute__((always_inline)) {
+    const uint32_t bw = d.w & 7;
+    const uint64_t src = (((uint64_t)d.y << 32) | d.x) + (uint32_t)(NS * wn) * (256 * bw);
+    const uint32_t hi = bw == 2 ? 0u : bw == 3 ? 0xFFFFu : 0xFFFFFFFFu;
+    const uint32_t lds = ws_base + slot * kWSlot;
+    lds_copy_tile(par_vbase + d.z, src, src + 256 * bw, lane16, lds, lds + kWPar, lds + kWPar + 1024, hi, G64 ? ~0u : 0u);
+  };
   u32x4 fw[NS];  // landing registers of the next tile's packed words
 #pragma unroll
   for (int q = 0; q < NS; ++q) fw[q] = u32x4{0u, 0u, 0u, 0u};
@@ -408,8 +500,33 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
   half2_ s2[NG][NS], z2[NG][NS];
   half8 a0[MI], a1[MI], b0[NS], b1[NS];
 
-  auto read_a = [&](int e, auto ktag, half8(&a)[MI]) __attribute__((always_inline)) {
-    const unsigned char* base = Xs + (e & 1) * kBufBytes + aoff[decltype(ktag)::value];
+  // (RING) words and parameters of the tile in ring slot `slot`, from LDS into the landing registers; the width known at
+  // compile time, or (the tile after the last one of a run) not
+  auto read_w_ring = [&](auto in_run, auto btag, int e, int slot) __attribute__((always_inline)) {
+    constexpr int B = decltype(btag)::value;
+    const unsigned char* base = ws + slot * kWSlot;
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      if constexpr (decltype(in_run)::value) {
+        const uint32_t* s = reinterpret_cast<const uint32_t*>(base + kWPar + q * 1024 + lane * (4 * B));
+        if constexpr (B == 4)
+          fw[q] = *reinterpret_cast<const u32x4*>(s);
+        else
+          fw[q] = u32x4{s[0], s[1], s[B - 1], 0u};
+      } else {
+        const int bw = e < end2 ? 2 : e < end3 ? 3 : 4;
+        const uint32_t* s = reinterpret_cast<const uint32_t*>(base + kWPar + q * 1024 + lane * (4 * bw));
+        fw[q] = u32x4{s[0], s[1], s[min(2, bw - 1)], s[bw - 1]};
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      fsz.s[g][0] = *reinterpret_cast<const uint32_t*>(base + g * 128 + i16 * 4);
+      fsz.z[g][0] = *reinterpret_cast<const uint32_t*>(base + g * 128 + 64 + i16 * 4);
+    }
+  };
+  auto read_a = [&](int buf, auto ktag, half8(&a)[MI]) __attribute__((always_inline)) {
+    const unsigned char* base = Xs + buf * kBufBytes + aoff[decltype(ktag)::value];
 #pragma unroll
     for (int i = 0; i < MI; ++i) a[i] = *reinterpret_cast<const half8*>(base + i * 4096);
   };
@@ -436,20 +553,18 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
       for (int j = 0; j < NS; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i], b[j], acc[i][j], 0, 0, 0);
   };
   auto interleave = [&]() __attribute__((always_inline)) {
-    if constexpr (IL > 0) {
 #pragma unroll
-      for (int g = 0; g < MI * NS; ++g) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // DS read
-        __builtin_amdgcn_sched_group_barrier(0x002, IL, 0);  // VALU
-      }
+    for (int g = 0; g < MI * NS; ++g) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
     }
   };
   // Synchronisation point.  Loads complete in issue order and X(e+1) was issued before W(e+1): the wait
   // the compiler puts in front of the moves out of the landing registers also covers the LDS-DMA loads of
   // block e+1.  No operand read may still be in the LDS queue when the barrier opens this step's buffer
   // for overwriting.
-  auto sync_and_issue = [&](int e, auto in_run, auto btag) __attribute__((always_inline)) {
+  auto take_w = [&]() __attribute__((always_inline)) {
     SZ rsz;
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
@@ -476,12 +591,16 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
         zv.u = rsz.z[g][j / 2];
         _Float16 sh = sv.h[j % 2], zh = zv.h[j % 2];
         if (p.bf16) {  // bfloat16 = top half of a float; the dequantisation runs in fp16
+          if constexpr (RING) asm volatile("; bfloat16 parameters");  // (a branch, not both and a choice)
           sh = (_Float16)__uint_as_float((j % 2 ? sv.u >> 16 : sv.u & 0xFFFFu) << 16);
           zh = (_Float16)__uint_as_float((j % 2 ? zv.u >> 16 : zv.u & 0xFFFFu) << 16);
         }
         s2[g][j] = half2_{sh, sh};
         z2[g][j] = half2_{zh, zh};
       }
+  };
+  auto sync_and_issue = [&](int e, auto in_run, auto btag) __attribute__((always_inline)) {
+    take_w();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -508,24 +627,24 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
     // pipe waits less on the other workgroup's bookkeeping (2-4 % measured, same box).
     __builtin_amdgcn_s_setprio(1);
     mfmas(a0, b0);
-    read_a(e, k1, a1);
+    read_a(e & 1, k1, a1);
     make_b(btag, k1, b1);
     interleave();
     __builtin_amdgcn_sched_barrier(0);
     mfmas(a1, b1);
-    read_a(e, k2, a0);
+    read_a(e & 1, k2, a0);
     make_b(btag, k2, b0);
     interleave();
     __builtin_amdgcn_sched_barrier(0);
     mfmas(a0, b0);
-    read_a(e, k3, a1);
+    read_a(e & 1, k3, a1);
     make_b(btag, k3, b1);
     interleave();
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(0);
     sync_and_issue(e, in_run, btag);
     mfmas(a1, b1);
-    read_a(e + 1, k0, a0);
+    read_a((e + 1) & 1, k0, a0);
     if constexpr (decltype(in_run)::value) {
       make_b(btag, k0, b0);
       interleave();
@@ -537,16 +656,6 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
     }
   };
 
-  // prologue: the first tile lands, then its k-step 0 is prepared while the second is on its way
-  issue_x(e_first, e_first);
-  __builtin_amdgcn_sched_barrier(0);
-  issue_w_generic(e_first, fw, fsz);
-  __builtin_amdgcn_sched_barrier(0);
-  sync_and_issue(e_first - 1, std::integral_constant<bool, false>{}, k0);
-  read_a(e_first, k0, a0);
-  make_b_any(e_first, k0, b0);
-  __builtin_amdgcn_sched_barrier(0);
-
   const std::integral_constant<bool, true> in_run;
   const std::integral_constant<bool, false> run_ends;
   const std::integral_constant<int, 2> b2;
@@ -554,40 +663,188 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
   const std::integral_constant<int, 4> b4;
   // the runs of this workgroup's share: [e_first, r2) 2-bit, [r2, r3) 3-bit, [r3, e_end) 4-bit
   const int r2 = min(max(end2, e_first), e_end), r3 = min(max(end3, e_first), e_end);
-  int e = e_first;
-  for (; e + 2 < r2; ++e) step(b2, in_run, e);
-  for (; e < r2; ++e) step(b2, run_ends, e);
-  for (; e + 2 < r3; ++e) step(b3, in_run, e);
-  for (; e < r3; ++e) step(b3, run_ends, e);
-  for (; e + 2 < e_end; ++e) step(b4, in_run, e);
-  for (; e < e_end; ++e) step(b4, run_ends, e);
+  if constexpr (RING) {
+    // State between steps: as below, but the packed words arrive in the ring and three activation blocks are in LDS or on
+    // their way.  After the synchronisation point of step e the slot of tile e + 1 (whose words are in registers by then)
+    // and the buffer of block e are free: tile e + 4 and block e + 3 are requested, the copies of the block spread over
+    // the four groups up to the next synchronisation point.  Nothing is requested past the end.
+    constexpr int kQuarter = S::kPasses / 4;
+    int xb = 0;  // buffer of block e = slot of tile e = (e - e_first) mod 3
+    auto next = [](int b) __attribute__((always_inline)) { return b == 2 ? 0 : b + 1; };
+    auto uniform = [](const uint4& d) __attribute__((always_inline)) {
+      return uint4{(uint32_t)__builtin_amdgcn_readfirstlane((int)d.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)d.y),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)d.z), (uint32_t)__builtin_amdgcn_readfirstlane((int)d.w)};
+    };
+    auto desc = [&](int e) __attribute__((always_inline)) { return uniform(tiles[min(e, e_last)]); };
+    // offset of the block of position e whose descriptor is d; past the end: an offset past the buffer, from which the
+    // copies read nothing (so that every step has the same number of copies)
+    const uint32_t x_end = (uint32_t)p.ntc << 15;
+    auto xsoff = [&](const uint4& d, int e) __attribute__((always_inline)) { return e <= e_last ? d.w & ~0x7FFFu : x_end; };
+    uint32_t xo2, xo3;  // offsets of blocks e + 2 and e + 3
+    uint4 wd;           // descriptor of tile e + 4
+    auto rstep = [&](auto btag, auto in_run, int e) __attribute__((always_inline)) {
+      const int b1n = next(xb), b2n = next(b1n);
+      const uint4 dn = tiles[min(e + 5, e_last)];
+      issue_x_part(xo2, b2n, kQuarter, 2 * kQuarter);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(a0, b0);
+      read_a(xb, k1, a1);
+      make_b(btag, k1, b1);
+      interleave();
+      __builtin_amdgcn_sched_barrier(0);
+      issue_x_part(xo2, b2n, 2 * kQuarter, 3 * kQuarter);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(a1, b1);
+      read_a(xb, k2, a0);
+      make_b(btag, k2, b0);
+      interleave();
+      __builtin_amdgcn_sched_barrier(0);
+      issue_x_part(xo2, b2n, 3 * kQuarter, S::kPasses);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(a0, b0);
+      read_a(xb, k3, a1);
+      make_b(btag, k3, b1);
+      read_w_ring(in_run, btag, min(e + 1, e_last), b1n);
+      interleave();
+      __builtin_amdgcn_sched_barrier(0);
+      take_w();
+      // block e + 1 has landed once only what was requested after it is outstanding: tile e + 3 (if any) and block e + 2
+      if (e + 3 <= e_last)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(S::kPasses + 3) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(S::kPasses) : "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (e + 4 <= e_last) issue_w_ring(wd, b1n);
+      issue_x_part(xo3, xb, 0, kQuarter);
+      xo2 = xo3;
+      xo3 = xsoff(wd, e + 4);
+      wd = uniform(dn);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(a1, b1);
+      read_a(b1n, k0, a0);
+      if constexpr (decltype(in_run)::value) {
+        make_b(btag, k0, b0);
+        interleave();
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        interleave();
+        __builtin_amdgcn_sched_barrier(0);
+        make_b_any(min(e + 1, e_last), k0, b0);
+      }
+      xb = b1n;
+    };
+    // prologue: in the order in which the loop would have requested them
+    {
+      const uint4 d0 = desc(e_first), d1 = desc(e_first + 1), d2 = desc(e_first + 2), d3 = desc(e_first + 3);
+      wd = desc(e_first + 4);
+      issue_w_ring(d0, 0);
+      issue_x_part(xsoff(d0, e_first), 0, 0, S::kPasses);
+      if (e_first + 1 <= e_last) issue_w_ring(d1, 1);
+      issue_x_part(xsoff(d1, e_first + 1), 1, 0, S::kPasses);
+      if (e_first + 2 <= e_last) issue_w_ring(d2, 2);
+      xo2 = xsoff(d2, e_first + 2);
+      xo3 = xsoff(d3, e_first + 3);
+      // tiles 0 and 1 and block 0 have landed (tile 2 and block 1 may be on their way)
+      if (e_first + 2 <= e_last)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::kPasses + 3) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::kPasses) : "memory");
+      read_w_ring(std::integral_constant<bool, false>{}, k0, e_first, 0);
+      take_w();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (e_first + 3 <= e_last) issue_w_ring(d3, 0);
+      issue_x_part(xo2, 2, 0, kQuarter);
+      read_a(0, k0, a0);
+      make_b_any(e_first, k0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    int e = e_first;
+    for (; e + 1 < r2; ++e) rstep(b2, in_run, e);
+    for (; e < r2; ++e) rstep(b2, run_ends, e);
+    for (; e + 1 < r3; ++e) rstep(b3, in_run, e);
+    for (; e < r3; ++e) rstep(b3, run_ends, e);
+    for (; e + 1 < e_end; ++e) rstep(b4, in_run, e);
+    for (; e < e_end; ++e) rstep(b4, run_ends, e);
+  } else {
+    // prologue: the first tile lands, then its k-step 0 is prepared while the second is on its way
+    issue_x(e_first, e_first);
+    __builtin_amdgcn_sched_barrier(0);
+    issue_w_generic(e_first, fw, fsz);
+    __builtin_amdgcn_sched_barrier(0);
+    sync_and_issue(e_first - 1, std::integral_constant<bool, false>{}, k0);
+    read_a(e_first & 1, k0, a0);
+    make_b_any(e_first, k0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    int e = e_first;
+    for (; e + 2 < r2; ++e) step(b2, in_run, e);
+    for (; e < r2; ++e) step(b2, run_ends, e);
+    for (; e + 2 < r3; ++e) step(b3, in_run, e);
+    for (; e < r3; ++e) step(b3, run_ends, e);
+    for (; e + 2 < e_end; ++e) step(b4, in_run, e);
+    for (; e < e_end; ++e) step(b4, run_ends, e);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the idle loads of the last two steps
+  // every wavefront of the workgroup passes the same number of barriers
+  if constexpr (KG > 1)
+    for (int n = e_end - e_first; n < longest; ++n) __builtin_amdgcn_s_barrier();
 
   // epilogue: the block goes through LDS (the activation buffers are free now) so that it leaves in whole
-  // 256-byte row segments: acc[i][j][r] = C[16*MI*wm + 16i + 4kb + r][8*i16 + NS*wn + j], the NS values j of
+  // row segments: acc[i][j][r] = C[16*MI*wm + 16i + 4kb + r][8*i16 + NS*wn + j], the NS values j of
   // a lane being consecutive columns.
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();  // every wavefront's idle loads have landed and its operand reads returned
   asm volatile("" ::: "memory");
-  if (p.ksplit > 1) {
-    // partial product in fp32: rows of 512 bytes through LDS (BM x 512 bytes = the two activation buffers)
+  if (KG > 1 || p.ksplit > 1) {
+    // fp32 sums, one block of BM rows of 512 bytes per K group (= its two activation buffers).  A wavefront stores
+    // the two columns 8 i16 + 2 wn of rows 4 kb + r with one instruction: without the two exchanges (neighbouring
+    // 16-byte units in rows with odd kb, the halves of a unit in rows with kb >= 2) the 64 lanes would hit 8 of the 32
+    // 8-byte slots of the LDS.
+    static_assert(NS == 2, "the exchange of units and halves below is written for two columns per wavefront");
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = 16 * MI * wm + 16 * i + 4 * kb + r;
-        float* dst = reinterpret_cast<float*>(Xs + row * 512 + (8 * i16 + NS * wn) * 4);
-#pragma unroll
-        for (int j = 0; j < NS; ++j) dst[j] = acc[i][j][r];
+        const int unit = (2 * i16 + wn / 2) ^ (kb & 1), half = (wn & 1) ^ (kb >> 1);
+        float2* dst = reinterpret_cast<float2*>(Xs + row * 512 + unit * 16 + half * 8);
+        *dst = float2{acc[i][0][r], acc[i][1][r]};
       }
     __syncthreads();
-    float* pbase = p.partial + ((int64_t)ks * p.M + m0) * p.N + (int64_t)tr * 128;
-    const int prow = tid / 32, punit = tid % 32;
+    // each thread adds up 8 consecutive columns of a row over the K groups, in their order
+    constexpr int kRows = kAllThreads / 16;  // rows per pass
+    static_assert(BM % kRows == 0, "whole passes");
+    const int prow = threadIdx.x / 16, pu = threadIdx.x % 16;
 #pragma unroll
-    for (int i = 0; i < BM / (S::kThreads / 32); ++i) {
-      const int row = prow + (S::kThreads / 32) * i;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(Xs + row * 512 + punit * 16);
-      if (m0 + row < p.M) *reinterpret_cast<u32x4*>(pbase + (int64_t)row * p.N + punit * 4) = v;
+    for (int i = 0; i < BM / kRows; ++i) {
+      const int row = prow + kRows * i, rkb = (row / 4) & 3;
+      floatx4 v[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int g = 0; g < KG; ++g)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const floatx4 t = *reinterpret_cast<const floatx4*>(Xs_all + g * (NB * kBufBytes) + row * 512 +
+                                                              ((2 * pu + q) ^ (rkb & 1)) * 16);
+          const floatx4 u = rkb & 2 ? floatx4{t[2], t[3], t[0], t[1]} : t;
+          v[q] = g == 0 ? u : v[q] + u;
+        }
+      if (m0 + row >= p.M) continue;
+      if (p.ksplit > 1) {
+        float* dst = p.partial + ((int64_t)ks * p.M + m0 + row) * p.N + (int64_t)tr * 128 + 8 * pu;
+        reinterpret_cast<floatx4*>(dst)[0] = v[0];
+        reinterpret_cast<floatx4*>(dst)[1] = v[1];
+      } else {
+        union {
+          _Float16 h[8];
+          u32x4 u;
+        } o;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) o.h[q] = (_Float16)v[q / 4][q % 4];
+        *reinterpret_cast<u32x4*>(p.Yt + (int64_t)(m0 + row) * p.N + (int64_t)tr * 128 + 8 * pu) = o.u;
+      }
     }
     return;
   }
@@ -616,19 +873,45 @@ __global__ __launch_bounds__(64 * WM * WN, (BM <= 128 ? 2 : 1) * ((WM * WN + 3) 
   }
 }
 
-template <int BM, int WM, int WN, bool G64>
-static void launch_prefill_shape(PrefillParams p, int M, hipStream_t stream) {
+template <int BM, bool RING>
+static void launch_prefill_shape(PrefillParams p, int M, bool g64, hipStream_t stream) {
   p.n_mtiles = (M + BM - 1) / BM;
   const unsigned grid = (unsigned)p.n_mtiles * (unsigned)p.ntr * (unsigned)p.ksplit;
-  hipLaunchKernelGGL((prefill_kernel<BM, WM, WN, 2, G64>), dim3(grid), dim3(64 * WM * WN), 0, stream, p);
+  if (g64)
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, true>), dim3(grid), dim3(RING ? 512 : 256), 0, stream, p);
+  else
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, false>), dim3(grid), dim3(RING ? 512 : 256), 0, stream, p);
+}
+
+// Time of a call in us by form (rows of a block, plain or ring), K ranges and shape: rounds of workgroups on 256 CUs,
+// each the steps of its longest range times the time of a step with 1, 2 or 3 workgroups on the CU plus the start and
+// end of a workgroup; the staging pass; and the last pass, over fp16 rows or over the fp32 partial products of the
+// ranges.  The constants are a fit to 880 measured calls (M = 24 ... 1100 on ten matrices from 512 x 512 to
+// 28672 x 8192, 1, 2, 4 and 8 ranges of each form), which it meets within 5 % (rms).
+static double prefill_time_us(int32_t N, int32_t K, int32_t M, int32_t bm, bool ring, int32_t ks) {
+  const int64_t ntr = N / kTile, ntc = K / kTile;
+  const int64_t per_cu = ((int64_t)((M + bm - 1) / bm) * ntr * ks + 255) / 256;
+  const int64_t groups = (ring ? 2 : 1) * ks;
+  const double steps = (double)((ntc + groups - 1) / groups);
+  static const double step128[] = {0.0, 1.03, 1.75}, step64[] = {0.0, 0.87, 1.21, 1.73}, step_ring[] = {0.0, 1.23};
+  const double* step = ring ? step_ring : bm == 64 ? step64 : step128;
+  const int64_t resident = ring ? 1 : bm == 64 ? 3 : 2;
+  const double edge = ring ? 2.64 : bm == 64 ? 1.85 : 2.53;
+  const int64_t full = per_cu / resident, rest = per_cu % resident;
+  double t = (double)full * (steps * step[resident] + edge) + (rest ? steps * step[rest] + edge : 0.0);
+  const double mn = (double)M * N * 1e-6, mk = (double)M * K * 1e-6;
+  t += ks > 1 ? 8.03 + 1.96 * ks * mn : 6.55 + 2.04 * mn;
+  return t + 0.87 * mk;
 }
 
 PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M) {
   PrefillPlan d;
   const int64_t ntr = N / kTile, ntc = K / kTile;
+  d.ring = false;
   // 64-row blocks when 128-row blocks would leave half of the CUs without a workgroup (short prompts on narrow
-  // matrices): twice the workgroups, each half as long; measured 8 to 13 % faster there, slower elsewhere
-  d.bm = (int64_t)((M + 127) / 128) * ntr <= 128 ? 64 : 128;
+  // matrices): twice the workgroups, each half as long
+  const int64_t blocks128 = (int64_t)((M + 127) / 128) * ntr;
+  d.bm = blocks128 <= 128 ? 64 : 128;
   // Still at most one workgroup per CU: a workgroup walks its K/128 tiles one after the other (about 0.95 us
   // each) while most of the machine idles, so K is cut into ranges of at least 8 tiles, one workgroup each
   // (up to two workgroups per CU), fp32 partial products, and a reduction pass in a fixed order.
@@ -641,6 +924,22 @@ PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M) {
     if (ks < 3 && ntc < 64) ks = 1;  // two ranges of a short K measured between -5 and +6 %; of a long K +20 %
   }
   d.ksplit = (int32_t)ks;
+  // The number of ranges decides the workspace.  Within it another form is taken where the times above make it at least
+  // 5 % faster (so that their error does not choose a slower one: of the measured shapes none is slower, those that
+  // change are 1 to 35 % faster): fewer ranges, 128-row blocks, or the ring form, which needs 4 tiles per K group to pay
+  // for its longer start (512 -> 512: 2 % slower with 2).  64-row blocks only where 128-row blocks would start at most one
+  // workgroup per CU (beyond they are slower throughout, by up to 30 %).
+  {
+    double best = 0.95 * prefill_time_us(N, K, M, d.bm, false, d.ksplit);
+    for (int form = 0; form < (blocks128 <= 256 ? 3 : 1); ++form) {
+      const int32_t bm = form == 0 ? 128 : 64;
+      const bool ring = form == 2;
+      for (int32_t k = 1; k <= ks && (!ring || ntc >= 8 * k); ++k) {
+        const double t = prefill_time_us(N, K, M, bm, ring, k);
+        if (t < best) best = t, d.bm = bm, d.ring = ring, d.ksplit = k;
+      }
+    }
+  }
   d.xperm_bytes = round_up_256((int64_t)((M + kTile - 1) / kTile) * kTile * K * 2);  // whole 128-row blocks
   d.ytmp_bytes = round_up_256(ks > 1 ? ks * (int64_t)M * N * 4 : (int64_t)M * N * 2);
   return d;
@@ -662,8 +961,11 @@ int launch_prefill(const GemmArgs& a, void* stream) {
   if (((a.row_perm || plan.ksplit > 1) && (int64_t)L->N * 2 > 160 * 1024) ||
       L->K / kTile > kPrefillMaxTiles)
     return SFMP_ERR_SHAPE;
+  const void* reduce_fn = plan.ksplit <= 2   ? reinterpret_cast<const void*>(&reduce_split_kernel<2>)
+                          : plan.ksplit <= 4 ? reinterpret_cast<const void*>(&reduce_split_kernel<4>)
+                                             : reinterpret_cast<const void*>(&reduce_split_kernel<8>);
   if (plan.ksplit > 1) {
-    if (int e = allow_full_lds(reinterpret_cast<const void*>(&reduce_split_kernel), "hipFuncSetAttribute(reduce)")) return e;
+    if (int e = allow_full_lds(reduce_fn, "hipFuncSetAttribute(reduce)")) return e;
   } else if (a.row_perm) {
     if (int e = allow_full_lds(reinterpret_cast<const void*>(&scatter_cols_kernel), "hipFuncSetAttribute(scatter)")) return e;
   }
@@ -712,21 +1014,24 @@ int launch_prefill(const GemmArgs& a, void* stream) {
   p.ksplit = plan.ksplit;
   p.partial = plan.ksplit > 1 ? (float*)((char*)a.workspace + plan.xperm_bytes) : nullptr;
   const bool g64 = L->group == 64;
-  if (plan.bm == 64) {
-    if (g64)
-      launch_prefill_shape<64, 1, 4, true>(p, a.M, (hipStream_t)stream);
-    else
-      launch_prefill_shape<64, 1, 4, false>(p, a.M, (hipStream_t)stream);
-  } else {
-    if (g64)
-      launch_prefill_shape<128, 1, 4, true>(p, a.M, (hipStream_t)stream);
-    else
-      launch_prefill_shape<128, 1, 4, false>(p, a.M, (hipStream_t)stream);
-  }
+  if (plan.ring)
+    launch_prefill_shape<64, true>(p, a.M, g64, (hipStream_t)stream);
+  else if (plan.bm == 64)
+    launch_prefill_shape<64, false>(p, a.M, g64, (hipStream_t)stream);
+  else
+    launch_prefill_shape<128, false>(p, a.M, g64, (hipStream_t)stream);
   if (int e = check_launch("sfmp_gemm prefill launch")) return e;
   if (plan.ksplit > 1) {
-    hipLaunchKernelGGL(reduce_split_kernel, dim3((unsigned)a.M), dim3(1024), (size_t)L->N * 2, (hipStream_t)stream,
-                       (const float*)p.partial, (int)plan.ksplit, (int)a.M, a.row_perm, (_Float16*)a.Y, (int)L->N);
+    const float* partial = p.partial;
+    int ks = plan.ksplit, Ma = a.M, Na = L->N;
+    const int32_t* rp = a.row_perm;
+    _Float16* Y = (_Float16*)a.Y;
+    void* kargs[] = {&partial, &ks, &Ma, &rp, &Y, &Na};
+    hipError_t e = hipLaunchKernel(reduce_fn, dim3((unsigned)a.M), dim3(1024), kargs, (size_t)L->N * 2, (hipStream_t)stream);
+    if (e != hipSuccess) {
+      note_hip_error("sfmp_gemm split-K reduction launch", hipGetErrorString(e));
+      return SFMP_ERR_HIP;
+    }
     if (int e = check_launch("sfmp_gemm split-K reduction launch")) return e;
   } else if (a.row_perm) {
     hipLaunchKernelGGL(scatter_cols_kernel, dim3((unsigned)a.M), dim3(256), (size_t)L->N * 2, (hipStream_t)stream,

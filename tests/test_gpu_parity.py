@@ -199,6 +199,24 @@ def test_short_prompt_split_k(torch_cuda, K, N, M, row_perm):
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed reduction order
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format,fractions", [
+    (1024, 1024, 17, 128, "fp16", {2: 1.0}), (1024, 1024, 64, 128, "bf16", {3: 1.0}), (1024, 1024, 65, 64, "fp16", {4: 1.0}),
+    (1408, 640, 130, 64, "bf16", {2: 1 / 3, 3: 1 / 3, 4: 1 / 3}), (1408, 640, 63, 128, "fp16", {2: 0.1, 4: 0.9}),
+    (2304, 512, 200, 256, "fp16", {2: 0.5, 3: 0.5}), (4224, 4096, 100, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}),
+    (4224, 4096, 130, 64, "fp16", {3: 0.5, 4: 0.5})])
+def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, scale_format, fractions):
+    # the form of the matrix-core kernel with two K groups per workgroup and weight rings: its shortest share (4 tiles
+    # per group), shares of different length (5 and 6 tiles), one width only and every change of width, both parameter
+    # formats and pairs per tile column, rows below, at and above a 64-row block, and with K in ranges besides (uneven)
+    from gpu_util import run_gemm
+    p = W.make_problem("kgroups", K, N, M, 7900 + K + M, fractions=fractions, outliers=True, group=group,
+                       scale_format=scale_format, fast_codes=N > 1024)
+    rows = None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False)
+    y1 = run_gemm(p)
+    _check(p, y1, rows)
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
+
+
 def test_workspace_is_reusable_and_result_deterministic(torch_cuda):
     from gpu_util import device_problem, make_workspace, run_gemm
     p = W.make_problem("reuse", 2048, 1024, 4, 31337, fractions={2: 0.5, 3: 0.5}, outliers=True)
