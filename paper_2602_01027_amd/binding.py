@@ -1,5 +1,8 @@
-"""ctypes binding of libsfmp.so.  Host buffers are numpy arrays, device buffers are torch tensors
-(torch only owns device memory and streams here).  No fallback: a missing library raises."""
+"""Binding of libsfmp.so.  Host buffers are numpy arrays, device buffers are torch tensors (torch only owns device
+memory and streams here).  No fallback: a missing library raises.
+
+The launch entry points are marshalled by a small extension (csrc/sfmp_torch.cpp), everything else by ctypes.  The
+extension takes calls whose arguments are plain tensors and leaves any other call to the ctypes path below it."""
 from __future__ import annotations
 
 import ctypes as C
@@ -76,6 +79,36 @@ def load_library():
             getattr(lib, name).restype = C.c_int
     _LIB = lib
     return lib
+
+
+_LAUNCHER = None  # (library, extension module bound to it)
+
+
+def launcher_path() -> str:
+    return os.path.join(_HERE, "_sfmp_torch.so")
+
+
+def _launcher():
+    """The extension that marshals the launch entry points, bound to the loaded library; raises like load_library."""
+    global _LAUNCHER
+    lib = load_library()
+    if _LAUNCHER is not None and _LAUNCHER[0] is lib:
+        return _LAUNCHER[1]
+    import importlib.util
+
+    import torch  # (first: the extension uses its libraries)
+    path = launcher_path()
+    if not os.path.exists(path):
+        raise FileNotFoundError(f"{path} is missing: build it with `python -m paper_2602_01027_amd.build` "
+                                "(or __graft_entry__.build())")
+    spec = importlib.util.spec_from_file_location("_sfmp_torch", path)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind(SfmpLayout, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+                *(C.cast(f, C.c_void_p).value for f in (lib.sfmp_gemm, lib.sfmp_gemm_static, lib.sfmp_gemv_batched,
+                                                        lib.sfmp_gemm_batched)))
+    _LAUNCHER = (lib, module)
+    return module
 
 
 def sfmp_strerror(code: int) -> str:
@@ -202,6 +235,9 @@ def sfmp_workspace_init(workspace, stream=None) -> None:
 
 def sfmp_gemm(X, col_perm, layout: SfmpLayout, s2, s3, s4, index, scales, zeros, bitmap, row_perm, Y, workspace,
               stream=None) -> None:
+    rc = _launcher().gemm(X, col_perm, layout, s2, s3, s4, index, scales, zeros, bitmap, row_perm, Y, workspace, stream)
+    if rc is not None:
+        return _check(rc)
     M = int(X.shape[0])
     nbytes = workspace.numel() * workspace.element_size()
     _check(load_library().sfmp_gemm(_dev_ptr(X), M, _dev_ptr(col_perm), C.byref(layout), _dev_ptr(s2), _dev_ptr(s3),
@@ -213,6 +249,9 @@ def sfmp_gemm(X, col_perm, layout: SfmpLayout, s2, s3, s4, index, scales, zeros,
 def sfmp_gemm_static(X, col_perm, layout: SfmpLayout, s2, s3, s4, index, scales, zeros, bitmap, row_perm, Y,
                      stream=None) -> None:
     """sfmp_gemm on the library's own static scratch memory (no workspace argument, no allocation)."""
+    rc = _launcher().gemm_static(X, col_perm, layout, s2, s3, s4, index, scales, zeros, bitmap, row_perm, Y, stream)
+    if rc is not None:
+        return _check(rc)
     M = int(X.shape[0])
     _check(load_library().sfmp_gemm_static(_dev_ptr(X), M, _dev_ptr(col_perm), C.byref(layout), _dev_ptr(s2),
                                            _dev_ptr(s3), _dev_ptr(s4), _dev_ptr(index), _dev_ptr(scales),
@@ -240,6 +279,9 @@ def make_gemv_batch(problems):
 
 def sfmp_gemv_batched(problems, stream=None) -> None:
     """problems: list of (X [1,K] fp16, col_perm or None, DevicePacked, row_perm or None, Y [1,N] fp16)."""
+    rc = _launcher().gemv_batched(problems, stream)
+    if rc is not None:
+        return _check(rc)
     arr, _keep = make_gemv_batch(problems)
     _check(load_library().sfmp_gemv_batched(C.cast(arr, C.c_void_p), len(problems), _stream_ptr(stream)))
 
@@ -255,6 +297,9 @@ def sfmp_gemm_batched_workspace(problems, M: int) -> int:
 
 def sfmp_gemm_batched(problems, M: int, workspace, stream=None) -> None:
     """Up to 8 independent products with a common M <= 16 in one launch (plus one staging launch for M >= 2)."""
+    rc = _launcher().gemm_batched(problems, M, workspace, stream)
+    if rc is not None:
+        return _check(rc)
     arr, _keep = make_gemv_batch(problems)
     _check(load_library().sfmp_gemm_batched(C.cast(arr, C.c_void_p), len(problems), C.c_int32(M),
                                             C.c_void_p(workspace.data_ptr()), C.c_int64(workspace.numel()),

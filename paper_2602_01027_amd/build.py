@@ -1,4 +1,5 @@
-"""Builds libsfmp.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libsfmp.so (HIP kernels + C ABI) for gfx950 with hipcc, and the extension that marshals torch tensors for it,
+in-tree."""
 from __future__ import annotations
 
 import os
@@ -9,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsfmp.so")
+TORCH_LIB = os.path.join(HERE, "_sfmp_torch.so")  # argument marshalling for torch tensors (host code only)
 PROBE_LIB = os.path.join(HERE, "libsfmp_probe.so")  # the benchmark's streaming-read probe, not part of the product
 SOURCES = ["sfmp_host.cpp", "sfmp_unpack.hip", "sfmp_decode.hip", "sfmp_prefill.hip", "sfmp_lut.hip", "sfmp_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -42,18 +44,38 @@ def _compile(src: str, objdir: str, extra) -> str:
     return obj
 
 
+def _build_torch_extension() -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I" + sysconfig.get_paths()["include"],
+           *("-I" + p for p in include_paths()), os.path.join(CSRC, "sfmp_torch.cpp"), "-o", TORCH_LIB, "-L" + libs, "-lc10",
+           "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("build of the torch extension failed")
+    return TORCH_LIB
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        extension = ex.submit(_build_torch_extension)
         objs = list(ex.map(lambda s: _compile(s, objdir, list(extra_flags)), SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
         raise RuntimeError("link failed")
+    extension.result()
     if verbose:
         print("built", LIB)
+        print("built", TORCH_LIB)
     probe_obj = _compile("sfmp_probe.hip", objdir, list(extra_flags))
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", probe_obj, "-o", PROBE_LIB],
                        capture_output=True, text=True)

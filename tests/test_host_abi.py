@@ -260,3 +260,33 @@ def test_float_reciprocal_item_index_is_exact():
         for rr in (lo, r, hi):
             j = (g * np.float32(rr)).astype(np.uint32)
             assert np.array_equal(j, e // c), c
+
+
+@pytest.mark.parametrize("odd", ["host tensor", "subclass", "layout", "no tensor", "short tuple", "property", "nine"])
+def test_launcher_leaves_calls_that_are_not_plain_to_the_general_path(odd):
+    # the extension that marshals the launches answers None (nothing launched) for anything but plain device tensors; the
+    # ctypes path then raises what it always raised
+    import torch
+    module = S.binding._launcher()
+    L = S.sfmp_pack_query(np.full((1, 1), 3, dtype=np.int8), 128, 128)
+    t = torch.zeros((1, 128), dtype=torch.float16)
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Packed:  # an attribute that is made by the access and kept by nobody
+        layout, s2, s3, s4, index, scales, zeros = L, t, t, t, t, t, t
+        bitmap = property(lambda self: torch.zeros(1))
+
+    gemm_args = [t, None, L, t, t, t, t, t, t, t, None, t, t, None]
+    dp = S.DevicePacked(L, t, t, t, t, t, t, t)
+    if odd in ("host tensor", "subclass", "layout", "no tensor"):
+        gemm_args[0] = {"subclass": t.as_subclass(Sub), "no tensor": 3}.get(odd, t)
+        gemm_args[2] = 7 if odd == "layout" else L
+        assert module.gemm(*gemm_args) is None
+        assert module.gemm_static(*gemm_args[:12], None) is None
+    else:
+        q = {"short tuple": [(t, None, dp, None)], "property": [(t, None, Packed(), None, t)],
+             "nine": [(t, None, dp, None, t)] * 9}[odd]
+        assert module.gemv_batched(q, None) is None
+        assert module.gemm_batched(q, 2, t, None) is None
