@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <cstddef>
 #include <cstdlib>
+#include <type_traits>
 
 #include "sfmp_device.h"
 #include "sfmp_internal.h"
@@ -729,9 +730,10 @@ __global__ __launch_bounds__(MB * 16) void stage_rows_kernel(const _Float16* __r
   stage_rows_tile<MB>(X, col_perm, xblk, M, K, (int)blockIdx.x);
 }
 
-// The same in operand order, for the kernels that keep their activations in registers: always 16 rows (rows >= M
-// zero), 4 KiB per tile column laid out as [k-step][lane][16 bytes], lane = 16 * (unit % 4) + row: a wavefront loads the
-// matrix-instruction operand of a k-step with one 16-byte load per lane, 1 KiB contiguous.
+// The same in operand order, for the kernels that take their activations into registers: MB rows (rows >= M zero), per
+// tile column [k-step][unit % 4][row][16 bytes]: a wavefront loads the matrix-instruction operand of a k-step with one
+// 16-byte load per lane (lane = 16 * (unit % 4) + row), MB * 64 bytes contiguous.
+template <int MB>
 __device__ __forceinline__ void stage_rows_tile_operand_order(const _Float16* __restrict__ X,
                                                               const int32_t* __restrict__ col_perm, unsigned char* xblk,
                                                               int M, int K, int tc) {
@@ -755,12 +757,13 @@ __device__ __forceinline__ void stage_rows_tile_operand_order(const _Float16* __
       v = *reinterpret_cast<const half8*>(X + (int64_t)m * K + k0);
     }
   }
-  *reinterpret_cast<half8*>(xblk + (((int64_t)tc * 4 + unit / 4) * 64 + 16 * (unit % 4) + m) * 16) = v;
+  *reinterpret_cast<half8*>(xblk + (((int64_t)tc * 16 + unit) * MB + m) * 16) = v;
 }
-__global__ __launch_bounds__(256) void stage_rows_operand_order_kernel(const _Float16* __restrict__ X,
-                                                                       const int32_t* __restrict__ col_perm,
-                                                                       unsigned char* xblk, int M, int K) {
-  stage_rows_tile_operand_order(X, col_perm, xblk, M, K, (int)blockIdx.x);
+template <int MB>
+__global__ __launch_bounds__(MB * 16) void stage_rows_operand_order_kernel(const _Float16* __restrict__ X,
+                                                                           const int32_t* __restrict__ col_perm,
+                                                                           unsigned char* xblk, int M, int K) {
+  stage_rows_tile_operand_order<MB>(X, col_perm, xblk, M, K, (int)blockIdx.x);
 }
 
 template <int MB>
@@ -781,20 +784,31 @@ __host__ __device__ inline size_t rskinny_raw_bytes(int32_t M, int32_t K) { retu
 // keeps them in registers (16 per tile column) for all its slabs: an item then brings only its slab and parameters
 // (small slots, two of them per wavefront at any M), and nothing is read from LDS for the activations.  16 rows
 // always (MB = 16).
-template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0>
+// RS (activations streamed through registers; 2 = slabs per workgroup at most): for a longer K.  Tile column by tile
+// column, the operands (staged in operand order, MB rows; lanes of rows past MB repeat the others) come from L2 straight
+// into registers, two tile columns ahead, and serve all slabs of the workgroup; they never pass through LDS, where a ring
+// slot with MB * 256 bytes of them per 0.5 to 1 KiB of weights was most of the traffic, again for every slab.  Three
+// register sets and three ring slots in rotation (the loop is unrolled by three, so every set has a name); the requests
+// go out as A(i+2) D(i+1) A(i+3) D(i+2) ... (A operands, D slabs and parameters), so that the wait for D(i) that is counted
+// by hand is the stricter one and the compiler's own for A(i) never waits for a copy it cannot see.  What is left is
+// mostly instruction issue (about 100 vector instructions per item and four wavefronts per SIMD).  28672 -> 8192, whole
+// call, M = 8 43.3 -> 38.5 us, M = 16 53.6 -> 45.0; 8320 -> 8192, M = 16 17.6 -> 15.5; 14336 -> 4096, M = 32 (two chunks)
+// 25.2 -> 21.5.
+template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
 __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int bid, const int G, unsigned char* lds_raw) {
   static_assert(!(RES && G64), "the resident form keeps one activation sum per tile column");
+  static_assert(!RS || (RS == 2 && !RES && !RA && S == 3 && NW == 16), "streamed operands: three sets and slots");
   static_assert(!(RES && RA) && (!RA || MB == 16) && (RA == 0 || RA == 2 || RA == 4), "activations in registers: 16 rows, no copy in LDS");
   constexpr int NT = NW * 64;
   constexpr int kBase = G64 ? kSlotBytes64 : kSlotBytes;  // slab + parameters; the staged activations follow
-  constexpr int kSlot = (RES || RA) ? kBase : kBase + MB * 256;
-  constexpr int kCopies = (RES || RA) ? 2 : 2 + MB / 4;  // direct copies per item: slab, scales+zeros, MB/4 x 1 KiB of activations
+  constexpr int kSlot = (RES || RA || RS) ? kBase : kBase + MB * 256;
+  constexpr int kCopies = (RES || RA || RS) ? 2 : 2 + MB / 4;  // direct copies per item: slab, scales+zeros, MB/4 x 1 KiB of activations
   constexpr int kRedGroups = NW / 4;  // the final sum over the wavefronts is taken in groups of four
   // DS: the sums of a finished slab go straight into the wavefront's own block of LDS and none are held in
   // registers: with the activations in registers (all 64 lanes hold sums) and with up to four activation rows
   // (lanes 0-15 hold them all: output rows 4 (lane / 16) + r)
-  constexpr bool DS = RA || MB == 4;
-  constexpr int kFinLanes = RA ? 64 : 16;
+  constexpr bool DS = RA || RS || MB == 4;
+  constexpr int kFinLanes = RA || RS ? 64 : 16;
   // LDS: red [NW/4][max_slabs][4][64] f32 | (Xs [ntc][MB][256 B] | SxL | raw activations [M][K] fp16) |
   //      rings [NW][S][kSlot];  with RA: fin [NW][max_slabs][64][4] f32 | rings
   float* red = reinterpret_cast<float*>(lds_raw);
@@ -851,8 +865,9 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
 
   // Issue item e into ring slot s: the slab (scalar address, 32/48/64 lanes), the 16 scale + 16 zero dwords, and
   // without resident activations MB/4 KiB of staged activations of the item's tile column (scalar address)
-  const uint32_t ring_off = (uint32_t)(uintptr_t)(lptr_t)(rings + (size_t)wave * S * kSlot);
-  const unsigned char* ring = rings + (size_t)wave * S * kSlot;
+  constexpr int kWaveSlots = S * (RS ? RS : 1);  // (RS: a slot holds the item of every slab)
+  const uint32_t ring_off = (uint32_t)(uintptr_t)(lptr_t)(rings + (size_t)wave * kWaveSlots * kSlot);
+  const unsigned char* ring = rings + (size_t)wave * kWaveSlots * kSlot;
   const uint64_t xb = (uint64_t)p.xblk;
   auto issue_item = [&](int e, int s) __attribute__((always_inline)) {
     const uint32_t wlo = (uint32_t)__builtin_amdgcn_readlane((int)it_wlo, e);
@@ -861,7 +876,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     const uint32_t soff = (uint32_t)__builtin_amdgcn_readlane((int)it_soff, e);
     const uint32_t slot = ring_off + (uint32_t)s * kSlot;
     lds_copy_item(par_vbase + soff, ((uint64_t)whi << 32) | wlo, data_voff, slot + 1024, slot, xhi, G64 ? ~0u : 0u);
-    if constexpr (!RES && !RA) {
+    if constexpr (!RES && !RA && !RS) {
       const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, e);
       const uint64_t xsrc = xb + (uint64_t)(misc & 0xFFFF) * (MB * 256);
 #pragma unroll
@@ -992,8 +1007,8 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
 
   // one item with its activation operands given (a: four k-steps of 32 columns)
   // (sx_known: the activation sums of the item's tile column when the caller has them already)
-  auto consume_with = [&](const uint32_t misc, const unsigned char* slot, const half8 (&a)[4],
-                          const floatx4 sx_known) __attribute__((always_inline)) {
+  auto consume_with = [&](const uint32_t misc, const unsigned char* slot, const half8 (&a)[4], const floatx4 sx_known,
+                          floatx4& acc_q, floatx4& acc_z) __attribute__((always_inline)) {
     if constexpr (G64) {
       // sums of the activations over columns 0-63 and 64-127, the code sums likewise, one parameter pair for each
       floatx4 sx_lo = {0.f, 0.f, 0.f, 0.f}, sx_hi = {0.f, 0.f, 0.f, 0.f};
@@ -1027,7 +1042,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       params_to_float(par[32], par[48], (misc >> 22) & 16u, p.bf16 != 0, s_hi, z_hi);
       acc_q += s_lo * t_lo + s_hi * t_hi;
       acc_z += z_lo * sx_lo + z_hi * sx_hi;
-      if (misc & 0x10000u) {  // this wavefront's share of slab j is complete
+      if (!RS && (misc & 0x10000u)) {  // this wavefront's share of slab j is complete
         asm volatile("" ::: "memory");
         const int q = (misc >> 17) & (DS ? 15 : ACC - 1);
         const floatx4 acc = acc_q * 16777216.f + acc_z;
@@ -1037,7 +1052,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       return;
     }
     floatx4 sx;
-    if constexpr (RA == 2) {
+    if constexpr (RA == 2 || RS) {
       sx = sx_known;
     } else if constexpr (RES) {
       sx = *reinterpret_cast<const floatx4*>(SxL + (misc & 0xFFFF) * 16 + kb * 4);
@@ -1074,7 +1089,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     params_to_float(scw, zrw, (misc >> 22) & 16u, p.bf16 != 0, sf, zf);  // bit 26 of misc: odd sigma -> high half
     acc_q += sf * t;
     acc_z += zf * sx;
-    if (misc & 0x10000u) {  // this wavefront's share of slab j is complete
+    if (!RS && (misc & 0x10000u)) {  // this wavefront's share of slab j is complete
       asm volatile("" ::: "memory");  // keeps this a branch rather than a select over all the sums
       const int q = (misc >> 17) & (DS ? 15 : ACC - 1);
       const floatx4 acc = acc_q * 16777216.f + acc_z;
@@ -1100,13 +1115,13 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       // operands into one more set of registers cost 16 more of them)
       const uint32_t t = (misc & 0xFFFF) >> (NW == 16 ? 4 : 3);
       if constexpr (RA == 2) {
-        if (t == 0) consume_with(misc, slot, aset[0], sx0);
-        else consume_with(misc, slot, aset[1], sx1);
+        if (t == 0) consume_with(misc, slot, aset[0], sx0, acc_q, acc_z);
+        else consume_with(misc, slot, aset[1], sx1, acc_q, acc_z);
       } else {
-        if (t == 0) consume_with(misc, slot, aset[0], sx0);
-        else if (t == 1) consume_with(misc, slot, aset[1], sx0);
-        else if (t == 2) consume_with(misc, slot, aset[2], sx0);
-        else consume_with(misc, slot, aset[3], sx0);
+        if (t == 0) consume_with(misc, slot, aset[0], sx0, acc_q, acc_z);
+        else if (t == 1) consume_with(misc, slot, aset[1], sx0, acc_q, acc_z);
+        else if (t == 2) consume_with(misc, slot, aset[2], sx0, acc_q, acc_z);
+        else consume_with(misc, slot, aset[3], sx0, acc_q, acc_z);
       }
     } else {
       if (MB == 16 || i16 < MB) {
@@ -1114,11 +1129,78 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
 #pragma unroll
         for (int kappa = 0; kappa < 4; ++kappa) a[kappa] = *reinterpret_cast<const half8*>(abase + a_off[kappa]);
       }
-      consume_with(misc, slot, a, floatx4{0.f, 0.f, 0.f, 0.f});
+      consume_with(misc, slot, a, floatx4{0.f, 0.f, 0.f, 0.f}, acc_q, acc_z);
     }
   };
 
-  for (int e0 = 0; e0 < E; e0 += 64) {
+  if constexpr (RS > 0) {
+    describe(0, E);  // (at most 64 items)
+    half8 as0[4], as1[4], as2[4];
+    auto load_a = [&](half8 (&set)[4], int i) __attribute__((always_inline)) {
+      const int tc = min(wave + NW * i, p.ntc - 1);  // (past the end: the last tile column again)
+#pragma unroll
+      for (int kappa = 0; kappa < 4; ++kappa)
+        set[kappa] = *reinterpret_cast<const half8*>(p.xblk + ((((size_t)tc * 4 + kappa) * 4 + kb) * MB + (i16 & (MB - 1))) * 16);
+    };
+    auto issue_column = [&](int i, int slot) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < RS; ++j)
+        if (j < nj) issue_item(j * my_cnt + i, slot * RS + j);
+    };
+    floatx4 accq[RS], accz[RS];
+#pragma unroll
+    for (int j = 0; j < RS; ++j) accq[j] = floatx4{0.f, 0.f, 0.f, 0.f}, accz[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // tile column i with its operands in `set`, its slabs in slot i mod 3; false behind the last one
+    auto column = [&](int i, half8 (&set)[4], auto slot_tag) __attribute__((always_inline)) {
+      constexpr int slot = decltype(slot_tag)::value;
+      // D(i) has landed once only A(i+2) and D(i+1) are outstanding (a workgroup with fewer slabs than RS: D(i+1) is
+      // shorter, and so is what may be outstanding)
+      if (i + 1 < my_cnt) {
+        if (nj == RS)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + 2 * RS) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      }
+      __builtin_amdgcn_s_setprio(1);
+      floatx4 sx = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (!G64) {
+#pragma unroll
+        for (int kappa = 0; kappa < 4; ++kappa) sx = __builtin_amdgcn_mfma_f32_16x16x32_f16(set[kappa], ones, sx, 0, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < RS; ++j)
+        if (j < nj) {
+          const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, j * my_cnt + i);
+          consume_with(misc, ring + (slot * RS + j) * kSlot, set, sx, accq[j], accz[j]);
+        }
+      __builtin_amdgcn_s_setprio(0);
+      load_a(set, i + 3);
+      if (i + 2 < my_cnt) issue_column(i + 2, (slot + 2) % 3);
+      return i + 1 < my_cnt;
+    };
+    if (my_cnt > 0) {
+      const std::integral_constant<int, 0> t0;
+      const std::integral_constant<int, 1> t1;
+      const std::integral_constant<int, 2> t2;
+      load_a(as0, 0);
+      load_a(as1, 1);
+      issue_column(0, 0);
+      load_a(as2, 2);
+      if (my_cnt > 1) issue_column(1, 1);
+      for (int i = 0;; i += 3) {
+        if (!column(i, as0, t0)) break;
+        if (!column(i + 1, as1, t1)) break;
+        if (!column(i + 2, as2, t2)) break;
+      }
+#pragma unroll
+      for (int j = 0; j < RS; ++j)
+        if (j < nj) keep_sums(j, accq[j] * 16777216.f + accz[j]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  for (int e0 = RS ? E : 0; e0 < E; e0 += 64) {
     const int Eb = min(64, E - e0);
     if (!RES || e0 > 0) describe(e0, Eb);
     const int npro = min(S, Eb);
@@ -1218,10 +1300,10 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   }
 }
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
 __global__ __launch_bounds__(NW * 64) void rskinny_kernel(const RSkinnyParams p) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  rskinny_body<NW, S, MB, RES, ACC, G64, RA>(p, (int)blockIdx.x, (int)gridDim.x, lds_raw);
+  rskinny_body<NW, S, MB, RES, ACC, G64, RA, RS>(p, (int)blockIdx.x, (int)gridDim.x, lds_raw);
 }
 
 // Several independent problems with the same M in one launch (q, k and v, or gate and up of a decoder
@@ -1234,12 +1316,12 @@ struct RSkinnyBatch {  // laid out as GemvBatch
 };
 static_assert(offsetof(RSkinnyBatch, p) == 64, "the header of a batch is one 64-byte line");
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
 __global__ __launch_bounds__(NW * 64) void rskinny_batched_kernel(const RSkinnyBatch b) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int i = batch_problem_of(b.first, (int)blockIdx.x);
   const RSkinnyParams p = b.p[i];
-  rskinny_body<NW, S, MB, RES, ACC, G64, RA>(p, (int)blockIdx.x - b.first[i], b.first[i + 1] - b.first[i], lds_raw);
+  rskinny_body<NW, S, MB, RES, ACC, G64, RA, RS>(p, (int)blockIdx.x - b.first[i], b.first[i + 1] - b.first[i], lds_raw);
 }
 
 // Staging for a batch: job j (one per distinct activation matrix) owns workgroups [first[j], first[j+1]).
@@ -1259,10 +1341,11 @@ __global__ __launch_bounds__(MB * 16) void stage_rows_batched_kernel(const Stage
   while (j + 1 < b.count && (int)blockIdx.x >= b.first[j + 1]) ++j;
   stage_rows_tile<MB>(b.X[j], b.col_perm[j], b.xblk[j], b.M[j], b.K[j], (int)blockIdx.x - b.first[j]);
 }
-__global__ __launch_bounds__(256) void stage_rows_operand_order_batched_kernel(const StageBatch b) {
+template <int MB>
+__global__ __launch_bounds__(MB * 16) void stage_rows_operand_order_batched_kernel(const StageBatch b) {
   int j = 0;
   while (j + 1 < b.count && (int)blockIdx.x >= b.first[j + 1]) ++j;
-  stage_rows_tile_operand_order(b.X[j], b.col_perm[j], b.xblk[j], b.M[j], b.K[j], (int)blockIdx.x - b.first[j]);
+  stage_rows_tile_operand_order<MB>(b.X[j], b.col_perm[j], b.xblk[j], b.M[j], b.K[j], (int)blockIdx.x - b.first[j]);
 }
 
 // ============================================================================================
@@ -1310,6 +1393,7 @@ static GemvFit gemv_fit(int32_t N, int32_t K, int32_t grid) {
 struct RSkinnyConfig {
   int32_t mb, nw, slots, acc;
   bool resident;
+  int32_t rs;  // activations streamed through registers: slabs per workgroup (2; 0: not)
   int32_t ra;  // activations in registers (at most 2 or 4 tile columns per wavefront; 0: not): 16-row operand-order staging, small slots
 };
 static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
@@ -1318,7 +1402,8 @@ static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
 static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int32_t M, int32_t K) {
   const int64_t red = (int64_t)max_slabs * 1024 * (c.nw / 4);
   // (slots sized for group length 64, 128 bytes larger, whatever the layout)
-  if (c.ra) return (int64_t)max_slabs * 1024 * c.nw + (int64_t)c.nw * c.slots * kSlotBytes64;  // fin | rings
+  if (c.ra || c.rs)  // fin | rings
+    return (int64_t)max_slabs * 1024 * c.nw + (int64_t)c.nw * c.slots * (c.rs ? c.rs : 1) * kSlotBytes64;
   return c.resident ? red + (int64_t)c.mb * K * 2 + (int64_t)(K / kTile) * 64 + (int64_t)rskinny_raw_bytes(M, K) +
                           (int64_t)c.nw * c.slots * kSlotBytes64
                     : red + (int64_t)c.nw * c.slots * (kSlotBytes64 + c.mb * 256);
@@ -1334,6 +1419,7 @@ constexpr int kSlotsResident = 3, kSlotsMb4 = 2, kSlotsMb8 = 2, kSlotsMb16 = 2;
 constexpr int kSlotsMb16Wide = 1;
 constexpr int kSkinnyWideSlabs = 8;  // slabs per workgroup up to which the ring-skinny kernels run 16 wavefronts
 constexpr int kSkinnyMaxRounds = 4;  // workgroups per CU, one after the other, accepted to get there
+constexpr int kSlotsStreamedActs = 3;
 constexpr int kSlotsRegisterActs = 2;  // activations in registers: the slots hold a slab and its parameters only
 // max_slabs: the largest number of slabs of a workgroup over the problems of the launch; K: the largest K
 // g64: group length 64, for which the resident form does not exist
@@ -1346,6 +1432,7 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
   c.acc = !wide ? 16 : max_slabs <= 4 ? 4 : 8;
   c.resident = false;
   c.ra = 0;
+  c.rs = 0;
   if (c.mb == 4) c.acc = wide ? 4 : 16;  // up to four rows: the finished sums live in LDS, acc only names the variant
   if (!g64 && c.mb == 4 && (int64_t)M * K * 2 <= kResidentMaxRawBytes && K / 8 <= kGemvUnitIters * c.nw * 64) {
     c.resident = true;
@@ -1362,6 +1449,16 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
     r.acc = r.nw == 16 ? 4 : 16;
     r.slots = kSlotsRegisterActs;
     if (rskinny_lds_bytes(r, max_slabs, M, K) <= 160 * 1024) return r;
+  }
+  // a longer K with two slabs per workgroup (4096 < N <= 8192 on a full grid): operands streamed through registers.  Not
+  // with one slab, where a tile column serves one item only (14336 -> 4096: M = 8 13.0 -> 14.2 us, M = 16 unchanged), and
+  // not for M <= 4, where the slot carries 1 KiB of activations and a register load of them costs as much as for 16 rows
+  // (28672 -> 8192, M = 2: 35.0 -> 35.9 us).
+  if (!c.resident && c.mb >= 8 && max_slabs == 2 && 2 * ((K / kTile + 15) / 16) <= kGemvMaxItems) {
+    c.rs = 2;
+    c.acc = 4;
+    c.slots = kSlotsStreamedActs;
+    return c;
   }
   if (!c.resident) c.slots = c.mb == 4 ? kSlotsMb4 : c.mb == 8 ? kSlotsMb8 : wide ? kSlotsMb16Wide : kSlotsMb16;
   return c;
@@ -1403,6 +1500,7 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
   d.acc = c.acc;
   d.resident = c.resident;
   d.ra = c.ra;
+  d.rs = c.rs;
   d.slots = c.slots;
   d.lds_bytes = (int32_t)rskinny_lds_bytes(c, d.max_slabs, M, K);
   d.workspace_bytes = round_up_256((int64_t)ntc * c.mb * 256);
@@ -1563,13 +1661,13 @@ static RSkinnyParams rskinny_params(const GemmArgs& a, int32_t M, const void* xb
   return p;
 }
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS>
 static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* stream) {
   const sfmp_layout_t* L = a.L;
-  const void* fn = reinterpret_cast<const void*>(&rskinny_kernel<NW, S, MB, RES, ACC, G64, RA>);
+  const void* fn = reinterpret_cast<const void*>(&rskinny_kernel<NW, S, MB, RES, ACC, G64, RA, RS>);
   if (int e = allow_full_lds(fn, "hipFuncSetAttribute(skinny)")) return e;
-  if (RA) {
-    hipLaunchKernelGGL(stage_rows_operand_order_kernel, dim3((unsigned)(L->K / kTile)), dim3(256), 0, (hipStream_t)stream,
+  if (RA || RS) {
+    hipLaunchKernelGGL(stage_rows_operand_order_kernel<MB>, dim3((unsigned)(L->K / kTile)), dim3(MB * 16), 0, (hipStream_t)stream,
                        (const _Float16*)a.X, a.col_perm, (unsigned char*)a.workspace, (int)a.M, (int)L->K);
     if (int e = after_launch("sfmp_gemm activation staging launch")) return e;
   } else if (!RES) {
@@ -1587,22 +1685,24 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   return after_launch("sfmp_gemm skinny launch");
 }
 
-// The compiled configurations (see rskinny_config): X(NW, S, MB, RES, ACC, RA)
-#define SFMP_RSKINNY_CONFIGS(X)                                                                                   \
-  X(16, kSlotsResident, 4, true, 4, 0) X(8, kSlotsResident, 4, true, 16, 0)                                        \
-  X(16, kSlotsMb4, 4, false, 4, 0) X(8, kSlotsMb4, 4, false, 16, 0)                                                \
-  X(16, kSlotsMb8, 8, false, 4, 0) X(16, kSlotsMb8, 8, false, 8, 0) X(8, kSlotsMb8, 8, false, 16, 0)             \
-  X(16, kSlotsMb16Wide, 16, false, 4, 0) X(16, kSlotsMb16Wide, 16, false, 8, 0) X(8, kSlotsMb16, 16, false, 16, 0) \
-  X(16, kSlotsRegisterActs, 16, false, 4, 2) X(8, kSlotsRegisterActs, 16, false, 16, 2)                                    \
-  X(16, kSlotsRegisterActs, 16, false, 4, 4) X(8, kSlotsRegisterActs, 16, false, 16, 4)
+// The compiled configurations (see rskinny_config): X(NW, S, MB, RES, ACC, RA, RS)
+#define SFMP_RSKINNY_CONFIGS(X)                                                                                    \
+  X(16, kSlotsResident, 4, true, 4, 0, 0) X(8, kSlotsResident, 4, true, 16, 0, 0)                                  \
+  X(16, kSlotsMb4, 4, false, 4, 0, 0) X(8, kSlotsMb4, 4, false, 16, 0, 0)                                          \
+  X(16, kSlotsMb8, 8, false, 4, 0, 0) X(16, kSlotsMb8, 8, false, 8, 0, 0) X(8, kSlotsMb8, 8, false, 16, 0, 0)      \
+  X(16, kSlotsMb16Wide, 16, false, 4, 0, 0) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0)                              \
+  X(8, kSlotsMb16, 16, false, 16, 0, 0)                                                                            \
+  X(16, kSlotsStreamedActs, 8, false, 4, 0, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2)                       \
+  X(16, kSlotsRegisterActs, 16, false, 4, 2, 0) X(8, kSlotsRegisterActs, 16, false, 16, 2, 0)                      \
+  X(16, kSlotsRegisterActs, 16, false, 4, 4, 0) X(8, kSlotsRegisterActs, 16, false, 16, 4, 0)
 
 static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) {
-#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_)                                                 \
-  if (d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_) { \
+#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_)                                                 \
+  if (d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
     if constexpr (!RES_) {                                                                    \
-      if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_>(a, d, stream); \
+      if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_>(a, d, stream); \
     }                                                                                         \
-    return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_>(a, d, stream);        \
+    return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_>(a, d, stream);        \
   }
   SFMP_RSKINNY_CONFIGS(SFMP_X)
 #undef SFMP_X
@@ -1640,7 +1740,7 @@ static BatchStagePlan plan_batch_staging(const GemmArgs* probs, int count, int32
 }
 
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS>
 static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int32_t M, const int32_t* g,
                                           void* workspace, void* stream) {
   const BatchStagePlan sp = plan_batch_staging(probs, count, MB);
@@ -1676,8 +1776,9 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
     if (max_slabs > kGemvMaxSlabs) return SFMP_ERR_SHAPE;
     b.p[i] = rskinny_params(probs[i], probs[i].M, (const unsigned char*)workspace + sp.offset[sp.job_of[i]], max_slabs,
                             g[i]);
-    const RSkinnyConfig cfg = {MB, NW, S, ACC, RES, RA};
-    if (!RA && MB != 4 && max_slabs > ACC) return SFMP_ERR_SHAPE;  // (those two forms keep no sums in registers)
+    const RSkinnyConfig cfg = {MB, NW, S, ACC, RES, RS, RA};
+    if (RS && max_slabs > RS) return SFMP_ERR_SHAPE;
+    if (!RA && !RS && MB != 4 && max_slabs > ACC) return SFMP_ERR_SHAPE;  // (those two forms keep no sums in registers)
     const int64_t need = rskinny_lds_bytes(cfg, max_slabs, probs[i].M, L->K);
     lds = need > lds ? need : lds;
     b.first[i] = first;
@@ -1686,10 +1787,10 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
   for (int i = count; i <= kGemvMaxBatch; ++i) b.first[i] = first;
   for (int i = count; i < kGemvMaxBatch; ++i) b.p[i] = b.p[0];
   if (lds > 160 * 1024) return SFMP_ERR_SHAPE;
-  const void* fn = reinterpret_cast<const void*>(&rskinny_batched_kernel<NW, S, MB, RES, ACC, G64, RA>);
+  const void* fn = reinterpret_cast<const void*>(&rskinny_batched_kernel<NW, S, MB, RES, ACC, G64, RA, RS>);
   if (int e = allow_full_lds(fn, "hipFuncSetAttribute(skinny batched)")) return e;
-  if (RA) {
-    hipLaunchKernelGGL(stage_rows_operand_order_batched_kernel, dim3((unsigned)sfirst), dim3(256), 0, (hipStream_t)stream, sb);
+  if (RA || RS) {
+    hipLaunchKernelGGL(stage_rows_operand_order_batched_kernel<MB>, dim3((unsigned)sfirst), dim3(MB * 16), 0, (hipStream_t)stream, sb);
     if (int e = after_launch("sfmp_gemm_batched activation staging launch")) return e;
   } else if (!RES) {
     hipLaunchKernelGGL((stage_rows_batched_kernel<MB>), dim3((unsigned)sfirst), dim3(MB * 16), 0, (hipStream_t)stream, sb);
@@ -1757,12 +1858,12 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
   RSkinnyConfig c;
   bool n64 = false;
   if (int e = batch_config(probs, count, M, g, &c, &n64)) return e;
-#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_)                                               \
-  if (c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_) { \
+#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_)                                               \
+  if (c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
     if constexpr (!RES_) {                                                                  \
-      if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_>(probs, count, M, g, workspace, stream); \
+      if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_>(probs, count, M, g, workspace, stream); \
     }                                                                                       \
-    return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_>(probs, count, M, g, workspace, stream); \
+    return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_>(probs, count, M, g, workspace, stream); \
   }
   SFMP_RSKINNY_CONFIGS(SFMP_X)
 #undef SFMP_X

@@ -545,6 +545,21 @@ def test_small_batch_long_K(torch_cuda, K, N, M, group):
         assert np.array_equal(run_gemm(p, dp, cp, rp).view(np.uint16), Y.view(np.uint16))
 
 
+@pytest.mark.parametrize("K,N,M,group", [(8320, 4224, 5, 128), (8320, 8192, 16, 64), (8704, 6272, 9, 512), (14336, 4096, 24, 128),
+                                         (14336, 4096, 32, 64)])
+def test_small_batch_long_K_two_slabs_per_workgroup(torch_cuda, K, N, M, group):
+    # activations streamed through registers: wavefronts with four, five and seven tile columns (the rotation of three
+    # register sets ends at each of its places), workgroups with one and with two slabs, the last row of 8 and of 16, two
+    # chunks of 16 rows with 2 x 2 slabs, two parameter pairs per tile column
+    from gpu_util import run_gemm
+    p = W.make_problem("stream", K, N, M, 8600 + M + K, fractions={2: 0.4, 3: 0.3, 4: 0.3}, outliers=True, group=group,
+                       block=(1, max(1, group // 128)), fast_codes=True)
+    rows = np.random.default_rng(M).choice(N, 384, replace=False)
+    y1 = run_gemm(p)
+    _check(p, y1, rows)
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
+
+
 @pytest.mark.parametrize("K,N,M", [(1024, 40960, 3), (1024, 40960, 8), (4224, 36864, 8), (4224, 36864, 16)])
 def test_small_batch_more_than_2048_slabs(torch_cuda, K, N, M):
     # more than 8 slabs per workgroup on 256 workgroups: the launch takes 512 workgroups (two per CU in turn, 5 slabs
