@@ -176,7 +176,7 @@ struct PrefillParams {
   _Float16* Yt;  // [M, N], rows of Wt in reordered order
   int32_t M, N, K, ntr, ntc, n_mtiles;
   int32_t gshift;  // log2(group / 128): tile column tc uses parameter row tc >> gshift
-  int32_t bf16;    // scales and zeros are bfloat16 (else fp16)
+  int32_t bf16;    // scales and zeros are bfloat16, else fp16 (read by the host only: it selects the instantiation)
   int32_t ksplit;  // K ranges (1 = the whole K in one workgroup)
   float* partial;  // ksplit > 1: fp32 partial products [ksplit][M][N], rows of Wt in reordered order
 };
@@ -288,7 +288,10 @@ struct PrefillShape {
 // hand (the loop has no load to a register), and the addresses of a tile's copies are computed once, when the tile
 // sequence is laid out.  Per 64-row step of both groups 2500 cycles.  512 x 4096 x 4096 47 -> 34 us, 300 x 2048 x 2048
 // 26 -> 19, 128 x 4096 x 14336 43 -> 33, 64 x 4096 x 14336 29 -> 24.5 (whole calls, same machine).
-template <int BM, bool RING, bool G64 = false>
+// BF16: scales and zeros are bfloat16.  An instantiation each: decided at run time, both conversions were computed and one
+// chosen, some 16 of 210 vector instructions of a tile (a branch instead costs 2 % of the large calls, at the
+// synchronisation point).
+template <int BM, bool RING, bool G64, bool BF16>
 __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const PrefillParams p) {
   static_assert(!RING || BM == 64, "the buffers of two K groups fit in LDS with 64 rows");
   constexpr int WM = 1, WN = 4, KG = RING ? 2 : 1;
@@ -590,8 +593,7 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
         sv.u = rsz.s[g][j / 2];
         zv.u = rsz.z[g][j / 2];
         _Float16 sh = sv.h[j % 2], zh = zv.h[j % 2];
-        if (p.bf16) {  // bfloat16 = top half of a float; the dequantisation runs in fp16
-          if constexpr (RING) asm volatile("; bfloat16 parameters");  // (a branch, not both and a choice)
+        if constexpr (BF16) {  // bfloat16 = top half of a float; the dequantisation runs in fp16
           sh = (_Float16)__uint_as_float((j % 2 ? sv.u >> 16 : sv.u & 0xFFFFu) << 16);
           zh = (_Float16)__uint_as_float((j % 2 ? zv.u >> 16 : zv.u & 0xFFFFu) << 16);
         }
@@ -877,10 +879,15 @@ template <int BM, bool RING>
 static void launch_prefill_shape(PrefillParams p, int M, bool g64, hipStream_t stream) {
   p.n_mtiles = (M + BM - 1) / BM;
   const unsigned grid = (unsigned)p.n_mtiles * (unsigned)p.ntr * (unsigned)p.ksplit;
-  if (g64)
-    hipLaunchKernelGGL((prefill_kernel<BM, RING, true>), dim3(grid), dim3(RING ? 512 : 256), 0, stream, p);
+  const dim3 threads(RING ? 512 : 256);
+  if (g64 && p.bf16)
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, true, true>), dim3(grid), threads, 0, stream, p);
+  else if (g64)
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, true, false>), dim3(grid), threads, 0, stream, p);
+  else if (p.bf16)
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, false, true>), dim3(grid), threads, 0, stream, p);
   else
-    hipLaunchKernelGGL((prefill_kernel<BM, RING, false>), dim3(grid), dim3(RING ? 512 : 256), 0, stream, p);
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, false, false>), dim3(grid), threads, 0, stream, p);
 }
 
 // Time of a call in us by form (rows of a block, plain or ring), K ranges and shape: rounds of workgroups on 256 CUs,
