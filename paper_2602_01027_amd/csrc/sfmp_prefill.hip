@@ -308,6 +308,7 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
   // tile, byte offset of its parameters, (tc << 15) | width
   __shared__ int32_t seq[RING ? 1 : kPrefillMaxTiles];
   __shared__ uint4 tiles[RING ? kPrefillMaxTiles : 1];
+  __shared__ int2 counts[8];  // 2-bit and 3-bit tiles per 64 tile columns
 
   const int tid = threadIdx.x % S::kThreads;  // within the K group
   const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / S::kThreads)) : 0;
@@ -332,39 +333,70 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
   const int longest = KG > 1 ? (p.ntc + ranges - 1) / ranges : 0;
 
   // The K reduction runs over the tiles of this tile row sorted by width (first all 2-bit tiles, then
-  // the 3-bit, then the 4-bit ones; the order of a sum is free): three loops, each with a straight-line
-  // body for its width.  The CSR part of the block-index table lists exactly these runs: the i-th
-  // width-b tile of row tr is tile number row_ptr_b[tr] + i of stream S_b, in tile column
-  // col_idx_b[row_ptr_b[tr] + i].
-  const int32_t* row_ptr = p.index + 3 + p.ntr * p.ntc;
-  const int32_t* col_idx = row_ptr + 3 * (p.ntr + 1);
-  const int32_t first2 = row_ptr[tr], first3 = row_ptr[(p.ntr + 1) + tr], first4 = row_ptr[2 * (p.ntr + 1) + tr];
-  const int end2 = row_ptr[tr + 1] - first2;
-  const int end3 = end2 + row_ptr[(p.ntr + 1) + tr + 1] - first3;
-  const int32_t total2 = p.index[0], total3 = p.index[1];
-  for (int e = threadIdx.x; e < p.ntc; e += kAllThreads) {
-    // Position in its stream, and position of that stream's column list.  Each tile row walks its runs
-    // from a slightly different starting point: the workgroups of one XCD all read the same activation rows,
-    // and 256-byte pieces at the same tile column of rows K*2 bytes apart sit in the same L2 channel, so
-    // workgroups marching exactly in step would all queue at one channel.  The starting points lie within 8
-    // tiles of each other, no further: the workgroups that share an M block then sweep the tile columns
-    // together, in ascending order inside a run, and an activation block that one of them has brought into
-    // the XCD's L2 is still there for the others.  (With starting points spread over the whole run, as they
-    // were at first, every workgroup streamed its M block by itself as soon as that no longer fitted in L2:
-    // 6.9 GB fetched per call on 28672 -> 8192 at M = 2048 instead of 1.9 GB, 1003 us instead of 901.)
-    const int32_t lo = e < end2 ? 0 : e < end3 ? end2 : end3;
-    const int32_t n = (e < end2 ? end2 : e < end3 ? end3 : p.ntc) - lo;
-    const int32_t i = (e - lo + (tr * 5) % 8) % n;
-    const int32_t slot = (e < end2 ? first2 : e < end3 ? first3 : first4) + i;
-    const int32_t cols = e < end2 ? 0 : e < end3 ? total2 : total2 + total3;
-    const int32_t tc = col_idx[cols + slot];
-    if constexpr (RING) {
-      const uint32_t bw = e < end2 ? 2 : e < end3 ? 3 : 4;
-      const uint64_t src = (uint64_t)(bw == 2 ? p.s2 : bw == 3 ? p.s3 : p.s4) + (uint64_t)(uint32_t)slot * (2048 * bw);
-      const uint32_t par = (uint32_t)(G64 ? 2 * tc : tc >> p.gshift) * (uint32_t)(2 * p.N);
-      tiles[e] = uint4{(uint32_t)src, (uint32_t)(src >> 32), par, ((uint32_t)tc << 15) | bw};
-    } else {
-      seq[e] = (slot << 9) | tc;
+  // the 3-bit, then the 4-bit ones, each in ascending column order; the order of a sum is free): three loops, each with a
+  // straight-line body for its width.  The sequence is laid out from the tile descriptors of the row (slot << 2 | width
+  // - 2, one per tile column), whose address depends on the arguments alone: ranks by ballots, per 64 columns, instead of
+  // the row's runs in the CSR part of the table, which are a dependent trip to memory later.
+  int end2 = 0, end3 = 0;  // positions of the first 3-bit and of the first 4-bit tile
+  {
+    const int32_t* desc = p.index + 3 + (int64_t)tr * p.ntc;
+    constexpr int kPer = (kPrefillMaxTiles + kAllThreads - 1) / kAllThreads;
+    constexpr int kChunks = kPer * (kAllThreads / kWave);
+    static_assert(kPrefillMaxTiles <= kPer * kAllThreads, "one descriptor per thread and pass");
+    int32_t d[kPer];
+    uint64_t is2[kPer], is3[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = (int)threadIdx.x + u * kAllThreads;
+      d[u] = e < p.ntc ? desc[e] : 3;
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      is2[u] = __ballot((d[u] & 3) == 0);
+      is3[u] = __ballot((d[u] & 3) == 1);
+      if (lane == 0) counts[(int)threadIdx.x / kWave + u * (kAllThreads / kWave)] = int2{__popcll(is2[u]), __popcll(is3[u])};
+    }
+    __syncthreads();
+    int2 before[kPer] = {};
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int2 n = counts[c];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        if (c < (int)threadIdx.x / kWave + u * (kAllThreads / kWave)) before[u].x += n.x, before[u].y += n.y;
+      end2 += n.x, end3 += n.y;
+    }
+    end2 = __builtin_amdgcn_readfirstlane(end2);
+    end3 = end2 + __builtin_amdgcn_readfirstlane(end3);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = (int)threadIdx.x + u * kAllThreads;  // = tile column
+      if (e < p.ntc) {
+        // Each tile row walks its runs from a slightly different starting point: the workgroups of one XCD all read the
+        // same activation rows, and 256-byte pieces at the same tile column of rows K*2 bytes apart sit in the same L2
+        // channel, so workgroups marching exactly in step would all queue at one channel.  The starting points lie
+        // within 8 tiles of each other, no further: the workgroups that share an M block then sweep the tile columns
+        // together, in ascending order inside a run, and an activation block that one of them has brought into
+        // the XCD's L2 is still there for the others.  (With starting points spread over the whole run, as they
+        // were at first, every workgroup streamed its M block by itself as soon as that no longer fitted in L2:
+        // 6.9 GB fetched per call on 28672 -> 8192 at M = 2048 instead of 1.9 GB, 1003 us instead of 901.)
+        const uint64_t below = (1ull << lane) - 1;
+        const int rank2 = before[u].x + __popcll(is2[u] & below), rank3 = before[u].y + __popcll(is3[u] & below);
+        const uint32_t bw = (uint32_t)(d[u] & 3) + 2;
+        const int lo = bw == 2 ? 0 : bw == 3 ? end2 : end3;
+        const int n = (bw == 2 ? end2 : bw == 3 ? end3 : p.ntc) - lo;
+        const int rank = bw == 2 ? rank2 : bw == 3 ? rank3 : e - rank2 - rank3;
+        const int back = rank - (int)((uint32_t)((tr * 5) % 8) % (uint32_t)n);
+        const int pos = lo + (back < 0 ? back + n : back);
+        const uint32_t slot = (uint32_t)d[u] >> 2;
+        if constexpr (RING) {
+          const uint64_t src = (uint64_t)(bw == 2 ? p.s2 : bw == 3 ? p.s3 : p.s4) + (uint64_t)slot * (2048 * bw);
+          const uint32_t par = (uint32_t)(G64 ? 2 * e : e >> p.gshift) * (uint32_t)(2 * p.N);
+          tiles[pos] = uint4{(uint32_t)src, (uint32_t)(src >> 32), par, ((uint32_t)e << 15) | bw};
+        } else {
+          seq[pos] = (int32_t)(slot << 9) | e;
+        }
+      }
     }
   }
   __syncthreads();
