@@ -10,7 +10,7 @@
 //  2. prefill_kernel: workgroup = 128 (M) x 128 (N, one tile row) output block, 4 wavefronts, each
 //     128 rows x 32 columns (two slabs), two workgroups per CU.  K is walked one 128x128 weight tile
 //     (= one quantisation group) per step, the tiles of the tile row sorted by width (the order of a
-//     sum is free, and the CSR part of the block-index table lists exactly these runs): three loops,
+//     sum is free; ranks by ballots over the row's tile descriptors): three loops,
 //     each with a straight-line body for its width.  A packed slab is already laid out as an MFMA B
 //     operand (lane = weight row-in-16 x k-block of 8), so the weights never touch LDS: each
 //     wavefront loads the slabs of its own output columns and dequantises them in registers (mask-or
