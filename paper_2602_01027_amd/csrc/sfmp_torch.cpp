@@ -67,7 +67,7 @@ Read tensor_rows(PyObject* o, int64_t* rows, int64_t* numel, int64_t* bytes) {
   }
 }
 
-// Address of the C struct of an SfmpLayout (which the caller keeps alive through the call)
+// Address of the C struct of an SfmpLayout (the caller holds a reference through the call)
 Read layout_address(PyObject* o, const sfmp_layout_t** out) {
   if ((PyObject*)Py_TYPE(o) != layout_type) return kOther;
   Py_buffer b;
@@ -135,13 +135,31 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 constexpr Py_ssize_t kMaxBatch = 8;  // more are refused by the library: left to the general path
 
+// References to everything whose address has been read, dropped when the call returns (with the GIL held).  The tensors
+// and layouts of a batch hang on a list and on attributes that other Python code - an attribute lookup of this call, a
+// stream object's property, another thread while the library runs without the GIL - may change or clear meanwhile.
+struct Held {
+  PyObject* ref[1 + 8 * kMaxBatch];
+  int count = 0;
+  void take(PyObject* owned) { ref[count++] = owned; }
+  Held() = default;
+  Held(const Held&) = delete;
+  Held& operator=(const Held&) = delete;
+  ~Held() {
+    while (count > 0) Py_DECREF(ref[--count]);
+  }
+};
+
 // problems: list or tuple of (X, col_perm, DevicePacked, row_perm, Y)
-Read read_problems(PyObject* problems, sfmp_gemv_problem_t* out, int32_t* count) {
+Read read_problems(PyObject* problems, sfmp_gemv_problem_t* out, int32_t* count, Held* held) {
   if (!PyList_CheckExact(problems) && !PyTuple_CheckExact(problems)) return kOther;
-  const Py_ssize_t n = PySequence_Fast_GET_SIZE(problems);
+  PyObject* all = PySequence_Tuple(problems);  // (its items, and theirs, stay as they are through the call)
+  if (!all) return kError;
+  held->take(all);
+  const Py_ssize_t n = PyTuple_GET_SIZE(all);
   if (n > kMaxBatch) return kOther;
   for (Py_ssize_t i = 0; i < n; ++i) {
-    PyObject* q = PySequence_Fast_GET_ITEM(problems, i);
+    PyObject* q = PyTuple_GET_ITEM(all, i);
     if (!PyTuple_CheckExact(q) || PyTuple_GET_SIZE(q) != 5) return kOther;
     PyObject* dp = PyTuple_GET_ITEM(q, 2);
     const void* v[12] = {};
@@ -150,12 +168,9 @@ Read read_problems(PyObject* problems, sfmp_gemv_problem_t* out, int32_t* count)
     for (int k = 0; k < 8; ++k) {
       PyObject* o = PyObject_GetAttr(dp, names[k]);
       if (!o) return kError;
-      // (the attribute stays alive: the DevicePacked holds it through the call, which runs no other Python code)
+      held->take(o);
       const Read r = k == 0 ? layout_address(o, (const sfmp_layout_t**)&v[2]) : tensor_address(o, false, &v[2 + k]);
-      const bool held = Py_REFCNT(o) > 1;
-      Py_DECREF(o);
       if (r != kTaken) return r;
-      if (!held) return kOther;  // made by the access itself: not kept by the object
     }
     if (Read r = tensor_address(PyTuple_GET_ITEM(q, 3), false, &v[10])) return r;
     if (Read r = tensor_address(PyTuple_GET_ITEM(q, 4), false, &v[11])) return r;
@@ -173,10 +188,11 @@ PyObject* gemv_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
     return nullptr;
   }
+  Held held;
   sfmp_gemv_problem_t q[kMaxBatch];
   int32_t count = 0;
   void* stream = nullptr;
-  SFMP_READ(read_problems(a[0], q, &count));
+  SFMP_READ(read_problems(a[0], q, &count, &held));
   SFMP_READ(stream_handle(a[1], &stream));
   int rc;
   Py_BEGIN_ALLOW_THREADS;
@@ -191,6 +207,7 @@ PyObject* gemm_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
     PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
     return nullptr;
   }
+  Held held;
   sfmp_gemv_problem_t q[kMaxBatch];
   int32_t count = 0;
   void* stream = nullptr;
@@ -200,7 +217,7 @@ PyObject* gemm_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
   int overflow = 0;
   const long M = PyLong_AsLongAndOverflow(a[1], &overflow);
   if (overflow || M < INT32_MIN || M > INT32_MAX) Py_RETURN_NONE;
-  SFMP_READ(read_problems(a[0], q, &count));
+  SFMP_READ(read_problems(a[0], q, &count, &held));
   if (a[2] == Py_None) Py_RETURN_NONE;
   SFMP_READ(tensor_rows(a[2], nullptr, &numel, nullptr));
   if (numel == 0) Py_RETURN_NONE;

@@ -262,7 +262,7 @@ def test_float_reciprocal_item_index_is_exact():
             assert np.array_equal(j, e // c), c
 
 
-@pytest.mark.parametrize("odd", ["host tensor", "subclass", "layout", "no tensor", "short tuple", "property", "nine"])
+@pytest.mark.parametrize("odd", ["host tensor", "subclass", "layout", "no tensor", "short tuple", "nine"])
 def test_launcher_leaves_calls_that_are_not_plain_to_the_general_path(odd):
     # the extension that marshals the launches answers None (nothing launched) for anything but plain device tensors; the
     # ctypes path then raises what it always raised
@@ -274,10 +274,6 @@ def test_launcher_leaves_calls_that_are_not_plain_to_the_general_path(odd):
     class Sub(torch.Tensor):
         pass
 
-    class Packed:  # an attribute that is made by the access and kept by nobody
-        layout, s2, s3, s4, index, scales, zeros = L, t, t, t, t, t, t
-        bitmap = property(lambda self: torch.zeros(1))
-
     gemm_args = [t, None, L, t, t, t, t, t, t, t, None, t, t, None]
     dp = S.DevicePacked(L, t, t, t, t, t, t, t)
     if odd in ("host tensor", "subclass", "layout", "no tensor"):
@@ -286,7 +282,78 @@ def test_launcher_leaves_calls_that_are_not_plain_to_the_general_path(odd):
         assert module.gemm(*gemm_args) is None
         assert module.gemm_static(*gemm_args[:12], None) is None
     else:
-        q = {"short tuple": [(t, None, dp, None)], "property": [(t, None, Packed(), None, t)],
-             "nine": [(t, None, dp, None, t)] * 9}[odd]
+        q = {"short tuple": [(t, None, dp, None)], "nine": [(t, None, dp, None, t)] * 9}[odd]
         assert module.gemv_batched(q, None) is None
         assert module.gemm_batched(q, 2, t, None) is None
+
+
+@pytest.mark.parametrize("entry", ["gemv_batched", "gemm_batched"])
+@pytest.mark.parametrize("when", ["attribute", "stream", "library", "made by the access"])
+def test_launcher_keeps_the_arguments_of_a_batch_alive(entry, when):
+    # The list of problems is emptied during the call: by an attribute lookup of the call itself, by the stream object's
+    # property, or while the library runs (without the GIL, where any other thread may do it).  What the library was given
+    # has to stay alive and unchanged until it returns; so has an attribute that its access makes and nobody else keeps.
+    import gc
+    import weakref
+    import torch
+    module = S.binding._launcher()
+    lib = S.load_library()
+    expected = bytes(S.sfmp_pack_query(np.full((2, 1), 3, dtype=np.int8), 256, 128))
+    seen, problems, refs = [], [], []
+
+    def drop(at):
+        if at == when:
+            problems.clear()
+            gc.collect()
+
+    class Packed(S.DevicePacked):
+        def __getattribute__(self, name):
+            if name == "s3":
+                drop("attribute")
+            if name == "bitmap" and when == "made by the access":
+                made = torch.zeros(128)
+                refs.append(weakref.ref(made))
+                return made
+            return super().__getattribute__(name)
+
+    class Stream:
+        @property
+        def cuda_stream(self):
+            drop("stream")
+            return 0
+
+    def fill():
+        t = lambda: torch.zeros((1, 128), dtype=torch.float16)
+        for _ in range(2):
+            layout = S.sfmp_pack_query(np.full((2, 1), 3, dtype=np.int8), 256, 128)
+            x, packed, y = t(), Packed(layout, *(t() for _ in range(7))), t()
+            refs.extend(weakref.ref(o) for o in (layout, packed, x, y))
+            problems.append((x, None, packed, None, y))
+
+    def library(array, count, *_rest):
+        drop("library")
+        seen.append(([r() is not None for r in refs], count,
+                     [C.string_at(S.binding.SfmpGemvProblem.from_address(array + i * C.sizeof(S.binding.SfmpGemvProblem)).layout, 72)
+                      for i in range(count)]))
+        return 0
+
+    fill()
+    int32, vp = C.c_int32, C.c_void_p
+    ours = (C.CFUNCTYPE(int32, vp, int32, vp)(library) if entry == "gemv_batched" else
+            C.CFUNCTYPE(int32, vp, int32, int32, vp, C.c_int64, vp)(library))
+    addresses = [C.cast(f, vp).value for f in (lib.sfmp_gemm, lib.sfmp_gemm_static, lib.sfmp_gemv_batched, lib.sfmp_gemm_batched)]
+    replaced = list(addresses)
+    replaced[2 if entry == "gemv_batched" else 3] = C.cast(ours, vp).value
+    bind = lambda a: module.bind(S.SfmpLayout, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, *a)
+    bind(replaced)
+    try:
+        if entry == "gemv_batched":
+            rc = module.gemv_batched(problems, Stream())
+        else:
+            rc = module.gemm_batched(problems, 2, torch.zeros(256, dtype=torch.uint8), Stream())
+    finally:
+        bind(addresses)
+    assert rc == 0 and (problems == [] or when == "made by the access")
+    assert seen == [([True] * len(refs), 2, [expected] * 2)] and len(refs) == (10 if when == "made by the access" else 8)
+    problems.clear()
+    assert not any(r() is not None for r in refs)  # and no longer than that
