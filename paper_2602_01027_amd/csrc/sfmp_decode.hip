@@ -27,6 +27,7 @@
 
 #include "sfmp_device.h"
 #include "sfmp_internal.h"
+#include "sfmp_stream_schedule.h"
 
 namespace sfmp {
 
@@ -1135,65 +1136,61 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
 
   if constexpr (RS > 0) {
     describe(0, E);  // (at most 64 items)
-    half8 as0[4], as1[4], as2[4];
-    auto load_a = [&](half8 (&set)[4], int i) __attribute__((always_inline)) {
-      const int tc = min(wave + NW * i, p.ntc - 1);  // (past the end: the last tile column again)
-#pragma unroll
-      for (int kappa = 0; kappa < 4; ++kappa)
-        set[kappa] = *reinterpret_cast<const half8*>(p.xblk + ((((size_t)tc * 4 + kappa) * 4 + kb) * MB + (i16 & (MB - 1))) * 16);
-    };
-    auto issue_column = [&](int i, int slot) __attribute__((always_inline)) {
-#pragma unroll
-      for (int j = 0; j < RS; ++j)
-        if (j < nj) issue_item(j * my_cnt + i, slot * RS + j);
-    };
     floatx4 accq[RS], accz[RS];
 #pragma unroll
     for (int j = 0; j < RS; ++j) accq[j] = floatx4{0.f, 0.f, 0.f, 0.f}, accz[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // tile column i with its operands in `set`, its slabs in slot i mod 3; false behind the last one
-    auto column = [&](int i, half8 (&set)[4], auto slot_tag) __attribute__((always_inline)) {
-      constexpr int slot = decltype(slot_tag)::value;
-      // D(i) has landed once only A(i+2) and D(i+1) are outstanding (a workgroup with fewer slabs than RS: D(i+1) is
-      // shorter, and so is what may be outstanding)
-      if (i + 1 < my_cnt) {
-        if (nj == RS)
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + 2 * RS) : "memory");
-        else
-          asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-      } else {
-        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-      }
-      __builtin_amdgcn_s_setprio(1);
-      floatx4 sx = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (!G64) {
-#pragma unroll
-        for (int kappa = 0; kappa < 4; ++kappa) sx = __builtin_amdgcn_mfma_f32_16x16x32_f16(set[kappa], ones, sx, 0, 0, 0);
-      }
-#pragma unroll
-      for (int j = 0; j < RS; ++j)
-        if (j < nj) {
-          const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, j * my_cnt + i);
-          consume_with(misc, ring + (slot * RS + j) * kSlot, set, sx, accq[j], accz[j]);
-        }
-      __builtin_amdgcn_s_setprio(0);
-      load_a(set, i + 3);
-      if (i + 2 < my_cnt) issue_column(i + 2, (slot + 2) % 3);
-      return i + 1 < my_cnt;
-    };
     if (my_cnt > 0) {
-      const std::integral_constant<int, 0> t0;
-      const std::integral_constant<int, 1> t1;
-      const std::integral_constant<int, 2> t2;
-      load_a(as0, 0);
-      load_a(as1, 1);
-      issue_column(0, 0);
-      load_a(as2, 2);
-      if (my_cnt > 1) issue_column(1, 1);
-      for (int i = 0;; i += 3) {
-        if (!column(i, as0, t0)) break;
-        if (!column(i + 1, as1, t1)) break;
-        if (!column(i + 2, as2, t2)) break;
-      }
+      half8 as0[4], as1[4], as2[4];
+      auto set_of = [&](auto set) __attribute__((always_inline)) -> half8(&)[4] {
+        constexpr int s = decltype(set)::value;
+        if constexpr (s == 0) return as0;
+        else if constexpr (s == 1) return as1;
+        else return as2;
+      };
+      auto load = [&](auto set, int i) __attribute__((always_inline)) {
+        half8(&v)[4] = set_of(set);
+        const int tc = min(wave + NW * i, p.ntc - 1);  // (past the end: the last tile column again)
+#pragma unroll
+        for (int kappa = 0; kappa < 4; ++kappa)
+          v[kappa] = *reinterpret_cast<const half8*>(p.xblk + ((((size_t)tc * 4 + kappa) * 4 + kb) * MB + (i16 & (MB - 1))) * 16);
+      };
+      auto copy = [&](auto slot, int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < RS; ++j)
+          if (j < nj) issue_item(j * my_cnt + i, decltype(slot)::value * RS + j);
+      };
+      auto wait = [&](int columns) __attribute__((always_inline)) {
+        // (4 loads, and 2 RS copies for a column; a workgroup with fewer slabs than RS makes 2)
+        if (columns) {
+          if (nj == RS)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + 2 * RS) : "memory");
+          else
+            asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        } else {
+          asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        }
+      };
+      auto use = [&](auto set, int i) __attribute__((always_inline)) {
+        half8(&v)[4] = set_of(set);
+        __builtin_amdgcn_s_setprio(1);
+        floatx4 sx = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (!G64) {
+#pragma unroll
+          for (int kappa = 0; kappa < 4; ++kappa) sx = __builtin_amdgcn_mfma_f32_16x16x32_f16(v[kappa], ones, sx, 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < RS; ++j)
+          if (j < nj) {
+            const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, j * my_cnt + i);
+            consume_with(misc, ring + (decltype(set)::value * RS + j) * kSlot, v, sx, accq[j], accz[j]);
+          }
+        __builtin_amdgcn_s_setprio(0);
+      };
+      auto keep_loads = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int kappa = 0; kappa < 4; ++kappa) asm volatile("" ::"v"(as0[kappa]), "v"(as1[kappa]), "v"(as2[kappa]));
+      };
+      stream_columns(my_cnt, load, copy, wait, use, keep_loads);
 #pragma unroll
       for (int j = 0; j < RS; ++j)
         if (j < nj) keep_sums(j, accq[j] * 16777216.f + accz[j]);

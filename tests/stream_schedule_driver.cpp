@@ -1,0 +1,79 @@
+// Runs the schedule of the streamed-activation form (csrc/sfmp_stream_schedule.h) against a model of a wavefront's memory
+// queue: requests complete in order, a wait returns with as many outstanding as it allows.  A load whose value nothing
+// reads may not be made at all (a compiler may leave it out), so every walk is checked with those loads and without them.
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "../paper_2602_01027_amd/csrc/sfmp_stream_schedule.h"
+
+struct Event {
+  enum Kind { kLoad, kCopy, kWait, kUse, kKeep } kind;
+  int place;   // set or slot (kWait: columns)
+  int column;
+  bool read;   // kLoad: something consumes the value
+};
+
+static void fail(const char* what, int count, int slabs, bool unread, int column) {
+  std::printf("%s: %d columns, %d slabs, unread loads %s, column %d\n", what, count, slabs, unread ? "made" : "left out", column);
+  std::exit(1);
+}
+
+static void check(const std::vector<Event>& events, int count, int slabs, bool unread) {
+  std::vector<int> requests;  // the queue: one entry per instruction, +column + 1 for slabs, -(column + 1) for activations
+  size_t complete = 0;        // how many of them are known to have completed
+  int in_set[3] = {-1, -1, -1}, in_slot[3] = {-1, -1, -1}, next = 0;
+  bool set_free[3] = {true, true, true}, slot_free[3] = {true, true, true};
+  for (const Event& e : events) {
+    switch (e.kind) {
+      case Event::kLoad:
+        if (!set_free[e.place]) fail("set overwritten before its use", count, slabs, unread, e.column);
+        in_set[e.place] = e.column, set_free[e.place] = e.column >= count;
+        if (e.read || unread) requests.insert(requests.end(), 4, -(e.column + 1));
+        break;
+      case Event::kCopy:
+        if (!slot_free[e.place]) fail("slot overwritten before its use", count, slabs, unread, e.column);
+        in_slot[e.place] = e.column, slot_free[e.place] = false;
+        requests.insert(requests.end(), 2 * slabs, e.column + 1);
+        break;
+      case Event::kWait: {
+        const size_t allowed = 4 + 2 * (size_t)slabs * e.place;
+        if (requests.size() > allowed && requests.size() - allowed > complete) complete = requests.size() - allowed;
+        break;
+      }
+      case Event::kUse:
+        if (e.column != next++) fail("columns out of order", count, slabs, unread, e.column);
+        if (in_set[e.place] != e.column || in_slot[e.place] != e.column) fail("another column's data", count, slabs, unread, e.column);
+        for (size_t r = complete; r < requests.size(); ++r)
+          if (requests[r] == e.column + 1) fail("slabs used before they have landed", count, slabs, unread, e.column);
+        set_free[e.place] = slot_free[e.place] = true;
+        break;
+      case Event::kKeep:
+        break;
+    }
+  }
+  if (next != count) fail("columns left out", count, slabs, unread, next);
+}
+
+int main() {
+  for (int count = 1; count <= 64; ++count) {
+    std::vector<Event> events;
+    auto load = [&](auto set, int i) { events.push_back({Event::kLoad, decltype(set)::value, i, false}); };
+    auto copy = [&](auto slot, int i) { events.push_back({Event::kCopy, decltype(slot)::value, i, false}); };
+    auto wait = [&](int columns) { events.push_back({Event::kWait, columns, 0, false}); };
+    auto use = [&](auto set, int i) { events.push_back({Event::kUse, decltype(set)::value, i, false}); };
+    auto keep = [&]() { events.push_back({Event::kKeep, 0, 0, false}); };
+    sfmp::stream_columns(count, load, copy, wait, use, keep);
+    for (size_t a = 0; a < events.size(); ++a) {
+      if (events[a].kind != Event::kLoad) continue;
+      for (size_t b = a + 1; b < events.size(); ++b) {
+        const bool same = events[b].place == events[a].place;
+        if (events[b].kind == Event::kKeep || (events[b].kind == Event::kUse && same)) events[a].read = true;
+        if (events[b].kind == Event::kLoad && same) break;
+      }
+    }
+    for (int slabs = 1; slabs <= 2; ++slabs)
+      for (bool unread : {false, true}) check(events, count, slabs, unread);
+  }
+  std::puts("ok");
+}
