@@ -27,7 +27,7 @@
 
 #include "sfmp_device.h"
 #include "sfmp_internal.h"
-#include "sfmp_stream_schedule.h"
+#include "sfmp_schedule.h"
 
 namespace sfmp {
 

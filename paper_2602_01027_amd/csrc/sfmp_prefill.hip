@@ -31,6 +31,7 @@
 
 #include "sfmp_device.h"
 #include "sfmp_internal.h"
+#include "sfmp_schedule.h"
 
 namespace sfmp {
 
@@ -427,18 +428,20 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
   // row block are never written and feed only output rows that are never stored
   const _Float16* xbase = p.Xp + (int64_t)(m0 / kTile) * p.ntc * (kTile * kTile) + (m0 % kTile) * kTile;
   const uint64_t xb64 = (uint64_t)xbase;
-  const u32x4 xrsrc = {(uint32_t)xb64, (uint32_t)(xb64 >> 32), (uint32_t)p.ntc * (uint32_t)(kTile * kTile * 2), 0x00020000u};
+  const uint32_t xbytes = (uint32_t)p.ntc * (uint32_t)(kTile * kTile * 2);  // of the row block
   const uint32_t xs_base = (uint32_t)(uintptr_t)(lptr_t)Xs;
-  // copies [first, last) of the block of tile position e into buffer `buf`
-  auto issue_x_part = [&](uint32_t soff, int buf, int first, int last) __attribute__((always_inline)) {
+  // copies [first, last) of a block into buffer `buf`
+  auto issue_x_part = [&](const BlockRequest& x, int buf, int first, int last) __attribute__((always_inline)) {
+    const u32x4 rsrc = {(uint32_t)xb64, (uint32_t)(xb64 >> 32), x.records, 0x00020000u};
     const uint32_t dst = xs_base + (uint32_t)buf * kBufBytes + wave * 1024;
 #pragma unroll
-    for (int i = first; i < last; ++i) load_to_lds_16(xrsrc, soff, xoff[i], dst + i * (S::kRowsPerPass * 256));
+    for (int i = first; i < last; ++i) load_to_lds_16(rsrc, x.offset, xoff[i], dst + i * (S::kRowsPerPass * 256));
   };
   // block of tile position e into the buffer that block `like` uses (like = e mod 2, except for the idle
   // loads past the end)
   auto issue_x = [&](int e, int like) __attribute__((always_inline)) {
-    issue_x_part((uint32_t)(__builtin_amdgcn_readfirstlane(seq[e]) & 511) << 15, like & 1, 0, S::kPasses);
+    const uint32_t tc = (uint32_t)(__builtin_amdgcn_readfirstlane(seq[e]) & 511);
+    issue_x_part(block_request(tc << 15, xbytes, true), like & 1, 0, S::kPasses);
   };
   // operand read addresses: row 16*(MI*wm + i) + i16, unit 4*kappa + kb -> byte offset aoff[kappa] + 4096*i
   uint32_t aoff[4];
@@ -710,11 +713,12 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
                    (uint32_t)__builtin_amdgcn_readfirstlane((int)d.z), (uint32_t)__builtin_amdgcn_readfirstlane((int)d.w)};
     };
     auto desc = [&](int e) __attribute__((always_inline)) { return uniform(tiles[min(e, e_last)]); };
-    // offset of the block of position e whose descriptor is d; past the end: an offset past the buffer, from which the
-    // copies read nothing (so that every step has the same number of copies)
-    const uint32_t x_end = (uint32_t)p.ntc << 15;
-    auto xsoff = [&](const uint4& d, int e) __attribute__((always_inline)) { return e <= e_last ? d.w & ~0x7FFFu : x_end; };
-    uint32_t xo2, xo3;  // offsets of blocks e + 2 and e + 3
+    // the block of position e whose descriptor is d; past the end: copies that read nothing (every step has the same
+    // number of copies)
+    auto xreq = [&](const uint4& d, int e) __attribute__((always_inline)) {
+      return block_request(d.w & ~0x7FFFu, xbytes, e <= e_last);
+    };
+    BlockRequest xo2, xo3;  // blocks e + 2 and e + 3
     uint4 wd;           // descriptor of tile e + 4
     auto rstep = [&](auto btag, auto in_run, int e) __attribute__((always_inline)) {
       const int b1n = next(xb), b2n = next(b1n);
@@ -752,7 +756,7 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
       if (e + 4 <= e_last) issue_w_ring(wd, b1n);
       issue_x_part(xo3, xb, 0, kQuarter);
       xo2 = xo3;
-      xo3 = xsoff(wd, e + 4);
+      xo3 = xreq(wd, e + 4);
       wd = uniform(dn);
       __builtin_amdgcn_sched_barrier(0);
       mfmas(a1, b1);
@@ -773,12 +777,12 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
       const uint4 d0 = desc(e_first), d1 = desc(e_first + 1), d2 = desc(e_first + 2), d3 = desc(e_first + 3);
       wd = desc(e_first + 4);
       issue_w_ring(d0, 0);
-      issue_x_part(xsoff(d0, e_first), 0, 0, S::kPasses);
+      issue_x_part(xreq(d0, e_first), 0, 0, S::kPasses);
       if (e_first + 1 <= e_last) issue_w_ring(d1, 1);
-      issue_x_part(xsoff(d1, e_first + 1), 1, 0, S::kPasses);
+      issue_x_part(xreq(d1, e_first + 1), 1, 0, S::kPasses);
       if (e_first + 2 <= e_last) issue_w_ring(d2, 2);
-      xo2 = xsoff(d2, e_first + 2);
-      xo3 = xsoff(d3, e_first + 3);
+      xo2 = xreq(d2, e_first + 2);
+      xo3 = xreq(d3, e_first + 3);
       // tiles 0 and 1 and block 0 have landed (tile 2 and block 1 may be on their way)
       if (e_first + 2 <= e_last)
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::kPasses + 3) : "memory");

@@ -1,7 +1,9 @@
-// Order of the requests and waits of one wavefront in the small-batch form whose activations are streamed through
-// registers (sfmp_decode.hip, RS): apart from the kernel so that a host program can run it against a model of the memory
-// queue (tests/stream_schedule_driver.cpp).
+// The parts of the kernels' requests to memory that a host program can run against a model (tests/schedule_driver.cpp):
+// the order of requests and waits of the small-batch form whose activations are streamed through registers (sfmp_decode.hip,
+// RS), and what a copy of an activation block asks for (sfmp_prefill.hip).
 #pragma once
+
+#include <stdint.h>
 
 #if defined(__HIP__)
 #define SFMP_SCHEDULE_FN __device__ __forceinline__
@@ -51,6 +53,16 @@ SFMP_SCHEDULE_FN void stream_columns(const int count, const Load& load, const Co
     if (!column(i + 2, Const<2>())) break;
   }
   keep_loads();
+}
+
+// Copy of the activation block of one tile column through a raw buffer descriptor: scalar offset and number of records
+// (bytes).  Past the end (of a schedule that makes the same number of copies in every step) a request of nothing: no
+// records and no scalar offset, out of range whether or not the scalar offset counts in the range check.
+struct BlockRequest {
+  uint32_t offset, records;
+};
+SFMP_SCHEDULE_FN BlockRequest block_request(const uint32_t column_offset, const uint32_t bytes, const bool wanted) {
+  return BlockRequest{wanted ? column_offset : 0u, wanted ? bytes : 0u};
 }
 
 }  // namespace sfmp

@@ -1,11 +1,16 @@
-// Runs the schedule of the streamed-activation form (csrc/sfmp_stream_schedule.h) against a model of a wavefront's memory
-// queue: requests complete in order, a wait returns with as many outstanding as it allows.  A load whose value nothing
-// reads may not be made at all (a compiler may leave it out), so every walk is checked with those loads and without them.
+// Host checks of csrc/sfmp_schedule.h.
+//
+// The schedule of the streamed-activation form against a model of a wavefront's memory queue: requests complete in order, a
+// wait returns with as many outstanding as it allows.  A load whose value nothing reads may not be made at all (a compiler
+// may leave it out), so every walk is checked with those loads and without them.
+//
+// Copies of activation blocks against the range check of a raw buffer, with the scalar offset counted in it and not: what is
+// wanted is read from inside the row block, and nothing is read past the end.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
 
-#include "../paper_2602_01027_amd/csrc/sfmp_stream_schedule.h"
+#include "../paper_2602_01027_amd/csrc/sfmp_schedule.h"
 
 struct Event {
   enum Kind { kLoad, kCopy, kWait, kUse, kKeep } kind;
@@ -55,7 +60,26 @@ static void check(const std::vector<Event>& events, int count, int slabs, bool u
   if (next != count) fail("columns left out", count, slabs, unread, next);
 }
 
+static void check_block_requests() {
+  constexpr uint32_t kBlock = 32768;  // bytes of a tile column's block of 128 rows
+  for (uint32_t ntc : {1u, 8u, 57u, 448u})
+    for (uint32_t tc = 0; tc < ntc; ++tc)
+      for (bool wanted : {true, false}) {
+        const sfmp::BlockRequest x = sfmp::block_request(tc * kBlock, ntc * kBlock, wanted);
+        for (uint32_t lane_offset = 0; lane_offset < kBlock; lane_offset += 16) {
+          const bool read_with = lane_offset < x.records - x.offset;  // (unsigned, as the hardware's documents put it)
+          const bool read_without = lane_offset < x.records;
+          const bool inside = (uint64_t)x.offset + lane_offset + 16 <= (uint64_t)ntc * kBlock;
+          if (wanted ? !(read_with && read_without && inside) : (read_with || read_without)) {
+            std::printf("block request: column %u of %u, wanted %d, lane offset %u\n", tc, ntc, (int)wanted, lane_offset);
+            std::exit(1);
+          }
+        }
+      }
+}
+
 int main() {
+  check_block_requests();
   for (int count = 1; count <= 64; ++count) {
     std::vector<Event> events;
     auto load = [&](auto set, int i) { events.push_back({Event::kLoad, decltype(set)::value, i, false}); };
