@@ -2,11 +2,14 @@
 memory and streams here).  No fallback: a missing library raises.
 
 The launch entry points are marshalled by a small extension (csrc/sfmp_torch.cpp), everything else by ctypes.  The
-extension takes calls whose arguments are plain tensors and leaves any other call to the ctypes path below it."""
+extension takes calls whose arguments are plain tensors and leaves any other call to the ctypes path below it, which calls
+the same library; without an extension built for the running torch and Python every call takes that path (with a warning)."""
 from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -81,11 +84,38 @@ def load_library():
     return lib
 
 
+class _NoExtension:
+    """Stands in for the extension where there is none to use: leaves every call to the ctypes path."""
+    gemm = gemm_static = gemv_batched = gemm_batched = staticmethod(lambda *args: None)
+
+
 _LAUNCHER = None  # (library, extension module bound to it)
 
 
 def launcher_path() -> str:
     return os.path.join(_HERE, "_sfmp_torch.so")
+
+
+def launcher_target() -> str:
+    """What an extension has to be built for: it reads torch's and Python's objects by the layout of their headers."""
+    import torch
+    return f"torch {torch.__version__}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
+def _load_extension():
+    import importlib.util
+
+    import torch  # noqa: F401  (first: the extension uses its libraries)
+    path = launcher_path()
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is missing")
+    spec = importlib.util.spec_from_file_location("_sfmp_torch", path)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    built_for = getattr(module, "built_for", "another version")
+    if built_for != launcher_target():
+        raise ImportError(f"{path} is built for {built_for}, running {launcher_target()}")
+    return module
 
 
 def _launcher():
@@ -94,19 +124,16 @@ def _launcher():
     lib = load_library()
     if _LAUNCHER is not None and _LAUNCHER[0] is lib:
         return _LAUNCHER[1]
-    import importlib.util
-
-    import torch  # (first: the extension uses its libraries)
-    path = launcher_path()
-    if not os.path.exists(path):
-        raise FileNotFoundError(f"{path} is missing: build it with `python -m paper_2602_01027_amd.build` "
-                                "(or __graft_entry__.build())")
-    spec = importlib.util.spec_from_file_location("_sfmp_torch", path)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    module.bind(SfmpLayout, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
-                *(C.cast(f, C.c_void_p).value for f in (lib.sfmp_gemm, lib.sfmp_gemm_static, lib.sfmp_gemv_batched,
-                                                        lib.sfmp_gemm_batched)))
+    import torch
+    try:
+        module = _load_extension()
+        module.bind(SfmpLayout, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+                    *(C.cast(f, C.c_void_p).value for f in (lib.sfmp_gemm, lib.sfmp_gemm_static, lib.sfmp_gemv_batched,
+                                                            lib.sfmp_gemm_batched)))
+    except ImportError as e:
+        warnings.warn(f"launches are marshalled by ctypes, some 8 us of host time more per call: {e}; build it with "
+                      "`python -m paper_2602_01027_amd.build` (or __graft_entry__.build())", RuntimeWarning, stacklevel=3)
+        module = _NoExtension
     _LAUNCHER = (lib, module)
     return module
 

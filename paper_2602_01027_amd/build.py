@@ -49,9 +49,11 @@ def _build_torch_extension() -> str:
 
     import torch
     from torch.utils.cpp_extension import include_paths
+
+    from .binding import launcher_target
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I" + sysconfig.get_paths()["include"],
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f'-DSFMP_BUILT_FOR="{launcher_target()}"', "-I" + sysconfig.get_paths()["include"],
            *("-I" + p for p in include_paths()), os.path.join(CSRC, "sfmp_torch.cpp"), "-o", TORCH_LIB, "-L" + libs, "-lc10",
            "-ltorch_cpu", "-ltorch_python"]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -24,7 +24,7 @@ struct Api {
   decltype(&sfmp_gemm_batched) gemm_batched = nullptr;
 };
 
-// per module: set by bind()
+// set by bind()
 Api api;
 PyObject* layout_type = nullptr;
 PyObject* get_device = nullptr;      // torch._C._cuda_getDevice
@@ -270,5 +270,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sfmp_torch", nullptr, -1, methods
 PyMODINIT_FUNC PyInit__sfmp_torch(void) {
   for (int i = 0; i < 9; ++i)
     if (!(names[i] = PyUnicode_InternFromString(kNames[i]))) return nullptr;
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  // (checked by binding.py before anything else of the module is used)
+  if (m && PyModule_AddStringConstant(m, "built_for", SFMP_BUILT_FOR) != 0) Py_CLEAR(m);
+  return m;
 }

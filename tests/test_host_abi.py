@@ -357,3 +357,36 @@ def test_launcher_keeps_the_arguments_of_a_batch_alive(entry, when):
     assert seen == [([True] * len(refs), 2, [expected] * 2)] and len(refs) == (10 if when == "made by the access" else 8)
     problems.clear()
     assert not any(r() is not None for r in refs)  # and no longer than that
+
+
+@pytest.mark.parametrize("extension", ["built", "missing", "not loadable", "built for another torch"])
+def test_launches_without_a_usable_extension_take_the_ctypes_path(extension, tmp_path, monkeypatch):
+    # the extension reads torch's objects by the layout of the headers it was built with: where it cannot be loaded or was
+    # built for another torch, the entry points say so and reach the library through ctypes
+    import types
+    import warnings
+    import torch
+    B = S.binding
+    monkeypatch.setattr(B, "_LAUNCHER", None)
+    path = tmp_path / "_sfmp_torch.so"
+    if extension == "not loadable":
+        path.write_bytes(b"not a shared object")
+    if extension in ("missing", "not loadable"):
+        monkeypatch.setattr(B, "launcher_path", lambda: str(path))
+    if extension == "built for another torch":
+        monkeypatch.setattr(torch, "__version__", "1.0")
+    L = S.sfmp_pack_query(np.full((1, 1), 3, dtype=np.int8), 128, 128)
+    empty, stream = torch.empty((1, 0), dtype=torch.float16), types.SimpleNamespace(cuda_stream=0)
+    with warnings.catch_warnings(record=True) as caught:
+        warnings.simplefilter("always")
+        # (null buffers: refused by the library before it touches a device)
+        for call in (lambda: S.sfmp_gemm(empty, None, L, *[empty] * 7, None, empty, empty, stream=stream),
+                     lambda: S.sfmp_gemm_static(empty, None, L, *[empty] * 7, None, empty, stream=stream),
+                     lambda: S.sfmp_gemv_batched([(empty, None, S.DevicePacked(L, *[empty] * 7), None, empty)], stream=stream),
+                     lambda: S.sfmp_gemm_batched([(empty, None, S.DevicePacked(L, *[empty] * 7), None, empty)], 2, empty,
+                                                 stream=stream)):
+            with pytest.raises(S.SfmpError) as e:
+                call()
+            assert e.value.code == -1
+    assert len([w for w in caught if "marshalled by ctypes" in str(w.message)]) == (0 if extension == "built" else 1)
+    assert (B._LAUNCHER[1] is B._NoExtension) == (extension != "built")
