@@ -292,7 +292,13 @@ struct PrefillShape {
 // BF16: scales and zeros are bfloat16.  An instantiation each: decided at run time, both conversions were computed and one
 // chosen, some 16 of 210 vector instructions of a tile (a branch instead costs 2 % of the large calls, at the
 // synchronisation point).
-template <int BM, bool RING, bool G64, bool BF16>
+// EARLY (128 rows, group length 64): the parameters of a tile are converted in front of the synchronisation point; else the
+// compiler puts most of that work behind it, between the barrier and the requests of the next block.  For launches of 257
+// to 512 workgroups, where some CUs have two workgroups and the others one: there the other order is up to 8 % slower (425
+// rows of 17280 -> 8704, bf16, 230 us against 213; before there was an instantiation per format 218), while with at most one
+// workgroup per CU it is the faster one by 0 to 2 %, and with more than one set of 512 by up to 5 % (809 rows of 18432 ->
+// 11904: 464 us against 492; from 700 workgroups on between -2 and +1 %).
+template <int BM, bool RING, bool G64, bool BF16, bool EARLY = false>
 __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const PrefillParams p) {
   static_assert(!RING || BM == 64, "the buffers of two K groups fit in LDS with 64 rows");
   constexpr int WM = 1, WN = 4, KG = RING ? 2 : 1;
@@ -638,6 +644,7 @@ __global__ __launch_bounds__(RING ? 512 : 256, 2) void prefill_kernel(const Pref
   };
   auto sync_and_issue = [&](int e, auto in_run, auto btag) __attribute__((always_inline)) {
     take_w();
+    if constexpr (EARLY) __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -916,7 +923,12 @@ static void launch_prefill_shape(PrefillParams p, int M, bool g64, hipStream_t s
   p.n_mtiles = (M + BM - 1) / BM;
   const unsigned grid = (unsigned)p.n_mtiles * (unsigned)p.ntr * (unsigned)p.ksplit;
   const dim3 threads(RING ? 512 : 256);
-  if (g64 && p.bf16)
+  const bool early = BM == 128 && g64 && grid > 256 && grid <= 512;
+  if (early && p.bf16)
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, true, true, BM == 128>), dim3(grid), threads, 0, stream, p);
+  else if (early)
+    hipLaunchKernelGGL((prefill_kernel<BM, RING, true, false, BM == 128>), dim3(grid), threads, 0, stream, p);
+  else if (g64 && p.bf16)
     hipLaunchKernelGGL((prefill_kernel<BM, RING, true, true>), dim3(grid), threads, 0, stream, p);
   else if (g64)
     hipLaunchKernelGGL((prefill_kernel<BM, RING, true, false>), dim3(grid), threads, 0, stream, p);

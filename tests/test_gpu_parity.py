@@ -217,6 +217,18 @@ def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, sca
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
 
 
+@pytest.mark.parametrize("K,N,M,scale_format,fractions", [
+    (128, 8320, 400, "fp16", {2: 0.5, 4: 0.5}), (640, 8320, 400, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}), (1152, 8320, 390, "fp16", {3: 1.0}),
+    (640, 8192, 1000, "bf16", {2: 0.5, 3: 0.5}), (640, 8192, 512, "fp16", {3: 0.5, 4: 0.5}), (640, 8320, 1000, "bf16", {2: 0.5, 4: 0.5})])
+def test_prefill_group_64_by_number_of_workgroups(torch_cuda, K, N, M, scale_format, fractions):
+    # group length 64 in 128-row blocks: 257 to 512 workgroups (260, 260, 260, 512 here) take the instantiation that converts
+    # the parameters early, 256 and 520 the other one; one tile (K = 128), one width, every change of width
+    from gpu_util import run_gemm
+    p = W.make_problem("early", K, N, M, 9100 + K + M, fractions=fractions, outliers=True, group=64, scale_format=scale_format,
+                       fast_codes=True)
+    _check(p, run_gemm(p), np.random.default_rng(M).choice(N, 384, replace=False))
+
+
 def test_workspace_is_reusable_and_result_deterministic(torch_cuda):
     from gpu_util import device_problem, make_workspace, run_gemm
     p = W.make_problem("reuse", 2048, 1024, 4, 31337, fractions={2: 0.5, 3: 0.5}, outliers=True)
