@@ -36,7 +36,8 @@ struct PrefillPlan {
   int64_t ytmp_bytes;   // product in reordered row order before the row un-permute pass (ksplit == 1: fp16
                         // [M, N] if a row permutation is given; ksplit > 1: fp32 [ksplit, M, N])
 };
-PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M);
+// (the sizes depend on N, K and M alone; the group length only on the way to the form)
+PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M, int32_t group);
 
 constexpr int32_t kDecodeMaxM = 16;
 

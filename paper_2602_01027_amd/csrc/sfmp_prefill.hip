@@ -942,7 +942,9 @@ static void launch_prefill_shape(PrefillParams p, int M, bool g64, hipStream_t s
 // each the steps of its longest range times the time of a step with 1, 2 or 3 workgroups on the CU plus the start and
 // end of a workgroup; the staging pass; and the last pass, over fp16 rows or over the fp32 partial products of the
 // ranges.  The constants are a fit to 880 measured calls (M = 24 ... 1100 on ten matrices from 512 x 512 to
-// 28672 x 8192, 1, 2, 4 and 8 ranges of each form), which it meets within 5 % (rms).
+// 28672 x 8192, 1, 2, 4 and 8 ranges of each form, group length 128 with a row permutation), which it meets within 5 %
+// (rms); 46000 later calls of random shapes, group lengths and parameter formats it meets within 8 %, 2 % too long in the
+// median.  A fit to those (4.8 % with terms for the share of CUs at work and the group length) chooses no better.
 static double prefill_time_us(int32_t N, int32_t K, int32_t M, int32_t bm, bool ring, int32_t ks) {
   const int64_t ntr = N / kTile, ntc = K / kTile;
   const int64_t per_cu = ((int64_t)((M + bm - 1) / bm) * ntr * ks + 255) / 256;
@@ -959,7 +961,7 @@ static double prefill_time_us(int32_t N, int32_t K, int32_t M, int32_t bm, bool 
   return t + 0.87 * mk;
 }
 
-PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M) {
+PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
   PrefillPlan d;
   const int64_t ntr = N / kTile, ntc = K / kTile;
   d.ring = false;
@@ -980,18 +982,30 @@ PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M) {
   }
   d.ksplit = (int32_t)ks;
   // The number of ranges decides the workspace.  Within it another form is taken where the times above make it at least
-  // 5 % faster (so that their error does not choose a slower one: of the measured shapes none is slower, those that
-  // change are 1 to 35 % faster): fewer ranges, 128-row blocks, or the ring form, which needs 4 tiles per K group to pay
-  // for its longer start (512 -> 512: 2 % slower with 2).  64-row blocks only where 128-row blocks would start at most one
-  // workgroup per CU (beyond they are slower throughout, by up to 30 %).
+  // 5 % faster: fewer ranges, 128-row blocks, or the ring form, which needs 4 tiles per K group to pay for its longer start
+  // (512 -> 512: 2 % slower with 2).  Every form was measured on 6436 random shapes (M = 17 ... 1100, K and N from 384 to
+  // 28672, all group lengths, both parameter formats): the choice is 5.1 % faster than the rule above in the geometric mean,
+  // and more than 2 % slower on 0.8 % of the shapes (2.3 % without the last three lines here):
+  //  - 64-row blocks only where 128-row blocks would start at most one workgroup per CU (beyond they are slower throughout,
+  //    by up to 30 %);
+  //  - 128-row blocks in place of 64-row ones only with group length 64, whose parameters are twice the work per workgroup
+  //    (1 to 4 % faster); with one pair per tile column they gain nothing in the median and lose up to 8 %;
+  //  - not seven ranges of the ring form for eight of the plain one while they are fewer than 200 workgroups: with eight the
+  //    workgroups of a range are on one XCD (block b on b % 8) and read its activations from one L2 (8832 -> 512, 152 rows:
+  //    19.7 us against 18.0);
+  //  - at most half of the ranges, but more than one, from seven row blocks on: only from 8 % on (13824 -> 1152, 391 rows:
+  //    36.1 us in four ranges of the ring form against 34.4 in eight).
   {
-    double best = 0.95 * prefill_time_us(N, K, M, d.bm, false, d.ksplit);
-    for (int form = 0; form < (blocks128 <= 256 ? 3 : 1); ++form) {
+    const double former = prefill_time_us(N, K, M, d.bm, false, d.ksplit);
+    double best = former;
+    for (int form = d.bm == 64 && group != 64 ? 1 : 0, forms = blocks128 <= 256 ? 3 : 1; form < forms; ++form) {
       const int32_t bm = form == 0 ? 128 : 64;
       const bool ring = form == 2;
       for (int32_t k = 1; k <= ks && (!ring || ntc >= 8 * k); ++k) {
+        if (ring && k == 7 && ks == 8 && (int64_t)((M + 63) / 64) * ntr * k < 200) continue;
         const double t = prefill_time_us(N, K, M, bm, ring, k);
-        if (t < best) best = t, d.bm = bm, d.ring = ring, d.ksplit = k;
+        const double margin = ring && M > 384 && k > 1 && k <= ks / 2 ? 0.92 : 0.95;
+        if (t < best && t < margin * former) best = t, d.bm = bm, d.ring = ring, d.ksplit = k;
       }
     }
   }
@@ -1011,7 +1025,7 @@ static int check_launch(const char* what) {
 
 int launch_prefill(const GemmArgs& a, void* stream) {
   const sfmp_layout_t* L = a.L;
-  const PrefillPlan plan = make_prefill_plan(L->N, L->K, a.M);
+  const PrefillPlan plan = make_prefill_plan(L->N, L->K, a.M, L->group);
   // the staging / scatter passes hold one fp16 row in LDS (K <= 57344 fits)
   if (((a.row_perm || plan.ksplit > 1) && (int64_t)L->N * 2 > 160 * 1024) ||
       L->K / kTile > kPrefillMaxTiles)

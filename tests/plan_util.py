@@ -1,0 +1,41 @@
+"""The library's own choice of kernels, read from its internal (C++) planning functions; host code only."""
+import ctypes as C
+
+import paper_2602_01027_amd as S
+
+
+class PrefillPlan(C.Structure):
+    _fields_ = [("bm", C.c_int32), ("ring", C.c_bool), ("ksplit", C.c_int32), ("xperm_bytes", C.c_int64),
+                ("ytmp_bytes", C.c_int64)]
+
+
+class DecodePlan(C.Structure):
+    _fields_ = [("gemv", C.c_bool), ("grid", C.c_int32), ("lds_bytes", C.c_int32), ("slots", C.c_int32), ("max_slabs", C.c_int32),
+                ("mb", C.c_int32), ("nw", C.c_int32), ("acc", C.c_int32), ("resident", C.c_bool), ("ra", C.c_int32),
+                ("rs", C.c_int32), ("workspace_bytes", C.c_int64)]
+
+
+def _call(symbol, result, *args):
+    f = getattr(S.load_library(), symbol)
+    f.restype, f.argtypes = result, [C.c_int32] * len(args)
+    return f(*args)
+
+
+def chunked(N, K, M):
+    """Do 17 <= M <= 128 rows run as chunks of 16 through the decode kernels?"""
+    return _call("_ZN4sfmp18use_chunked_decodeEiii", C.c_bool, N, K, M)
+
+
+def prefill_form(N, K, M, group=128):
+    """(rows of a block, ring form, K ranges) of a matrix-core call."""
+    p = _call("_ZN4sfmp17make_prefill_planEiiii", PrefillPlan, N, K, M, group)
+    return p.bm, p.ring, p.ksplit
+
+
+def prefill_bytes(N, K, M, group=128):
+    p = _call("_ZN4sfmp17make_prefill_planEiiii", PrefillPlan, N, K, M, group)
+    return p.xperm_bytes, p.ytmp_bytes
+
+
+def decode_plan(N, K, M, group=128):
+    return _call("_ZN4sfmp16make_decode_planEiiii", DecodePlan, N, K, M, group)

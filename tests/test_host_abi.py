@@ -390,3 +390,30 @@ def test_launches_without_a_usable_extension_take_the_ctypes_path(extension, tmp
             assert e.value.code == -1
     assert len([w for w in caught if "marshalled by ctypes" in str(w.message)]) == (0 if extension == "built" else 1)
     assert (B._LAUNCHER[1] is B._NoExtension) == (extension != "built")
+
+
+@pytest.mark.parametrize("N,K,M,group,form", [
+    (4480, 19968, 295, 512, (64, False, 2)), (4480, 19968, 295, 64, (128, False, 2)),  # 128 rows for 64: group length 64 only
+    (512, 8832, 152, 128, (64, False, 8)), (1152, 14336, 214, 128, (64, True, 7)),     # seven ring ranges for eight: from 200
+    (1152, 13824, 391, 128, (64, False, 8)), (1024, 13824, 384, 128, (64, True, 5)),   # half of the ranges, seven row blocks
+    (14336, 4096, 64, 128, (64, True, 2)), (4096, 4096, 777, 128, (128, False, 1)), (14336, 4096, 2048, 128, (128, False, 1))])
+def test_form_of_a_matrix_core_call(N, K, M, group, form):
+    import plan_util
+    assert plan_util.prefill_form(N, K, M, group) == form
+
+
+def test_form_of_a_matrix_core_call_stays_within_the_documented_workspace():
+    import plan_util
+    rng = np.random.default_rng(11)
+    for _ in range(4000):
+        K, N = (int(128 * np.ceil(2 ** rng.uniform(0, 7.8))) for _ in range(2))
+        M = int(2 ** rng.uniform(4.1, 11))
+        name, nbytes = _plan_mirror(N, K, M) if not plan_util.chunked(N, K, M) else (None, None)
+        if name is None:
+            continue
+        documented = int(name.split("ksplit=")[1])
+        for group in (64, 128):
+            bm, ring, ksplit = plan_util.prefill_form(N, K, M, group)
+            assert bm in (64, 128) and 1 <= ksplit <= documented and ksplit <= K // 128, (N, K, M)
+            assert not ring or (bm == 64 and K // 128 >= 8 * ksplit), (N, K, M)  # at least four tiles per K group
+            assert sum(plan_util.prefill_bytes(N, K, M, group)) == nbytes, (N, K, M)
