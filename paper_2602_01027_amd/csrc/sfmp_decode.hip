@@ -1450,8 +1450,10 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
   // a longer K with two slabs per workgroup (4096 < N <= 8192 on a full grid): operands streamed through registers.  Not
   // with one slab, where a tile column serves one item only (14336 -> 4096: M = 8 13.0 -> 14.2 us, M = 16 unchanged), and
   // not for M <= 4, where the slot carries 1 KiB of activations and a register load of them costs as much as for 16 rows
-  // (28672 -> 8192, M = 2: 35.0 -> 35.9 us).
-  if (!c.resident && c.mb >= 8 && max_slabs == 2 && 2 * ((K / kTile + 15) / 16) <= kGemvMaxItems) {
+  // (28672 -> 8192, M = 2: 35.0 -> 35.9 us).  With up to 8 rows and group length 64, whose activation sums are taken per slab
+  // in either form, only from K = 12288 on (M = 5 ... 8, 4096 < N <= 8192, random shapes: K about 8.5k 1.7 % slower, 10.5k
+  // 1.0 %, 11.5k to 13.5k equal, 16k and longer 2.8 % faster).
+  if (!c.resident && c.mb >= 8 && !(g64 && c.mb == 8 && K < 12288) && max_slabs == 2 && 2 * ((K / kTile + 15) / 16) <= kGemvMaxItems) {
     c.rs = 2;
     c.acc = 4;
     c.slots = kSlotsStreamedActs;
@@ -1804,7 +1806,7 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
 
 // One configuration for a whole batched launch: the one that fits the problem with the most slabs per workgroup and
 // the largest K (resident or register activations only when every problem of the batch fits them).
-static int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinnyConfig* c, bool* g64) {
+int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinnyConfig* c, bool* g64) {
   int32_t max_slabs = 0, max_k = 0;
   int n64 = 0;
   // one workgroup per CU, or (rounds) two to four per CU one after the other while that brings a workgroup's share

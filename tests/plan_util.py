@@ -39,3 +39,27 @@ def prefill_bytes(N, K, M, group=128):
 
 def decode_plan(N, K, M, group=128):
     return _call("_ZN4sfmp16make_decode_planEiiii", DecodePlan, N, K, M, group)
+
+
+class _GemmArgs(C.Structure):
+    _fields_ = [("X", C.c_void_p), ("M", C.c_int32), ("col_perm", C.c_void_p), ("L", C.POINTER(S.SfmpLayout))] + [
+        (n, C.c_void_p) for n in ("s2", "s3", "s4", "index", "scales", "zeros", "bitmap", "row_perm", "Y", "workspace")] + [
+        ("workspace_bytes", C.c_int64)]
+
+
+class SmallBatchConfig(C.Structure):
+    _fields_ = [("mb", C.c_int32), ("nw", C.c_int32), ("slots", C.c_int32), ("acc", C.c_int32), ("resident", C.c_bool),
+                ("rs", C.c_int32), ("ra", C.c_int32)]
+
+
+def batched_config(layouts, M):
+    """(configuration, workgroups per problem) of one small-batch launch of several matrices."""
+    n = len(layouts)
+    args = (_GemmArgs * n)()
+    for a, layout in zip(args, layouts):
+        a.M, a.L = M, C.pointer(layout)
+    g, c, g64 = (C.c_int32 * 8)(), SmallBatchConfig(), C.c_bool()
+    f = S.load_library()._ZN4sfmp12batch_configEPK8GemmArgsiiPiPNS_13RSkinnyConfigEPb
+    f.restype = C.c_int
+    assert f(args, C.c_int(n), C.c_int32(M), g, C.byref(c), C.byref(g64)) == 0
+    return c, list(g[:n])

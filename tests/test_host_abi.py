@@ -417,3 +417,12 @@ def test_form_of_a_matrix_core_call_stays_within_the_documented_workspace():
             assert bm in (64, 128) and 1 <= ksplit <= documented and ksplit <= K // 128, (N, K, M)
             assert not ring or (bm == 64 and K // 128 >= 8 * ksplit), (N, K, M)  # at least four tiles per K group
             assert sum(plan_util.prefill_bytes(N, K, M, group)) == nbytes, (N, K, M)
+
+
+@pytest.mark.parametrize("N,K,M,group,streamed", [
+    (8192, 28672, 8, 128, True), (8192, 28672, 16, 64, True), (4224, 8320, 5, 128, True), (8192, 8320, 16, 64, True),
+    (8192, 12288, 8, 64, True), (8192, 12160, 8, 64, False),  # up to 8 rows, group length 64: from K = 12288 on
+    (4096, 14336, 16, 128, False), (8192, 28672, 4, 128, False), (8192, 8192, 16, 128, False), (8320, 14336, 16, 128, False)])
+def test_small_batches_that_stream_their_activations(N, K, M, group, streamed):
+    import plan_util
+    assert plan_util.decode_plan(N, K, M, group).rs == (2 if streamed else 0)
