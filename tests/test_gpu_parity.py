@@ -199,18 +199,25 @@ def test_short_prompt_split_k(torch_cuda, K, N, M, row_perm):
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed reduction order
 
 
-@pytest.mark.parametrize("K,N,M,group,scale_format,fractions", [
-    (1024, 1024, 17, 128, "fp16", {2: 1.0}), (1024, 1024, 64, 128, "bf16", {3: 1.0}), (1024, 1024, 65, 64, "fp16", {4: 1.0}),
-    (1408, 640, 130, 64, "bf16", {2: 1 / 3, 3: 1 / 3, 4: 1 / 3}), (1408, 640, 63, 128, "fp16", {2: 0.1, 4: 0.9}),
-    (2304, 512, 200, 256, "fp16", {2: 0.5, 3: 0.5}), (4224, 4096, 100, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}),
-    (4224, 4096, 130, 64, "fp16", {3: 0.5, 4: 0.5})])
-def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, scale_format, fractions):
+@pytest.mark.parametrize("K,N,M,group,scale_format,fractions,ranges", [
+    (1024, 1024, 17, 128, "fp16", {2: 1.0}, 1), (1024, 1024, 64, 128, "bf16", {3: 1.0}, 1), (1024, 1024, 65, 64, "fp16", {4: 1.0}, 1),
+    (1408, 640, 130, 64, "bf16", {2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, 1), (1408, 640, 63, 128, "fp16", {2: 0.1, 4: 0.9}, 1),
+    (2304, 512, 200, 256, "fp16", {2: 0.5, 3: 0.5}, 1), (3200, 384, 17, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, 3),
+    (3200, 256, 17, 128, "bf16", {2: 0.2, 3: 0.8}, 3), (3968, 256, 130, 64, "fp16", {3: 0.5, 4: 0.5}, 3),
+    (3968, 256, 65, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, 3), (9856, 256, 129, 128, "fp16", {2: 0.5, 4: 0.5}, 8),
+    (9856, 256, 200, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, 8), (4224, 4096, 100, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, None),
+    (4224, 4096, 130, 64, "fp16", {3: 0.5, 4: 0.5}, None)])
+def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, scale_format, fractions, ranges):
     # the form of the matrix-core kernel with two K groups per workgroup and weight rings: its shortest share (4 tiles
     # per group), shares of different length (5 and 6 tiles), one width only and every change of width, both parameter
-    # formats and pairs per tile column, rows below, at and above a 64-row block, and with K in ranges besides (uneven)
+    # formats and pairs per tile column, rows below, at and above a 64-row block, and K in ranges besides (25, 31 and 77 tiles
+    # in 6, 6 and 16 groups); beside it the plain 64-row form in four ranges (None)
+    import plan_util
     from gpu_util import run_gemm
+    assert not plan_util.chunked(N, K, M)
+    assert plan_util.prefill_form(N, K, M, group) == ((64, True, ranges) if ranges else (64, False, 4))
     p = W.make_problem("kgroups", K, N, M, 7900 + K + M, fractions=fractions, outliers=True, group=group,
-                       scale_format=scale_format, fast_codes=N > 1024)
+                       scale_format=scale_format, fast_codes=K > 2304)
     rows = None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False)
     y1 = run_gemm(p)
     _check(p, y1, rows)
@@ -557,19 +564,58 @@ def test_small_batch_long_K(torch_cuda, K, N, M, group):
         assert np.array_equal(run_gemm(p, dp, cp, rp).view(np.uint16), Y.view(np.uint16))
 
 
-@pytest.mark.parametrize("K,N,M,group", [(8320, 4224, 5, 128), (8320, 8192, 16, 64), (8704, 6272, 9, 512), (14336, 4096, 24, 128),
-                                         (14336, 4096, 32, 64)])
-def test_small_batch_long_K_two_slabs_per_workgroup(torch_cuda, K, N, M, group):
-    # activations streamed through registers: wavefronts with four, five and seven tile columns (the rotation of three
+@pytest.mark.parametrize("K,N,M,group,scale_format", [
+    (8320, 4224, 5, 128, "fp16"), (8320, 8192, 16, 64, "fp16"), (8704, 6272, 9, 512, "fp16"), (14336, 4096, 24, 128, "fp16"),
+    (14336, 4096, 32, 64, "fp16"), (12288, 4224, 6, 128, "bf16"), (12288, 4352, 8, 64, "bf16"), (9984, 4224, 13, 256, "bf16")])
+def test_small_batch_long_K_two_slabs_per_workgroup(torch_cuda, K, N, M, group, scale_format):
+    # activations streamed through registers: wavefronts with four, five, six and seven tile columns (the rotation of three
     # register sets ends at each of its places), workgroups with one and with two slabs, the last row of 8 and of 16, two
-    # chunks of 16 rows with 2 x 2 slabs, two parameter pairs per tile column
+    # chunks of 16 rows with 2 x 2 slabs, two parameter pairs per tile column, both parameter formats
+    import paper_2602_01027_amd as S
+    import plan_util
     from gpu_util import run_gemm
     p = W.make_problem("stream", K, N, M, 8600 + M + K, fractions={2: 0.4, 3: 0.3, 4: 0.3}, outliers=True, group=group,
-                       block=(1, max(1, group // 128)), fast_codes=True)
+                       scale_format=scale_format, block=(1, max(1, group // 128)), fast_codes=True)
+    layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(p.bitmap, N, K), group, scale_format)
+    assert (plan_util.batched_config([layout] * 2, 16)[0] if M > 16 else plan_util.decode_plan(N, K, M, group)).rs == 2
     rows = np.random.default_rng(M).choice(N, 384, replace=False)
     y1 = run_gemm(p)
     _check(p, y1, rows)
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
+
+
+@pytest.mark.parametrize("M,group,scale_format,shapes", [
+    (8, 128, "fp16", [(9216, 2304), (1024, 512), (2560, 512), (4224, 1024), (128, 256)]),
+    (16, 128, "bf16", [(12416, 1536), (1024, 768), (2560, 768), (4224, 1024), (128, 256)]),
+    (7, 64, "bf16", [(12288, 2048), (1024, 768), (2560, 512), (4224, 768), (128, 256)]),
+    (16, 64, "fp16", [(9216, 2304), (1024, 512), (2560, 512), (4224, 1024), (128, 256)])])
+def test_gemm_batched_streamed_activations_with_different_K(torch_cuda, M, group, scale_format, shapes):
+    # one form for the whole launch, by its longest K: beside it problems whose wavefronts have three, two, one and no tile
+    # columns (a walk that ends in its prologue, and sums of zeros), with one slab per workgroup, with two, and with both
+    import paper_2602_01027_amd as S
+    import plan_util
+    from gpu_util import device_problem
+    torch = torch_cuda
+    probs = [W.make_problem(f"sb{K}", K, N, M, 8900 + K, fractions={2: 0.4, 3: 0.3, 4: 0.3}, outliers=True, group=group,
+                            scale_format=scale_format, fast_codes=True) for K, N in shapes]
+    batch = []
+    for p in probs:
+        dp, cp, rp = device_problem(p)
+        batch.append((torch.from_numpy(p.X).to("cuda:0"), cp, dp, rp,
+                      torch.full((M, p.N), float("nan"), dtype=torch.float16, device="cuda:0")))
+    config, grids = plan_util.batched_config([b[2].layout for b in batch], M)
+    assert config.rs == 2
+    assert {-(-N // 16 // g) for (_, N), g in zip(shapes, grids)} == {1, 2}
+    ws = torch.empty(S.sfmp_gemm_batched_workspace(batch, M), dtype=torch.uint8, device="cuda:0")
+    outs = []
+    for fill in (0xFF, 0x7F):
+        ws.fill_(fill)
+        S.sfmp_gemm_batched(batch, M, ws)
+        torch.cuda.synchronize()
+        outs.append([b[4].cpu().numpy() for b in batch])
+    for p, y0, y1 in zip(probs, *outs):
+        _check(p, y0)
+        assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
 
 
 @pytest.mark.parametrize("K,N,M", [(1024, 40960, 3), (1024, 40960, 8), (4224, 36864, 8), (4224, 36864, 16)])
