@@ -1026,3 +1026,93 @@ def test_lut_gemv_argument_errors(torch_cuda):
     with pytest.raises(S.SfmpError) as e:
         S.sfmp_lut_gemv(d(p.X[0]), None, p.N, p.K, d(planes), d(tile_off.view(np.int32)), d(p.scales), d(p.zeros), None, Y, small)
     assert e.value.code == -5
+
+
+# ---- the extension that marshals the launches -------------------------------------------------------------------------
+def _launcher_calls(torch, M):
+    """Arguments of the extension's entry points for valid problems of M rows, and the outputs."""
+    import paper_2602_01027_amd as S
+    from gpu_util import device_problem, make_workspace
+    p = W.make_problem("launcher", 512, 384, M, 8650 + M, fractions={2: 0.4, 3: 0.3, 4: 0.3})
+    dp, cp, rp = device_problem(p)
+    X = torch.from_numpy(p.X).to("cuda:0")
+    Y = torch.full((M, p.N), float("nan"), dtype=torch.float16, device="cuda:0")
+    gemm = [X, cp, dp.layout, dp.s2, dp.s3, dp.s4, dp.index, dp.scales, dp.zeros, dp.bitmap, rp, Y]
+    problems = [(X, cp, dp, rp, Y)]
+    ws = make_workspace(dp.layout, M)
+    calls = {"gemm": [*gemm, ws], "gemm_static": gemm}
+    if M == 1:
+        calls["gemv_batched"] = [problems]
+    else:
+        calls["gemm_batched"] = [problems, M, torch.empty(S.sfmp_gemm_batched_workspace(problems, M), dtype=torch.uint8,
+                                                          device="cuda:0")]
+    return p, calls, Y
+
+
+@pytest.mark.parametrize("M", [1, 6])
+@pytest.mark.parametrize("stream", ["current", "given"])
+def test_plain_launches_are_marshalled_by_the_extension(torch_cuda, monkeypatch, M, stream):
+    # plain calls are taken (an extension that left every call to ctypes would pass all other tests), and give the bits of the
+    # ctypes path
+    import paper_2602_01027_amd as S
+    torch = torch_cuda
+    B = S.binding
+    module = B._launcher()
+    assert module is not B._NoExtension
+    p, calls, Y = _launcher_calls(torch, M)
+    given = torch.cuda.Stream() if stream == "given" else None
+    for name, args in calls.items():
+        outs = []
+        for path in ("extension", "ctypes"):
+            Y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            if path == "extension":
+                assert getattr(module, name)(*args, given) == 0, name
+            else:
+                with monkeypatch.context() as m:
+                    m.setattr(B, "_LAUNCHER", (S.load_library(), B._NoExtension))
+                    getattr(S, "sfmp_" + name)(*args, stream=given)
+            torch.cuda.synchronize()
+            outs.append(Y.cpu().numpy())
+        assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16)), name
+        _check(p, outs[0])
+
+
+@pytest.mark.parametrize("odd", ["subclass", "not contiguous", "host tensor", "no tensor", "layout", "short tuple", "nine",
+                                 "no tuple", "list subclass", "number"])
+def test_launches_with_one_argument_that_is_not_plain_are_left_alone(torch_cuda, odd):
+    # everything else about the call is valid, the stream included: the one odd argument is the only reason to refuse it
+    import paper_2602_01027_amd as S
+    torch = torch_cuda
+    module = S.binding._launcher()
+    _, calls, Y = _launcher_calls(torch, 6)
+    stream = torch.cuda.current_stream()
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Problems(list):
+        pass
+
+    class Layout(S.SfmpLayout):
+        pass
+
+    X = calls["gemm"][0]
+    problem = calls["gemm_batched"][0][0]
+    if odd in ("subclass", "not contiguous", "host tensor", "no tensor", "layout"):
+        value = {"subclass": X.as_subclass(Sub), "not contiguous": X.t().contiguous().t(), "host tensor": X.cpu(), "no tensor": 3,
+                 "layout": Layout.from_buffer_copy(calls["gemm"][2])}[odd]
+        for name in ("gemm", "gemm_static"):
+            args = list(calls[name])
+            args[2 if odd == "layout" else 0] = value
+            assert getattr(module, name)(*args, stream) is None, name
+    if odd in ("subclass", "no tensor", "short tuple", "nine", "no tuple", "list subclass", "number"):
+        problems = {"subclass": [(X.as_subclass(Sub), *problem[1:])], "no tensor": [(3, *problem[1:])], "short tuple": [problem[:4]],
+                    "nine": [problem] * 9, "no tuple": [list(problem)], "list subclass": Problems([problem]),
+                    "number": [problem]}[odd]
+        M = np.int64(6) if odd == "number" else 6
+        assert module.gemm_batched(problems, M, calls["gemm_batched"][2], stream) is None
+        if odd != "number":
+            assert module.gemv_batched(problems, stream) is None
+    torch.cuda.synchronize()
+    assert torch.isnan(Y).all()  # nothing was launched
