@@ -758,7 +758,9 @@ __device__ __forceinline__ void stage_rows_tile_operand_order(const _Float16* __
       v = *reinterpret_cast<const half8*>(X + (int64_t)m * K + k0);
     }
   }
-  *reinterpret_cast<half8*>(xblk + (((int64_t)tc * 16 + unit) * MB + m) * 16) = v;
+  // (written as k-step and unit of the k-step: as (tc * 16 + unit) * MB + m, the same number, the compiler's order of the
+  // address arithmetic made batched calls of 16 rows and chunks 0.15 us longer: 4096 -> 4096, 32 rows 10.95 us, now 10.76)
+  *reinterpret_cast<half8*>(xblk + (((int64_t)tc * 4 + unit / 4) * (4 * MB) + MB * (unit % 4) + m) * 16) = v;
 }
 template <int MB>
 __global__ __launch_bounds__(MB * 16) void stage_rows_operand_order_kernel(const _Float16* __restrict__ X,
