@@ -1874,15 +1874,18 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
 // 16 < M <= 128: the product may be cut into chunks of 16 activation rows, one problem of the batched ring kernel
 // each (the same weights, its own rows of X and Y).  The chunks run side by side on their shares of the CUs and read
 // the same weights at about the same time, so the matrix comes from HBM once and from the caches for the other
-// chunks.  Against the MFMA kernel (with a split K on these sizes) the cost grows with the number of chunks and with
-// the matrix; measured on the 8B / 70B shapes (same-box A/B, whole calls) the chunked form wins
-//   with K <= 8192 (the chunks keep their activations in registers): two chunks on every shape tried (4096 -> 4096
-//   12 us against 19 for the MFMA kernel at M = 32, 4096 -> 14336 22 against 27, 8192 -> 28672 66 against 73); three
-//   and four chunks up to 1536 tiles (4096 -> 6144: 17 against 21, 20 against 21.5; not 4096 -> 14336: 31 against 29,
-//   nor 8192 -> 8192: 33 against 31); five and six up to 1024 tiles (4096 -> 4096: 18.4 against 21.1, 20.1 against 21.8;
-//   eight: 33.5 against 22.9); eight on N <= 1024;
-//   with a longer K (activations through the ring slots): N <= 1024 up to 8 chunks (14336 -> 1024), N <= 4096 two;
+// chunks.  Against the MFMA kernel (short-prompt forms) the cost grows with the number of chunks and with the matrix.  Whole
+// calls, both sides on one machine, us chunked / MFMA:
+//   with K <= 8192 (the chunks keep their activations in registers) two chunks (M = 32): 4096 -> 4096 11.4 / 16.0, 4096 ->
+//   14336 20.3 / 25.4, 8192 -> 8192 23.0 / 27.2, 8192 -> 14336 31.6 / 35.0; three and four chunks up to 1536 tiles: 4096 ->
+//   6144 15.8 / 18.3 and 18.1 / 19.3 (not 4096 -> 14336: 28.6 / 23.6; nor 8192 -> 8192: 30.4 / 25.1); five and six up to 1024
+//   tiles: 4096 -> 4096 17.2 / 19.0 and 19.3 / 19.2 (eight: 31.0 / 21.4);
+//   with a longer K (activations through the ring slots, or streamed) N <= 1024 up to eight chunks, N <= 4096 two (14336 ->
+//   4096 20.6 / 23.2; with three 37.8 / 24.8);
 //   with K below 4096 (not measured): never.
+// The lines were drawn when the MFMA side had no ring form.  Where they are now on the wrong side: two chunks of the largest
+// matrices (4096 -> 28672 34.6 / 34.1, 8192 -> 28672 55.7 / 52.0 at M = 32), and N <= 1024 with K > 8192 from five chunks on
+// (14336 -> 1024 23.5 / 21.0 at M = 80, 26.6 / 23.7 at M = 128; 28672 -> 1024 36.2 / 32.8 and 42.9 / 34.3).
 bool use_chunked_decode(int32_t N, int32_t K, int32_t M) {
   if (M <= kDecodeMaxM || M > kDecodeMaxM * kGemvMaxBatch) return false;
   const int32_t ntr = N / kTile, ntc = K / kTile, chunks = (M + kDecodeMaxM - 1) / kDecodeMaxM;

@@ -290,8 +290,10 @@ struct PrefillShape {
 // sequence is laid out.  Per 64-row step of both groups 2500 cycles.  512 x 4096 x 4096 47 -> 34 us, 300 x 2048 x 2048
 // 26 -> 19, 128 x 4096 x 14336 43 -> 33, 64 x 4096 x 14336 29 -> 24.5 (whole calls, same machine).
 // BF16: scales and zeros are bfloat16.  An instantiation each: decided at run time, both conversions were computed and one
-// chosen, some 16 of 210 vector instructions of a tile (a branch instead costs 2 % of the large calls, at the
-// synchronisation point).
+// chosen, in a 128-row step 12 of 138 to 152 vector instructions with fp16 parameters and 6 with bf16 ones, at group length
+// 64 26 and 16 of 159 to 173 (a branch instead costs 2 % of the large calls, at the synchronisation point).  Whole calls
+// with one parameter pair per tile column within 1 %; at group length 64 with more than 512 workgroups 1 to 8 % faster
+// (768 -> 24064, 501 rows 50.2 -> 47.6 us).
 // EARLY (128 rows, group length 64): the parameters of a tile are converted in front of the synchronisation point; else the
 // compiler puts most of that work behind it, between the barrier and the requests of the next block.  For launches of 257
 // to 512 workgroups, where some CUs have two workgroups and the others one: there the other order is up to 8 % slower (425
