@@ -27,7 +27,8 @@ struct DecodePlan {
 };
 DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group);
 
-// Prefill path (M > 16): workspace holds the column-gathered activation.
+// Prefill path (M > 16): workspace holds the column-gathered activation.  bm, ring and ksplit: the form by the rule from
+// before prefill_fed_kernel, the yardstick for choose_prefill_form, which has the say over what is launched.
 struct PrefillPlan {
   int32_t bm;           // rows of a workgroup's block: 128, or 64 on small grids
   bool ring;            // 64 rows, two K groups per workgroup, packed words through LDS rings
@@ -38,6 +39,12 @@ struct PrefillPlan {
 };
 // (the sizes depend on N, K and M alone; the group length only on the way to the form)
 PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M, int32_t group);
+
+// What sfmp_gemm launches for M > 16: prefill_fed_kernel<mi, kg> in ksplit K ranges, or prefill_kernel (mi = 0).
+struct PrefillForm {
+  int32_t mi, kg, ksplit;
+};
+PrefillForm choose_prefill_form(int32_t N, int32_t K, int32_t M);
 
 constexpr int32_t kDecodeMaxM = 16;
 

@@ -63,3 +63,13 @@ def batched_config(layouts, M):
     f.restype = C.c_int
     assert f(args, C.c_int(n), C.c_int32(M), g, C.byref(c), C.byref(g64)) == 0
     return c, list(g[:n])
+
+
+class _PrefillForm(C.Structure):
+    _fields_ = [("mi", C.c_int32), ("kg", C.c_int32), ("ksplit", C.c_int32)]
+
+
+def launched_form(N, K, M):
+    """(16-row blocks of a wavefront, K groups of a workgroup, K ranges) of a matrix-core call; (0, 1, 1): prefill_kernel."""
+    f = _call("_ZN4sfmp19choose_prefill_formEiii", _PrefillForm, N, K, M)
+    return f.mi, f.kg, f.ksplit

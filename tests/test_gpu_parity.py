@@ -224,6 +224,37 @@ def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, sca
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format,fractions,form", [
+    (128, 128, 17, 64, "bf16", {4: 1.0}, (4, 1, 1)), (256, 128, 17, 256, "fp16", {2: 1.0}, (4, 2, 1)),
+    (640, 512, 64, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 1)), (3200, 128, 17, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 3)),
+    (9856, 128, 129, 128, "fp16", {3: 0.5, 4: 0.5}, (4, 2, 8)), (256, 16512, 65, 64, "fp16", {2: 0.5, 4: 0.5}, (5, 2, 1)),
+    (3200, 5632, 65, 128, "bf16", {3: 1.0}, (5, 2, 3)), (640, 16512, 81, 128, "bf16", {2: 0.5, 3: 0.5}, (6, 2, 1)),
+    (3200, 8320, 81, 64, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (6, 2, 3)), (896, 16512, 97, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (7, 2, 1)),
+    (4224, 8320, 97, 128, "fp16", {2: 0.1, 4: 0.9}, (7, 2, 3)), (1408, 16512, 113, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (8, 2, 1)),
+    (1536, 16512, 128, 512, "bf16", {3: 0.5, 4: 0.5}, (8, 2, 1)), (256, 16512, 81, 128, "fp16", {2: 0.5, 4: 0.5}, (4, 1, 1)),
+    (128, 16512, 129, 64, "fp16", {3: 0.5, 4: 0.5}, (5, 1, 1)), (256, 16512, 161, 128, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (6, 1, 1)),
+    (256, 16512, 200, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (7, 1, 1)), (256, 16512, 225, 64, "fp16", {3: 0.5, 4: 0.5}, (8, 1, 1)),
+    (256, 16512, 300, 128, "fp16", {3: 0.5, 4: 0.5}, (0, 1, 1)),
+    # a last block of rows that reaches past the last 128 staged rows
+    (640, 8320, 300, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, None), (640, 8320, 600, 64, "bf16", {2: 0.5, 4: 0.5}, None),
+    (896, 2048, 777, 256, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, None)])
+def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format, fractions, form):
+    # rows per wavefront (4 to 8 blocks of 16), K groups and row groups, K ranges; one tile, fewer tiles than buffers, shares of
+    # different length, one width and every change of width, both parameter formats and pairs per tile column, a row more
+    # than the next smaller block holds
+    import plan_util
+    from gpu_util import run_gemm
+    if group > 128 and K % group:
+        K = K // group * group
+    assert not plan_util.chunked(N, K, M)
+    assert form is None or plan_util.launched_form(N, K, M) == form
+    p = W.make_problem("forms", K, N, M, 9500 + K + M, fractions=fractions, outliers=True, group=group, scale_format=scale_format,
+                       fast_codes=K * N > 2 ** 20)
+    y1 = run_gemm(p)
+    _check(p, y1, None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
+
+
 @pytest.mark.parametrize("K,N,M,scale_format,fractions", [
     (128, 8320, 400, "fp16", {2: 0.5, 4: 0.5}), (640, 8320, 400, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}), (1152, 8320, 390, "fp16", {3: 1.0}),
     (640, 8192, 1000, "bf16", {2: 0.5, 3: 0.5}), (640, 8192, 512, "fp16", {3: 0.5, 4: 0.5}), (640, 8320, 1000, "bf16", {2: 0.5, 4: 0.5})])

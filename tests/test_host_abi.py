@@ -416,6 +416,25 @@ def test_form_of_a_matrix_core_call_stays_within_the_documented_workspace():
             assert sum(plan_util.prefill_bytes(N, K, M, group)) == nbytes, (N, K, M)
 
 
+def test_launched_form_of_a_matrix_core_call():
+    # at least one tile per K group, at most the documented ranges, the plain kernel only with more than 256 blocks of 128 rows
+    import plan_util
+    rng = np.random.default_rng(12)
+    for _ in range(4000):
+        K, N = (int(128 * np.ceil(2 ** rng.uniform(0, 7.8))) for _ in range(2))
+        M = int(2 ** rng.uniform(4.1, 11))
+        if plan_util.chunked(N, K, M):
+            continue
+        mi, kg, ksplit = plan_util.launched_form(N, K, M)
+        documented = int(_plan_mirror(N, K, M)[0].split("ksplit=")[1])
+        assert (mi == 0 and (kg, ksplit) == (1, 1) and -(-M // 128) * (N // 128) > 256) or 4 <= mi <= 8, (N, K, M)
+        assert 1 <= ksplit <= documented and kg * ksplit <= K // 128, (N, K, M)
+        assert ksplit == 1 or (kg == 2 and ksplit * M * N * 4 <= plan_util.prefill_bytes(N, K, M)[1]), (N, K, M)
+    for shape, form in (((4096, 4096, 777), (7, 2, 1)), ((14336, 4096, 64), (4, 2, 2)), ((4096, 14336, 200), (7, 2, 4)),
+                        ((14336, 4096, 2048), (8, 1, 1)), ((8192, 28672, 2048), (8, 1, 1)), ((128, 128, 17), (4, 1, 1))):
+        assert plan_util.launched_form(*shape) == form, shape
+
+
 @pytest.mark.parametrize("N,K,M,group,streamed", [
     (8192, 28672, 8, 128, True), (8192, 28672, 16, 64, True), (4224, 8320, 5, 128, True), (8192, 8320, 16, 64, True),
     (8192, 12288, 8, 64, True), (8192, 12160, 8, 64, False),  # up to 8 rows, group length 64: from K = 12288 on
