@@ -781,7 +781,9 @@ __host__ __device__ inline size_t rskinny_raw_bytes(int32_t M, int32_t K) { retu
 // the kernel needs about 130 vector registers and runs 8 wavefronts per CU; with 4 or 8 it stays below 128 and runs
 // 16, which is what covers the latencies of its loop.  The forms with MB = 4 and with RA hold no sums in registers
 // (they write them to LDS as a slab finishes); there ACC only tells the variants for 16 and for 8 wavefronts apart.
-// G64: group length 64 (two parameter pairs per row and tile column; never together with RES).
+// G64: group length 64 (two parameter pairs per row and tile column; never together with RES without RA).
+// RES with RA = 2: the operands are gathered by every workgroup itself, through a transposed copy of the activations in LDS that
+// lies where the second ring slots and the finished sums come later; no staging launch.
 // RA (activations in registers; 0, 2 or 4): when a wavefront has at most RA tile columns (K <= 128 RA NW) it loads
 // their matrix-instruction operands once, from a staged copy in operand order (stage_rows_operand_order_kernel), and
 // keeps them in registers (16 per tile column) for all its slabs: an item then brings only its slab and parameters
@@ -797,11 +799,22 @@ __host__ __device__ inline size_t rskinny_raw_bytes(int32_t M, int32_t K) { retu
 // mostly instruction issue (about 100 vector instructions per item and four wavefronts per SIMD).  28672 -> 8192, whole
 // call, M = 8 43.3 -> 38.5 us, M = 16 53.6 -> 45.0; 8320 -> 8192, M = 16 17.6 -> 15.5; 14336 -> 4096, M = 32 (two chunks)
 // 25.2 -> 21.5.
+// Resident operands (RES with RA): LDS bytes of the transposed activations (16 or 8 rows of a column together), and where a
+// byte of them lies.
+__host__ __device__ inline int64_t rskinny_xt_bytes(int32_t M, int32_t K) { return (int64_t)K * (M <= 8 ? 16 : 32); }
+// (byte `at` of the plain layout; bits 4-7, the 16-byte unit of 256 bytes, are exchanged by the number of the 256 bytes)
+__device__ __forceinline__ uint32_t xt_offset(uint32_t at) { return at ^ ((at >> 4) & 0xF0u); }
+typedef short v4i16 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4i16* v4i16_lds;
+
 template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
 __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int bid, const int G, unsigned char* lds_raw) {
-  static_assert(!(RES && G64), "the resident form keeps one activation sum per tile column");
+  // RES with RA: the operands are gathered by the kernel itself (XT below); RESL: resident in LDS
+  constexpr bool XT = RES && RA > 0, RESL = RES && !XT;
+  static_assert(!(RESL && G64), "the resident form keeps one activation sum per tile column");
   static_assert(!RS || (RS == 2 && !RES && !RA && S == 3 && NW == 16), "streamed operands: three sets and slots");
-  static_assert(!(RES && RA) && (!RA || MB == 16) && (RA == 0 || RA == 2 || RA == 4), "activations in registers: 16 rows, no copy in LDS");
+  static_assert((!RA || MB == 16) && (RA == 0 || RA == 2 || RA == 4), "activations in registers: 16 rows");
+  static_assert(!XT || (S == 2 && NW == 16 && RA == 2), "operands gathered by the kernel: two slots, 4 columns per thread");
   constexpr int NT = NW * 64;
   constexpr int kBase = G64 ? kSlotBytes64 : kSlotBytes;  // slab + parameters; the staged activations follow
   constexpr int kSlot = (RES || RA || RS) ? kBase : kBase + MB * 256;
@@ -817,9 +830,9 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   float* red = reinterpret_cast<float*>(lds_raw);
   unsigned char* Xs = lds_raw + (DS ? (size_t)p.max_slabs * NW * kFinLanes * 16 : (size_t)p.max_slabs * 1024 * kRedGroups);
   // (resident) SxL [ntc][4 lane groups][4] f32: the sums of the activations of rows 4g..4g+3 over a tile column
-  float* SxL = reinterpret_cast<float*>(Xs + (RES ? (size_t)p.ntc * (MB * 256) : (size_t)0));
-  unsigned char* raw_region = reinterpret_cast<unsigned char*>(SxL) + (RES ? (size_t)p.ntc * 64 : (size_t)0);
-  unsigned char* rings = raw_region + (RES ? rskinny_raw_bytes(p.M, p.K) : (size_t)0);
+  float* SxL = reinterpret_cast<float*>(Xs + (RESL ? (size_t)p.ntc * (MB * 256) : (size_t)0));
+  unsigned char* raw_region = reinterpret_cast<unsigned char*>(SxL) + (RESL ? (size_t)p.ntc * 64 : (size_t)0);
+  unsigned char* rings = raw_region + (RESL ? rskinny_raw_bytes(p.M, p.K) : (size_t)0);
 
   const int tid = threadIdx.x;
   const int lane = tid % kWave;
@@ -868,7 +881,9 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
 
   // Issue item e into ring slot s: the slab (scalar address, 32/48/64 lanes), the 16 scale + 16 zero dwords, and
   // without resident activations MB/4 KiB of staged activations of the item's tile column (scalar address)
-  constexpr int kWaveSlots = S * (RS ? RS : 1);  // (RS: a slot holds the item of every slab)
+  constexpr int kWaveSlots = XT ? 1 : S * (RS ? RS : 1);  // (RS: a slot holds the item of every slab)
+  // (XT) the first slots of all wavefronts lie behind the transposed activations, the second ones where a slot lies anyway
+  const uint32_t xt_first = XT ? (uint32_t)max((int)rskinny_xt_bytes(p.M, p.K) - (int)(rings - lds_raw), NW * kSlot) : 0u;
   const uint32_t ring_off = (uint32_t)(uintptr_t)(lptr_t)(rings + (size_t)wave * kWaveSlots * kSlot);
   const unsigned char* ring = rings + (size_t)wave * kWaveSlots * kSlot;
   const uint64_t xb = (uint64_t)p.xblk;
@@ -877,7 +892,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     const uint32_t whi = (uint32_t)__builtin_amdgcn_readlane((int)it_whi, e);
     const uint32_t xhi = (uint32_t)__builtin_amdgcn_readlane((int)it_xhi, e);
     const uint32_t soff = (uint32_t)__builtin_amdgcn_readlane((int)it_soff, e);
-    const uint32_t slot = ring_off + (uint32_t)s * kSlot;
+    const uint32_t slot = ring_off + (XT ? (s == 0 ? xt_first : 0u) : (uint32_t)s * kSlot);
     lds_copy_item(par_vbase + soff, ((uint64_t)whi << 32) | wlo, data_voff, slot + 1024, slot, xhi, G64 ? ~0u : 0u);
     if constexpr (!RES && !RA && !RS) {
       const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, e);
@@ -888,7 +903,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   };
 
   int issued_early = 0;  // items of the first batch that are already on their way when the loop below starts
-  if constexpr (RES) {
+  if constexpr (RESL) {
     // Start of the resident form, ordered as in the GEMV kernel: everything that depends on the arguments alone is
     // requested at once (raw copies of the M rows into their own LDS region, 1 KiB per wavefront and copy; the
     // column permutation into registers; the tile descriptors of the first batch of items), the first items of
@@ -971,7 +986,92 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   // (RA) the operands of this wavefront's tile columns, requested now (the address of the last tile column for a
   // wavefront that has fewer: the loads are unconditional); first used when the first item is consumed
   half8 aset[RA > 0 ? RA : 1][4];
-  if constexpr (RA > 0) {
+  if constexpr (XT) {
+    // Everything that depends on the arguments alone is requested at once: the raw activations (4 columns of all rows per
+    // thread), the permutation entries of this wavefront's tile columns, the tile descriptors.  The activations go into LDS
+    // transposed - the 16 (or 8) rows of a column together - so that one transposing read per 4 columns gathers all rows of
+    // a matrix-instruction operand: lane 4r + c of a group of 16 gives the address of rows 4c .. 4c + 3 of the r-th
+    // column and receives row (its number) of the four columns.
+    // 16-byte units of 256 bytes change places with the number of the 256 bytes: a store of a wavefront hits every bank equally.
+    // The first item of every wavefront is on its way meanwhile.  Against a staging launch: see rskinny_config.
+    const int chunk = i16 % 4;
+    int pk[RA][8];
+#pragma unroll
+    for (int t = 0; t < RA; ++t) {
+      const int k0 = min(wave + NW * t, p.ntc - 1) * kTile + kb * 8 + i16 / 4;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) pk[t][q] = k0 + (q / 2) * 32 + (q % 2) * 4;
+    }
+    if (p.col_perm) {
+#pragma unroll
+      for (int t = 0; t < RA; ++t) {
+        const int32_t* at = p.col_perm + pk[t][0];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) pk[t][q] = at[(q / 2) * 32 + (q % 2) * 4];
+      }
+    }
+    const int units = p.K / 4;
+    auto stage = [&](auto rtag) __attribute__((always_inline)) {
+      constexpr int R = decltype(rtag)::value;
+      u32x2 x[R];
+      const _Float16* const from = p.X + 4 * min(tid, units - 1);
+#pragma unroll
+      for (int m = 0; m < R; ++m)  // (rows past the last: the last again; their products are not stored)
+        x[m] = *reinterpret_cast<const u32x2*>(from + (size_t)min(m, p.M - 1) * p.K);
+      const int Eb0 = min(64, E);
+      describe(0, Eb0);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // one trip to memory for all of the above
+#pragma unroll
+      for (int m = 0; m < R; ++m) asm volatile("" : "+v"(x[m]));
+#pragma unroll
+      for (int t = 0; t < RA; ++t)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(pk[t][q]));
+      asm volatile("" : "+v"(it_wlo), "+v"(it_whi), "+v"(it_xhi), "+v"(it_soff), "+v"(it_misc));
+      issued_early = min(1, Eb0);
+      if (issued_early) issue_item(0, 0);
+      if (tid < units) {
+        const uint32_t base = xt_offset((uint32_t)tid * (8 * R));  // (4 columns: the low bits of the unit are added by XOR)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          uint32_t v[R / 2];
+#pragma unroll
+          for (int m = 0; m < R / 2; ++m)
+            v[m] = __builtin_amdgcn_perm(x[2 * m + 1][kk / 2], x[2 * m][kk / 2], kk % 2 ? 0x07060302u : 0x05040100u);
+#pragma unroll
+          for (int h = 0; h < R / 8; ++h)
+            *reinterpret_cast<u32x4*>(lds_raw + (base ^ (uint32_t)(kk * 2 * R + h * 16))) =
+                u32x4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
+        }
+      }
+      barrier_lds_only();
+      const uint32_t in_column = (uint32_t)(R == 16 ? chunk : chunk % 2) * 8;
+#pragma unroll
+      for (int t = 0; t < RA; ++t)
+#pragma unroll
+        for (int kappa = 0; kappa < 4; ++kappa) {
+          union {
+            v4i16 h[2];
+            half8 v;
+          } o;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * R) + in_column);
+            o.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16_lds)(at));
+          }
+          aset[t][kappa] = o.v;
+        }
+#pragma unroll
+      for (int t = 0; t < RA; ++t)
+#pragma unroll
+        for (int kappa = 0; kappa < 4; ++kappa) asm volatile("" : "+v"(aset[t][kappa]));
+      barrier_lds_only();  // every wavefront has its operands: the second slots and the finished sums may overwrite the rest
+    };
+    if (p.M <= 8)
+      stage(std::integral_constant<int, 8>{});
+    else
+      stage(std::integral_constant<int, 16>{});
+  } else if constexpr (RA > 0) {
 #pragma unroll
     for (int t = 0; t < RA; ++t) {
       const int tc = min(wave + NW * t, p.ntc - 1);
@@ -984,7 +1084,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   uint32_t a_off[4];
 #pragma unroll
   for (int kappa = 0; kappa < 4; ++kappa)
-    a_off[kappa] = (RES ? 0 : kBase) + i16 * 256 + (((4 * kappa + kb) ^ i16) * 16);
+    a_off[kappa] = (RESL ? 0 : kBase) + i16 * 256 + (((4 * kappa + kb) ^ i16) * 16);
 
   // finished sums: accs[r][q] = output element r of this lane for slab q (register-indexed writes, no switch)
   static_assert(ACC == 4 || ACC == 8 || ACC == 16, "the finished sums live in 4-, 8- or 16-wide register vectors");
@@ -1057,7 +1157,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     floatx4 sx;
     if constexpr (RA == 2 || RS) {
       sx = sx_known;
-    } else if constexpr (RES) {
+    } else if constexpr (RESL) {
       sx = *reinterpret_cast<const floatx4*>(SxL + (misc & 0xFFFF) * 16 + kb * 4);
     } else {
       sx = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1112,7 +1212,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   }
   auto consume = [&](int e, int s) __attribute__((always_inline)) {
     const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, e);
-    const unsigned char* slot = ring + s * kSlot;
+    const unsigned char* slot = ring + (XT ? (s == 0 ? xt_first : 0u) : (uint32_t)(s * kSlot));
     if constexpr (RA) {
       // which of this wavefront's tile columns (a uniform branch over RA copies of the item's code: selecting the
       // operands into one more set of registers cost 16 more of them)
@@ -1128,7 +1228,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       }
     } else {
       if (MB == 16 || i16 < MB) {
-        const unsigned char* abase = RES ? Xs + (size_t)(misc & 0xFFFF) * (MB * 256) : slot;
+        const unsigned char* abase = RESL ? Xs + (size_t)(misc & 0xFFFF) * (MB * 256) : slot;
 #pragma unroll
         for (int kappa = 0; kappa < 4; ++kappa) a[kappa] = *reinterpret_cast<const half8*>(abase + a_off[kappa]);
       }
@@ -1401,6 +1501,10 @@ static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
 static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int32_t M, int32_t K) {
   const int64_t red = (int64_t)max_slabs * 1024 * (c.nw / 4);
   // (slots sized for group length 64, 128 bytes larger, whatever the layout)
+  if (c.ra && c.resident) {  // fin | second slots, beside them the transposed activations | first slots
+    const int64_t slots = (int64_t)c.nw * kSlotBytes64, second = (int64_t)max_slabs * 1024 * c.nw + slots;
+    return std::max(second, rskinny_xt_bytes(M, K)) + slots;
+  }
   if (c.ra || c.rs)  // fin | rings
     return (int64_t)max_slabs * 1024 * c.nw + (int64_t)c.nw * c.slots * (c.rs ? c.rs : 1) * kSlotBytes64;
   return c.resident ? red + (int64_t)c.mb * K * 2 + (int64_t)(K / kTile) * 64 + (int64_t)rskinny_raw_bytes(M, K) +
@@ -1447,6 +1551,13 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
     r.mb = 16;
     r.acc = r.nw == 16 ? 4 : 16;
     r.slots = kSlotsRegisterActs;
+    // Two tile columns per wavefront and 16 wavefronts (K <= 4096): the operands are gathered by every workgroup itself, without
+    // a staging launch.  Graph replays, staged / gathered: 4096 -> 4096 M = 8 8.12 / 6.68 us, M = 16 8.35 / 7.95; 4096 -> 14336
+    // 11.90 / 10.46 and 12.76 / 12.24; 512 -> 512 6.15 / 4.97 and 6.13 / 6.00; 4096 -> 4096 M = 64 (chunks) 14.23 / 12.95.  Not with
+    // four (K <= 8192, up to 8 rows): 8192 -> 8192 12.72 / 12.73, 8192 -> 28672 26.96 / 27.34.  And not for the resident form's
+    // M <= 4, whose start is shorter still: 512 -> 512 M = 4 4.22 / 4.92, 4096 -> 14336 10.43 / 10.39.
+    // (It fits wherever the sums and slots do: 128 KiB of transposed activations and the first slots are 148 KiB.)
+    r.resident = r.nw == 16 && r.ra == 2;
     if (rskinny_lds_bytes(r, max_slabs, M, K) <= 160 * 1024) return r;
   }
   // a longer K with two slabs per workgroup (4096 < N <= 8192 on a full grid): operands streamed through registers.  Not
@@ -1667,7 +1778,7 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   const sfmp_layout_t* L = a.L;
   const void* fn = reinterpret_cast<const void*>(&rskinny_kernel<NW, S, MB, RES, ACC, G64, RA, RS>);
   if (int e = allow_full_lds(fn, "hipFuncSetAttribute(skinny)")) return e;
-  if (RA || RS) {
+  if ((RA || RS) && !RES) {
     hipLaunchKernelGGL(stage_rows_operand_order_kernel<MB>, dim3((unsigned)(L->K / kTile)), dim3(MB * 16), 0, (hipStream_t)stream,
                        (const _Float16*)a.X, a.col_perm, (unsigned char*)a.workspace, (int)a.M, (int)L->K);
     if (int e = after_launch("sfmp_gemm activation staging launch")) return e;
@@ -1694,13 +1805,13 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   X(16, kSlotsMb16Wide, 16, false, 4, 0, 0) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0)                              \
   X(8, kSlotsMb16, 16, false, 16, 0, 0)                                                                            \
   X(16, kSlotsStreamedActs, 8, false, 4, 0, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2)                       \
-  X(16, kSlotsRegisterActs, 16, false, 4, 2, 0) X(8, kSlotsRegisterActs, 16, false, 16, 2, 0)                      \
+  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0) X(8, kSlotsRegisterActs, 16, false, 16, 2, 0)                       \
   X(16, kSlotsRegisterActs, 16, false, 4, 4, 0) X(8, kSlotsRegisterActs, 16, false, 16, 4, 0)
 
 static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) {
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_)                                                 \
   if (d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
-    if constexpr (!RES_) {                                                                    \
+    if constexpr (!RES_ || RA_) {                                                             \
       if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_>(a, d, stream); \
     }                                                                                         \
     return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_>(a, d, stream);        \
@@ -1790,7 +1901,7 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
   if (lds > 160 * 1024) return SFMP_ERR_SHAPE;
   const void* fn = reinterpret_cast<const void*>(&rskinny_batched_kernel<NW, S, MB, RES, ACC, G64, RA, RS>);
   if (int e = allow_full_lds(fn, "hipFuncSetAttribute(skinny batched)")) return e;
-  if (RA || RS) {
+  if ((RA || RS) && !RES) {
     hipLaunchKernelGGL(stage_rows_operand_order_batched_kernel<MB>, dim3((unsigned)sfirst), dim3(MB * 16), 0, (hipStream_t)stream, sb);
     if (int e = after_launch("sfmp_gemm_batched activation staging launch")) return e;
   } else if (!RES) {
@@ -1861,7 +1972,7 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
   if (int e = batch_config(probs, count, M, g, &c, &n64)) return e;
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_)                                               \
   if (c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
-    if constexpr (!RES_) {                                                                  \
+    if constexpr (!RES_ || RA_) {                                                           \
       if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_>(probs, count, M, g, workspace, stream); \
     }                                                                                       \
     return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_>(probs, count, M, g, workspace, stream); \

@@ -577,6 +577,28 @@ def test_small_batch_three_and_four_tile_columns_per_wavefront(torch_cuda, K, N,
     _check(p, run_gemm(p))
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format,perm", [
+    (128, 128, 5, 128, "fp16", True), (384, 512, 8, 64, "bf16", True), (512, 512, 9, 128, "fp16", False), (2048, 384, 16, 256, "bf16", True),
+    (2176, 640, 13, 128, "fp16", True), (3968, 8192, 8, 128, "fp16", True), (4096, 28672, 7, 128, "fp16", True),
+    (4096, 28672, 16, 64, "fp16", True), (4096, 4096, 16, 128, "fp16", False), (4096, 1024, 3, 64, "fp16", True),
+    (4096, 256, 20, 128, "fp16", True), (4096, 512, 72, 64, "bf16", True)])
+def test_small_batch_operands_gathered_without_a_staging_launch(torch_cuda, K, N, M, group, scale_format, perm):
+    # activations transposed in LDS, 8 rows of a column together or 16: first and last row of each, one tile column (wavefronts
+    # without any), one and two per wavefront, one to seven slabs per workgroup, without a permutation, chunks of 16 rows
+    # whose last has 4 and 8; calls give the same bits
+    import plan_util
+    import paper_2602_01027_amd as S
+    from gpu_util import device_problem, run_gemm
+    p = W.make_problem("gathered", K, N, M, 9700 + K + M, fractions={2: 0.3, 3: 0.4, 4: 0.3}, outliers=True, group=group,
+                       scale_format=scale_format, block=(1, max(1, group // 128)), fast_codes=N * K > 2 ** 22, use_col_perm=perm)
+    layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(p.bitmap, N, K), group, scale_format)
+    d = plan_util.batched_config([layout] * -(-M // 16), 16)[0] if M > 16 else plan_util.decode_plan(N, K, M, group)
+    assert d.ra == 2 and d.resident and (M <= 16 or plan_util.chunked(N, K, M))
+    y1 = run_gemm(p)
+    _check(p, y1, None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
+
+
 @pytest.mark.parametrize("K,N,M,group", [(9216, 512, 5, 128), (14336, 1024, 16, 128), (14336, 4096, 16, 128), (28672, 1024, 8, 64),
                                          (16512, 384, 7, 128), (14336, 1024, 40, 128), (28672, 8192, 8, 256)])
 def test_small_batch_long_K(torch_cuda, K, N, M, group):
