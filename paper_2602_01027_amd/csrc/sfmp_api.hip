@@ -196,7 +196,8 @@ static int gemm_with_workspace(const void* X_dev, int32_t M, const int32_t* col_
   a.workspace = workspace_dev;
   a.workspace_bytes = workspace_bytes;
   if (M <= kDecodeMaxM) return launch_decode(a, hip_stream);
-  if (use_chunked_decode(layout->N, layout->K, M)) return launch_decode_chunked(a, hip_stream);
+  if (use_chunked_decode(layout->N, layout->K, M) || use_chunks_without_staging(layout->N, layout->K, M))
+    return launch_decode_chunked(a, hip_stream);
   return launch_prefill(a, hip_stream);
 }
 

@@ -2009,6 +2009,21 @@ bool use_chunked_decode(int32_t N, int32_t K, int32_t M) {
   return chunks <= 2 && ntr <= 32;
 }
 
+// The same beyond those lines where the chunks need no staging launch (K <= 4096, at most seven slabs per workgroup: the
+// operands are gathered by the workgroups, no workspace is used, and the whole call is one launch instead of three).  On 10643
+// calls of random shapes (M = 17 ... 128, K and N from 512 to 4096 and 16384) chunks are 1.5 times as fast as the matrix-core
+// path (geometric mean; 0.3 % of them more than 2 % slower, the worst 4096 -> 7168 with 49 rows, 0.895), with more than seven
+// slabs up to 3 % faster at best.  Their time, a fit to these calls (5.2 % rms), has to be below 0.95 of the other path's: 512
+// -> 512, 64 rows 7.0 us against 10.9; 2048 -> 2048, 32 rows 7.6 against 11.9; 4096 -> 4096 with 65 to 128 rows stays where it was.
+bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M) {
+  if (M <= kDecodeMaxM || M > kDecodeMaxM * kGemvMaxBatch || K > 4096) return false;
+  const int32_t chunks = (M + kDecodeMaxM - 1) / kDecodeMaxM, nslab = 8 * (N / kTile);
+  const int32_t share = kGemvMaxGrid / chunks / 8 * 8;  // workgroups of a chunk, at least (split_grid deals them in eights)
+  const int32_t slabs = (nslab + share - 1) / share, cols = (K / kTile + kGemvWaves - 1) / kGemvWaves;
+  if (slabs > 7) return false;
+  return 6.415 + 0.37 * slabs * (cols + 1) + 0.014 * chunks + 0.32e-3 * K < 0.95 * matrix_core_time_us(N, K, M);
+}
+
 static int chunk_problems(const GemmArgs& a, GemmArgs* probs) {
   const sfmp_layout_t* L = a.L;
   const int count = (a.M + kDecodeMaxM - 1) / kDecodeMaxM;

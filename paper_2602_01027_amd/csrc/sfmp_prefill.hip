@@ -1199,7 +1199,7 @@ static double plain_time_us(int32_t N, int32_t K, int32_t M) {
 // form of each), and more than 2 % slower on 0.4 % of them.  prefill_kernel where it is estimated less than 3 % slower: with
 // a little more than a multiple of 256 workgroups the last round of the others is nearly empty (631 x 3072 -> 23936, 118.7
 // us against 125.6; without it 0.75 % of the shapes are more than 2 % slower).  One K group where a workgroup has a single tile.
-PrefillForm choose_prefill_form(int32_t N, int32_t K, int32_t M) {
+static PrefillForm choose_form(int32_t N, int32_t K, int32_t M, double* time_us) {
   const int64_t ntr = N / kTile, ntc = K / kTile;
   int32_t bm = 0;
   const int32_t most = documented_ranges(N, K, M, &bm);
@@ -1214,8 +1214,20 @@ PrefillForm choose_prefill_form(int32_t N, int32_t K, int32_t M) {
         const double t = fed_time_us(N, K, M, mi, kg, k);
         if (least < 0.0 || t < least) least = t, best = PrefillForm{mi, kg, k};
       }
+  *time_us = least;
   if ((int64_t)((M + 127) / 128) * ntr > 256 && plain_time_us(N, K, M) < 1.03 * least) best = PrefillForm{0, 1, 1};
   return best;
+}
+
+PrefillForm choose_prefill_form(int32_t N, int32_t K, int32_t M) {
+  double t;
+  return choose_form(N, K, M, &t);
+}
+
+double matrix_core_time_us(int32_t N, int32_t K, int32_t M) {
+  double t;
+  choose_form(N, K, M, &t);
+  return t;
 }
 
 static int check_launch(const char* what) {

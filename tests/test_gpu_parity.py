@@ -225,8 +225,9 @@ def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, sca
 
 
 @pytest.mark.parametrize("K,N,M,group,scale_format,fractions,form", [
-    (128, 128, 17, 64, "bf16", {4: 1.0}, (4, 1, 1)), (256, 128, 17, 256, "fp16", {2: 1.0}, (4, 2, 1)),
-    (640, 512, 64, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 1)), (3200, 128, 17, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 3)),
+    (128, 128, 129, 64, "bf16", {4: 1.0}, (4, 1, 1)), (256, 128, 129, 256, "fp16", {2: 1.0}, (4, 2, 1)),
+    (640, 512, 130, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 1)), (3200, 128, 129, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 3)),
+    (3200, 12288, 33, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 2)),
     (9856, 128, 129, 128, "fp16", {3: 0.5, 4: 0.5}, (4, 2, 8)), (256, 16512, 65, 64, "fp16", {2: 0.5, 4: 0.5}, (5, 2, 1)),
     (3200, 5632, 65, 128, "bf16", {3: 1.0}, (5, 2, 3)), (640, 16512, 81, 128, "bf16", {2: 0.5, 3: 0.5}, (6, 2, 1)),
     (3200, 8320, 81, 64, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (6, 2, 3)), (896, 16512, 97, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (7, 2, 1)),
@@ -246,7 +247,7 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
     from gpu_util import run_gemm
     if group > 128 and K % group:
         K = K // group * group
-    assert not plan_util.chunked(N, K, M)
+    assert not plan_util.chunked(N, K, M) and not plan_util.chunks_without_staging(N, K, M)
     assert form is None or plan_util.launched_form(N, K, M) == form
     p = W.make_problem("forms", K, N, M, 9500 + K + M, fractions=fractions, outliers=True, group=group, scale_format=scale_format,
                        fast_codes=K * N > 2 ** 20)
@@ -581,7 +582,9 @@ def test_small_batch_three_and_four_tile_columns_per_wavefront(torch_cuda, K, N,
     (128, 128, 5, 128, "fp16", True), (384, 512, 8, 64, "bf16", True), (512, 512, 9, 128, "fp16", False), (2048, 384, 16, 256, "bf16", True),
     (2176, 640, 13, 128, "fp16", True), (3968, 8192, 8, 128, "fp16", True), (4096, 28672, 7, 128, "fp16", True),
     (4096, 28672, 16, 64, "fp16", True), (4096, 4096, 16, 128, "fp16", False), (4096, 1024, 3, 64, "fp16", True),
-    (4096, 256, 20, 128, "fp16", True), (4096, 512, 72, 64, "bf16", True)])
+    (4096, 256, 20, 128, "fp16", True), (4096, 512, 72, 64, "bf16", True), (128, 128, 17, 128, "fp16", True),
+    (512, 512, 65, 64, "fp16", True), (2048, 1024, 128, 128, "bf16", False), (4096, 7168, 40, 128, "fp16", True),
+    (896, 4096, 33, 128, "fp16", True)])
 def test_small_batch_operands_gathered_without_a_staging_launch(torch_cuda, K, N, M, group, scale_format, perm):
     # activations transposed in LDS, 8 rows of a column together or 16: first and last row of each, one tile column (wavefronts
     # without any), one and two per wavefront, one to seven slabs per workgroup, without a permutation, chunks of 16 rows
@@ -593,7 +596,7 @@ def test_small_batch_operands_gathered_without_a_staging_launch(torch_cuda, K, N
                        scale_format=scale_format, block=(1, max(1, group // 128)), fast_codes=N * K > 2 ** 22, use_col_perm=perm)
     layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(p.bitmap, N, K), group, scale_format)
     d = plan_util.batched_config([layout] * -(-M // 16), 16)[0] if M > 16 else plan_util.decode_plan(N, K, M, group)
-    assert d.ra == 2 and d.resident and (M <= 16 or plan_util.chunked(N, K, M))
+    assert d.ra == 2 and d.resident and (M <= 16 or plan_util.chunked(N, K, M) or plan_util.chunks_without_staging(N, K, M))
     y1 = run_gemm(p)
     _check(p, y1, None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))

@@ -435,6 +435,24 @@ def test_launched_form_of_a_matrix_core_call():
         assert plan_util.launched_form(*shape) == form, shape
 
 
+def test_chunks_without_staging_touch_no_workspace():
+    # whatever the mix of widths and the group length: the whole launch takes the form whose operands the kernel gathers itself
+    import plan_util
+    rng = np.random.default_rng(13)
+    taken = 0
+    for _ in range(300):
+        K, N = (int(128 * np.ceil(2 ** rng.uniform(0, hi))) for hi in (5.2, 7.5))
+        M, group = int(rng.integers(15, 132)), int(rng.choice((64, 128)))
+        if not plan_util.chunks_without_staging(N, K, M):
+            continue
+        taken += 1
+        layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(rng.integers(2, 5, (N // 128, K // 128)).astype(np.int8), N, K), group, "fp16")
+        config, grids = plan_util.batched_config([layout] * -(-M // 16), 16)
+        assert 17 <= M <= 128 and K <= 4096 and config.ra == 2 and config.resident, (N, K, M)
+        assert max(-(-N // 16 // g) for g in grids) <= 7, (N, K, M)
+    assert taken > 60
+
+
 @pytest.mark.parametrize("N,K,M,group,streamed", [
     (8192, 28672, 8, 128, True), (8192, 28672, 16, 64, True), (4224, 8320, 5, 128, True), (8192, 8320, 16, 64, True),
     (8192, 12288, 8, 64, True), (8192, 12160, 8, 64, False),  # up to 8 rows, group length 64: from K = 12288 on
