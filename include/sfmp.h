@@ -180,7 +180,8 @@ int sfmp_workspace_init(void* workspace_dev, int64_t bytes, void* hip_stream);
  * M = 1 runs the bandwidth-bound GEMV kernel, 2 <= M <= 16 (and M = 1 with K above about 32k) the
  * same scheme with the activations staged per tile column, 16 < M <= 128 with K >= 4096 on matrices and
  * batch sizes where that measured faster (N <= 1024: M <= 128; K <= 8192: M <= 32 on any N, M <= 64 up to
- * 1536 tiles of 128 x 128, M <= 96 up to 1024 tiles; longer K: M <= 32 on N <= 4096) that kernel once more, on
+ * 1536 tiles of 128 x 128, M <= 96 up to 1024 tiles; longer K: M <= 32 on N <= 4096; K <= 4096: also where the chunks
+ * need no workspace and are estimated to be faster) that kernel once more, on
  * chunks of 16 rows side by side in one launch, and everything else the MFMA prefill kernels (with K
  * cut into ranges and fp32 partial products in the workspace when there would be few workgroups;
  * SFMP_ERR_SHAPE there if K > 57344, or, with a row permutation or a split K, N > 81920; the kernels for
@@ -236,7 +237,7 @@ int sfmp_gemv_batched(const sfmp_gemv_problem_t* problems_host, int32_t count, v
 
 /* The same for a small batch: up to 8 independent products with a common M, 1 <= M <= 16 (each exactly what
  * sfmp_gemm computes; X_dev of a problem is fp16 [M, K], Y_dev fp16 [M, N]), in one launch of the GEMM kernel plus,
- * for M >= 2, one launch of the activation staging kernel.  Problems that pass the same X_dev, col_perm_dev and K
+ * for M >= 2 where the kernel does not gather its activations itself, one launch of the activation staging kernel.  Problems that pass the same X_dev, col_perm_dev and K
  * (q, k and v; gate and up) share one staged copy of the activations.  M = 1 is sfmp_gemv_batched.
  * One launch runs one form of the kernel, chosen for the whole batch (by its largest K and its largest share of
  * slabs per workgroup), which may not be the form a single sfmp_gemm call takes for one of its problems: the operation

@@ -323,7 +323,7 @@ def sfmp_gemm_batched_workspace(problems, M: int) -> int:
 
 
 def sfmp_gemm_batched(problems, M: int, workspace, stream=None) -> None:
-    """Up to 8 independent products with a common M <= 16 in one launch (plus one staging launch for M >= 2)."""
+    """Up to 8 independent products with a common M <= 16 in one launch (for M >= 2 plus a staging launch where one is needed)."""
     rc = _launcher().gemm_batched(problems, M, workspace, stream)
     if rc is not None:
         return _check(rc)

@@ -1139,6 +1139,7 @@ PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
   const int64_t blocks128 = (int64_t)((M + 127) / 128) * ntr;
   const int64_t ks = documented_ranges(N, K, M, &d.bm);
   d.ksplit = (int32_t)ks;
+  // (What is launched is choose_prefill_form's choice; the 64-row and ring forms named here are gone.)
   // The number of ranges decides the workspace.  Within it another form is taken where the times above make it at least
   // 5 % faster: fewer ranges, 128-row blocks, or the ring form, which needs 4 tiles per K group to pay for its longer start
   // (512 -> 512: 2 % slower with 2).  Every form was measured on 6436 random shapes (M = 17 ... 1100, K and N from 384 to
