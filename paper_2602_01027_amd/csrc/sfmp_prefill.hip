@@ -732,19 +732,15 @@ __global__ __launch_bounds__(768, 3) void prefill_fed_kernel(const PrefillParams
       // unit u ^ (r / 2 % 8).
       constexpr int C = BM / 16;
       const uint32_t xlane = (uint32_t)(lane / 8) * 256 + (uint32_t)(((lane & 7) ^ ((4 * pw + lane / 16) & 7)) * 16);
-      const uint32_t blk_bytes = (uint32_t)p.ntc * (uint32_t)(kTile * kTile * 2);
-      const int sub = BM < kTile && kTile % BM == 0 ? m0 % kTile : 0;
-      const uint64_t xb64 = (uint64_t)(p.Xp + (int64_t)(m0 / kTile) * p.ntc * (kTile * kTile) + sub * kTile);
+      const StagedRows<BM> staged(p.M, m0, (uint32_t)p.ntc * (uint32_t)(kTile * kTile * 2));
+      const uint64_t xb64 = (uint64_t)p.Xp + (uint64_t)staged.base;
       // (a workgroup's rows may reach past the last block of 128: no request for a block that is not there)
-      const int rows = ((p.M + kTile - 1) / kTile - m0 / kTile) * kTile;
-      const uint32_t xbytes = (uint32_t)(rows / kTile) * blk_bytes - (uint32_t)sub * (kTile * 2);
-      uint32_t xso[C], xrec[C];  // offset of a copy's rows, records (none: rows that are not there)
+      uint32_t xso[C], xrec[C];  // offset of a copy's rows, records
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const int row = (BM % kTile == 0 || kTile % BM == 0 ? 0 : m0 % kTile) + 8 * (2 * c + pw);
-        const bool there = row < rows;
-        xso[c] = there ? (uint32_t)(row / kTile) * blk_bytes + (uint32_t)(row % kTile) * 256 : 0u;
-        xrec[c] = there ? xbytes : 0u;
+        const BlockRequest rows = staged.copy(8 * (2 * c + pw));
+        xso[c] = rows.offset;
+        xrec[c] = rows.records;
       }
       auto half_block = [&](int h, int buf) __attribute__((always_inline)) {
 #pragma unroll

@@ -1,6 +1,6 @@
 // The parts of the kernels' requests to memory that a host program can run against a model (tests/schedule_driver.cpp):
 // the order of requests and waits of the small-batch form whose activations are streamed through registers (sfmp_decode.hip,
-// RS), and what a copy of an activation block asks for (sfmp_prefill.hip).
+// RS), and what the copies of activation blocks ask for (sfmp_prefill.hip).
 #pragma once
 
 #include <stdint.h>
@@ -64,5 +64,36 @@ struct BlockRequest {
 SFMP_SCHEDULE_FN BlockRequest block_request(const uint32_t column_offset, const uint32_t bytes, const bool wanted) {
   return BlockRequest{wanted ? column_offset : 0u, wanted ? bytes : 0u};
 }
+
+// What a workgroup with BM rows of the batch from row m0 on (a multiple of BM) copies of the staged activations, which lie in
+// blocks of 128 rows (block_bytes = K * 256 each, 256 bytes per row and tile column): copies of 8 rows, no more row blocks than
+// there are.
+template <int BM>
+struct StagedRows {
+  static constexpr int kBlock = 128;
+  static constexpr bool kInside = kBlock % BM == 0, kWhole = BM % kBlock == 0;  // the rows lie in one block; they start one
+  int64_t base;  // first byte of the range in the staged activations
+  int rows;      // rows of the row blocks that the workgroup's rows reach into, as far as they are there
+  uint32_t bytes, block_bytes;
+  int first;     // the workgroup's first row, counted from `base` (where the rows may cross from block to block)
+
+  SFMP_SCHEDULE_FN StagedRows(const int M, const int m0, const uint32_t bytes_of_block) {
+    block_bytes = bytes_of_block;
+    const int sub = kInside ? m0 % kBlock : 0;
+    first = kInside || kWhole ? 0 : m0 % kBlock;
+    base = (int64_t)(m0 / kBlock) * block_bytes + sub * 256;
+    // at most three blocks of 14.7 MB (all that are left, in bytes, pass 32 bits from M * K = 2^31 on)
+    const int left = (M + kBlock - 1) / kBlock - m0 / kBlock, reached = kInside ? 1 : (first + BM + kBlock - 1) / kBlock;
+    const int blocks = left < reached ? left : reached;
+    rows = blocks * kBlock;
+    bytes = (uint32_t)blocks * block_bytes - (uint32_t)sub * 256u;
+  }
+  // Rows `row` ... `row` + 7 of the workgroup in tile column 0: offset from `base` and records (none: rows that are not there)
+  SFMP_SCHEDULE_FN BlockRequest copy(const int row) const {
+    const int r = first + row;
+    const bool there = r < rows;
+    return BlockRequest{there ? (uint32_t)(r / kBlock) * block_bytes + (uint32_t)(r % kBlock) * 256u : 0u, there ? bytes : 0u};
+  }
+};
 
 }  // namespace sfmp

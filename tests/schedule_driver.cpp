@@ -5,7 +5,8 @@
 // may leave it out), so every walk is checked with those loads and without them.
 //
 // Copies of activation blocks against the range check of a raw buffer, with the scalar offset counted in it and not: what is
-// wanted is read from inside the row block, and nothing is read past the end.
+// wanted is read from inside the row block, and nothing is read past the end.  And the copies of a workgroup's rows, which may
+// lie in two or three row blocks of a batch of any length: the bytes that are meant, inside the staged activations.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -78,8 +79,59 @@ static void check_block_requests() {
       }
 }
 
+template <int BM>
+static void check_staged_rows(const int M, const uint32_t ntc) {
+  const int64_t block = (int64_t)ntc * 32768, blocks = (M + 127) / 128, end = blocks * block;
+  const int groups = (M + BM - 1) / BM;
+  for (int g = 0; g < groups; ++g) {
+    const sfmp::StagedRows<BM> staged(M, g * BM, (uint32_t)block);
+    for (int row = 0; row < BM; row += 8) {
+      const sfmp::BlockRequest rows = staged.copy(row);
+      const int64_t m = (int64_t)g * BM + row;  // (eight rows from a multiple of 8 on are in one block)
+      const bool there = m / 128 < blocks;
+      for (const uint32_t tc : {0u, ntc - 1})
+        for (const uint32_t half : {0u, 128u}) {
+          const sfmp::BlockRequest x = sfmp::block_request(tc * 32768u + half + rows.offset, rows.records, true);
+          const int64_t meant = m / 128 * block + (int64_t)tc * 32768 + (m % 128) * 256 + half;
+          const uint64_t last = 7 * 256 + 112;  // offset of the last 16 bytes of the copy within its 8 rows
+          const bool read_with = x.records >= 16 && x.offset <= x.records && last + 16 <= x.records - x.offset;
+          const bool read_without = last + 16 <= x.records;
+          const bool right = there ? read_with && read_without && staged.base + x.offset == meant &&
+                                         staged.base + (int64_t)x.records <= end && (uint64_t)x.offset + last + 16 <= x.records
+                                   : x.records == 0;
+          if (!right) {
+            std::printf("staged rows: %d rows in workgroups of %d, %u tile columns: row %lld, column %u + %u: offset %u of %u records\n",
+                        M, BM, ntc, (long long)m, tc, half, x.offset, x.records);
+            std::exit(1);
+          }
+        }
+    }
+  }
+}
+
+static void check_staged_rows_of_all_forms(const int M, const uint32_t ntc) {
+  check_staged_rows<64>(M, ntc);
+  check_staged_rows<80>(M, ntc);
+  check_staged_rows<96>(M, ntc);
+  check_staged_rows<112>(M, ntc);
+  check_staged_rows<128>(M, ntc);
+  check_staged_rows<160>(M, ntc);
+  check_staged_rows<192>(M, ntc);
+  check_staged_rows<224>(M, ntc);
+  check_staged_rows<256>(M, ntc);
+}
+
 int main() {
   check_block_requests();
+  for (const uint32_t ntc : {1u, 2u, 31u, 128u, 224u, 448u}) {
+    for (int M = 17; M < 800; M += 61) check_staged_rows_of_all_forms(M, ntc);
+    if (ntc < 31) continue;
+    // staged activations of a little less than 4 and 8 GiB, just that and a little more
+    for (const int64_t bytes : {(int64_t)1 << 32, (int64_t)1 << 33}) {
+      const int M = (int)(bytes / ((int64_t)ntc * 256));
+      for (const int rows : {M - 200, M, M + 1, M + 700}) check_staged_rows_of_all_forms(rows, ntc);
+    }
+  }
   for (int count = 1; count <= 64; ++count) {
     std::vector<Event> events;
     auto load = [&](auto set, int i) { events.push_back({Event::kLoad, decltype(set)::value, i, false}); };

@@ -256,6 +256,30 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
 
 
+@pytest.mark.parametrize("K,N,M,form", [(16384, 128, 131072, (8, 1, 1)), (28672, 256, 75008, (7, 1, 1))])
+def test_prompt_with_4_gib_of_activations(torch_cuda, K, N, M, form):
+    # byte counts of the staged activations at and above 2^32: rows of the first, of middle and of the last workgroups, with
+    # row blocks of whole workgroups (256 rows) and with workgroups across them (224)
+    import paper_2602_01027_amd as S
+    import plan_util
+    from gpu_util import device_problem, make_workspace
+    torch = torch_cuda
+    assert 2 * M * K >= 2 ** 32 and plan_util.launched_form(N, K, M) == form
+    p = W.make_problem("long prompt", K, N, 17, 9900 + K, fractions={2: 0.3, 3: 0.3, 4: 0.4}, fast_codes=True)
+    dp, cp, rp = device_problem(p)
+    X = torch.empty((M, K), dtype=torch.float16, device="cuda:0")
+    gen = torch.Generator(device="cuda:0").manual_seed(K)
+    for r in range(0, M, 8192):
+        X[r:r + 8192].normal_(generator=gen)
+    Y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda:0")
+    S.sfmp_gemm(X, cp, dp.layout, dp.s2, dp.s3, dp.s4, dp.index, dp.scales, dp.zeros, dp.bitmap, rp, Y, make_workspace(dp.layout, M))
+    assert bool(torch.isfinite(Y).all())
+    rows = np.unique([0, 7, 8, 127, 128, 223, 224, 255, 256, 447, 448, M // 3, M // 2 - 1, M // 2, M - 257, M - 256, M - 225, M - 224,
+                      M - 129, M - 128, M - 1, *np.random.default_rng(K).choice(M, 24, replace=False)])
+    at = torch.from_numpy(rows).to("cuda:0")
+    _check(dataclasses.replace(p, M=rows.size, X=X[at].cpu().numpy()), Y[at].cpu().numpy())
+
+
 @pytest.mark.parametrize("K,N,M,scale_format,fractions", [
     (128, 8320, 400, "fp16", {2: 0.5, 4: 0.5}), (640, 8320, 400, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}), (1152, 8320, 390, "fp16", {3: 1.0}),
     (640, 8192, 1000, "bf16", {2: 0.5, 3: 0.5}), (640, 8192, 512, "fp16", {3: 0.5, 4: 0.5}), (640, 8320, 1000, "bf16", {2: 0.5, 4: 0.5})])
