@@ -160,7 +160,9 @@ int sfmp_workspace_init(void* workspace_dev, int64_t bytes, void* hip_stream);
  *   Y         fp16 [M, N] row-major; fully overwritten.  fp32 accumulation, one
  *             round-to-nearest-even conversion at the end.  The order of the fp32 sums is fixed for a given
  *             (N, K, M, group length): the same call on the same inputs gives the same bits, on any stream
- *             (no floating-point atomics anywhere).
+ *             (no floating-point atomics anywhere).  Y may lie over X for M >= 5: the activations have then been read
+ *             before the first result is stored (which may take another form of the kernel, with its own fixed order, than
+ *             the call with separate buffers).  For M <= 4 X and Y must not overlap.
  *   workspace device memory of at least sfmp_gemm_workspace() bytes, 256-byte aligned; contents
  *             on entry are irrelevant, contents on return are unspecified.
  * Alignment (SFMP_ERR_ALIGN otherwise): X, col_perm, row_perm, s2, s3, s4, scales and zeros 16 bytes (the kernels
@@ -236,8 +238,9 @@ typedef struct sfmp_gemv_problem {
 int sfmp_gemv_batched(const sfmp_gemv_problem_t* problems_host, int32_t count, void* hip_stream);
 
 /* The same for a small batch: up to 8 independent products with a common M, 1 <= M <= 16 (each exactly what
- * sfmp_gemm computes; X_dev of a problem is fp16 [M, K], Y_dev fp16 [M, N]), in one launch of the GEMM kernel plus,
- * for M >= 2 where the kernel does not gather its activations itself, one launch of the activation staging kernel.  Problems that pass the same X_dev, col_perm_dev and K
+ * sfmp_gemm computes; X_dev of a problem is fp16 [M, K], Y_dev fp16 [M, N]; for M >= 5 a Y_dev may lie over any X_dev), in
+ * one launch of the GEMM kernel plus, for M >= 2 where the kernel does not gather its activations itself, one launch of
+ * the activation staging kernel.  Problems that pass the same X_dev, col_perm_dev and K
  * (q, k and v; gate and up) share one staged copy of the activations.  M = 1 is sfmp_gemv_batched.
  * One launch runs one form of the kernel, chosen for the whole batch (by its largest K and its largest share of
  * slabs per workgroup), which may not be the form a single sfmp_gemm call takes for one of its problems: the operation

@@ -80,7 +80,7 @@ int sfmp_gemm_workspace(const sfmp_layout_t* layout, int32_t M, int64_t* bytes) 
   if (int e = check_layout(layout)) return e;
   if (M < 1) return SFMP_ERR_SHAPE;
   if (M <= kDecodeMaxM) {
-    const DecodePlan d = make_decode_plan(layout->N, layout->K, M, layout->group);
+    const DecodePlan d = make_decode_plan(layout->N, layout->K, M, layout->group, false);
     *bytes = d.workspace_bytes;
   } else if (use_chunked_decode(layout->N, layout->K, M)) {
     GemmArgs a{};
@@ -196,8 +196,7 @@ static int gemm_with_workspace(const void* X_dev, int32_t M, const int32_t* col_
   a.workspace = workspace_dev;
   a.workspace_bytes = workspace_bytes;
   if (M <= kDecodeMaxM) return launch_decode(a, hip_stream);
-  if (use_chunked_decode(layout->N, layout->K, M) || use_chunks_without_staging(layout->N, layout->K, M))
-    return launch_decode_chunked(a, hip_stream);
+  if (runs_in_chunks(a)) return launch_decode_chunked(a, hip_stream);
   return launch_prefill(a, hip_stream);
 }
 

@@ -1526,7 +1526,8 @@ constexpr int kSlotsStreamedActs = 3;
 constexpr int kSlotsRegisterActs = 2;  // activations in registers: the slots hold a slab and its parameters only
 // max_slabs: the largest number of slabs of a workgroup over the problems of the launch; K: the largest K
 // g64: group length 64, for which the resident form does not exist
-static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, bool g64) {
+// overwrites: outputs lie over activations, so the operands are not gathered in the launch that stores the products
+static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, bool g64, bool overwrites) {
   RSkinnyConfig c;
   c.mb = rskinny_mb(M);
   // 16 wavefronts where the finished sums fit beside the rest in 128 registers and the rings in LDS
@@ -1557,7 +1558,12 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
     // four (K <= 8192, up to 8 rows): 8192 -> 8192 12.72 / 12.73, 8192 -> 28672 26.96 / 27.34.  And not for the resident form's
     // M <= 4, whose start is shorter still: 512 -> 512 M = 4 4.22 / 4.92, 4096 -> 14336 10.43 / 10.39.
     // (It fits wherever the sums and slots do: 128 KiB of transposed activations and the first slots are 148 KiB.)
-    r.resident = r.nw == 16 && r.ra == 2;
+    if (r.nw == 16 && r.ra == 2) {
+      if (overwrites)
+        r.ra = 4;  // the form with a staging launch
+      else
+        r.resident = true;
+    }
     if (rskinny_lds_bytes(r, max_slabs, M, K) <= 160 * 1024) return r;
   }
   // a longer K with two slabs per workgroup (4096 < N <= 8192 on a full grid): operands streamed through registers.  Not
@@ -1576,7 +1582,18 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
   return c;
 }
 
-DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
+// Does an output lie over activations, its own problem's or another's?  (A plan may be asked for without buffers.)
+bool overwrites_activations(const GemmArgs* probs, int count) {
+  for (int i = 0; i < count; ++i)
+    for (int j = 0; j < count; ++j) {
+      const uintptr_t y = (uintptr_t)probs[i].Y, x = (uintptr_t)probs[j].X;
+      const uintptr_t ny = (uintptr_t)probs[i].M * (uintptr_t)probs[i].L->N * 2, nx = (uintptr_t)probs[j].M * (uintptr_t)probs[j].L->K * 2;
+      if (y && x && y < x + nx && x < y + ny) return true;
+    }
+  return false;
+}
+
+DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool overwrites) {
   DecodePlan d;
   const int32_t ntr = N / kTile, ntc = K / kTile, nslab = 8 * ntr;
   // GEMV: persistent grid of at most 256 workgroups (multiple of 8), 16 wavefronts each.
@@ -1606,7 +1623,7 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
   d.gemv = false;
   d.grid = grid;
   d.max_slabs = (nslab + grid - 1) / grid;
-  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, group == 64);
+  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, group == 64, overwrites);
   d.mb = c.mb;
   d.nw = c.nw;
   d.acc = c.acc;
@@ -1617,6 +1634,12 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
   d.lds_bytes = (int32_t)rskinny_lds_bytes(c, d.max_slabs, M, K);
   d.workspace_bytes = round_up_256((int64_t)ntc * c.mb * 256);
   return d;
+}
+
+DecodePlan decode_plan_of(const GemmArgs& a) {
+  const DecodePlan d = make_decode_plan(a.L->N, a.L->K, a.M, a.L->group, false);
+  const bool gathers = !d.gemv && d.resident && d.ra;
+  return gathers && overwrites_activations(&a, 1) ? make_decode_plan(a.L->N, a.L->K, a.M, a.L->group, true) : d;
 }
 
 static GemvParams gemv_params(const GemmArgs& a, int32_t max_slabs, int32_t grid) {
@@ -1719,7 +1742,7 @@ int launch_gemv_batched(const GemmArgs* probs, int count, void* stream) {
   for (int i = 0; i < count; ++i)
     if (!decode_offsets_fit(probs[i].L)) return SFMP_ERR_SHAPE;
   // a single problem takes the plain kernel: its arguments are the kernel's own, one line fetched once
-  if (count == 1 && probs[0].M == 1 && make_decode_plan(probs[0].L->N, probs[0].L->K, 1, probs[0].L->group).gemv)
+  if (count == 1 && probs[0].M == 1 && make_decode_plan(probs[0].L->N, probs[0].L->K, 1, probs[0].L->group, false).gemv)
     return launch_decode(probs[0], stream);
   int32_t g[kGemvMaxBatch];
   if (int e = split_grid(probs, count, g)) return e;
@@ -1947,7 +1970,8 @@ int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinn
   }
   if (n64 != 0 && n64 != count) return SFMP_ERR_SHAPE;  // one launch runs one group-length class: 64, or the others
   *g64 = n64 != 0;
-  *c = rskinny_config(M, max_k, max_slabs, n64 != 0);
+  *c = rskinny_config(M, max_k, max_slabs, n64 != 0, false);
+  if (c->resident && c->ra && overwrites_activations(probs, count)) *c = rskinny_config(M, max_k, max_slabs, n64 != 0, true);
   return SFMP_OK;
 }
 
@@ -2024,6 +2048,11 @@ bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M) {
   return 6.415 + 0.37 * slabs * (cols + 1) + 0.014 * chunks + 0.32e-3 * K < 0.95 * matrix_core_time_us(N, K, M);
 }
 
+bool runs_in_chunks(const GemmArgs& a) {
+  if (use_chunked_decode(a.L->N, a.L->K, a.M)) return true;
+  return use_chunks_without_staging(a.L->N, a.L->K, a.M) && !overwrites_activations(&a, 1);
+}
+
 static int chunk_problems(const GemmArgs& a, GemmArgs* probs) {
   const sfmp_layout_t* L = a.L;
   const int count = (a.M + kDecodeMaxM - 1) / kDecodeMaxM;
@@ -2055,7 +2084,7 @@ static bool decode_offsets_fit(const sfmp_layout_t* L) { return (int64_t)L->N * 
 int launch_decode(const GemmArgs& a, void* stream) {
   const sfmp_layout_t* L = a.L;
   if (!decode_offsets_fit(L)) return SFMP_ERR_SHAPE;
-  const DecodePlan d = make_decode_plan(L->N, L->K, a.M, L->group);
+  const DecodePlan d = decode_plan_of(a);
   if (d.gemv) {
     const GemvParams p = gemv_params(a, d.max_slabs, d.grid);
     return launch_gemv_plain(p, d.grid, (size_t)d.lds_bytes, stream);

@@ -25,7 +25,8 @@ struct DecodePlan {
   int32_t rs;        // ring-skinny: slabs per workgroup with the activations streamed through registers (0 or 2)
   int64_t workspace_bytes;  // staged activations of the ring-skinny kernel
 };
-DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group);
+// overwrites: the output lies over the activations (the workspace is the same)
+DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool overwrites);
 
 // Prefill path (M > 16): workspace holds the column-gathered activation.  bm, ring and ksplit: the form by the rule from
 // before prefill_fed_kernel, the yardstick for choose_prefill_form, which has the say over what is launched.
@@ -82,6 +83,8 @@ namespace sfmp {
 int launch_unpack(const sfmp_layout_t* L, const uint8_t* s2, const uint8_t* s3, const uint8_t* s4,
                   const int32_t* index, uint8_t* codes, void* stream);
 int launch_fill_zero(void* ptr, int64_t bytes, void* stream);
+bool overwrites_activations(const GemmArgs* problems, int count);
+DecodePlan decode_plan_of(const GemmArgs& a);  // of the launch with these buffers
 int launch_decode(const GemmArgs& a, void* stream);
 int launch_gemv_batched(const GemmArgs* problems, int count, void* stream);
 int launch_decode_batched(const GemmArgs* problems, int count, int32_t M, void* workspace, void* stream);
@@ -89,6 +92,7 @@ int64_t batched_workspace_bytes(const GemmArgs* problems, int count, int32_t M);
 // 16 < M <= 128 on matrices with few tile rows: chunks of 16 rows through the batched ring kernel
 bool use_chunked_decode(int32_t N, int32_t K, int32_t M);
 bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M);  // also: chunks that touch no workspace
+bool runs_in_chunks(const GemmArgs& a);  // one or the other, with these buffers
 int64_t chunked_decode_workspace_bytes(const GemmArgs& a);
 int launch_decode_chunked(const GemmArgs& a, void* stream);
 int launch_prefill(const GemmArgs& a, void* stream);

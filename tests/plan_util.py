@@ -38,7 +38,7 @@ def prefill_bytes(N, K, M, group=128):
 
 
 def decode_plan(N, K, M, group=128):
-    return _call("_ZN4sfmp16make_decode_planEiiii", DecodePlan, N, K, M, group)
+    return _call("_ZN4sfmp16make_decode_planEiiiib", DecodePlan, N, K, M, group, False)
 
 
 class _GemmArgs(C.Structure):
@@ -52,12 +52,19 @@ class SmallBatchConfig(C.Structure):
                 ("rs", C.c_int32), ("ra", C.c_int32)]
 
 
-def batched_config(layouts, M):
+def _gemm_args(layouts, M, X=None, Y=None):
+    """Arguments of products of M rows; X, Y: device addresses (never dereferenced here)."""
+    args = (_GemmArgs * len(layouts))()
+    for i, layout in enumerate(layouts):
+        args[i].M, args[i].L = M, C.pointer(layout)
+        args[i].X, args[i].Y = X[i] if X else None, Y[i] if Y else None
+    return args
+
+
+def batched_config(layouts, M, X=None, Y=None):
     """(configuration, workgroups per problem) of one small-batch launch of several matrices."""
     n = len(layouts)
-    args = (_GemmArgs * n)()
-    for a, layout in zip(args, layouts):
-        a.M, a.L = M, C.pointer(layout)
+    args = _gemm_args(layouts, M, X, Y)
     g, c, g64 = (C.c_int32 * 8)(), SmallBatchConfig(), C.c_bool()
     f = S.load_library()._ZN4sfmp12batch_configEPK8GemmArgsiiPiPNS_13RSkinnyConfigEPb
     f.restype = C.c_int
@@ -78,3 +85,17 @@ def launched_form(N, K, M):
 def chunks_without_staging(N, K, M):
     """Do 17 <= M <= 128 rows beyond the documented chunked shapes run in chunks, without touching the workspace?"""
     return _call("_ZN4sfmp26use_chunks_without_stagingEiii", C.c_bool, N, K, M)
+
+
+def launched_decode_plan(layout, M, X, Y):
+    """The plan of a single small-batch launch with these activations and this output."""
+    f = S.load_library()._ZN4sfmp14decode_plan_ofERK8GemmArgs
+    f.restype = DecodePlan
+    return f(_gemm_args([layout], M, [X], [Y]))
+
+
+def runs_in_chunks(layout, M, X, Y):
+    """Do 17 <= M <= 128 rows run in chunks with these activations and this output?"""
+    f = S.load_library()._ZN4sfmp14runs_in_chunksERK8GemmArgs
+    f.restype = C.c_bool
+    return f(_gemm_args([layout], M, [X], [Y]))

@@ -626,6 +626,50 @@ def test_small_batch_operands_gathered_without_a_staging_launch(torch_cuda, K, N
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
 
 
+@pytest.mark.parametrize("K,N,M,group,shift", [
+    (2048, 2048, 5, 128, 0), (4096, 4096, 16, 128, 0), (4096, 14336, 8, 64, 0), (4096, 1024, 16, 128, 4096), (128, 256, 7, 128, 128),
+    (512, 512, 64, 128, 0), (2048, 1024, 33, 64, 1024), (4096, 4096, 64, 128, 0), (4096, 512, 128, 64, 0), (1024, 2048, 200, 128, 0)])
+def test_output_over_the_activations(torch_cuda, K, N, M, group, shift):
+    # Y starts `shift` elements after X in one buffer: one problem per form that gathers its own activations otherwise (single
+    # launches, chunks within and beyond the documented shapes), and the matrix-core path
+    import paper_2602_01027_amd as S
+    from gpu_util import device_problem, make_workspace
+    torch = torch_cuda
+    p = W.make_problem("over", K, N, M, 9950 + K + M, fractions={2: 0.3, 3: 0.4, 4: 0.3}, group=group, block=(1, max(1, group // 128)),
+                       fast_codes=N * K > 2 ** 22)
+    dp, cp, rp = device_problem(p)
+    buffer = torch.full((max(M * K, shift + M * N),), float("nan"), dtype=torch.float16, device="cuda:0")
+    X, Y = buffer[:M * K].view(M, K), buffer[shift:shift + M * N].view(M, N)
+    X.copy_(torch.from_numpy(p.X))
+    S.sfmp_gemm(X, cp, dp.layout, dp.s2, dp.s3, dp.s4, dp.index, dp.scales, dp.zeros, dp.bitmap, rp, Y, make_workspace(dp.layout, M))
+    _check(p, Y.cpu().numpy(), None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+
+
+def test_batched_output_over_the_activations_of_another_problem(torch_cuda):
+    # q|k|v of one input, the last output over that input; and two chained buffers: the first output over the second's input
+    import paper_2602_01027_amd as S
+    from gpu_util import device_problem
+    torch = torch_cuda
+    M, K = 8, 2048
+    probs = [W.make_problem("over.b", K, N, M, 9990, fractions={2: 0.3, 3: 0.4, 4: 0.3}) for N in (1024, 512, 2048)]
+    packed = [device_problem(p) for p in probs]
+    for over in ("the input they share", "the second one's input"):
+        X = [torch.from_numpy(probs[0].X).to("cuda:0")] * 3
+        Y = [torch.full((M, p.N), float("nan"), dtype=torch.float16, device="cuda:0") for p in probs]
+        if over == "the input they share":
+            Y[2] = X[0].view(M, probs[2].N)
+        else:
+            X[1] = torch.from_numpy(probs[1].X).to("cuda:0")
+            Y[0] = X[1].view(-1)[:M * probs[0].N].view(M, probs[0].N)
+        inputs = [x.cpu().numpy() for x in X]
+        batch = [(x, cp, dp, rp, y) for x, (dp, cp, rp), y in zip(X, packed, Y)]
+        ws = torch.empty(S.sfmp_gemm_batched_workspace(batch, M), dtype=torch.uint8, device="cuda:0").fill_(0xFF)
+        S.sfmp_gemm_batched(batch, M, ws)
+        torch.cuda.synchronize()
+        for p, x, y in zip(probs, inputs, Y):
+            _check(dataclasses.replace(p, X=x), y.cpu().numpy(), None if p.N <= 1024 else np.arange(0, p.N, 5))
+
+
 @pytest.mark.parametrize("K,N,M,group", [(9216, 512, 5, 128), (14336, 1024, 16, 128), (14336, 4096, 16, 128), (28672, 1024, 8, 64),
                                          (16512, 384, 7, 128), (14336, 1024, 40, 128), (28672, 8192, 8, 256)])
 def test_small_batch_long_K(torch_cuda, K, N, M, group):

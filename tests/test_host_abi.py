@@ -453,6 +453,33 @@ def test_chunks_without_staging_touch_no_workspace():
     assert taken > 60
 
 
+def test_outputs_over_activations_are_staged_first():
+    # a launch whose workgroups gather their own activations may not store a row that another one has yet to read: where an
+    # output overlaps activations (its own problem's or another's) they are staged in a launch of their own, as for M >= 5 on any
+    # other matrix
+    import plan_util
+    at = 0x7f0000000000
+    for M, group, n in ((5, 128, 1), (16, 128, 3), (3, 64, 2)):
+        layouts = [S.sfmp_layout_set_quant(S.sfmp_pack_query(np.full((N // 128, 16), 3, dtype=np.int8), N, 2048), group, "fp16")
+                   for N in (2048, 1024, 4096)[:n]]
+        nx, ny = M * 2048 * 2, [M * layout.N * 2 for layout in layouts]
+        apart_x, apart_y = [at + i * 2 ** 20 for i in range(n)], [at + (8 + i) * 2 ** 20 for i in range(n)]
+        last = n - 1
+        for x0, y, gathered in ((at, apart_y, True), (at, [*apart_y[:last], at + nx], True), (at, [*apart_y[:last], at - ny[last]], True),
+                                (at, [*apart_y[:last], at], False), (at, [*apart_y[:last], at + nx - 2], False),
+                                (at, [*apart_y[:last], at - ny[last] + 2], False)):
+            c = plan_util.batched_config(layouts, M, [x0, *apart_x[1:]], y)[0]
+            assert (c.ra, c.resident) == ((2, True) if gathered else (4, False)), (M, group, [hex(v) for v in y])
+            if n == 1:
+                d = plan_util.launched_decode_plan(layouts[0], M, x0, y[0])
+                assert (d.ra, d.resident) == ((2, True) if gathered else (4, False)) and d.lds_bytes <= 160 * 1024
+                assert d.workspace_bytes == plan_util.decode_plan(layouts[0].N, 2048, M, group).workspace_bytes
+    # 17 to 128 rows beyond the documented chunked shapes: the matrix-core path, which stages them
+    layout = S.sfmp_pack_query(np.full((4, 4), 3, dtype=np.int8), 512, 512)
+    assert plan_util.chunks_without_staging(512, 512, 64)
+    assert plan_util.runs_in_chunks(layout, 64, at, at + 2 ** 20) and not plan_util.runs_in_chunks(layout, 64, at, at + 16)
+
+
 @pytest.mark.parametrize("N,K,M,group,streamed", [
     (8192, 28672, 8, 128, True), (8192, 28672, 16, 64, True), (4224, 8320, 5, 128, True), (8192, 8320, 16, 64, True),
     (8192, 12288, 8, 64, True), (8192, 12160, 8, 64, False),  # up to 8 rows, group length 64: from K = 12288 on
