@@ -2039,18 +2039,27 @@ bool use_chunked_decode(int32_t N, int32_t K, int32_t M) {
 // path (geometric mean; 0.3 % of them more than 2 % slower, the worst 4096 -> 7168 with 49 rows, 0.895), with more than seven
 // slabs up to 3 % faster at best.  Their time, a fit to these calls (5.2 % rms), has to be below 0.95 of the other path's: 512
 // -> 512, 64 rows 7.0 us against 10.9; 2048 -> 2048, 32 rows 7.6 against 11.9; 4096 -> 4096 with 65 to 128 rows stays where it was.
-bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M) {
+// Those calls had one parameter pair per tile column.  At group length 64 (two pairs, two activation sums) chunks take up to
+// 17 % longer than that fit: of 673 calls with four to seven slabs 42 were more than 2 % slower than the matrix-core path (4096 ->
+// 6272 with 53 rows 20.1 us against 17.9), none of them in two chunks.  From three chunks on they have to meet a fit of their own
+// besides (3.0 % rms), in which the work follows the mean share of a workgroup; in three chunks, where the other path's time is
+// estimated too low, with 1.04 for the 0.98 that suits four and more.
+bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M, int32_t group) {
   if (M <= kDecodeMaxM || M > kDecodeMaxM * kGemvMaxBatch || K > 4096) return false;
   const int32_t chunks = (M + kDecodeMaxM - 1) / kDecodeMaxM, nslab = 8 * (N / kTile);
   const int32_t share = kGemvMaxGrid / chunks / 8 * 8;  // workgroups of a chunk, at least (split_grid deals them in eights)
   const int32_t slabs = (nslab + share - 1) / share, cols = (K / kTile + kGemvWaves - 1) / kGemvWaves;
   if (slabs > 7) return false;
-  return 6.415 + 0.37 * slabs * (cols + 1) + 0.014 * chunks + 0.32e-3 * K < 0.95 * matrix_core_time_us(N, K, M);
+  const double other = matrix_core_time_us(N, K, M);
+  if (group == 64 && chunks > 2 &&
+      6.08 + 0.408e-3 * K * nslab / share + 0.47 * slabs + 0.0385 * chunks >= (chunks == 3 ? 1.04 : 0.98) * other)
+    return false;
+  return 6.415 + 0.37 * slabs * (cols + 1) + 0.014 * chunks + 0.32e-3 * K < 0.95 * other;
 }
 
 bool runs_in_chunks(const GemmArgs& a) {
   if (use_chunked_decode(a.L->N, a.L->K, a.M)) return true;
-  return use_chunks_without_staging(a.L->N, a.L->K, a.M) && !overwrites_activations(&a, 1);
+  return use_chunks_without_staging(a.L->N, a.L->K, a.M, a.L->group) && !overwrites_activations(&a, 1);
 }
 
 static int chunk_problems(const GemmArgs& a, GemmArgs* probs) {

@@ -91,7 +91,7 @@ int launch_decode_batched(const GemmArgs* problems, int count, int32_t M, void* 
 int64_t batched_workspace_bytes(const GemmArgs* problems, int count, int32_t M);
 // 16 < M <= 128 on matrices with few tile rows: chunks of 16 rows through the batched ring kernel
 bool use_chunked_decode(int32_t N, int32_t K, int32_t M);
-bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M);  // also: chunks that touch no workspace
+bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M, int32_t group);  // also: chunks that touch no workspace
 bool runs_in_chunks(const GemmArgs& a);  // one or the other, with these buffers
 int64_t chunked_decode_workspace_bytes(const GemmArgs& a);
 int launch_decode_chunked(const GemmArgs& a, void* stream);

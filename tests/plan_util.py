@@ -82,9 +82,9 @@ def launched_form(N, K, M):
     return f.mi, f.kg, f.ksplit
 
 
-def chunks_without_staging(N, K, M):
+def chunks_without_staging(N, K, M, group=128):
     """Do 17 <= M <= 128 rows beyond the documented chunked shapes run in chunks, without touching the workspace?"""
-    return _call("_ZN4sfmp26use_chunks_without_stagingEiii", C.c_bool, N, K, M)
+    return _call("_ZN4sfmp26use_chunks_without_stagingEiiii", C.c_bool, N, K, M, group)
 
 
 def launched_decode_plan(layout, M, X, Y):

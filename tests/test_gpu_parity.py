@@ -247,7 +247,7 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
     from gpu_util import run_gemm
     if group > 128 and K % group:
         K = K // group * group
-    assert not plan_util.chunked(N, K, M) and not plan_util.chunks_without_staging(N, K, M)
+    assert not plan_util.chunked(N, K, M) and not plan_util.chunks_without_staging(N, K, M, group)
     assert form is None or plan_util.launched_form(N, K, M) == form
     p = W.make_problem("forms", K, N, M, 9500 + K + M, fractions=fractions, outliers=True, group=group, scale_format=scale_format,
                        fast_codes=K * N > 2 ** 20)
@@ -620,7 +620,7 @@ def test_small_batch_operands_gathered_without_a_staging_launch(torch_cuda, K, N
                        scale_format=scale_format, block=(1, max(1, group // 128)), fast_codes=N * K > 2 ** 22, use_col_perm=perm)
     layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(p.bitmap, N, K), group, scale_format)
     d = plan_util.batched_config([layout] * -(-M // 16), 16)[0] if M > 16 else plan_util.decode_plan(N, K, M, group)
-    assert d.ra == 2 and d.resident and (M <= 16 or plan_util.chunked(N, K, M) or plan_util.chunks_without_staging(N, K, M))
+    assert d.ra == 2 and d.resident and (M <= 16 or plan_util.chunked(N, K, M) or plan_util.chunks_without_staging(N, K, M, group))
     y1 = run_gemm(p)
     _check(p, y1, None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))

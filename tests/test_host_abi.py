@@ -443,7 +443,7 @@ def test_chunks_without_staging_touch_no_workspace():
     for _ in range(300):
         K, N = (int(128 * np.ceil(2 ** rng.uniform(0, hi))) for hi in (5.2, 7.5))
         M, group = int(rng.integers(15, 132)), int(rng.choice((64, 128)))
-        if not plan_util.chunks_without_staging(N, K, M):
+        if not plan_util.chunks_without_staging(N, K, M, group):
             continue
         taken += 1
         layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(rng.integers(2, 5, (N // 128, K // 128)).astype(np.int8), N, K), group, "fp16")
@@ -478,6 +478,15 @@ def test_outputs_over_activations_are_staged_first():
     layout = S.sfmp_pack_query(np.full((4, 4), 3, dtype=np.int8), 512, 512)
     assert plan_util.chunks_without_staging(512, 512, 64)
     assert plan_util.runs_in_chunks(layout, 64, at, at + 2 ** 20) and not plan_util.runs_in_chunks(layout, 64, at, at + 16)
+
+
+@pytest.mark.parametrize("N,K,M,both", [
+    (6272, 4096, 53, False), (3328, 4096, 97, False), (7168, 4096, 49, False), (6784, 3200, 55, False),  # 7 to 12 % slower in chunks
+    (7168, 2048, 49, True), (4096, 2048, 32, True), (512, 512, 64, True), (14208, 1024, 20, True)])
+def test_chunks_without_staging_by_group_length(N, K, M, both):
+    # two parameter pairs per tile column make chunks slower: with many slabs and a long K the matrix-core path is the faster one
+    import plan_util
+    assert plan_util.chunks_without_staging(N, K, M, 128) and plan_util.chunks_without_staging(N, K, M, 64) == both
 
 
 @pytest.mark.parametrize("N,K,M,group,streamed", [
