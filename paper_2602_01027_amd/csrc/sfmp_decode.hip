@@ -994,6 +994,11 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     // column and receives row (its number) of the four columns.
     // 16-byte units of 256 bytes change places with the number of the 256 bytes: a store of a wavefront hits every bank equally.
     // The first item of every wavefront is on its way meanwhile.  Against a staging launch: see rskinny_config.
+    // A wavefront that has no activations to bring or no tile column does neither: at K = 512 two of the 16 have the one and four
+    // the other.  (All of them asked for the last ones again, 64 bytes a cycle and CU: up to 16 rows of K <= 2048 took longer
+    // than with a staging launch.  Graph replays before -> now, with staging: 512 -> 14336, group length 64, 9 rows 8.31 -> 6.65 us,
+    // 7.82; 2048 -> 4096, 9 rows 6.82 -> 5.71, 7.03; 256 -> 2048, group length 64, 9 rows 5.97 -> 4.35, 5.01.  The same test in
+    // front of the permutation entries: 2 % more at K = 2048, 0.6 % less at K = 4096.)
     const int chunk = i16 % 4;
     int pk[RA][8];
 #pragma unroll
@@ -1014,10 +1019,15 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     auto stage = [&](auto rtag) __attribute__((always_inline)) {
       constexpr int R = decltype(rtag)::value;
       u32x2 x[R];
-      const _Float16* const from = p.X + 4 * min(tid, units - 1);
+      if (wave * kWave < units) {
+        const _Float16* const from = p.X + 4 * min(tid, units - 1);
 #pragma unroll
-      for (int m = 0; m < R; ++m)  // (rows past the last: the last again; their products are not stored)
-        x[m] = *reinterpret_cast<const u32x2*>(from + (size_t)min(m, p.M - 1) * p.K);
+        for (int m = 0; m < R; ++m)  // (rows past the last: the last again; their products are not stored)
+          x[m] = *reinterpret_cast<const u32x2*>(from + (size_t)min(m, p.M - 1) * p.K);
+      } else {
+#pragma unroll
+        for (int m = 0; m < R; ++m) asm volatile("" : "=v"(x[m]));  // (any value: not stored)
+      }
       const int Eb0 = min(64, E);
       describe(0, Eb0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // one trip to memory for all of the above
@@ -1047,20 +1057,26 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       barrier_lds_only();
       const uint32_t in_column = (uint32_t)(R == 16 ? chunk : chunk % 2) * 8;
 #pragma unroll
-      for (int t = 0; t < RA; ++t)
+      for (int t = 0; t < RA; ++t) {
+        if (wave + NW * t < p.ntc) {
 #pragma unroll
-        for (int kappa = 0; kappa < 4; ++kappa) {
-          union {
-            v4i16 h[2];
-            half8 v;
-          } o;
+          for (int kappa = 0; kappa < 4; ++kappa) {
+            union {
+              v4i16 h[2];
+              half8 v;
+            } o;
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * R) + in_column);
-            o.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16_lds)(at));
+            for (int h = 0; h < 2; ++h) {
+              const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * R) + in_column);
+              o.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16_lds)(at));
+            }
+            aset[t][kappa] = o.v;
           }
-          aset[t][kappa] = o.v;
+        } else {
+#pragma unroll
+          for (int kappa = 0; kappa < 4; ++kappa) aset[t][kappa] = half8{};
         }
+      }
 #pragma unroll
       for (int t = 0; t < RA; ++t)
 #pragma unroll
