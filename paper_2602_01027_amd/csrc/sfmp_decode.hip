@@ -2059,7 +2059,8 @@ bool use_chunked_decode(int32_t N, int32_t K, int32_t M) {
 // 17 % longer than that fit: of 673 calls with four to seven slabs 42 were more than 2 % slower than the matrix-core path (4096 ->
 // 6272 with 53 rows 20.1 us against 17.9), none of them in two chunks.  From three chunks on they have to meet a fit of their own
 // besides (3.0 % rms), in which the work follows the mean share of a workgroup; in three chunks, where the other path's time is
-// estimated too low, with 1.04 for the 0.98 that suits four and more.
+// estimated too low, with 1.04 for the 0.99 that suits four and more.  Of 450 such calls 5 are still slower, by up to 4 %; the 300
+// that it moves are 4.8 % faster on the other path (7 slower, by up to 4 %).
 bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M, int32_t group) {
   if (M <= kDecodeMaxM || M > kDecodeMaxM * kGemvMaxBatch || K > 4096) return false;
   const int32_t chunks = (M + kDecodeMaxM - 1) / kDecodeMaxM, nslab = 8 * (N / kTile);
@@ -2068,7 +2069,7 @@ bool use_chunks_without_staging(int32_t N, int32_t K, int32_t M, int32_t group) 
   if (slabs > 7) return false;
   const double other = matrix_core_time_us(N, K, M);
   if (group == 64 && chunks > 2 &&
-      6.08 + 0.408e-3 * K * nslab / share + 0.47 * slabs + 0.0385 * chunks >= (chunks == 3 ? 1.04 : 0.98) * other)
+      2.82 + 0.309e-3 * K * nslab / share + 0.63 * slabs + 0.0815 * chunks + 1.01e-3 * K >= (chunks == 3 ? 1.04 : 0.99) * other)
     return false;
   return 6.415 + 0.37 * slabs * (cols + 1) + 0.014 * chunks + 0.32e-3 * K < 0.95 * other;
 }

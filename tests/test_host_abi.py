@@ -481,7 +481,7 @@ def test_outputs_over_activations_are_staged_first():
 
 
 @pytest.mark.parametrize("N,K,M,both", [
-    (6272, 4096, 53, False), (3328, 4096, 97, False), (7168, 4096, 49, False), (6784, 3200, 55, False),  # 7 to 12 % slower in chunks
+    (6272, 4096, 53, False), (3328, 4096, 97, False), (7168, 4096, 49, False), (6528, 4096, 55, False),  # 5 to 11 % slower in chunks
     (7168, 2048, 49, True), (4096, 2048, 32, True), (512, 512, 64, True), (14208, 1024, 20, True)])
 def test_chunks_without_staging_by_group_length(N, K, M, both):
     # two parameter pairs per tile column make chunks slower: with many slabs and a long K the matrix-core path is the faster one
