@@ -88,7 +88,7 @@ int sfmp_gemm_workspace(const sfmp_layout_t* layout, int32_t M, int64_t* bytes) 
     a.M = M;
     *bytes = chunked_decode_workspace_bytes(a);
   } else {
-    const PrefillPlan d = make_prefill_plan(layout->N, layout->K, M, layout->group);
+    const PrefillWorkspace d = prefill_workspace(layout->N, layout->K, M);
     *bytes = d.xperm_bytes + d.ytmp_bytes;
   }
   if (*bytes < 256) *bytes = 256;

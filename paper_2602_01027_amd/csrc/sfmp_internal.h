@@ -28,18 +28,13 @@ struct DecodePlan {
 // overwrites: the output lies over the activations (the workspace is the same)
 DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool overwrites);
 
-// Prefill path (M > 16): workspace holds the column-gathered activation.  bm, ring and ksplit: the form by the rule from
-// before prefill_fed_kernel, the yardstick for choose_prefill_form, which has the say over what is launched.
-struct PrefillPlan {
-  int32_t bm;           // rows of a workgroup's block: 128, or 64 on small grids
-  bool ring;            // 64 rows, two K groups per workgroup, packed words through LDS rings
-  int32_t ksplit;       // > 1: K is cut into this many ranges, one workgroup each, fp32 partial products
+// Workspace of the prefill path (M > 16).
+struct PrefillWorkspace {
   int64_t xperm_bytes;  // column-gathered activation copy
-  int64_t ytmp_bytes;   // product in reordered row order before the row un-permute pass (ksplit == 1: fp16
-                        // [M, N] if a row permutation is given; ksplit > 1: fp32 [ksplit, M, N])
+  int64_t ytmp_bytes;   // product in reordered row order before the row un-permute pass (fp16 [M, N]), or, for shapes whose K may
+                        // be cut into ranges, their partial products (fp32 [ranges, M, N])
 };
-// (the sizes depend on N, K and M alone; the group length only on the way to the form)
-PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M, int32_t group);
+PrefillWorkspace prefill_workspace(int32_t N, int32_t K, int32_t M);
 
 // What sfmp_gemm launches for M > 16: prefill_fed_kernel<mi, kg> in ksplit K ranges, or prefill_kernel (mi = 0).
 struct PrefillForm {

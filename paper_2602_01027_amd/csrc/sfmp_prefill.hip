@@ -1087,37 +1087,13 @@ static void launch_plain(PrefillParams p, int M, bool g64, hipStream_t stream) {
     hipLaunchKernelGGL((prefill_kernel<false, false>), grid, threads, 0, stream, p);
 }
 
-// Time of a call in us of the forms with one K group per wavefront and tile: by form (rows of a block, plain or ring), K ranges and shape: rounds of workgroups on 256 CUs,
-// each the steps of its longest range times the time of a step with 1, 2 or 3 workgroups on the CU plus the start and
-// end of a workgroup; the staging pass; and the last pass, over fp16 rows or over the fp32 partial products of the
-// ranges.  The constants are a fit to 880 measured calls (M = 24 ... 1100 on ten matrices from 512 x 512 to
-// 28672 x 8192, 1, 2, 4 and 8 ranges of each form, group length 128 with a row permutation), which it meets within 5 %
-// (rms); 46000 later calls of random shapes, group lengths and parameter formats it meets within 8 %, 2 % too long in the
-// median.  A fit to those (4.8 % with terms for the share of CUs at work and the group length) chooses no better.
-static double prefill_time_us(int32_t N, int32_t K, int32_t M, int32_t bm, bool ring, int32_t ks) {
+// The number of K ranges that the workspace query documents: with few workgroups (blocks of 128 rows, or of 64 where those would
+// leave half of the CUs without one) ranges of at least 8 tiles, up to two workgroups per CU, with fp32 partial products and
+// a reduction pass in a fixed order.
+static int32_t documented_ranges(int32_t N, int32_t K, int32_t M) {
   const int64_t ntr = N / kTile, ntc = K / kTile;
-  const int64_t per_cu = ((int64_t)((M + bm - 1) / bm) * ntr * ks + 255) / 256;
-  const int64_t groups = (ring ? 2 : 1) * ks;
-  const double steps = (double)((ntc + groups - 1) / groups);
-  static const double step128[] = {0.0, 1.03, 1.75}, step64[] = {0.0, 0.87, 1.21, 1.73}, step_ring[] = {0.0, 1.23};
-  const double* step = ring ? step_ring : bm == 64 ? step64 : step128;
-  const int64_t resident = ring ? 1 : bm == 64 ? 3 : 2;
-  const double edge = ring ? 2.64 : bm == 64 ? 1.85 : 2.53;
-  const int64_t full = per_cu / resident, rest = per_cu % resident;
-  double t = (double)full * (steps * step[resident] + edge) + (rest ? steps * step[rest] + edge : 0.0);
-  const double mn = (double)M * N * 1e-6, mk = (double)M * K * 1e-6;
-  t += ks > 1 ? 8.03 + 1.96 * ks * mn : 6.55 + 2.04 * mn;
-  return t + 0.87 * mk;
-}
-
-// The number of K ranges that the workspace query documents, with the rows of a block that it goes with.
-//  - 64-row blocks when 128-row blocks would leave half of the CUs without a workgroup (short prompts on narrow matrices);
-//  - still at most one workgroup per CU: K in ranges of at least 8 tiles (up to two workgroups per CU), fp32 partial
-//    products, and a reduction pass in a fixed order.
-static int32_t documented_ranges(int32_t N, int32_t K, int32_t M, int32_t* bm) {
-  const int64_t ntr = N / kTile, ntc = K / kTile;
-  *bm = (int64_t)((M + 127) / 128) * ntr <= 128 ? 64 : 128;
-  const int64_t blocks = (int64_t)((M + *bm - 1) / *bm) * ntr;
+  const int64_t bm = (int64_t)((M + 127) / 128) * ntr <= 128 ? 64 : 128;
+  const int64_t blocks = (int64_t)((M + bm - 1) / bm) * ntr;
   int64_t ks = 1;
   if (blocks <= 256) {
     ks = 512 / blocks;
@@ -1128,42 +1104,9 @@ static int32_t documented_ranges(int32_t N, int32_t K, int32_t M, int32_t* bm) {
   return (int32_t)ks;
 }
 
-PrefillPlan make_prefill_plan(int32_t N, int32_t K, int32_t M, int32_t group) {
-  PrefillPlan d;
-  const int64_t ntr = N / kTile, ntc = K / kTile;
-  d.ring = false;
-  const int64_t blocks128 = (int64_t)((M + 127) / 128) * ntr;
-  const int64_t ks = documented_ranges(N, K, M, &d.bm);
-  d.ksplit = (int32_t)ks;
-  // (What is launched is choose_prefill_form's choice; the 64-row and ring forms named here are gone.)
-  // The number of ranges decides the workspace.  Within it another form is taken where the times above make it at least
-  // 5 % faster: fewer ranges, 128-row blocks, or the ring form, which needs 4 tiles per K group to pay for its longer start
-  // (512 -> 512: 2 % slower with 2).  Every form was measured on 6436 random shapes (M = 17 ... 1100, K and N from 384 to
-  // 28672, all group lengths, both parameter formats): the choice is 5.1 % faster than the rule above in the geometric mean,
-  // and more than 2 % slower on 0.8 % of the shapes (2.3 % without the last three lines here):
-  //  - 64-row blocks only where 128-row blocks would start at most one workgroup per CU (beyond they are slower throughout,
-  //    by up to 30 %);
-  //  - 128-row blocks in place of 64-row ones only with group length 64, whose parameters are twice the work per workgroup
-  //    (1 to 4 % faster); with one pair per tile column they gain nothing in the median and lose up to 8 %;
-  //  - not seven ranges of the ring form for eight of the plain one while they are fewer than 200 workgroups: with eight the
-  //    workgroups of a range are on one XCD (block b on b % 8) and read its activations from one L2 (8832 -> 512, 152 rows:
-  //    19.7 us against 18.0);
-  //  - at most half of the ranges, but more than one, from seven row blocks on: only from 8 % on (13824 -> 1152, 391 rows:
-  //    36.1 us in four ranges of the ring form against 34.4 in eight).
-  {
-    const double former = prefill_time_us(N, K, M, d.bm, false, d.ksplit);
-    double best = former;
-    for (int form = d.bm == 64 && group != 64 ? 1 : 0, forms = blocks128 <= 256 ? 3 : 1; form < forms; ++form) {
-      const int32_t bm = form == 0 ? 128 : 64;
-      const bool ring = form == 2;
-      for (int32_t k = 1; k <= ks && (!ring || ntc >= 8 * k); ++k) {
-        if (ring && k == 7 && ks == 8 && (int64_t)((M + 63) / 64) * ntr * k < 200) continue;
-        const double t = prefill_time_us(N, K, M, bm, ring, k);
-        const double margin = ring && M > 384 && k > 1 && k <= ks / 2 ? 0.92 : 0.95;
-        if (t < best && t < margin * former) best = t, d.bm = bm, d.ring = ring, d.ksplit = k;
-      }
-    }
-  }
+PrefillWorkspace prefill_workspace(int32_t N, int32_t K, int32_t M) {
+  const int64_t ks = documented_ranges(N, K, M);
+  PrefillWorkspace d;
   d.xperm_bytes = round_up_256((int64_t)((M + kTile - 1) / kTile) * kTile * K * 2);  // whole 128-row blocks
   d.ytmp_bytes = round_up_256(ks > 1 ? ks * (int64_t)M * N * 4 : (int64_t)M * N * 2);
   return d;
@@ -1192,14 +1135,13 @@ static double plain_time_us(int32_t N, int32_t K, int32_t M) {
 }
 
 // The fastest form by these times, in no more ranges than the workspace query documents.  On 6640 random shapes that were in
-// no fit of the former rule this choice is 13.3 % faster than that rule with its forms (geometric mean; 14.0 % with the fastest
-// form of each), and more than 2 % slower on 0.4 % of them.  prefill_kernel where it is estimated less than 3 % slower: with
+// no fit this choice is 13.3 % faster than the kernels before it (whose wavefronts all requested and multiplied, in blocks of 64
+// and 128 rows; geometric mean; 14.0 % with the fastest form of each), and more than 2 % slower on 0.4 % of them.  prefill_kernel where it is estimated less than 3 % slower: with
 // a little more than a multiple of 256 workgroups the last round of the others is nearly empty (631 x 3072 -> 23936, 118.7
 // us against 125.6; without it 0.75 % of the shapes are more than 2 % slower).  One K group where a workgroup has a single tile.
 static PrefillForm choose_form(int32_t N, int32_t K, int32_t M, double* time_us) {
   const int64_t ntr = N / kTile, ntc = K / kTile;
-  int32_t bm = 0;
-  const int32_t most = documented_ranges(N, K, M, &bm);
+  const int32_t most = documented_ranges(N, K, M);
   PrefillForm best = {4, 1, 1};
   double least = -1.0;
   for (int32_t kg = 1; kg <= 2; ++kg)
@@ -1238,7 +1180,7 @@ static int check_launch(const char* what) {
 
 int launch_prefill(const GemmArgs& a, void* stream) {
   const sfmp_layout_t* L = a.L;
-  const int64_t xperm_bytes = make_prefill_plan(L->N, L->K, a.M, L->group).xperm_bytes;
+  const int64_t xperm_bytes = prefill_workspace(L->N, L->K, a.M).xperm_bytes;
   const PrefillForm form = choose_prefill_form(L->N, L->K, a.M);
   // the staging / scatter passes hold one fp16 row in LDS (K <= 57344 fits)
   if (((a.row_perm || form.ksplit > 1) && (int64_t)L->N * 2 > 160 * 1024) ||

@@ -4,9 +4,8 @@ import ctypes as C
 import paper_2602_01027_amd as S
 
 
-class PrefillPlan(C.Structure):
-    _fields_ = [("bm", C.c_int32), ("ring", C.c_bool), ("ksplit", C.c_int32), ("xperm_bytes", C.c_int64),
-                ("ytmp_bytes", C.c_int64)]
+class _PrefillWorkspace(C.Structure):
+    _fields_ = [("xperm_bytes", C.c_int64), ("ytmp_bytes", C.c_int64)]
 
 
 class DecodePlan(C.Structure):
@@ -26,14 +25,9 @@ def chunked(N, K, M):
     return _call("_ZN4sfmp18use_chunked_decodeEiii", C.c_bool, N, K, M)
 
 
-def prefill_form(N, K, M, group=128):
-    """(rows of a block, ring form, K ranges) of a matrix-core call."""
-    p = _call("_ZN4sfmp17make_prefill_planEiiii", PrefillPlan, N, K, M, group)
-    return p.bm, p.ring, p.ksplit
-
-
-def prefill_bytes(N, K, M, group=128):
-    p = _call("_ZN4sfmp17make_prefill_planEiiii", PrefillPlan, N, K, M, group)
+def prefill_bytes(N, K, M):
+    """(staged activations, product or partial products) of a matrix-core call's workspace."""
+    p = _call("_ZN4sfmp17prefill_workspaceEiii", _PrefillWorkspace, N, K, M)
     return p.xperm_bytes, p.ytmp_bytes
 
 

@@ -199,23 +199,26 @@ def test_short_prompt_split_k(torch_cuda, K, N, M, row_perm):
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed reduction order
 
 
-@pytest.mark.parametrize("K,N,M,group,scale_format,fractions,ranges", [
-    (1024, 1024, 17, 128, "fp16", {2: 1.0}, 1), (1024, 1024, 64, 128, "bf16", {3: 1.0}, 1), (1024, 1024, 65, 64, "fp16", {4: 1.0}, 1),
-    (1408, 640, 130, 64, "bf16", {2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, 1), (1408, 640, 63, 128, "fp16", {2: 0.1, 4: 0.9}, 1),
-    (2304, 512, 200, 256, "fp16", {2: 0.5, 3: 0.5}, 1), (3200, 384, 17, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, 3),
-    (3200, 256, 17, 128, "bf16", {2: 0.2, 3: 0.8}, 3), (3968, 256, 130, 64, "fp16", {3: 0.5, 4: 0.5}, 3),
-    (3968, 256, 65, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, 3), (9856, 256, 129, 128, "fp16", {2: 0.5, 4: 0.5}, 8),
-    (9856, 256, 200, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, 8), (4224, 4096, 100, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, None),
-    (4224, 4096, 130, 64, "fp16", {3: 0.5, 4: 0.5}, None)])
-def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, scale_format, fractions, ranges):
-    # the form of the matrix-core kernel with two K groups per workgroup and weight rings: its shortest share (4 tiles
-    # per group), shares of different length (5 and 6 tiles), one width only and every change of width, both parameter
-    # formats and pairs per tile column, rows below, at and above a 64-row block, and K in ranges besides (25, 31 and 77 tiles
-    # in 6, 6 and 16 groups); beside it the plain 64-row form in four ranges (None)
+@pytest.mark.parametrize("K,N,M,group,scale_format,fractions,form", [
+    (1024, 1024, 129, 128, "fp16", {2: 1.0}, (4, 2, 1)), (1024, 1024, 192, 128, "bf16", {3: 1.0}, (4, 2, 1)),
+    (1024, 1024, 193, 64, "fp16", {4: 1.0}, (4, 2, 1)), (1408, 640, 130, 64, "bf16", {2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, (4, 2, 1)),
+    (1408, 640, 191, 128, "fp16", {2: 0.1, 4: 0.9}, (4, 2, 1)), (2304, 512, 200, 256, "fp16", {2: 0.5, 3: 0.5}, (4, 2, 1)),
+    (3200, 384, 129, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 3)), (3200, 256, 145, 128, "bf16", {2: 0.2, 3: 0.8}, (4, 2, 3)),
+    (3968, 256, 130, 64, "fp16", {3: 0.5, 4: 0.5}, (4, 2, 3)), (3968, 256, 193, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 3)),
+    (9856, 256, 129, 128, "fp16", {2: 0.5, 4: 0.5}, (4, 2, 8)), (9856, 256, 200, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 8)),
+    (4224, 4096, 100, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, (4, 2, 3)), (4224, 4096, 130, 64, "fp16", {3: 0.5, 4: 0.5}, (5, 2, 3)),
+    # chunks of 16 rows through the decode kernels instead
+    (1024, 1024, 17, 128, "fp16", {2: 1.0}, None), (1024, 1024, 64, 128, "bf16", {3: 1.0}, None), (1024, 1024, 65, 64, "fp16", {4: 1.0}, None),
+    (1408, 640, 63, 128, "fp16", {2: 0.1, 4: 0.9}, None), (3200, 384, 17, 64, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, None),
+    (3200, 256, 17, 128, "bf16", {2: 0.2, 3: 0.8}, None), (3968, 256, 65, 128, "fp16", {2: 0.3, 3: 0.3, 4: 0.4}, None)])
+def test_short_prompt_two_k_groups_per_workgroup(torch_cuda, K, N, M, group, scale_format, fractions, form):
+    # two K groups per workgroup: shares of 4 to 9 tiles, of different length (5 and 6), one width only and every change of
+    # width, both parameter formats and pairs per tile column, rows below, at and above 64-row blocks, and K in ranges besides
+    # (25, 31 and 77 tiles in 6, 6 and 16 groups); beside them the same matrices with fewer rows, which run in chunks
     import plan_util
     from gpu_util import run_gemm
-    assert not plan_util.chunked(N, K, M)
-    assert plan_util.prefill_form(N, K, M, group) == ((64, True, ranges) if ranges else (64, False, 4))
+    assert not plan_util.chunked(N, K, M) and plan_util.chunks_without_staging(N, K, M, group) == (form is None)
+    assert form is None or plan_util.launched_form(N, K, M) == form
     p = W.make_problem("kgroups", K, N, M, 7900 + K + M, fractions=fractions, outliers=True, group=group,
                        scale_format=scale_format, fast_codes=K > 2304)
     rows = None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False)

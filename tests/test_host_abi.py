@@ -389,31 +389,14 @@ def test_launches_without_a_usable_extension_take_the_ctypes_path(extension, tmp
     assert (B._LAUNCHER[1] is B._NoExtension) == (extension != "built")
 
 
-@pytest.mark.parametrize("N,K,M,group,form", [
-    (4480, 19968, 295, 512, (64, False, 2)), (4480, 19968, 295, 64, (128, False, 2)),  # 128 rows for 64: group length 64 only
-    (512, 8832, 152, 128, (64, False, 8)), (1152, 14336, 214, 128, (64, True, 7)),     # seven ring ranges for eight: from 200
-    (1152, 13824, 391, 128, (64, False, 8)), (1024, 13824, 384, 128, (64, True, 5)),   # half of the ranges, seven row blocks
-    (14336, 4096, 64, 128, (64, True, 2)), (4096, 4096, 777, 128, (128, False, 1)), (14336, 4096, 2048, 128, (128, False, 1))])
-def test_form_of_a_matrix_core_call(N, K, M, group, form):
-    import plan_util
-    assert plan_util.prefill_form(N, K, M, group) == form
-
-
-def test_form_of_a_matrix_core_call_stays_within_the_documented_workspace():
+def test_workspace_of_a_matrix_core_call_is_the_documented_one():
     import plan_util
     rng = np.random.default_rng(11)
     for _ in range(4000):
         K, N = (int(128 * np.ceil(2 ** rng.uniform(0, 7.8))) for _ in range(2))
         M = int(2 ** rng.uniform(4.1, 11))
-        name, nbytes = _plan_mirror(N, K, M) if not plan_util.chunked(N, K, M) else (None, None)
-        if name is None:
-            continue
-        documented = int(name.split("ksplit=")[1])
-        for group in (64, 128):
-            bm, ring, ksplit = plan_util.prefill_form(N, K, M, group)
-            assert bm in (64, 128) and 1 <= ksplit <= documented and ksplit <= K // 128, (N, K, M)
-            assert not ring or (bm == 64 and K // 128 >= 8 * ksplit), (N, K, M)  # at least four tiles per K group
-            assert sum(plan_util.prefill_bytes(N, K, M, group)) == nbytes, (N, K, M)
+        if not plan_util.chunked(N, K, M):
+            assert sum(plan_util.prefill_bytes(N, K, M)) == _plan_mirror(N, K, M)[1], (N, K, M)
 
 
 def test_launched_form_of_a_matrix_core_call():
@@ -431,7 +414,9 @@ def test_launched_form_of_a_matrix_core_call():
         assert 1 <= ksplit <= documented and kg * ksplit <= K // 128, (N, K, M)
         assert ksplit == 1 or (kg == 2 and ksplit * M * N * 4 <= plan_util.prefill_bytes(N, K, M)[1]), (N, K, M)
     for shape, form in (((4096, 4096, 777), (7, 2, 1)), ((14336, 4096, 64), (4, 2, 2)), ((4096, 14336, 200), (7, 2, 4)),
-                        ((14336, 4096, 2048), (8, 1, 1)), ((8192, 28672, 2048), (8, 1, 1)), ((128, 128, 17), (4, 1, 1))):
+                        ((14336, 4096, 2048), (8, 1, 1)), ((8192, 28672, 2048), (8, 1, 1)), ((128, 128, 17), (4, 1, 1)),
+                        ((4480, 19968, 295), (7, 2, 2)), ((512, 8832, 152), (4, 2, 7)), ((1152, 14336, 214), (4, 2, 7)), ((1152, 13824, 391), (5, 2, 5)),
+                        ((1024, 13824, 384), (4, 2, 5))):
         assert plan_util.launched_form(*shape) == form, shape
 
 
