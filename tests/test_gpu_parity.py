@@ -283,16 +283,35 @@ def test_prompt_with_4_gib_of_activations(torch_cuda, K, N, M, form):
     _check(dataclasses.replace(p, M=rows.size, X=X[at].cpu().numpy()), Y[at].cpu().numpy())
 
 
-@pytest.mark.parametrize("K,N,M,scale_format,fractions", [
-    (128, 8320, 400, "fp16", {2: 0.5, 4: 0.5}), (640, 8320, 400, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}), (1152, 8320, 390, "fp16", {3: 1.0}),
-    (640, 8192, 1000, "bf16", {2: 0.5, 3: 0.5}), (640, 8192, 512, "fp16", {3: 0.5, 4: 0.5}), (640, 8320, 1000, "bf16", {2: 0.5, 4: 0.5})])
-def test_prefill_group_64_by_number_of_workgroups(torch_cuda, K, N, M, scale_format, fractions):
-    # group length 64 in 128-row blocks: 257 to 512 workgroups (260, 260, 260, 512 here) take the instantiation that converts
-    # the parameters early, 256 and 520 the other one; one tile (K = 128), one width, every change of width
+@pytest.mark.parametrize("K,N,M,scale_format,fractions,form", [
+    (128, 8320, 400, "fp16", {2: 0.5, 4: 0.5}, (5, 1, 1)), (640, 8320, 400, "bf16", {2: 0.3, 3: 0.3, 4: 0.4}, (5, 1, 1)),
+    (1152, 8320, 390, "fp16", {3: 1.0}, (5, 1, 1)), (640, 8192, 1000, "bf16", {2: 0.5, 3: 0.5}, (8, 1, 1)),
+    (640, 8192, 512, "fp16", {3: 0.5, 4: 0.5}, (4, 1, 1)), (640, 8320, 1000, "bf16", {2: 0.5, 4: 0.5}, (5, 1, 1))])
+def test_prompt_at_group_64_in_two_row_groups(torch_cuda, K, N, M, scale_format, fractions, form):
+    # group length 64 in blocks of 128, 160 and 256 rows, two row groups per workgroup, 195 to 455 workgroups; one tile (K = 128), one
+    # width, every change of width
+    import plan_util
     from gpu_util import run_gemm
+    assert plan_util.launched_form(N, K, M) == form
     p = W.make_problem("early", K, N, M, 9100 + K + M, fractions=fractions, outliers=True, group=64, scale_format=scale_format,
                        fast_codes=True)
     _check(p, run_gemm(p), np.random.default_rng(M).choice(N, 384, replace=False))
+
+
+@pytest.mark.parametrize("group,scale_format", [(64, "fp16"), (64, "bf16"), (128, "fp16"), (128, "bf16")])
+@pytest.mark.parametrize("K,N,M,form", [
+    (1152, 512, 129, (4, 2, 1)), (1152, 4096, 600, (5, 2, 1)), (1152, 8320, 241, (6, 2, 1)), (1152, 5632, 512, (7, 2, 1)),
+    (1152, 5632, 600, (8, 2, 1)), (640, 8192, 512, (4, 1, 1)), (1152, 8320, 400, (5, 1, 1)), (1152, 8320, 512, (6, 1, 1)),
+    (1152, 8320, 600, (7, 1, 1)), (1152, 12288, 512, (8, 1, 1)), (1152, 16512, 300, (0, 1, 1))])
+def test_matrix_core_kernels_in_every_parameter_format(torch_cuda, K, N, M, form, group, scale_format):
+    # every compiled combination of form, pairs per tile column and parameter format, on nine tile columns of all widths (three of
+    # each on average: the loops inside a run of one width and the steps between runs)
+    import plan_util
+    from gpu_util import run_gemm
+    assert plan_util.launched_form(N, K, M) == form and not plan_util.chunks_without_staging(N, K, M, group)
+    p = W.make_problem("formats", K, N, M, 9300 + K + M + group, fractions={2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, outliers=True, group=group,
+                       scale_format=scale_format, fast_codes=True)
+    _check(p, run_gemm(p), None if N <= 1024 else np.random.default_rng(M).choice(N, 256, replace=False))
 
 
 def test_workspace_is_reusable_and_result_deterministic(torch_cuda):
@@ -763,28 +782,34 @@ def test_small_batch_more_than_2048_slabs(torch_cuda, K, N, M):
                                                       (256, "fp16", (2, 2)), (256, "bf16", (4, 2)), (512, "bf16", (4, 4))])
 def test_group_length_and_parameter_format(torch_cuda, group, scale_format, block, M):
     # K = 1536: 12 tile columns = 24 groups of 64 (two per tile) or 6 / 3 groups of 256 / 512; N = 1024: two
-    # (512 x n_b) block rows.  M = 200: the matrix-core kernel with 128-row blocks
+    # (512 x n_b) block rows.  M = 48: three chunks of 16 rows; M = 200: the matrix-core kernel with 64-row blocks, two K groups
+    import plan_util
     from gpu_util import run_gemm
+    assert plan_util.chunks_without_staging(1024, 1536, M, group) == (M == 48)
+    assert M != 200 or plan_util.launched_form(1024, 1536, M) == (4, 2, 1)
     p = W.make_problem("fmt", 1536, 1024, M, 606 + group, fractions={2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, outliers=True,
                        group=group, scale_format=scale_format, block=block)
     assert p.scales.shape == (1536 // group, 1024)
     _check(p, run_gemm(p))
 
 
-@pytest.mark.parametrize("M", [1, 8, 64])
+@pytest.mark.parametrize("M", [1, 8, 64, 140])
 def test_small_magnitude_weights_bf16_parameters(torch_cuda, M):
     # weights of standard deviation 1e-5 with bf16 scales and zeros: the scales (about 3e-6) lie below fp16's normal
-    # range.  The decode kernels (M <= 16) widen the parameters to fp32 and meet the usual bounds.  The matrix-core path
-    # (M = 64 here) converts them to fp16 and rounds the dequantised weight to fp16, which the header documents as
+    # range.  The decode kernels (M <= 16, and M = 64 in chunks of 16 rows) widen the parameters to fp32 and meet the usual
+    # bounds.  The matrix-core path (M = 140 here) converts them to fp16 and rounds the dequantised weight to fp16, which the header documents as
     # costing up to 2^-25 absolute per parameter and per weight below 2^-14: a code of at most 15 times the scale's
     # error, the zero's error and the weight's rounding give 17 * 2^-25 per weight on top of the usual bound.
+    import plan_util
     from gpu_util import run_gemm, elementwise_tolerance, FLOOR16
     p = W.make_problem("tinyw", 1024, 512, M, 4711, w_std=1e-5, fractions={2: 1 / 3, 3: 1 / 3, 4: 1 / 3},
                        scale_format="bf16")
     assert float(np.abs(p.scales).max()) < 2.0 ** -14
     Y = run_gemm(p)
-    if M <= 16:
-        _check(p, Y)
+    assert plan_util.chunks_without_staging(512, 1024, M) == (M == 64) and not plan_util.chunked(512, 1024, M)
+    if M <= 64:
+        for m in range(0, M, 16):  # (16 rows at a time: the bound of the decode kernels alone)
+            _check(dataclasses.replace(p, M=len(Y[m:m + 16]), X=p.X[m:m + 16]), Y[m:m + 16])
         return
     ref = O.gemm(p.X, p.col_perm, p.codes, p.scales, p.zeros, p.row_perm)
     w_hat = O.dequant(p.codes, p.scales, p.zeros)
