@@ -231,28 +231,15 @@ __device__ __forceinline__ half8 dequant_operand(const uint32_t* w, half2_ s2, h
   return out.v;
 }
 
-// Workgroup = BM x 128 output block, WM x WN wavefronts, wavefront tile (BM/WM) x (128/WN): MI = BM/WM/16
-// row blocks x NS = 8/WN slabs.  A dequantised B operand feeds MI MFMAs, so the dequantisation cost per
-// MFMA falls with MI; the activation operand reads from LDS grow with WN.
-template <int BM, int WM, int WN>
-struct PrefillShape {
-  static constexpr int kThreads = 64 * WM * WN;
-  static constexpr int kMI = BM / WM / 16;
-  static constexpr int kNS = 8 / WN;
-  static constexpr int kRowsPerPass = kThreads / 16;
-  static constexpr int kPasses = BM / kRowsPerPass;
-};
-
-// Lays out the tiles of tile row tr in the order of the K reduction: put(position, tile column, width, slot) once per tile
-// column; end2, end3 = the positions of the first 3-bit and the first 4-bit tile.
+// Lays out the tiles of tile row tr in the order of the K reduction: seq[position] = (slot << 9) | tile column; end2, end3 = the
+// positions of the first 3-bit and the first 4-bit tile.
 // Sorted by width (first all 2-bit tiles, then the 3-bit, then the 4-bit ones, each in ascending column order; the order
 // of a sum is free): three loops, each with a straight-line body for its width.  The sequence is laid out from the tile
 // descriptors of the row (slot << 2 | width - 2, one per tile column), whose address depends on the arguments alone:
 // ranks by ballots, per 64 columns, instead of the row's runs in the CSR part of the table, which are a dependent trip to
 // memory later.
-template <int THREADS, class Put>
-__device__ __forceinline__ void lay_out_tiles(const PrefillParams& p, const int tr, int2* counts, int& end2, int& end3,
-                                              const Put& put) {
+template <int THREADS>
+__device__ __forceinline__ void lay_out_tiles(const PrefillParams& p, const int tr, int2* counts, int& end2, int& end3, int32_t* seq) {
   const int32_t* desc = p.index + 3 + (int64_t)tr * p.ntc;
   constexpr int kPer = (kPrefillMaxTiles + THREADS - 1) / THREADS;
   constexpr int kChunks = kPer * (THREADS / kWave);
@@ -303,7 +290,7 @@ __device__ __forceinline__ void lay_out_tiles(const PrefillParams& p, const int 
       const int back = rank - (int)((uint32_t)((tr * 5) % 8) % (uint32_t)n);
       const int pos = lo + (back < 0 ? back + n : back);
       const uint32_t slot = (uint32_t)d[u] >> 2;
-      put(pos, e, bw, slot);
+      seq[pos] = (int32_t)(slot << 9) | e;
     }
   }
 }
@@ -314,9 +301,9 @@ __device__ __forceinline__ void lay_out_tiles(const PrefillParams& p, const int 
 // 64 26 and 16 of 159 to 173 (a branch instead costs 2 % of the large calls, at the synchronisation point).
 template <bool G64, bool BF16>
 __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) {
-  constexpr int BM = 128, WM = 1, WN = 4;
-  using S = PrefillShape<BM, WM, WN>;
-  constexpr int MI = S::kMI, NS = S::kNS;
+  // 128 x 128 outputs, four wavefronts of all 128 rows x two slabs each: a dequantised B operand feeds MI MFMAs
+  constexpr int BM = 128, MI = BM / 16, NS = 2;
+  constexpr int kRowsPerPass = 256 / 16, kPasses = BM / kRowsPerPass;
   constexpr uint32_t kBufBytes = BM * 256;
   __shared__ __align__(16) unsigned char Xs[2 * kBufBytes];  // activation blocks
   __shared__ int32_t seq[kPrefillMaxTiles];  // the tiles of this tile row, width-sorted: (slot << 9) | tc
@@ -335,11 +322,10 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) 
   const int e_last = p.ntc - 1;
 
   int end2 = 0, end3 = 0;  // positions of the first 3-bit and of the first 4-bit tile
-  lay_out_tiles<S::kThreads>(p, tr, counts, end2, end3,
-                             [&](int pos, int tc, uint32_t, uint32_t slot) { seq[pos] = (int32_t)(slot << 9) | tc; });
+  lay_out_tiles<256>(p, tr, counts, end2, end3, seq);
   __syncthreads();
 
-  const int wm = wave / WN, wn = wave % WN;  // this wavefront: rows 16*MI*wm.., slabs NS*wn .. NS*wn+NS-1
+  const int wn = wave;  // this wavefront: slabs NS*wn .. NS*wn+NS-1
   floatx4 acc[MI][NS];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -355,10 +341,10 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) 
   // LDS-DMA load of a wavefront fills 1024 contiguous bytes = four 256-byte rows, lane l -> row l/16,
   // 16-byte position l%16; the swizzle is applied on the global side: position u of row r receives
   // unit u ^ (r%16).
-  uint32_t xoff[S::kPasses];  // byte offsets from Xp + m0*K + tc*128
+  uint32_t xoff[kPasses];  // byte offsets from Xp + m0*K + tc*128
 #pragma unroll
-  for (int i = 0; i < S::kPasses; ++i) {
-    const int row = xrow + S::kRowsPerPass * i;
+  for (int i = 0; i < kPasses; ++i) {
+    const int row = xrow + kRowsPerPass * i;
     xoff[i] = 2u * (uint32_t)(row * kTile + swz(row, xunit) * 8);
   }
   // block (mt, tc) of the staged activations starts at (mt * ntc + tc) * 16384 elements; rows past M of the last
@@ -372,18 +358,18 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) 
     const u32x4 rsrc = {(uint32_t)xb64, (uint32_t)(xb64 >> 32), x.records, 0x00020000u};
     const uint32_t dst = xs_base + (uint32_t)buf * kBufBytes + wave * 1024;
 #pragma unroll
-    for (int i = first; i < last; ++i) load_to_lds_16(rsrc, x.offset, xoff[i], dst + i * (S::kRowsPerPass * 256));
+    for (int i = first; i < last; ++i) load_to_lds_16(rsrc, x.offset, xoff[i], dst + i * (kRowsPerPass * 256));
   };
   // block of tile position e into the buffer that block `like` uses (like = e mod 2, except for the idle
   // loads past the end)
   auto issue_x = [&](int e, int like) __attribute__((always_inline)) {
     const uint32_t tc = (uint32_t)(__builtin_amdgcn_readfirstlane(seq[e]) & 511);
-    issue_x_part(block_request(tc << 15, xbytes, true), like & 1, 0, S::kPasses);
+    issue_x_part(block_request(tc << 15, xbytes, true), like & 1, 0, kPasses);
   };
-  // operand read addresses: row 16*(MI*wm + i) + i16, unit 4*kappa + kb -> byte offset aoff[kappa] + 4096*i
+  // operand read addresses: row 16*i + i16, unit 4*kappa + kb -> byte offset aoff[kappa] + 4096*i
   uint32_t aoff[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) aoff[k] = (uint32_t)((16 * MI * wm + i16) * 256 + swz(i16, 4 * k + kb) * 16);
+  for (int k = 0; k < 4; ++k) aoff[k] = (uint32_t)(i16 * 256 + swz(i16, 4 * k + kb) * 16);
 
   // Packed weights of one tile for this wavefront: one load of 4*b bytes per slab and lane, whatever the
   // width (equal load counts on the three paths keep the compiler's wait counts exact), plus NS
@@ -615,7 +601,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) 
   for (; e < p.ntc; ++e) step(b4, run_ends, e);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the idle loads of the last two steps
   // epilogue: the block goes through LDS (the activation buffers are free now) so that it leaves in whole
-  // row segments: acc[i][j][r] = C[16*MI*wm + 16i + 4kb + r][8*i16 + NS*wn + j], the NS values j of
+  // row segments: acc[i][j][r] = C[16i + 4kb + r][8*i16 + NS*wn + j], the NS values j of
   // a lane being consecutive columns.
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();  // every wavefront's idle loads have landed and its operand reads returned
@@ -624,7 +610,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) 
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int row = 16 * MI * wm + 16 * i + 4 * kb + r;
+      const int row = 16 * i + 4 * kb + r;
       union {
         _Float16 h[NS];
         uint32_t u[NS / 2];
@@ -638,8 +624,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillParams p) 
   __syncthreads();
   _Float16* ybase = p.Yt + (int64_t)m0 * p.N + (int64_t)tr * 128;
 #pragma unroll
-  for (int i = 0; i < S::kPasses; ++i) {
-    const int row = xrow + S::kRowsPerPass * i;
+  for (int i = 0; i < kPasses; ++i) {
+    const int row = xrow + kRowsPerPass * i;
     const u32x4 v = *reinterpret_cast<const u32x4*>(Xs + row * 256 + xunit * 16);
     if (m0 + row < p.M) *reinterpret_cast<u32x4*>(ybase + (int64_t)row * p.N + xunit * 8) = v;
   }
@@ -710,8 +696,7 @@ __global__ __launch_bounds__(768, 3) void prefill_fed_kernel(const PrefillParams
   const int longest = (p.ntc + ranges - 1) / ranges;  // tiles of the longest share
 
   int end2 = 0, end3 = 0;
-  lay_out_tiles<kThreads>(p, tr, counts, end2, end3,
-                          [&](int pos, int tc, uint32_t, uint32_t slot) { seq[pos] = (int32_t)(slot << 9) | tc; });
+  lay_out_tiles<kThreads>(p, tr, counts, end2, end3, seq);
   __syncthreads();
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lptr_t)lds;
 
