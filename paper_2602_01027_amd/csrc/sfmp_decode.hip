@@ -996,9 +996,9 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     // The first item of every wavefront is on its way meanwhile.  Against a staging launch: see rskinny_config.
     // A wavefront that has no activations to bring or no tile column does neither: at K = 512 two of the 16 have the one and four
     // the other.  (All of them asked for the last ones again, 64 bytes a cycle and CU: up to 16 rows of K <= 2048 took longer
-    // than with a staging launch.  Graph replays before -> now, with staging: 512 -> 14336, group length 64, 9 rows 8.31 -> 6.65 us,
-    // 7.82; 2048 -> 4096, 9 rows 6.82 -> 5.71, 7.03; 256 -> 2048, group length 64, 9 rows 5.97 -> 4.35, 5.01.  The same test in
-    // front of the permutation entries: 2 % more at K = 2048, 0.6 % less at K = 4096.)
+    // than with a staging launch.  Graph replays before -> now, with staging; 9 rows, group length 64: 512 -> 14336 8.35 -> 6.56 us,
+    // 7.92; 2048 -> 4096 6.99 -> 5.82, 6.85; 256 -> 2048 6.09 -> 4.20, 5.25.  The same test in front of the permutation entries:
+    // 2 % shorter at K = 2048, 0.6 % longer at K = 4096.)
     const int chunk = i16 % 4;
     int pk[RA][8];
 #pragma unroll
@@ -1569,10 +1569,11 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
     r.acc = r.nw == 16 ? 4 : 16;
     r.slots = kSlotsRegisterActs;
     // Two tile columns per wavefront and 16 wavefronts (K <= 4096): the operands are gathered by every workgroup itself, without
-    // a staging launch.  Graph replays, staged / gathered: 4096 -> 4096 M = 8 8.12 / 6.68 us, M = 16 8.35 / 7.95; 4096 -> 14336
-    // 11.90 / 10.46 and 12.76 / 12.24; 512 -> 512 6.15 / 4.97 and 6.13 / 6.00; 4096 -> 4096 M = 64 (chunks) 14.23 / 12.95.  Not with
-    // four (K <= 8192, up to 8 rows): 8192 -> 8192 12.72 / 12.73, 8192 -> 28672 26.96 / 27.34.  And not for the resident form's
-    // M <= 4, whose start is shorter still: 512 -> 512 M = 4 4.22 / 4.92, 4096 -> 14336 10.43 / 10.39.
+    // a staging launch.  Graph replays, staged / gathered: 4096 -> 4096 M = 8 8.05 / 6.75 us, M = 16 8.22 / 7.95; 4096 -> 14336
+    // 11.75 / 10.35 and 12.83 / 12.08; 512 -> 512 6.16 / 3.91 and 6.23 / 4.29; 4096 -> 4096 M = 64 (chunks) 13.85 / 12.51.  Not with
+    // four (K <= 8192, up to 8 rows): 8192 -> 8192 12.72 / 12.73, 8192 -> 28672 26.96 / 27.34.  For M <= 4 the resident form stays
+    // (resident / gathered: 4096 -> 4096 M = 2 5.95 / 6.58, M = 4 6.50 / 6.67; with a short K the gathered form is now the shorter
+    // one, 512 -> 512 M = 4 4.23 / 3.88, 2048 -> 2048 5.30 / 5.16, called one by one the same).
     // (It fits wherever the sums and slots do: 128 KiB of transposed activations and the first slots are 148 KiB.)
     if (r.nw == 16 && r.ra == 2) {
       if (overwrites)
@@ -2025,18 +2026,18 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
 // 16 < M <= 128: the product may be cut into chunks of 16 activation rows, one problem of the batched ring kernel
 // each (the same weights, its own rows of X and Y).  The chunks run side by side on their shares of the CUs and read
 // the same weights at about the same time, so the matrix comes from HBM once and from the caches for the other
-// chunks.  Against the MFMA kernel (short-prompt forms) the cost grows with the number of chunks and with the matrix.  Whole
-// calls, both sides on one machine, us chunked / MFMA:
-//   with K <= 8192 (the chunks keep their activations in registers) two chunks (M = 32): 4096 -> 4096 11.4 / 16.0, 4096 ->
-//   14336 20.3 / 25.4, 8192 -> 8192 23.0 / 27.2, 8192 -> 14336 31.6 / 35.0; three and four chunks up to 1536 tiles: 4096 ->
-//   6144 15.8 / 18.3 and 18.1 / 19.3 (not 4096 -> 14336: 28.6 / 23.6; nor 8192 -> 8192: 30.4 / 25.1); five and six up to 1024
-//   tiles: 4096 -> 4096 17.2 / 19.0 and 19.3 / 19.2 (eight: 31.0 / 21.4);
+// chunks.  Against the matrix-core path the cost grows with the number of chunks and with the matrix.  Graph replays, both
+// sides on one machine, us chunked / matrix cores:
+//   with K <= 8192 (the chunks keep their activations in registers) two chunks (M = 32): 4096 -> 4096 9.9 / 14.7, 4096 ->
+//   14336 17.3 / 19.6, 8192 -> 8192 22.5 / 22.6, 8192 -> 14336 30.5 / 29.0; three and four chunks up to 1536 tiles: 4096 ->
+//   6144 13.6 / 16.7 and 15.8 / 17.7; five and six up to 1024 tiles: 4096 -> 4096 15.1 / 17.7 and 16.6 / 18.0;
 //   with a longer K (activations through the ring slots, or streamed) N <= 1024 up to eight chunks, N <= 4096 two (14336 ->
-//   4096 20.6 / 23.2; with three 37.8 / 24.8);
-//   with K below 4096 (not measured): never.
-// The lines were drawn when the MFMA side had no ring form.  Where they are now on the wrong side: two chunks of the largest
-// matrices (4096 -> 28672 34.6 / 34.1, 8192 -> 28672 55.7 / 52.0 at M = 32), and N <= 1024 with K > 8192 from five chunks on
-// (14336 -> 1024 23.5 / 21.0 at M = 80, 26.6 / 23.7 at M = 128; 28672 -> 1024 36.2 / 32.8 and 42.9 / 34.3).
+//   4096 20.6 / 22.1);
+//   with K below 4096: use_chunks_without_staging.
+// The lines were drawn against an earlier matrix-core kernel, and the workspace query documents them.  Where they are now on
+// the wrong side: two chunks of the largest matrices (4096 -> 28672 33.3 / 31.2, 8192 -> 28672 54.3 / 47.5), and K >= 8192 with
+// few rows of tiles from four chunks on (14336 -> 1024 19.1 / 18.1 at M = 64 and 25.9 / 21.2 at M = 128, 28672 -> 1024 29.2 / 26.8
+// and 41.8 / 29.9, 8192 -> 2048 23.5 / 19.6 at M = 96, 8192 -> 1024 19.2 / 17.3 at M = 128).
 bool use_chunked_decode(int32_t N, int32_t K, int32_t M) {
   if (M <= kDecodeMaxM || M > kDecodeMaxM * kGemvMaxBatch) return false;
   const int32_t ntr = N / kTile, ntc = K / kTile, chunks = (M + kDecodeMaxM - 1) / kDecodeMaxM;
@@ -2054,7 +2055,8 @@ bool use_chunked_decode(int32_t N, int32_t K, int32_t M) {
 // calls of random shapes (M = 17 ... 128, K and N from 512 to 4096 and 16384) chunks are 1.5 times as fast as the matrix-core
 // path (geometric mean; 0.3 % of them more than 2 % slower, the worst 4096 -> 7168 with 49 rows, 0.895), with more than seven
 // slabs up to 3 % faster at best.  Their time, a fit to these calls (5.2 % rms), has to be below 0.95 of the other path's: 512
-// -> 512, 64 rows 7.0 us against 10.9; 2048 -> 2048, 32 rows 7.6 against 11.9; 4096 -> 4096 with 65 to 128 rows stays where it was.
+// -> 512, 64 rows 6.5 us against 11.5 before; 2048 -> 2048, 32 rows 7.6 against 17.7; 4096 -> 4096 with 97 to 128 rows stays where it
+// was.  (With K < 4096 chunks are shorter since then, 4.7 and 6.4 us here; the fit was left.)
 // Those calls had one parameter pair per tile column.  At group length 64 (two pairs, two activation sums) chunks take up to
 // 17 % longer than that fit: of 673 calls with four to seven slabs 42 were more than 2 % slower than the matrix-core path (4096 ->
 // 6272 with 53 rows 20.1 us against 17.9), none of them in two chunks.  From three chunks on they have to meet a fit of their own

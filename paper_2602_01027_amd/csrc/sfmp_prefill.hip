@@ -663,9 +663,13 @@ __device__ __forceinline__ void load_lanes_to_lds_16(uint64_t vaddr, uint32_t ld
 // with two wavefronts and n vector instructions per 16x16x32 instruction: max(17.4, 4.3 n + 8.7) cycles), n is 2.1 at MI = 7
 // and falls with MI; a step of two tiles takes 2100, 2550, 2640, 2760 cycles at MI = 4, 6, 7, 8 (128 MI of matrix instructions
 // per wavefront and step, twice 256 MI per SIMD), 3300 pass before the tiles are laid out, 3600 until the first data is there
-// and 4500 at the end.  From about three rounds of workgroups on the chip's power limit lowers the clock instead.
-// Whole calls, before -> now: 777 x 4096 -> 4096 54.3 -> 42.3 us, 200 x 14336 -> 4096 (group length 64) 53.7 -> 42.4, 64 x 4096 ->
-// 14336 24.7 -> 22.5, 2048 x 4096 -> 14336 267 -> 254, 2048 x 28672 -> 8192 882 -> 835.
+// and 4500 at the end.  With several full rounds of workgroups the chip's power limit lowers the clock instead (2048 x 28672 -> 8192:
+// pipe 0.73 busy at 1.51 GHz); 2048 x 4096 -> 14336 loses half of its fourth round first (0.55 busy at 1.78 GHz).
+// Whole calls back to back, the kernels before (whose wavefronts did all of this themselves) -> now: 777 x 4096 -> 4096 49.1 -> 37.7 us,
+// 200 x 14336 -> 4096 (group length 64) 47.7 -> 39.3, 64 x 4096 -> 14336 22.6 -> 20.6, 2048 x 4096 -> 14336 266.7 -> 248.6, 2048 x
+// 28672 -> 8192 884.8 -> 818.0.
+// MI = 8 reaches the 168 registers of 12 wavefronts and spills 1 to 11 of them, most with two K groups and at group length 64
+// (there with reloads inside the tile loops; the choice of the form does not know of it).
 // Not better: 32x32x16 instructions (the words of two slabs exchanged between rows of 16 lanes): 2770 cycles where 16x16x32
 // takes 2550, and 290 us instead of 253 on 2048 x 4096 -> 14336, where the clock falls further; the order of every phase fixed
 // by hand (spills at 168 registers).
