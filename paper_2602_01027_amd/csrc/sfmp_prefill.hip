@@ -172,12 +172,13 @@ struct PrefillParams {
   const _Float16* scales;
   const _Float16* zeros;
   _Float16* Yt;  // [M, N], rows of Wt in reordered order
-  int32_t M, N, K, ntr, ntc, n_mtiles;
+  int32_t M, N, ntr, ntc, n_mtiles;
   int32_t gshift;  // log2(group / 128): tile column tc uses parameter row tc >> gshift
-  int32_t bf16;    // scales and zeros are bfloat16, else fp16 (read by the host only: it selects the instantiation)
   int32_t ksplit;  // K ranges (1 = the whole K in one workgroup; prefill_fed_kernel only)
+  WorkItems items;  // the order of the work items (prefill_fed_kernel only)
   float* partial;  // ksplit > 1: fp32 partial products [ksplit][M][N], rows of Wt in reordered order
 };
+static_assert(sizeof(PrefillParams) <= 128, "two 64-byte lines of arguments (with a third calls of 11 us took 0.1 us longer)");
 
 constexpr int kPrefillMaxTiles = 224 * 2;  // K <= 57344
 
@@ -690,10 +691,12 @@ __global__ __launch_bounds__(768, 3) void prefill_fed_kernel(const PrefillParams
   const int tid = threadIdx.x;
   const int lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  // M blocks inside tile rows, as in prefill_kernel; with K split into ranges, those are innermost
-  const int ks = (int)blockIdx.x % p.ksplit;
-  const int mt = ((int)blockIdx.x / p.ksplit) % p.n_mtiles;
-  const int tr = ((int)blockIdx.x / p.ksplit) / p.n_mtiles;
+  // M blocks inside tile rows, as in prefill_kernel, in launches of many rounds eight at a time (see launch_fed).  (All that the
+  // place needs in one request: each one that waits for the one before is 0.05 us of a call.)
+  WorkItems items = p.items;
+  asm volatile("" : "+s"(items.whole), "+s"(items.by_ranges), "+s"(items.by_group), "+s"(items.last.by), "+s"(items.last.inverse));
+  const Place place = items.place(blockIdx.x, (uint32_t)p.ntr, (uint32_t)p.ksplit);
+  const int ks = place.ks, mt = place.mt, tr = place.tr;
   const int m0 = mt * BM;
   const int ranges = p.ksplit * KG;
   auto first_of = [&](int range) __attribute__((always_inline)) { return (int)((uint32_t)(range * p.ntc) / (uint32_t)ranges); };
@@ -1049,28 +1052,39 @@ __global__ __launch_bounds__(768, 3) void prefill_fed_kernel(const PrefillParams
 }
 
 template <int MI, int KG>
-static void launch_fed(PrefillParams p, int M, bool g64, hipStream_t stream) {
+static void launch_fed(PrefillParams p, int M, bool g64, bool bf16, hipStream_t stream) {
   constexpr int BM = 16 * MI * (2 / KG);
   p.n_mtiles = (M + BM - 1) / BM;
   const unsigned grid = (unsigned)p.n_mtiles * (unsigned)p.ntr * (unsigned)p.ksplit;
-  if (g64 && p.bf16)
+  // Block b runs on XCD b % 8.  With all M blocks inside a tile row every XCD sees every one of them unless their number is a
+  // multiple of eight, and from about 20 on a round takes the time of its activations from the memory-side cache (64 KiB per
+  // workgroup and tile of 256 rows: 2.15 us a tile where 1.5 are spent multiplying, and prefill_kernel was the faster one by up
+  // to 10 %).  In groups of eight an XCD keeps one M block, and its workgroups share what one of them has fetched (prefill_kernel /
+  // one order / groups): 8714 x 2176 -> 7936 453 / 475 / 371 us, 5000 x 14336 -> 4096 664 / 731 / 606, 30248 x 1664 -> 13952 2133 / 2250 /
+  // 1774, 5000 x 8192 -> 28672 2445 / 2336 / 2157.
+  // Not with one round of workgroups, nor with two and up to 16 blocks, where the weights that come once more for every group cost up to
+  // 4 %, nor with a multiple of eight (up to 2 %).
+  const unsigned blocks = (unsigned)p.n_mtiles;
+  const bool grouped = blocks % kMGroup != 0 && blocks > (grid > 512 ? kMGroup : 2 * kMGroup) && grid > 256;
+  p.items = work_items((unsigned)p.ntr, blocks, (unsigned)p.ksplit, grouped);
+  if (g64 && bf16)
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, true, true>), dim3(grid), dim3(768), 0, stream, p);
   else if (g64)
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, true, false>), dim3(grid), dim3(768), 0, stream, p);
-  else if (p.bf16)
+  else if (bf16)
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, false, true>), dim3(grid), dim3(768), 0, stream, p);
   else
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, false, false>), dim3(grid), dim3(768), 0, stream, p);
 }
 
-static void launch_plain(PrefillParams p, int M, bool g64, hipStream_t stream) {
+static void launch_plain(PrefillParams p, int M, bool g64, bool bf16, hipStream_t stream) {
   p.n_mtiles = (M + 127) / 128;
   const dim3 grid((unsigned)p.n_mtiles * (unsigned)p.ntr), threads(256);
-  if (g64 && p.bf16)
+  if (g64 && bf16)
     hipLaunchKernelGGL((prefill_kernel<true, true>), grid, threads, 0, stream, p);
   else if (g64)
     hipLaunchKernelGGL((prefill_kernel<true, false>), grid, threads, 0, stream, p);
-  else if (p.bf16)
+  else if (bf16)
     hipLaunchKernelGGL((prefill_kernel<false, true>), grid, threads, 0, stream, p);
   else
     hipLaunchKernelGGL((prefill_kernel<false, false>), grid, threads, 0, stream, p);
@@ -1127,7 +1141,8 @@ static double plain_time_us(int32_t N, int32_t K, int32_t M) {
 // no fit this choice is 13.3 % faster than the kernels before it (whose wavefronts all requested and multiplied, in blocks of 64
 // and 128 rows; geometric mean; 14.0 % with the fastest form of each), and more than 2 % slower on 0.4 % of them.  prefill_kernel where it is estimated less than 3 % slower: with
 // a little more than a multiple of 256 workgroups the last round of the others is nearly empty (631 x 3072 -> 23936, 118.7
-// us against 125.6; without it 0.75 % of the shapes are more than 2 % slower).  One K group where a workgroup has a single tile.
+// us against 125.6; without it 0.75 % of the shapes are more than 2 % slower), and not beyond the 2048 rows of the fits (on 300
+// shapes with 1024 to 32768 rows it was never the faster one by more than 2 %).  One K group where a workgroup has a single tile.
 static PrefillForm choose_form(int32_t N, int32_t K, int32_t M, double* time_us) {
   const int64_t ntr = N / kTile, ntc = K / kTile;
   const int32_t most = documented_ranges(N, K, M);
@@ -1143,7 +1158,7 @@ static PrefillForm choose_form(int32_t N, int32_t K, int32_t M, double* time_us)
         if (least < 0.0 || t < least) least = t, best = PrefillForm{mi, kg, k};
       }
   *time_us = least;
-  if ((int64_t)((M + 127) / 128) * ntr > 256 && plain_time_us(N, K, M) < 1.03 * least) best = PrefillForm{0, 1, 1};
+  if (M <= 2048 && (int64_t)((M + 127) / 128) * ntr > 256 && plain_time_us(N, K, M) < 1.03 * least) best = PrefillForm{0, 1, 1};
   return best;
 }
 
@@ -1219,28 +1234,27 @@ int launch_prefill(const GemmArgs& a, void* stream) {
   p.Yt = Yt;
   p.M = a.M;
   p.N = L->N;
-  p.K = L->K;
   p.ntr = L->N / kTile;
   p.ntc = L->K / kTile;
   p.gshift = L->group == 512 ? 2 : L->group == 256 ? 1 : 0;
-  p.bf16 = L->scale_format == SFMP_SCALE_BF16;
   p.n_mtiles = 0;
+  p.items = WorkItems{};
   p.ksplit = form.ksplit;
   p.partial = form.ksplit > 1 ? (float*)((char*)a.workspace + xperm_bytes) : nullptr;
-  const bool g64 = L->group == 64;
+  const bool g64 = L->group == 64, bf16 = L->scale_format == SFMP_SCALE_BF16;
   const hipStream_t s = (hipStream_t)stream;
   switch (8 * form.kg + form.mi) {
-    case 8: launch_plain(p, a.M, g64, s); break;
-    case 12: launch_fed<4, 1>(p, a.M, g64, s); break;
-    case 13: launch_fed<5, 1>(p, a.M, g64, s); break;
-    case 14: launch_fed<6, 1>(p, a.M, g64, s); break;
-    case 15: launch_fed<7, 1>(p, a.M, g64, s); break;
-    case 16: launch_fed<8, 1>(p, a.M, g64, s); break;
-    case 20: launch_fed<4, 2>(p, a.M, g64, s); break;
-    case 21: launch_fed<5, 2>(p, a.M, g64, s); break;
-    case 22: launch_fed<6, 2>(p, a.M, g64, s); break;
-    case 23: launch_fed<7, 2>(p, a.M, g64, s); break;
-    case 24: launch_fed<8, 2>(p, a.M, g64, s); break;
+    case 8: launch_plain(p, a.M, g64, bf16, s); break;
+    case 12: launch_fed<4, 1>(p, a.M, g64, bf16, s); break;
+    case 13: launch_fed<5, 1>(p, a.M, g64, bf16, s); break;
+    case 14: launch_fed<6, 1>(p, a.M, g64, bf16, s); break;
+    case 15: launch_fed<7, 1>(p, a.M, g64, bf16, s); break;
+    case 16: launch_fed<8, 1>(p, a.M, g64, bf16, s); break;
+    case 20: launch_fed<4, 2>(p, a.M, g64, bf16, s); break;
+    case 21: launch_fed<5, 2>(p, a.M, g64, bf16, s); break;
+    case 22: launch_fed<6, 2>(p, a.M, g64, bf16, s); break;
+    case 23: launch_fed<7, 2>(p, a.M, g64, bf16, s); break;
+    case 24: launch_fed<8, 2>(p, a.M, g64, bf16, s); break;
     default: return SFMP_ERR_SHAPE;
   }
   if (int e = check_launch("sfmp_gemm prefill launch")) return e;

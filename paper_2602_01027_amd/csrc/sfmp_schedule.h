@@ -1,6 +1,6 @@
 // The parts of the kernels' requests to memory that a host program can run against a model (tests/schedule_driver.cpp):
 // the order of requests and waits of the small-batch form whose activations are streamed through registers (sfmp_decode.hip,
-// RS), and what the copies of activation blocks ask for (sfmp_prefill.hip).
+// RS), and what the copies of activation blocks ask for and which blocks a workgroup owns (sfmp_prefill.hip).
 #pragma once
 
 #include <stdint.h>
@@ -63,6 +63,43 @@ struct BlockRequest {
 };
 SFMP_SCHEDULE_FN BlockRequest block_request(const uint32_t column_offset, const uint32_t bytes, const bool wanted) {
   return BlockRequest{wanted ? column_offset : 0u, wanted ? bytes : 0u};
+}
+
+// Division by a number that the host knows: a few scalar instructions where the compiler's own goes through vector floats.
+struct Divisor {
+  uint32_t by, inverse;  // floor(2^32 / by), 2^32 - 1 for one: the estimate is right or one too small
+};
+inline Divisor divisor(const uint32_t by) { return Divisor{by, by == 1 ? 0xFFFFFFFFu : (uint32_t)(((uint64_t)1 << 32) / by)}; }
+struct Quotient {
+  uint32_t q, rest;
+};
+SFMP_SCHEDULE_FN Quotient divide(const uint32_t x, const Divisor d) {
+  const uint32_t q = (uint32_t)(((uint64_t)x * d.inverse) >> 32), rest = x - q * d.by;
+  return rest >= d.by ? Quotient{q + 1, rest - d.by} : Quotient{q, rest};
+}
+
+// The work items of a product of ntr tile rows and n_mtiles blocks of activation rows, in `ksplit` K ranges: the ranges innermost,
+// then M blocks inside tile rows - all of them, or (grouped) kMGroup at a time, the last group being what is left.
+constexpr uint32_t kMGroup = 8;
+struct Place {
+  int ks, mt, tr;
+};
+struct WorkItems {
+  uint32_t whole;                  // M blocks in whole groups
+  uint32_t by_ranges, by_group;    // inverses of the K ranges and of the items of a whole group
+  Divisor last;                    // M blocks of the last (or only) group
+
+  SFMP_SCHEDULE_FN Place place(const uint32_t block, const uint32_t ntr, const uint32_t ksplit) const {
+    const Quotient k = divide(block, Divisor{ksplit, by_ranges});
+    const uint32_t whole_items = whole * ntr;
+    const bool in_whole = k.q < whole_items;
+    const Quotient d = divide(k.q - (in_whole ? 0u : whole_items), in_whole ? Divisor{kMGroup * ntr, by_group} : last);
+    return Place{(int)k.rest, (int)(in_whole ? d.q * kMGroup + d.rest % kMGroup : whole + d.rest), (int)(in_whole ? d.rest / kMGroup : d.q)};
+  }
+};
+inline WorkItems work_items(const uint32_t ntr, const uint32_t n_mtiles, const uint32_t ksplit, const bool grouped) {
+  const uint32_t whole = grouped ? n_mtiles / kMGroup * kMGroup : 0u, left = n_mtiles - whole;
+  return WorkItems{whole, divisor(ksplit).inverse, divisor(kMGroup * ntr).inverse, divisor(left ? left : 1u)};
 }
 
 // What a workgroup with BM rows of the batch from row m0 on (a multiple of BM) copies of the staged activations, which lie in

@@ -6,7 +6,8 @@
 //
 // Copies of activation blocks against the range check of a raw buffer, with the scalar offset counted in it and not: what is
 // wanted is read from inside the row block, and nothing is read past the end.  And the copies of a workgroup's rows, which may
-// lie in two or three row blocks of a batch of any length: the bytes that are meant, inside the staged activations.
+// lie in two or three row blocks of a batch of any length: the bytes that are meant, inside the staged activations.  And the
+// numbering of the work items.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -121,8 +122,40 @@ static void check_staged_rows_of_all_forms(const int M, const uint32_t ntc) {
   check_staged_rows<256>(M, ntc);
 }
 
+// Every tile row, M block and K range is the place of one work item; without groups in the plain order.
+static void check_work_items() {
+  for (uint32_t ntr : {1u, 3u, 8u, 57u})
+    for (uint32_t n_mtiles = 1; n_mtiles <= 70; ++n_mtiles)
+      for (uint32_t ksplit : {1u, 2u, 7u, 8u})
+        for (bool grouped : {false, true}) {
+          const sfmp::WorkItems items = sfmp::work_items(ntr, n_mtiles, ksplit, grouped);
+          std::vector<int> owners((size_t)ntr * n_mtiles * ksplit, 0);
+          for (uint32_t block = 0; block < ntr * n_mtiles * ksplit; ++block) {
+            const sfmp::Place w = items.place(block, ntr, ksplit);
+            const bool inside = w.ks >= 0 && w.ks < (int)ksplit && w.tr >= 0 && w.tr < (int)ntr && w.mt >= 0 && w.mt < (int)n_mtiles;
+            const bool plain = w.ks == (int)(block % ksplit) && w.mt == (int)(block / ksplit % n_mtiles) && w.tr == (int)(block / ksplit / n_mtiles);
+            if (!inside || !(grouped || plain) || owners[((size_t)w.tr * n_mtiles + w.mt) * ksplit + w.ks]++ != 0) {
+              std::printf("work item %u of %u x %u x %u: tile row %d, M block %d, range %d\n", block, ntr, n_mtiles, ksplit, w.tr, w.mt, w.ks);
+              std::exit(1);
+            }
+          }
+        }
+  for (uint32_t by : {1u, 2u, 3u, 7u, 8u, 57u, 640u, 1792u, 65535u, 1u << 20, (1u << 31) - 1})
+    for (uint64_t q : {0ull, 1ull, 2ull, 1000ull, 65536ull, 4000000ull})
+      for (int64_t off = -2; off <= 2; ++off) {
+        const int64_t x = (int64_t)(q * by) + off;
+        if (x < 0 || x > 0xFFFFFFFFll) continue;
+        const sfmp::Quotient r = sfmp::divide((uint32_t)x, sfmp::divisor(by));
+        if (r.q != (uint32_t)x / by || r.rest != (uint32_t)x % by) {
+          std::printf("%lld / %u: %u, rest %u\n", (long long)x, by, r.q, r.rest);
+          std::exit(1);
+        }
+      }
+}
+
 int main() {
   check_block_requests();
+  check_work_items();
   for (const uint32_t ntc : {1u, 2u, 31u, 128u, 224u, 448u}) {
     for (int M = 17; M < 800; M += 61) check_staged_rows_of_all_forms(M, ntc);
     if (ntc < 31) continue;

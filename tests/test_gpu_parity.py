@@ -259,6 +259,25 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
 
 
+@pytest.mark.parametrize("K,N,M,group,row_perm,form", [
+    (256, 16512, 2100, 128, True, (8, 1, 1)), (640, 8320, 3001, 64, False, (7, 1, 1)), (384, 2304, 5000, 128, True, (6, 1, 1)),
+    (896, 2048, 5800, 256, True, (6, 1, 1)), (256, 1280, 9000, 128, True, (6, 1, 1))])
+def test_long_prompt_with_m_blocks_in_groups(torch_cuda, K, N, M, group, row_perm, form):
+    # more than eight blocks of rows, not a multiple of eight: 9 and 14 of them in many rounds of workgroups, 27, 31 and 47 in two;
+    # blocks of 256, 224 and 192 rows
+    import plan_util
+    from gpu_util import run_gemm
+    if group > 128 and K % group:
+        K = K // group * group
+    assert plan_util.launched_form(N, K, M) == form
+    p = W.make_problem("groups", K, N, M, 9600 + K + M, fractions={2: 0.3, 3: 0.3, 4: 0.4}, outliers=True, group=group,
+                       use_row_perm=row_perm, fast_codes=K * N > 2 ** 20)
+    rng = np.random.default_rng(M)
+    m_rows = np.unique([0, 255, 256, 2047, 2048, 2303, M - 1, *rng.choice(M, 60, replace=False)])
+    m_rows = m_rows[m_rows < M]
+    _check(p, run_gemm(p), rng.choice(N, 384, replace=False), m_rows=m_rows)
+
+
 @pytest.mark.parametrize("K,N,M,form", [(16384, 128, 131072, (8, 1, 1)), (28672, 256, 75008, (7, 1, 1))])
 def test_prompt_with_4_gib_of_activations(torch_cuda, K, N, M, form):
     # byte counts of the staged activations at and above 2^32: rows of the first, of middle and of the last workgroups, with
