@@ -1542,8 +1542,9 @@ constexpr int kSlotsStreamedActs = 3;
 constexpr int kSlotsRegisterActs = 2;  // activations in registers: the slots hold a slab and its parameters only
 // max_slabs: the largest number of slabs of a workgroup over the problems of the launch; K: the largest K
 // g64: group length 64, for which the resident form does not exist
-// overwrites: outputs lie over activations, so the operands are not gathered in the launch that stores the products
-static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, bool g64, bool overwrites) {
+// rounds: workgroups per CU, one after the other; overwrites: outputs lie over activations, so the operands are not gathered in
+// the launch that stores the products
+static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int32_t rounds, bool g64, bool overwrites) {
   RSkinnyConfig c;
   c.mb = rskinny_mb(M);
   // 16 wavefronts where the finished sums fit beside the rest in 128 registers and the rings in LDS
@@ -1575,12 +1576,11 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, boo
     // (resident / gathered: 4096 -> 4096 M = 2 5.95 / 6.58, M = 4 6.50 / 6.67; with a short K the gathered form is now the shorter
     // one, 512 -> 512 M = 4 4.23 / 3.88, 2048 -> 2048 5.30 / 5.16, called one by one the same).
     // (It fits wherever the sums and slots do: 128 KiB of transposed activations and the first slots are 148 KiB.)
-    if (r.nw == 16 && r.ra == 2) {
-      if (overwrites)
-        r.ra = 4;  // the form with a staging launch
-      else
-        r.resident = true;
-    }
+    // Workgroups that take turns on a CU gather once each, which the launch saved only outweighs while it is short: with more than 8
+    // rows not with two rounds and K > 3072, nor with more and K > 2048 (260 calls with N > 32768, staged / gathered in the mean 0.98
+    // to 0.99 there, up to 0.94: 68096 outputs of K = 4096, 12 rows 40.5 / 43.3 us; with a shorter K 1.00 to 1.08).
+    const bool long_start = M > 8 && rounds > 1 && K > (rounds == 2 ? 3072 : 2048);
+    r.resident = r.nw == 16 && r.ra == 2 && !overwrites && !long_start;
     if (rskinny_lds_bytes(r, max_slabs, M, K) <= 160 * 1024) return r;
   }
   // a longer K with two slabs per workgroup (4096 < N <= 8192 on a full grid): operands streamed through registers.  Not
@@ -1640,7 +1640,7 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool
   d.gemv = false;
   d.grid = grid;
   d.max_slabs = (nslab + grid - 1) / grid;
-  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, group == 64, overwrites);
+  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, (grid + kGemvMaxGrid - 1) / kGemvMaxGrid, group == 64, overwrites);
   d.mb = c.mb;
   d.nw = c.nw;
   d.acc = c.acc;
@@ -1845,7 +1845,8 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   X(16, kSlotsMb16Wide, 16, false, 4, 0, 0) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0)                              \
   X(8, kSlotsMb16, 16, false, 16, 0, 0)                                                                            \
   X(16, kSlotsStreamedActs, 8, false, 4, 0, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2)                       \
-  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0) X(8, kSlotsRegisterActs, 16, false, 16, 2, 0)                       \
+  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0) X(16, kSlotsRegisterActs, 16, false, 4, 2, 0)                       \
+  X(8, kSlotsRegisterActs, 16, false, 16, 2, 0)                                                                    \
   X(16, kSlotsRegisterActs, 16, false, 4, 4, 0) X(8, kSlotsRegisterActs, 16, false, 16, 4, 0)
 
 static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) {
@@ -1987,8 +1988,11 @@ int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinn
   }
   if (n64 != 0 && n64 != count) return SFMP_ERR_SHAPE;  // one launch runs one group-length class: 64, or the others
   *g64 = n64 != 0;
-  *c = rskinny_config(M, max_k, max_slabs, n64 != 0, false);
-  if (c->resident && c->ra && overwrites_activations(probs, count)) *c = rskinny_config(M, max_k, max_slabs, n64 != 0, true);
+  int32_t grid = 0;
+  for (int i = 0; i < count; ++i) grid += g[i];
+  const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
+  *c = rskinny_config(M, max_k, max_slabs, rounds, n64 != 0, false);
+  if (c->resident && c->ra && overwrites_activations(probs, count)) *c = rskinny_config(M, max_k, max_slabs, rounds, n64 != 0, true);
   return SFMP_OK;
 }
 

@@ -793,6 +793,21 @@ def test_small_batch_more_than_2048_slabs(torch_cuda, K, N, M):
     _check(p, run_gemm(p))
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format", [(3200, 32896, 9, 128, "fp16"), (2176, 65664, 16, 64, "bf16"), (4096, 32896, 24, 128, "bf16")])
+def test_small_batch_in_rounds_of_workgroups_with_staged_operands(torch_cuda, K, N, M, group, scale_format):
+    # two and three workgroups per CU in turn, operands of two tile columns per wavefront staged in operand order; M = 24: two
+    # chunks of 16 rows in one launch
+    import paper_2602_01027_amd as S
+    import plan_util
+    from gpu_util import run_gemm
+    p = W.make_problem("rounds", K, N, M, 8600 + M, fractions={2: 0.5, 3: 0.25, 4: 0.25}, group=group, scale_format=scale_format, outliers=True,
+                       fast_codes=True)
+    layout = S.sfmp_layout_set_quant(S.sfmp_pack_query(p.bitmap, N, K), group, scale_format)
+    d = plan_util.batched_config([layout] * -(-M // 16), 16)[0] if M > 16 else plan_util.decode_plan(N, K, M, group)
+    assert (d.ra, d.resident, d.nw) == (2, False, 16) and (M <= 16 or plan_util.chunked(N, K, M))
+    _check(p, run_gemm(p), np.random.default_rng(M).choice(N, 512, replace=False))
+
+
 # ---------------------------------------------------------------------------------------------
 # group lengths 256 / 512, bf16 parameters, (m_b, n_b) bit-allocation blocks
 # ---------------------------------------------------------------------------------------------

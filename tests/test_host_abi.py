@@ -454,10 +454,10 @@ def test_outputs_over_activations_are_staged_first():
                                 (at, [*apart_y[:last], at], False), (at, [*apart_y[:last], at + nx - 2], False),
                                 (at, [*apart_y[:last], at - ny[last] + 2], False)):
             c = plan_util.batched_config(layouts, M, [x0, *apart_x[1:]], y)[0]
-            assert (c.ra, c.resident) == ((2, True) if gathered else (4, False)), (M, group, [hex(v) for v in y])
+            assert (c.ra, c.resident) == (2, gathered), (M, group, [hex(v) for v in y])
             if n == 1:
                 d = plan_util.launched_decode_plan(layouts[0], M, x0, y[0])
-                assert (d.ra, d.resident) == ((2, True) if gathered else (4, False)) and d.lds_bytes <= 160 * 1024
+                assert (d.ra, d.resident) == (2, gathered) and d.lds_bytes <= 160 * 1024
                 assert d.workspace_bytes == plan_util.decode_plan(layouts[0].N, 2048, M, group).workspace_bytes
     # 17 to 128 rows beyond the documented chunked shapes: the matrix-core path, which stages them
     layout = S.sfmp_pack_query(np.full((4, 4), 3, dtype=np.int8), 512, 512)
@@ -472,6 +472,17 @@ def test_chunks_without_staging_by_group_length(N, K, M, both):
     # two parameter pairs per tile column make chunks slower: with many slabs and a long K the matrix-core path is the faster one
     import plan_util
     assert plan_util.chunks_without_staging(N, K, M, 128) and plan_util.chunks_without_staging(N, K, M, 64) == both
+
+
+@pytest.mark.parametrize("N,K,M,gathered", [
+    (32768, 4096, 16, None), (28672, 4096, 16, True), (32896, 4096, 16, False), (32896, 3072, 16, True), (32896, 4096, 8, True),
+    (57344, 3200, 9, False), (65664, 2176, 9, False), (65664, 2048, 16, True), (65664, 4096, 8, True)])
+def test_activations_are_gathered_where_the_start_is_paid_for_seldom(N, K, M, gathered):
+    # more than 8 rows: one round of workgroups (up to 7 slabs each), two with K <= 3072, more with K <= 2048; staged beyond
+    import plan_util
+    d = plan_util.decode_plan(N, K, M)
+    assert (d.ra, d.resident) == ((0, False) if gathered is None else (2, gathered))
+    assert d.workspace_bytes == K // 128 * 16 * 256
 
 
 @pytest.mark.parametrize("N,K,M,group,streamed", [
