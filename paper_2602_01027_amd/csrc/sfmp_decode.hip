@@ -32,11 +32,41 @@
 namespace sfmp {
 
 
-// Sum over the slab's 128 columns of q * x for the 16 rows of the slab (lane%16) and the 16 activation rows
-// (4*(lane/16) + r), in units of 2^-24 (class 0 counts 1, class i counts 2^-pos(i)): the caller multiplies by 2^24
+// The first R sums of a lane of a 16 x 16 product.  A lane holds the sums of operand rows 4*(lane/16) + 0 ... 3; with up to
+// eight activation rows the operand carries them two (R = 2), with up to four one (R = 1) to every four rows, so that the
+// vector instructions on sums work for all 64 lanes, and there are R of each instead of four for a half or a quarter of the
+// lanes.  What bounds these kernels is instruction issue (about 55 vector instructions per item with four sums): 3 to 15 fewer
+// per item and 6 to 9 per finished slab.  Each sum is formed as before, the same bits.  Four rows / spread, back-to-back calls:
+// the four launches of an 8B-shaped layer at M = 4 40.6 / 38.2 us, 4096 -> 4096 M = 2 5.80 / 5.53, 14336 -> 4096 M = 4 10.55 / 9.92 and
+// M = 8 11.63 / 11.29, 8192 -> 28672 M = 8 25.6 / 24.6, 8192 -> 8192 M = 4 12.34 / 11.95.
+template <int R>
+struct RowSums {
+  typedef float type __attribute__((ext_vector_type(R)));
+  static __device__ __forceinline__ type of(const floatx4& c) {
+    type v;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = c[r];
+    return v;
+  }
+  // sum + a * b, rounded once
+  static __device__ __forceinline__ type fma(const type& a, float b, const type& sum) {
+    type v;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = __builtin_fmaf(a[r], b, sum[r]);
+    return v;
+  }
+};
+// Activation row of row `at` (0 ... 15) of the operand, and whether it carries one.
+template <int R>
+__device__ __forceinline__ int row_at(int at) { return at / 4 * R + at % R; }
+template <int R>
+__device__ __forceinline__ bool carries_row(int at) { return R == 4 || at % 4 < R; }
+
+// Sum over the slab's 128 columns of q * x for the 16 rows of the slab (lane%16) and the activation rows
+// (R*(lane/16) + r), in units of 2^-24 (class 0 counts 1, class i counts 2^-pos(i)): the caller multiplies by 2^24
 // once per slab instead of once per item.
-template <int B>
-__device__ __forceinline__ floatx4 slab_dot_units(const uint32_t* w, const half8 (&a)[4]) {
+template <int B, int R>
+__device__ __forceinline__ typename RowSums<R>::type slab_dot_units(const uint32_t* w, const half8 (&a)[4]) {
   uint32_t op[4][4];
   unpack_slab<B>(w, op);
   floatx4 c[num_classes<B>()];
@@ -46,9 +76,9 @@ __device__ __forceinline__ floatx4 slab_dot_units(const uint32_t* w, const half8
   for (int kappa = 0; kappa < 4; ++kappa)
     c[step_class<B>(kappa)] =
         __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kappa], as_half8(op[kappa]), c[step_class<B>(kappa)], 0, 0, 0);
-  floatx4 t = c[0];
+  typename RowSums<R>::type t = RowSums<R>::of(c[0]);
 #pragma unroll
-  for (int i = 1; i < num_classes<B>(); ++i) t += c[i] * pow2f(-class_pos<B>(i));
+  for (int i = 1; i < num_classes<B>(); ++i) t = RowSums<R>::fma(RowSums<R>::of(c[i]), pow2f(-class_pos<B>(i)), t);
   return t;
 }
 
@@ -86,16 +116,17 @@ __device__ __forceinline__ void slab_dot_row0_halves(const uint32_t* w, const ha
   t_lo = c[0][0] * pow2f(-step_pos<B>(0)) + c[1][0] * pow2f(-step_pos<B>(1));
   t_hi = c[2][0] * pow2f(-step_pos<B>(2)) + c[3][0] * pow2f(-step_pos<B>(3));
 }
-template <int B>
-__device__ __forceinline__ void slab_dot_halves(const uint32_t* w, const half8 (&a)[4], floatx4& t_lo, floatx4& t_hi) {
+template <int B, int R>
+__device__ __forceinline__ void slab_dot_halves(const uint32_t* w, const half8 (&a)[4], typename RowSums<R>::type& t_lo,
+                                                typename RowSums<R>::type& t_hi) {
   uint32_t op[4][4];
   unpack_slab<B>(w, op);
   floatx4 c[4];
 #pragma unroll
   for (int kappa = 0; kappa < 4; ++kappa)
     c[kappa] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kappa], as_half8(op[kappa]), floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-  t_lo = c[0] * pow2f(-step_pos<B>(0)) + c[1] * pow2f(-step_pos<B>(1));
-  t_hi = c[2] * pow2f(-step_pos<B>(2)) + c[3] * pow2f(-step_pos<B>(3));
+  t_lo = RowSums<R>::of(c[0]) * pow2f(-step_pos<B>(0)) + RowSums<R>::of(c[1]) * pow2f(-step_pos<B>(1));
+  t_hi = RowSums<R>::of(c[2]) * pow2f(-step_pos<B>(2)) + RowSums<R>::of(c[3]) * pow2f(-step_pos<B>(3));
 }
 
 // Direct global->LDS copies written out by hand: scalar base address + 32-bit lane offset (no 64-bit vector
@@ -733,14 +764,15 @@ __global__ __launch_bounds__(MB * 16) void stage_rows_kernel(const _Float16* __r
 
 // The same in operand order, for the kernels that take their activations into registers: MB rows (rows >= M zero), per
 // tile column [k-step][unit % 4][row][16 bytes]: a wavefront loads the matrix-instruction operand of a k-step with one
-// 16-byte load per lane (lane = 16 * (unit % 4) + row), MB * 64 bytes contiguous.
-template <int MB>
+// 16-byte load per lane (lane = 16 * (unit % 4) + row), MB * 64 bytes contiguous.  R: activation rows to every four of
+// the operand (see RowSums), the other rows zero; with MB = 8 the kernel itself spreads the rows.
+template <int MB, int R>
 __device__ __forceinline__ void stage_rows_tile_operand_order(const _Float16* __restrict__ X,
                                                               const int32_t* __restrict__ col_perm, unsigned char* xblk,
                                                               int M, int K, int tc) {
-  const int m = threadIdx.x / 16, unit = threadIdx.x % 16;
+  const int at = threadIdx.x / 16, m = row_at<R>(at), unit = threadIdx.x % 16;
   half8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (m < M) {
+  if (carries_row<R>(at) && m < M) {
     const int k0 = tc * kTile + unit * 8;
     if (col_perm) {
       const int4 c0 = reinterpret_cast<const int4*>(col_perm + k0)[0];
@@ -760,13 +792,13 @@ __device__ __forceinline__ void stage_rows_tile_operand_order(const _Float16* __
   }
   // (written as k-step and unit of the k-step: as (tc * 16 + unit) * MB + m, the same number, the compiler's order of the
   // address arithmetic made batched calls of 16 rows and chunks 0.15 us longer: 4096 -> 4096, 32 rows 10.95 us, now 10.76)
-  *reinterpret_cast<half8*>(xblk + (((int64_t)tc * 4 + unit / 4) * (4 * MB) + MB * (unit % 4) + m) * 16) = v;
+  *reinterpret_cast<half8*>(xblk + (((int64_t)tc * 4 + unit / 4) * (4 * MB) + MB * (unit % 4) + at) * 16) = v;
 }
-template <int MB>
+template <int MB, int R>
 __global__ __launch_bounds__(MB * 16) void stage_rows_operand_order_kernel(const _Float16* __restrict__ X,
                                                                            const int32_t* __restrict__ col_perm,
                                                                            unsigned char* xblk, int M, int K) {
-  stage_rows_tile_operand_order<MB>(X, col_perm, xblk, M, K, (int)blockIdx.x);
+  stage_rows_tile_operand_order<MB, R>(X, col_perm, xblk, M, K, (int)blockIdx.x);
 }
 
 template <int MB>
@@ -807,12 +839,15 @@ __device__ __forceinline__ uint32_t xt_offset(uint32_t at) { return at ^ ((at >>
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16* v4i16_lds;
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS, int R>
 __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int bid, const int G, unsigned char* lds_raw) {
   // RES with RA: the operands are gathered by the kernel itself (XT below); RESL: resident in LDS
   constexpr bool XT = RES && RA > 0, RESL = RES && !XT;
   static_assert(!(RESL && G64), "the resident form keeps one activation sum per tile column");
   static_assert(!RS || (RS == 2 && !RES && !RA && S == 3 && NW == 16), "streamed operands: three sets and slots");
+  static_assert(R == 4 || (R == 2 && (MB == 8 || (RA && !RES))) || (R == 1 && (MB == 4 || (RA && !RES))), "rows of the operand");
+  typedef RowSums<R> Rows;
+  typedef typename Rows::type sums_t;
   static_assert((!RA || MB == 16) && (RA == 0 || RA == 2 || RA == 4), "activations in registers: 16 rows");
   static_assert(!XT || (S == 2 && NW == 16 && RA == 2), "operands gathered by the kernel: two slots, 4 columns per thread");
   constexpr int NT = NW * 64;
@@ -821,15 +856,15 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   constexpr int kCopies = (RES || RA || RS) ? 2 : 2 + MB / 4;  // direct copies per item: slab, scales+zeros, MB/4 x 1 KiB of activations
   constexpr int kRedGroups = NW / 4;  // the final sum over the wavefronts is taken in groups of four
   // DS: the sums of a finished slab go straight into the wavefront's own block of LDS and none are held in
-  // registers: with the activations in registers (all 64 lanes hold sums) and with up to four activation rows
-  // (lanes 0-15 hold them all: output rows 4 (lane / 16) + r)
+  // registers: with the activations in registers and with up to four activation rows
   constexpr bool DS = RA || RS || MB == 4;
-  constexpr int kFinLanes = RA || RS ? 64 : 16;
-  // LDS: red [NW/4][max_slabs][4][64] f32 | (Xs [ntc][MB][256 B] | SxL | raw activations [M][K] fp16) |
-  //      rings [NW][S][kSlot];  with RA: fin [NW][max_slabs][64][4] f32 | rings
+  constexpr int kFin = 64 * R;  // sums of a slab
+  // LDS: red [NW/4][max_slabs][R][64] f32 (in the room of R = 4) | (Xs [ntc][MB][256 B] | SxL | raw activations [M][K] fp16) |
+  //      rings [NW][S][kSlot];  with DS: fin [max_slabs][NW][64][R] f32 | ...
   float* red = reinterpret_cast<float*>(lds_raw);
-  unsigned char* Xs = lds_raw + (DS ? (size_t)p.max_slabs * NW * kFinLanes * 16 : (size_t)p.max_slabs * 1024 * kRedGroups);
-  // (resident) SxL [ntc][4 lane groups][4] f32: the sums of the activations of rows 4g..4g+3 over a tile column
+  unsigned char* Xs = lds_raw + (DS ? (size_t)p.max_slabs * NW * kFin * 4 : (size_t)p.max_slabs * 1024 * kRedGroups);
+  // (resident) SxL [ntc][4] f32: the sums of the activations of the four rows over a tile column, one for every lane group
+  // of the product (64 bytes a tile column are set aside, as for a product with all 16 rows)
   float* SxL = reinterpret_cast<float*>(Xs + (RESL ? (size_t)p.ntc * (MB * 256) : (size_t)0));
   unsigned char* raw_region = reinterpret_cast<unsigned char*>(SxL) + (RESL ? (size_t)p.ntc * 64 : (size_t)0);
   unsigned char* rings = raw_region + (RESL ? rskinny_raw_bytes(p.M, p.K) : (size_t)0);
@@ -969,9 +1004,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
           *reinterpret_cast<half8*>(Xs + ((size_t)tc * MB + m) * 256 + ((unit ^ m) * 16)) = v;
           sums[m] = unit_group_sum(v);  // over the 16 units of the tile column (16 consecutive lanes)
         }
-        // rows 0-3 belong to lane group 0 of the product; the groups of rows 4-15 (not present) read zeros
-        if (unit < 4)
-          *reinterpret_cast<floatx4*>(SxL + tc * 16 + unit * 4) = unit == 0 ? sums : floatx4{0.f, 0.f, 0.f, 0.f};
+        if (unit == 0) *reinterpret_cast<floatx4*>(SxL + tc * 4) = sums;
       }
     }
     barrier_lds_only();  // Xs and SxL are complete
@@ -1017,22 +1050,22 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     }
     const int units = p.K / 4;
     auto stage = [&](auto rtag) __attribute__((always_inline)) {
-      constexpr int R = decltype(rtag)::value;
-      u32x2 x[R];
+      constexpr int RL = decltype(rtag)::value;
+      u32x2 x[RL];
       if (wave * kWave < units) {
         const _Float16* const from = p.X + 4 * min(tid, units - 1);
 #pragma unroll
-        for (int m = 0; m < R; ++m)  // (rows past the last: the last again; their products are not stored)
+        for (int m = 0; m < RL; ++m)  // (rows past the last: the last again; their products are not stored)
           x[m] = *reinterpret_cast<const u32x2*>(from + (size_t)min(m, p.M - 1) * p.K);
       } else {
 #pragma unroll
-        for (int m = 0; m < R; ++m) asm volatile("" : "=v"(x[m]));  // (any value: not stored)
+        for (int m = 0; m < RL; ++m) asm volatile("" : "=v"(x[m]));  // (any value: not stored)
       }
       const int Eb0 = min(64, E);
       describe(0, Eb0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // one trip to memory for all of the above
 #pragma unroll
-      for (int m = 0; m < R; ++m) asm volatile("" : "+v"(x[m]));
+      for (int m = 0; m < RL; ++m) asm volatile("" : "+v"(x[m]));
 #pragma unroll
       for (int t = 0; t < RA; ++t)
 #pragma unroll
@@ -1041,21 +1074,21 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       issued_early = min(1, Eb0);
       if (issued_early) issue_item(0, 0);
       if (tid < units) {
-        const uint32_t base = xt_offset((uint32_t)tid * (8 * R));  // (4 columns: the low bits of the unit are added by XOR)
+        const uint32_t base = xt_offset((uint32_t)tid * (8 * RL));  // (4 columns: the low bits of the unit are added by XOR)
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-          uint32_t v[R / 2];
+          uint32_t v[RL / 2];
 #pragma unroll
-          for (int m = 0; m < R / 2; ++m)
+          for (int m = 0; m < RL / 2; ++m)
             v[m] = __builtin_amdgcn_perm(x[2 * m + 1][kk / 2], x[2 * m][kk / 2], kk % 2 ? 0x07060302u : 0x05040100u);
 #pragma unroll
-          for (int h = 0; h < R / 8; ++h)
-            *reinterpret_cast<u32x4*>(lds_raw + (base ^ (uint32_t)(kk * 2 * R + h * 16))) =
+          for (int h = 0; h < RL / 8; ++h)
+            *reinterpret_cast<u32x4*>(lds_raw + (base ^ (uint32_t)(kk * 2 * RL + h * 16))) =
                 u32x4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
         }
       }
       barrier_lds_only();
-      const uint32_t in_column = (uint32_t)(R == 16 ? chunk : chunk % 2) * 8;
+      const uint32_t in_column = (uint32_t)(RL == 16 ? chunk : chunk % 2) * 8;
 #pragma unroll
       for (int t = 0; t < RA; ++t) {
         if (wave + NW * t < p.ntc) {
@@ -1067,7 +1100,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
             } o;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-              const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * R) + in_column);
+              const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * RL) + in_column);
               o.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16_lds)(at));
             }
             aset[t][kappa] = o.v;
@@ -1096,11 +1129,12 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
         aset[t][kappa] = *reinterpret_cast<const half8*>(p.xblk + (((size_t)tc * 4 + kappa) * 64 + lane) * 16);
     }
   }
-  // operand addresses inside a slot: activation row i16, unit 4*kappa + kb at position unit ^ i16
+  // operand addresses inside a slot: activation row m of this lane, unit 4*kappa + kb at position unit ^ m
+  const int m_lane = row_at<R>(i16);
   uint32_t a_off[4];
 #pragma unroll
   for (int kappa = 0; kappa < 4; ++kappa)
-    a_off[kappa] = (RESL ? 0 : kBase) + i16 * 256 + (((4 * kappa + kb) ^ i16) * 16);
+    a_off[kappa] = (RESL ? 0 : kBase) + m_lane * 256 + (((4 * kappa + kb) ^ m_lane) * 16);
 
   // finished sums: accs[r][q] = output element r of this lane for slab q (register-indexed writes, no switch)
   static_assert(ACC == 4 || ACC == 8 || ACC == 16, "the finished sums live in 4-, 8- or 16-wide register vectors");
@@ -1110,24 +1144,26 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   for (int q = 0; q < ACC; ++q) accs0[q] = 0.f, accs1[q] = 0.f, accs2[q] = 0.f, accs3[q] = 0.f;
   // Keeping the sums of a finished slab (q is uniform).  A wavefront with one or two tile columns finishes a slab
   // with every or every second item, and a register-indexed write into vectors of up to eight elements costs one
-  // conditional move per element (32 per finished slab).  DS: one 16-byte write into fin [NW][max_slabs][kFinLanes][4]
+  // conditional move per element (32 per finished slab).  DS: one write into fin [max_slabs][NW][64][R]
   // f32 instead, and no sums in registers at all.
   float* fin = reinterpret_cast<float*>(lds_raw);
-  auto keep_sums = [&](const int q, const floatx4 acc) __attribute__((always_inline)) {
+  auto keep_sums = [&](const int q, const sums_t acc) __attribute__((always_inline)) {
     if constexpr (DS) {
-      if (kFinLanes == 64 || lane < kFinLanes)
-        *reinterpret_cast<floatx4*>(fin + (((size_t)wave * p.max_slabs + q) * kFinLanes + lane) * 4) = acc;
+      *reinterpret_cast<sums_t*>(fin + ((size_t)q * NW + wave) * kFin + lane * R) = acc;
     } else {
-      accs0[q] = acc[0], accs1[q] = acc[1], accs2[q] = acc[2], accs3[q] = acc[3];
+      accs0[q] = acc[0];
+      if constexpr (R > 1) accs1[q] = acc[1];
+      if constexpr (R > 2) accs2[q] = acc[2], accs3[q] = acc[3];
     }
   };
   // running sums of the current slab: scale * (code sums, in units of 2^-24) and zero * (activation sums)
-  floatx4 acc_q = {0.f, 0.f, 0.f, 0.f}, acc_z = {0.f, 0.f, 0.f, 0.f};
+  const sums_t none = 0.f;
+  sums_t acc_q = none, acc_z = none;
 
   // one item with its activation operands given (a: four k-steps of 32 columns)
   // (sx_known: the activation sums of the item's tile column when the caller has them already)
-  auto consume_with = [&](const uint32_t misc, const unsigned char* slot, const half8 (&a)[4], const floatx4 sx_known,
-                          floatx4& acc_q, floatx4& acc_z) __attribute__((always_inline)) {
+  auto consume_with = [&](const uint32_t misc, const unsigned char* slot, const half8 (&a)[4], const sums_t sx_known,
+                          sums_t& acc_q, sums_t& acc_z) __attribute__((always_inline)) {
     if constexpr (G64) {
       // sums of the activations over columns 0-63 and 64-127, the code sums likewise, one parameter pair for each
       floatx4 sx_lo = {0.f, 0.f, 0.f, 0.f}, sx_hi = {0.f, 0.f, 0.f, 0.f};
@@ -1135,24 +1171,24 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       sx_lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[1], ones, sx_lo, 0, 0, 0);
       sx_hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[2], ones, sx_hi, 0, 0, 0);
       sx_hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[3], ones, sx_hi, 0, 0, 0);
-      floatx4 t_lo, t_hi;
+      sums_t t_lo, t_hi;
       uint32_t w[4];
       const uint32_t* src;
       switch ((misc >> 24) & 3) {
         case 0:
           src = reinterpret_cast<const uint32_t*>(slot + lane * 8);
           w[0] = src[0], w[1] = src[1];
-          slab_dot_halves<2>(w, a, t_lo, t_hi);
+          slab_dot_halves<2, R>(w, a, t_lo, t_hi);
           break;
         case 1:
           src = reinterpret_cast<const uint32_t*>(slot + lane * 12);
           w[0] = src[0], w[1] = src[1], w[2] = src[2];
-          slab_dot_halves<3>(w, a, t_lo, t_hi);
+          slab_dot_halves<3, R>(w, a, t_lo, t_hi);
           break;
         default:
           src = reinterpret_cast<const uint32_t*>(slot + lane * 16);
           w[0] = src[0], w[1] = src[1], w[2] = src[2], w[3] = src[3];
-          slab_dot_halves<4>(w, a, t_lo, t_hi);
+          slab_dot_halves<4, R>(w, a, t_lo, t_hi);
           break;
       }
       const uint32_t* par = reinterpret_cast<const uint32_t*>(slot + 1024 + (lane & 15) * 4);
@@ -1160,27 +1196,28 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       params_to_float(par[0], par[16], (misc >> 22) & 16u, p.bf16 != 0, s_lo, z_lo);
       params_to_float(par[32], par[48], (misc >> 22) & 16u, p.bf16 != 0, s_hi, z_hi);
       acc_q += s_lo * t_lo + s_hi * t_hi;
-      acc_z += z_lo * sx_lo + z_hi * sx_hi;
+      acc_z += z_lo * Rows::of(sx_lo) + z_hi * Rows::of(sx_hi);
       if (!RS && (misc & 0x10000u)) {  // this wavefront's share of slab j is complete
         asm volatile("" ::: "memory");
         const int q = (misc >> 17) & (DS ? 15 : ACC - 1);
-        const floatx4 acc = acc_q * 16777216.f + acc_z;
+        const sums_t acc = Rows::fma(acc_q, 16777216.f, acc_z);
         keep_sums(q, acc);
-        acc_q = floatx4{0.f, 0.f, 0.f, 0.f}, acc_z = floatx4{0.f, 0.f, 0.f, 0.f};
+        acc_q = none, acc_z = none;
       }
       return;
     }
-    floatx4 sx;
+    sums_t sx;
     if constexpr (RA == 2 || RS) {
       sx = sx_known;
     } else if constexpr (RESL) {
-      sx = *reinterpret_cast<const floatx4*>(SxL + (misc & 0xFFFF) * 16 + kb * 4);
+      sx = SxL[(misc & 0xFFFF) * 4 + kb];
     } else {
-      sx = floatx4{0.f, 0.f, 0.f, 0.f};
+      floatx4 all = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kappa = 0; kappa < 4; ++kappa) sx = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kappa], ones, sx, 0, 0, 0);
+      for (int kappa = 0; kappa < 4; ++kappa) all = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kappa], ones, all, 0, 0, 0);
+      sx = Rows::of(all);
     }
-    floatx4 t;
+    sums_t t;
     {
       uint32_t w[4];
       const uint32_t* src;
@@ -1188,17 +1225,17 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
         case 0:
           src = reinterpret_cast<const uint32_t*>(slot + lane * 8);
           w[0] = src[0], w[1] = src[1];
-          t = slab_dot_units<2>(w, a);
+          t = slab_dot_units<2, R>(w, a);
           break;
         case 1:
           src = reinterpret_cast<const uint32_t*>(slot + lane * 12);
           w[0] = src[0], w[1] = src[1], w[2] = src[2];
-          t = slab_dot_units<3>(w, a);
+          t = slab_dot_units<3, R>(w, a);
           break;
         default:
           src = reinterpret_cast<const uint32_t*>(slot + lane * 16);
           w[0] = src[0], w[1] = src[1], w[2] = src[2], w[3] = src[3];
-          t = slab_dot_units<4>(w, a);
+          t = slab_dot_units<4, R>(w, a);
           break;
       }
     }
@@ -1206,25 +1243,27 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     const uint32_t zrw = *reinterpret_cast<const uint32_t*>(slot + 1088 + (lane & 15) * 4);
     float sf, zf;
     params_to_float(scw, zrw, (misc >> 22) & 16u, p.bf16 != 0, sf, zf);  // bit 26 of misc: odd sigma -> high half
-    acc_q += sf * t;
-    acc_z += zf * sx;
+    acc_q = Rows::fma(t, sf, acc_q);
+    acc_z = Rows::fma(sx, zf, acc_z);
     if (!RS && (misc & 0x10000u)) {  // this wavefront's share of slab j is complete
       asm volatile("" ::: "memory");  // keeps this a branch rather than a select over all the sums
       const int q = (misc >> 17) & (DS ? 15 : ACC - 1);
-      const floatx4 acc = acc_q * 16777216.f + acc_z;
+      const sums_t acc = Rows::fma(acc_q, 16777216.f, acc_z);
       keep_sums(q, acc);
-      acc_q = floatx4{0.f, 0.f, 0.f, 0.f}, acc_z = floatx4{0.f, 0.f, 0.f, 0.f};
+      acc_q = none, acc_z = none;
     }
   };
   // (two tile columns in registers, one parameter pair per tile column) the activation sums of the two tile columns,
   // taken once for all slabs: the same four matrix instructions against ones, in the same order, that the other forms
   // issue per item (with four tile columns the registers go to the operands, and the sums are taken per item)
-  floatx4 sx0 = {0.f, 0.f, 0.f, 0.f}, sx1 = {0.f, 0.f, 0.f, 0.f};
+  sums_t sx0 = none, sx1 = none;
   if constexpr (RA == 2 && !G64) {
+    floatx4 all0 = {0.f, 0.f, 0.f, 0.f}, all1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kappa = 0; kappa < 4; ++kappa) sx0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aset[0][kappa], ones, sx0, 0, 0, 0);
+    for (int kappa = 0; kappa < 4; ++kappa) all0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aset[0][kappa], ones, all0, 0, 0, 0);
 #pragma unroll
-    for (int kappa = 0; kappa < 4; ++kappa) sx1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aset[1][kappa], ones, sx1, 0, 0, 0);
+    for (int kappa = 0; kappa < 4; ++kappa) all1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aset[1][kappa], ones, all1, 0, 0, 0);
+    sx0 = Rows::of(all0), sx1 = Rows::of(all1);
   }
   auto consume = [&](int e, int s) __attribute__((always_inline)) {
     const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, e);
@@ -1243,20 +1282,20 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
         else consume_with(misc, slot, aset[3], sx0, acc_q, acc_z);
       }
     } else {
-      if (MB == 16 || i16 < MB) {
+      if (carries_row<R>(i16)) {
         const unsigned char* abase = RESL ? Xs + (size_t)(misc & 0xFFFF) * (MB * 256) : slot;
 #pragma unroll
         for (int kappa = 0; kappa < 4; ++kappa) a[kappa] = *reinterpret_cast<const half8*>(abase + a_off[kappa]);
       }
-      consume_with(misc, slot, a, floatx4{0.f, 0.f, 0.f, 0.f}, acc_q, acc_z);
+      consume_with(misc, slot, a, none, acc_q, acc_z);
     }
   };
 
   if constexpr (RS > 0) {
     describe(0, E);  // (at most 64 items)
-    floatx4 accq[RS], accz[RS];
+    sums_t accq[RS], accz[RS];
 #pragma unroll
-    for (int j = 0; j < RS; ++j) accq[j] = floatx4{0.f, 0.f, 0.f, 0.f}, accz[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < RS; ++j) accq[j] = none, accz[j] = none;
     if (my_cnt > 0) {
       half8 as0[4], as1[4], as2[4];
       auto set_of = [&](auto set) __attribute__((always_inline)) -> half8(&)[4] {
@@ -1270,7 +1309,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
         const int tc = min(wave + NW * i, p.ntc - 1);  // (past the end: the last tile column again)
 #pragma unroll
         for (int kappa = 0; kappa < 4; ++kappa)
-          v[kappa] = *reinterpret_cast<const half8*>(p.xblk + ((((size_t)tc * 4 + kappa) * 4 + kb) * MB + (i16 & (MB - 1))) * 16);
+          v[kappa] = *reinterpret_cast<const half8*>(p.xblk + ((((size_t)tc * 4 + kappa) * 4 + kb) * MB + m_lane) * 16);
       };
       auto copy = [&](auto slot, int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -1300,7 +1339,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
         for (int j = 0; j < RS; ++j)
           if (j < nj) {
             const uint32_t misc = (uint32_t)__builtin_amdgcn_readlane((int)it_misc, j * my_cnt + i);
-            consume_with(misc, ring + (decltype(set)::value * RS + j) * kSlot, v, sx, accq[j], accz[j]);
+            consume_with(misc, ring + (decltype(set)::value * RS + j) * kSlot, v, Rows::of(sx), accq[j], accz[j]);
           }
         __builtin_amdgcn_s_setprio(0);
       };
@@ -1311,7 +1350,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       stream_columns(my_cnt, load, copy, wait, use, keep_loads);
 #pragma unroll
       for (int j = 0; j < RS; ++j)
-        if (j < nj) keep_sums(j, accq[j] * 16777216.f + accz[j]);
+        if (j < nj) keep_sums(j, Rows::fma(accq[j], 16777216.f, accz[j]));
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
@@ -1354,21 +1393,22 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   // (wavefronts 4g..4g+3) one after the other, then the groups in turn.
   if constexpr (DS) {
     // every wavefront's sums are in its block of fin already (a wavefront without a tile column wrote none: zeros)
-    if (my_cnt == 0 && lane < kFinLanes)
+    if (my_cnt == 0)
       for (int q = 0; q < nj; ++q)
-        *reinterpret_cast<floatx4*>(fin + (((size_t)wave * p.max_slabs + q) * kFinLanes + lane) * 4) = floatx4{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<sums_t*>(fin + ((size_t)q * NW + wave) * kFin + lane * R) = none;
     __syncthreads();
-    for (int o = tid; o < nj * kFinLanes * 4; o += NT) {
-      const int jj = o / (kFinLanes * 4), rem = o % (kFinLanes * 4);
-      const int l = rem / 4, r = rem % 4;
-      const int m = 4 * (l / 16) + r;
+    for (int o = tid; o < nj * kFin; o += NT) {
+      const int jj = o / kFin, rem = o % kFin;
+      const int l = rem / R, r = rem % R;
+      const int m = R * (l / 16) + r;
       if (m < p.M) {
+        const float* of_slab = fin + (size_t)jj * NW * kFin + rem;
         float sum = 0.f;
 #pragma unroll
         for (int g = 0; g < kRedGroups; ++g) {
           float part = 0.f;
 #pragma unroll
-          for (int w = 0; w < 4; ++w) part += fin[(((size_t)(4 * g + w) * p.max_slabs + jj) * kFinLanes + l) * 4 + r];
+          for (int w = 0; w < 4; ++w) part += of_slab[(4 * g + w) * kFin];
           sum = g == 0 ? part : sum + part;
         }
         const int v = bid + G * jj;
@@ -1381,7 +1421,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     return;
   }
   {
-    float* mine = red + (size_t)(wave / 4) * p.max_slabs * 256;
+    float* mine = red + (size_t)(wave / 4) * p.max_slabs * kFin;
     for (int w = 0; w < 4; ++w) {
       if (wave % 4 == w) {
 #pragma unroll
@@ -1389,8 +1429,8 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
           if (q < nj) {
             const float fin4[4] = {accs0[q], accs1[q], accs2[q], accs3[q]};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              float* dst = mine + (q * 4 + r) * 64 + lane;
+            for (int r = 0; r < R; ++r) {
+              float* dst = mine + (q * R + r) * 64 + lane;
               *dst = (w == 0 ? 0.f : *dst) + fin4[r];
             }
           }
@@ -1398,14 +1438,14 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       __syncthreads();
     }
   }
-  for (int o = tid; o < nj * 256; o += NT) {
-    const int jj = o / 256, rem = o % 256;
+  for (int o = tid; o < nj * kFin; o += NT) {
+    const int jj = o / kFin, rem = o % kFin;
     const int r = rem / 64, l = rem % 64;
-    const int m = 4 * (l / 16) + r;
+    const int m = R * (l / 16) + r;
     if (m < p.M) {
       float sum = red[o];
 #pragma unroll
-      for (int g = 1; g < kRedGroups; ++g) sum += red[(size_t)g * p.max_slabs * 256 + o];
+      for (int g = 1; g < kRedGroups; ++g) sum += red[(size_t)g * p.max_slabs * kFin + o];
       const int v = bid + G * jj;
       const int slab = (v % 8) * p.ntr + v / 8;
       const int64_t row = (int64_t)(slab / 8) * kTile + 8 * (l % 16) + (slab % 8);
@@ -1415,10 +1455,10 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   }
 }
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS, int R>
 __global__ __launch_bounds__(NW * 64) void rskinny_kernel(const RSkinnyParams p) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  rskinny_body<NW, S, MB, RES, ACC, G64, RA, RS>(p, (int)blockIdx.x, (int)gridDim.x, lds_raw);
+  rskinny_body<NW, S, MB, RES, ACC, G64, RA, RS, R>(p, (int)blockIdx.x, (int)gridDim.x, lds_raw);
 }
 
 // Several independent problems with the same M in one launch (q, k and v, or gate and up of a decoder
@@ -1431,12 +1471,12 @@ struct RSkinnyBatch {  // laid out as GemvBatch
 };
 static_assert(offsetof(RSkinnyBatch, p) == 64, "the header of a batch is one 64-byte line");
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64 = false, int RA = 0, int RS = 0>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS, int R>
 __global__ __launch_bounds__(NW * 64) void rskinny_batched_kernel(const RSkinnyBatch b) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int i = batch_problem_of(b.first, (int)blockIdx.x);
   const RSkinnyParams p = b.p[i];
-  rskinny_body<NW, S, MB, RES, ACC, G64, RA, RS>(p, (int)blockIdx.x - b.first[i], b.first[i + 1] - b.first[i], lds_raw);
+  rskinny_body<NW, S, MB, RES, ACC, G64, RA, RS, R>(p, (int)blockIdx.x - b.first[i], b.first[i + 1] - b.first[i], lds_raw);
 }
 
 // Staging for a batch: job j (one per distinct activation matrix) owns workgroups [first[j], first[j+1]).
@@ -1456,11 +1496,11 @@ __global__ __launch_bounds__(MB * 16) void stage_rows_batched_kernel(const Stage
   while (j + 1 < b.count && (int)blockIdx.x >= b.first[j + 1]) ++j;
   stage_rows_tile<MB>(b.X[j], b.col_perm[j], b.xblk[j], b.M[j], b.K[j], (int)blockIdx.x - b.first[j]);
 }
-template <int MB>
+template <int MB, int R>
 __global__ __launch_bounds__(MB * 16) void stage_rows_operand_order_batched_kernel(const StageBatch b) {
   int j = 0;
   while (j + 1 < b.count && (int)blockIdx.x >= b.first[j + 1]) ++j;
-  stage_rows_tile_operand_order<MB>(b.X[j], b.col_perm[j], b.xblk[j], b.M[j], b.K[j], (int)blockIdx.x - b.first[j]);
+  stage_rows_tile_operand_order<MB, R>(b.X[j], b.col_perm[j], b.xblk[j], b.M[j], b.K[j], (int)blockIdx.x - b.first[j]);
 }
 
 // ============================================================================================
@@ -1813,13 +1853,14 @@ static RSkinnyParams rskinny_params(const GemmArgs& a, int32_t M, const void* xb
   return p;
 }
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS, int R>
 static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* stream) {
   const sfmp_layout_t* L = a.L;
-  const void* fn = reinterpret_cast<const void*>(&rskinny_kernel<NW, S, MB, RES, ACC, G64, RA, RS>);
+  const void* fn = reinterpret_cast<const void*>(&rskinny_kernel<NW, S, MB, RES, ACC, G64, RA, RS, R>);
   if (int e = allow_full_lds(fn, "hipFuncSetAttribute(skinny)")) return e;
+  constexpr int kStagedRows = RS ? 4 : R;  // (RS: the kernel spreads the rows as it reads them)
   if ((RA || RS) && !RES) {
-    hipLaunchKernelGGL(stage_rows_operand_order_kernel<MB>, dim3((unsigned)(L->K / kTile)), dim3(MB * 16), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL((stage_rows_operand_order_kernel<MB, kStagedRows>), dim3((unsigned)(L->K / kTile)), dim3(MB * 16), 0, (hipStream_t)stream,
                        (const _Float16*)a.X, a.col_perm, (unsigned char*)a.workspace, (int)a.M, (int)L->K);
     if (int e = after_launch("sfmp_gemm activation staging launch")) return e;
   } else if (!RES) {
@@ -1837,25 +1878,36 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   return after_launch("sfmp_gemm skinny launch");
 }
 
-// The compiled configurations (see rskinny_config): X(NW, S, MB, RES, ACC, RA, RS)
+// Activation rows to every four of the operand: as few as the launch's rows (at most M) allow.  The operands that a workgroup
+// gathers itself have all four: a transposing read takes four consecutive rows of a column from an address of 8 bytes.
+static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M) {
+  if (!ra) return mb / 4;
+  return resident ? 4 : M <= 4 ? 1 : M <= 8 ? 2 : 4;
+}
+
+// The compiled configurations (see rskinny_config and rows_to_four): X(NW, S, MB, RES, ACC, RA, RS, R)
 #define SFMP_RSKINNY_CONFIGS(X)                                                                                    \
-  X(16, kSlotsResident, 4, true, 4, 0, 0) X(8, kSlotsResident, 4, true, 16, 0, 0)                                  \
-  X(16, kSlotsMb4, 4, false, 4, 0, 0) X(8, kSlotsMb4, 4, false, 16, 0, 0)                                          \
-  X(16, kSlotsMb8, 8, false, 4, 0, 0) X(16, kSlotsMb8, 8, false, 8, 0, 0) X(8, kSlotsMb8, 8, false, 16, 0, 0)      \
-  X(16, kSlotsMb16Wide, 16, false, 4, 0, 0) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0)                              \
-  X(8, kSlotsMb16, 16, false, 16, 0, 0)                                                                            \
-  X(16, kSlotsStreamedActs, 8, false, 4, 0, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2)                       \
-  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0) X(16, kSlotsRegisterActs, 16, false, 4, 2, 0)                       \
-  X(8, kSlotsRegisterActs, 16, false, 16, 2, 0)                                                                    \
-  X(16, kSlotsRegisterActs, 16, false, 4, 4, 0) X(8, kSlotsRegisterActs, 16, false, 16, 4, 0)
+  X(16, kSlotsResident, 4, true, 4, 0, 0, 1) X(8, kSlotsResident, 4, true, 16, 0, 0, 1)                            \
+  X(16, kSlotsMb4, 4, false, 4, 0, 0, 1) X(8, kSlotsMb4, 4, false, 16, 0, 0, 1)                                    \
+  X(16, kSlotsMb8, 8, false, 4, 0, 0, 2) X(16, kSlotsMb8, 8, false, 8, 0, 0, 2) X(8, kSlotsMb8, 8, false, 16, 0, 0, 2) \
+  X(16, kSlotsMb16Wide, 16, false, 4, 0, 0, 4) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0, 4)                        \
+  X(8, kSlotsMb16, 16, false, 16, 0, 0, 4)                                                                         \
+  X(16, kSlotsStreamedActs, 8, false, 4, 0, 2, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2, 4)                 \
+  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 4)                                                                  \
+  SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 2) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 2)                            \
+  SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 4) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 4)
+#define SFMP_RSKINNY_REGISTER_CONFIGS(X, NW, ACC, RA)                                                              \
+  X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 1) X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 2)          \
+  X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 4)
 
 static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) {
-#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_)                                                 \
-  if (d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
+  const int32_t r = rows_to_four(d.mb, d.resident, d.ra, a.M);
+#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                             \
+  if (r == R_ && d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
     if constexpr (!RES_ || RA_) {                                                             \
-      if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_>(a, d, stream); \
+      if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_, R_>(a, d, stream); \
     }                                                                                         \
-    return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_>(a, d, stream);        \
+    return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(a, d, stream);        \
   }
   SFMP_RSKINNY_CONFIGS(SFMP_X)
 #undef SFMP_X
@@ -1893,7 +1945,7 @@ static BatchStagePlan plan_batch_staging(const GemmArgs* probs, int count, int32
 }
 
 
-template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS>
+template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS, int R>
 static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int32_t M, const int32_t* g,
                                           void* workspace, void* stream) {
   const BatchStagePlan sp = plan_batch_staging(probs, count, MB);
@@ -1940,10 +1992,11 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
   for (int i = count; i <= kGemvMaxBatch; ++i) b.first[i] = first;
   for (int i = count; i < kGemvMaxBatch; ++i) b.p[i] = b.p[0];
   if (lds > 160 * 1024) return SFMP_ERR_SHAPE;
-  const void* fn = reinterpret_cast<const void*>(&rskinny_batched_kernel<NW, S, MB, RES, ACC, G64, RA, RS>);
+  const void* fn = reinterpret_cast<const void*>(&rskinny_batched_kernel<NW, S, MB, RES, ACC, G64, RA, RS, R>);
   if (int e = allow_full_lds(fn, "hipFuncSetAttribute(skinny batched)")) return e;
+  constexpr int kStagedRows = RS ? 4 : R;  // (RS: the kernel spreads the rows as it reads them)
   if ((RA || RS) && !RES) {
-    hipLaunchKernelGGL(stage_rows_operand_order_batched_kernel<MB>, dim3((unsigned)sfirst), dim3(MB * 16), 0, (hipStream_t)stream, sb);
+    hipLaunchKernelGGL((stage_rows_operand_order_batched_kernel<MB, kStagedRows>), dim3((unsigned)sfirst), dim3(MB * 16), 0, (hipStream_t)stream, sb);
     if (int e = after_launch("sfmp_gemm_batched activation staging launch")) return e;
   } else if (!RES) {
     hipLaunchKernelGGL((stage_rows_batched_kernel<MB>), dim3((unsigned)sfirst), dim3(MB * 16), 0, (hipStream_t)stream, sb);
@@ -2015,12 +2068,13 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
   RSkinnyConfig c;
   bool n64 = false;
   if (int e = batch_config(probs, count, M, g, &c, &n64)) return e;
-#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_)                                               \
-  if (c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
+  const int32_t r = rows_to_four(c.mb, c.resident, c.ra, M);
+#define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                           \
+  if (r == R_ && c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
     if constexpr (!RES_ || RA_) {                                                           \
-      if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_>(probs, count, M, g, workspace, stream); \
+      if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \
     }                                                                                       \
-    return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_>(probs, count, M, g, workspace, stream); \
+    return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \
   }
   SFMP_RSKINNY_CONFIGS(SFMP_X)
 #undef SFMP_X

@@ -783,6 +783,35 @@ def test_gemm_batched_streamed_activations_with_different_K(torch_cuda, M, group
         assert np.array_equal(y0.view(np.uint16), y1.view(np.uint16))
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format,over,form", [
+    (512, 256, 2, 128, "fp16", False, (4, 0, 0)), (4096, 384, 3, 256, "bf16", False, (4, 0, 0)), (128, 131200, 4, 128, "fp16", False, (4, 0, 0)),
+    (8320, 256, 1, 64, "bf16", True, (4, 0, 0)), (8320, 384, 3, 128, "fp16", False, (4, 0, 0)), (8320, 4224, 4, 64, "fp16", False, (4, 0, 0)),
+    (512, 256, 3, 64, "fp16", True, (16, 2, 0)), (2176, 512, 4, 64, "bf16", True, (16, 2, 0)), (4096, 256, 7, 128, "fp16", True, (16, 2, 0)),
+    (128, 131200, 2, 64, "fp16", False, (16, 2, 0)), (128, 131200, 6, 128, "bf16", False, (16, 2, 0)),
+    (8192, 256, 3, 128, "fp16", False, (16, 4, 0)), (4224, 512, 4, 64, "bf16", False, (16, 4, 0)), (8192, 384, 5, 128, "fp16", False, (16, 4, 0)),
+    (4224, 256, 8, 64, "fp16", False, (16, 4, 0)), (9216, 256, 5, 128, "fp16", False, (8, 0, 0)), (9216, 512, 6, 64, "bf16", False, (8, 0, 0)),
+    (12288, 4224, 7, 128, "fp16", False, (8, 0, 2))])
+def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, scale_format, over, form):
+    # one activation row to every four of the matrix-instruction operand (M <= 4) or two (M <= 8), in every form that has them:
+    # resident, through the ring slots, in registers (staged: the output lies over the activations, or 8 wavefronts), streamed
+    import paper_2602_01027_amd as S
+    import plan_util
+    from gpu_util import device_problem, make_workspace
+    torch = torch_cuda
+    p = W.make_problem("rows", K, N, M, 9300 + K + M, fractions={2: 0.3, 3: 0.4, 4: 0.3}, outliers=True, group=group,
+                       scale_format=scale_format, block=(1, max(1, group // 128)), fast_codes=N * K > 2 ** 22)
+    dp, cp, rp = device_problem(p)
+    X = torch.full((max(M * K, M * N),), float("nan"), dtype=torch.float16, device="cuda:0")
+    Y = X[:M * N].view(M, N) if over else torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda:0")
+    X = X[:M * K].view(M, K)
+    X.copy_(torch.from_numpy(p.X))
+    if M > 1:
+        d = plan_util.launched_decode_plan(dp.layout, M, X.data_ptr(), Y.data_ptr())
+        assert (d.mb, d.ra, d.rs) == form and not (d.resident and d.ra)
+    S.sfmp_gemm(X, cp, dp.layout, dp.s2, dp.s3, dp.s4, dp.index, dp.scales, dp.zeros, dp.bitmap, rp, Y, make_workspace(dp.layout, M))
+    _check(p, Y.cpu().numpy(), None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+
+
 @pytest.mark.parametrize("K,N,M", [(1024, 40960, 3), (1024, 40960, 8), (4224, 36864, 8), (4224, 36864, 16)])
 def test_small_batch_more_than_2048_slabs(torch_cuda, K, N, M):
     # more than 8 slabs per workgroup on 256 workgroups: the launch takes 512 workgroups (two per CU in turn, 5 slabs
