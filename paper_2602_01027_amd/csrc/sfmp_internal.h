@@ -41,6 +41,12 @@ struct PrefillForm {
   int32_t mi, kg, ksplit;
 };
 PrefillForm choose_prefill_form(int32_t N, int32_t K, int32_t M);
+// ... or, where mi is not zero, whole rounds of prefill_fed_kernel<8, 1>'s workgroups, and the last tile_rows tile rows in
+// workgroups of its <mi, 2> (prefill_mixed_kernel).
+struct PrefillTail {
+  int32_t mi, tile_rows;
+};
+PrefillTail choose_prefill_tail(int32_t N, int32_t K, int32_t M);
 double matrix_core_time_us(int32_t N, int32_t K, int32_t M);  // estimated time of that call
 
 constexpr int32_t kDecodeMaxM = 16;

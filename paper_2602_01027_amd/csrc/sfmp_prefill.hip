@@ -674,28 +674,24 @@ __device__ __forceinline__ void load_lanes_to_lds_16(uint64_t vaddr, uint32_t ld
 // Not better: 32x32x16 instructions (the words of two slabs exchanged between rows of 16 lanes): 2770 cycles where 16x16x32
 // takes 2550, and 290 us instead of 253 on 2048 x 4096 -> 14336, where the clock falls further; the order of every phase fixed
 // by hand (spills at 168 registers).
+constexpr int kFedThreads = 768;
+template <int MI, int KG, bool G64>
+constexpr uint32_t fed_lds_bytes() { return KG * 3 * (16 * MI * (2 / KG) * 128 + (G64 ? 1024 : 512) + 8192); }
+
 template <int MI, int KG, bool G64, bool BF16>
-__global__ __launch_bounds__(768, 3) void prefill_fed_kernel(const PrefillParams p) {
-  constexpr int NB = 3, WS = 3, NS = 2, MG = 2 / KG, BM = 16 * MI * MG, kConsumers = 512, kThreads = 768;
+__device__ __forceinline__ void fed_body(const PrefillParams& p, const Place place, unsigned char* const lds, int32_t* const seq, int2* const counts) {
+  constexpr int NB = 3, WS = 3, NS = 2, MG = 2 / KG, BM = 16 * MI * MG, kConsumers = 512, kThreads = kFedThreads;
   constexpr uint32_t kBuf = BM * 128;              // half a block: BM rows x 64 columns
   constexpr uint32_t kPar = G64 ? 1024 : 512;      // scales and zeros of a tile (twice at group length 64)
   constexpr uint32_t kSlot = kPar + 8192;          // and its packed words
   constexpr uint32_t kLds = KG * (NB * kBuf + WS * kSlot);
   // the end: sums of the K groups on their way to each other, then the rows
   constexpr uint32_t kOut = KG == 2 ? 8 * MI * 1024 : 0;
-  static_assert(kOut + BM * (KG == 2 ? 512 : 256) <= kLds, "the rows fit in the buffers");
-  __shared__ __align__(16) unsigned char lds[kLds];
-  __shared__ int32_t seq[kPrefillMaxTiles];
-  __shared__ int2 counts[kThreads / kWave];
+  static_assert(kOut + BM * (KG == 2 ? 512 : 256) <= kLds && kLds == fed_lds_bytes<MI, KG, G64>(), "the rows fit in the buffers");
 
   const int tid = threadIdx.x;
   const int lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  // M blocks inside tile rows, as in prefill_kernel, in launches of many rounds eight at a time (see launch_fed).  (All that the
-  // place needs in one request: each one that waits for the one before is 0.05 us of a call.)
-  WorkItems items = p.items;
-  asm volatile("" : "+s"(items.whole), "+s"(items.by_ranges), "+s"(items.by_group), "+s"(items.last.by), "+s"(items.last.inverse));
-  const Place place = items.place(blockIdx.x, (uint32_t)p.ntr, (uint32_t)p.ksplit);
   const int ks = place.ks, mt = place.mt, tr = place.tr;
   const int m0 = mt * BM;
   const int ranges = p.ksplit * KG;
@@ -1051,11 +1047,46 @@ __global__ __launch_bounds__(768, 3) void prefill_fed_kernel(const PrefillParams
   }
 }
 
-template <int MI, int KG>
-static void launch_fed(PrefillParams p, int M, bool g64, bool bf16, hipStream_t stream) {
-  constexpr int BM = 16 * MI * (2 / KG);
-  p.n_mtiles = (M + BM - 1) / BM;
-  const unsigned grid = (unsigned)p.n_mtiles * (unsigned)p.ntr * (unsigned)p.ksplit;
+// The arguments that a workgroup needs for its place, in one request: each one that waits for the one before is 0.05 us of a call.
+__device__ __forceinline__ Place place_of(WorkItems items, const uint32_t block, const int32_t ntr, const int32_t ksplit) {
+  asm volatile("" : "+s"(items.whole), "+s"(items.by_ranges), "+s"(items.by_group), "+s"(items.last.by), "+s"(items.last.inverse));
+  return items.place(block, (uint32_t)ntr, (uint32_t)ksplit);
+}
+
+// M blocks inside tile rows, as in prefill_kernel, in launches of many rounds eight at a time (see order_of)
+template <int MI, int KG, bool G64, bool BF16>
+__global__ __launch_bounds__(kFedThreads, 3) void prefill_fed_kernel(const PrefillParams p) {
+  __shared__ __align__(16) unsigned char lds[fed_lds_bytes<MI, KG, G64>()];
+  __shared__ int32_t seq[kPrefillMaxTiles];
+  __shared__ int2 counts[kFedThreads / kWave];
+  fed_body<MI, KG, G64, BF16>(p, place_of(p.items, blockIdx.x, p.ntr, p.ksplit), lds, seq, counts);
+}
+
+// The same in two forms: whole rounds of workgroups of 256 rows on the first tile rows, and smaller workgroups (MI = 4 or 8 in
+// two K groups: 64 or 128 rows) on the last ones, where the large ones would leave part of a round empty.  The tail follows in
+// the same launch: a CU takes its first piece of it when it is done with its last large one.
+struct PrefillMixed {
+  PrefillParams p;      // ntr: tile rows of the large workgroups
+  WorkItems tail;       // order of the others
+  int32_t tail_ntr;
+  uint32_t large;       // number of large workgroups
+};
+template <int MI, bool G64, bool BF16>
+__global__ __launch_bounds__(kFedThreads, 3) void prefill_mixed_kernel(const PrefillMixed m) {
+  constexpr uint32_t kLarge = fed_lds_bytes<8, 1, G64>(), kTail = fed_lds_bytes<MI, 2, G64>();
+  __shared__ __align__(16) unsigned char lds[kLarge > kTail ? kLarge : kTail];
+  __shared__ int32_t seq[kPrefillMaxTiles];
+  __shared__ int2 counts[kFedThreads / kWave];
+  if (blockIdx.x < m.large) {
+    fed_body<8, 1, G64, BF16>(m.p, place_of(m.p.items, blockIdx.x, m.p.ntr, 1), lds, seq, counts);
+  } else {
+    Place place = place_of(m.tail, blockIdx.x - m.large, m.tail_ntr, 1);
+    place.tr += m.p.ntr;
+    fed_body<MI, 2, G64, BF16>(m.p, place, lds, seq, counts);
+  }
+}
+
+static WorkItems order_of(int32_t ntr, int32_t n_mtiles, int32_t ksplit) {
   // Block b runs on XCD b % 8.  With all M blocks inside a tile row every XCD sees every one of them unless their number is a
   // multiple of eight, and from about 20 on a round takes the time of its activations from the memory-side cache (64 KiB per
   // workgroup and tile of 256 rows: 2.15 us a tile where 1.5 are spent multiplying, and prefill_kernel was the faster one by up
@@ -1064,9 +1095,17 @@ static void launch_fed(PrefillParams p, int M, bool g64, bool bf16, hipStream_t 
   // 1774, 5000 x 8192 -> 28672 2445 / 2336 / 2157.
   // Not with one round of workgroups, nor with two and up to 16 blocks, where the weights that come once more for every group cost up to
   // 4 %, nor with a multiple of eight (up to 2 %).
-  const unsigned blocks = (unsigned)p.n_mtiles;
+  const unsigned blocks = (unsigned)n_mtiles, grid = blocks * (unsigned)ntr * (unsigned)ksplit;
   const bool grouped = blocks % kMGroup != 0 && blocks > (grid > 512 ? kMGroup : 2 * kMGroup) && grid > 256;
-  p.items = work_items((unsigned)p.ntr, blocks, (unsigned)p.ksplit, grouped);
+  return work_items((unsigned)ntr, blocks, (unsigned)ksplit, grouped);
+}
+
+template <int MI, int KG>
+static void launch_fed(PrefillParams p, int M, bool g64, bool bf16, hipStream_t stream) {
+  constexpr int BM = 16 * MI * (2 / KG);
+  p.n_mtiles = (M + BM - 1) / BM;
+  const unsigned grid = (unsigned)p.n_mtiles * (unsigned)p.ntr * (unsigned)p.ksplit;
+  p.items = order_of(p.ntr, p.n_mtiles, p.ksplit);
   if (g64 && bf16)
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, true, true>), dim3(grid), dim3(768), 0, stream, p);
   else if (g64)
@@ -1075,6 +1114,28 @@ static void launch_fed(PrefillParams p, int M, bool g64, bool bf16, hipStream_t 
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, false, true>), dim3(grid), dim3(768), 0, stream, p);
   else
     hipLaunchKernelGGL((prefill_fed_kernel<MI, KG, false, false>), dim3(grid), dim3(768), 0, stream, p);
+}
+
+template <int MI>
+static void launch_mixed(PrefillParams p, int M, int tail_rows, bool g64, bool bf16, hipStream_t stream) {
+  PrefillMixed m;
+  p.ntr -= tail_rows;
+  p.n_mtiles = (M + 255) / 256;
+  p.items = order_of(p.ntr, p.n_mtiles, 1);
+  const int32_t tail_blocks = (M + 16 * MI - 1) / (16 * MI);
+  m.tail = order_of(tail_rows, tail_blocks, 1);
+  m.tail_ntr = tail_rows;
+  m.large = (uint32_t)p.n_mtiles * (uint32_t)p.ntr;
+  m.p = p;
+  const dim3 grid(m.large + (unsigned)tail_blocks * (unsigned)tail_rows), threads(kFedThreads);
+  if (g64 && bf16)
+    hipLaunchKernelGGL((prefill_mixed_kernel<MI, true, true>), grid, threads, 0, stream, m);
+  else if (g64)
+    hipLaunchKernelGGL((prefill_mixed_kernel<MI, true, false>), grid, threads, 0, stream, m);
+  else if (bf16)
+    hipLaunchKernelGGL((prefill_mixed_kernel<MI, false, true>), grid, threads, 0, stream, m);
+  else
+    hipLaunchKernelGGL((prefill_mixed_kernel<MI, false, false>), grid, threads, 0, stream, m);
 }
 
 static void launch_plain(PrefillParams p, int M, bool g64, bool bf16, hipStream_t stream) {
@@ -1167,6 +1228,40 @@ PrefillForm choose_prefill_form(int32_t N, int32_t K, int32_t M) {
   return choose_form(N, K, M, &t);
 }
 
+// Time of a call in several rounds of workgroups of one form: a fit to 809 calls (M = 257 ... 2048, K and N from 512 to 28672,
+// more than 256 workgroups of 256 rows), 3.5 and 4.1 % rms where fed_time_us, which has to place every form and K range of the
+// shorter ones too, is 8 % off.
+static double rounds_time_us(int32_t N, int32_t K, int32_t M, const PrefillForm& f) {
+  if (f.mi == 0) return plain_time_us(N, K, M);
+  const int64_t bm = 16 * f.mi * (2 / f.kg), rounds = ((M + bm - 1) / bm * (N / kTile) + 255) / 256;
+  const double steps = (double)((K / kTile + f.kg - 1) / f.kg), mn = (double)M * N * 1e-6, mk = (double)M * K * 1e-6;
+  if (f.kg == 2) return 8.0 + steps * (double)rounds * (0.458 + 0.147 * f.mi) + 1.10 * mk + 2.50 * mn;
+  return 10.1 + steps * (0.402 + 0.119 * f.mi + (double)(rounds - 1) * (0.541 + 0.137 * f.mi)) + 1.84 * mk + 1.29 * mn;
+}
+
+// Whole rounds of 256-row workgroups and a tail of smaller ones (see PrefillMixed).  Up to four whole rounds and 2048 rows, where
+// its time was fitted (1000 calls of each tail, 3.3 and 4.0 % rms), and where that is below 0.945 of the form's own: of these calls
+// 13 % take it, which are 5.8 % faster in the geometric mean (up to 14 %), and 0.3 % are more than 2 % slower (with 0.97 for 0.945 20 %,
+// 4.1 % faster, and 1.5 % slower).  2048 x 4096 -> 14336, three and a half rounds, 255.3 -> 245.7 us (252.4 -> 248.1 on another
+// machine); 1970 x 13184 -> 4736 302 -> 265; 1442 x 6912 -> 12928 293 -> 270; 510 x 5504 -> 19840 134 -> 118.
+PrefillTail choose_prefill_tail(int32_t N, int32_t K, int32_t M) {
+  PrefillTail best = {0, 0};
+  const int64_t ntr = N / kTile, ntc = K / kTile, blocks = (M + 255) / 256, full = blocks * ntr / 256;
+  if (M <= 256 || M > 2048 || full == 0 || full > 4 || blocks * ntr % 256 == 0 || ntc < 4) return best;
+  // the last tile rows, those that do not fit in the whole rounds; CUs without a workgroup in the last whole round take pieces then
+  const int64_t rows = ntr - 256 * full / blocks, idle = 256 * full - blocks * (ntr - rows), steps = (ntc + 1) / 2;
+  const double mn = (double)M * N * 1e-6, mk = (double)M * K * 1e-6;
+  double least = 0.945 * rounds_time_us(N, K, M, choose_prefill_form(N, K, M));
+  for (int32_t mi = 4; mi <= 8; mi += 4) {
+    const int64_t early = idle * (mi == 4 ? 2 : 1), pieces = (M + 16 * mi - 1) / (16 * mi) * rows;
+    const double rounds = (double)(pieces > early ? (pieces - early + 255) / 256 : 0);
+    const double t = mi == 4 ? 10.55 + (double)ntc * (1.436 + 1.669 * (double)(full - 1)) + rounds * (1.125 * (double)steps + 1.82) + 1.51 * mk + 1.33 * mn
+                             : 10.19 + (double)ntc * (1.249 + 1.655 * (double)(full - 1)) + rounds * (1.812 * (double)steps + 3.55) + 1.95 * mk + 1.33 * mn;
+    if (t < least) least = t, best = PrefillTail{mi, (int32_t)rows};
+  }
+  return best;
+}
+
 double matrix_core_time_us(int32_t N, int32_t K, int32_t M) {
   double t;
   choose_form(N, K, M, &t);
@@ -1243,7 +1338,10 @@ int launch_prefill(const GemmArgs& a, void* stream) {
   p.partial = form.ksplit > 1 ? (float*)((char*)a.workspace + xperm_bytes) : nullptr;
   const bool g64 = L->group == 64, bf16 = L->scale_format == SFMP_SCALE_BF16;
   const hipStream_t s = (hipStream_t)stream;
-  switch (8 * form.kg + form.mi) {
+  const PrefillTail tail = choose_prefill_tail(L->N, L->K, a.M);
+  switch (tail.mi ? tail.mi - 8 : 8 * form.kg + form.mi) {
+    case -4: launch_mixed<4>(p, a.M, tail.tile_rows, g64, bf16, s); break;
+    case 0: launch_mixed<8>(p, a.M, tail.tile_rows, g64, bf16, s); break;
     case 8: launch_plain(p, a.M, g64, bf16, s); break;
     case 12: launch_fed<4, 1>(p, a.M, g64, bf16, s); break;
     case 13: launch_fed<5, 1>(p, a.M, g64, bf16, s); break;

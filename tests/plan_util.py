@@ -93,3 +93,13 @@ def runs_in_chunks(layout, M, X, Y):
     f = S.load_library()._ZN4sfmp14runs_in_chunksERK8GemmArgs
     f.restype = C.c_bool
     return f(_gemm_args([layout], M, [X], [Y]))
+
+
+class _PrefillTail(C.Structure):
+    _fields_ = [("mi", C.c_int32), ("tile_rows", C.c_int32)]
+
+
+def launched_tail(N, K, M):
+    """(16-row blocks of a wavefront, tile rows) of the tail of a matrix-core call in two forms; (0, 0): one form."""
+    t = _call("_ZN4sfmp19choose_prefill_tailEiii", _PrefillTail, N, K, M)
+    return t.mi, t.tile_rows

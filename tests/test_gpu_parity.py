@@ -259,6 +259,27 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format,row_perm,tail", [
+    (640, 13184, 2047, 128, "fp16", True, (4, 7)), (640, 13184, 2047, 128, "bf16", True, (4, 7)), (640, 13184, 2000, 64, "fp16", False, (4, 7)),
+    (640, 13184, 2000, 64, "bf16", True, (4, 7)), (640, 13696, 2047, 128, "fp16", False, (8, 11)), (640, 13696, 2000, 128, "bf16", True, (8, 11)),
+    (640, 13696, 2047, 64, "fp16", True, (8, 11)), (640, 13696, 2000, 64, "bf16", True, (8, 11)), (512, 26240, 1034, 128, "fp16", True, (4, 1)),
+    (640, 26240, 1000, 128, "fp16", True, (4, 13)), (1152, 27264, 1000, 128, "fp16", True, (8, 21)), (512, 23936, 405, 256, "bf16", True, (8, 59))])
+def test_matrix_core_call_in_two_forms(torch_cuda, K, N, M, group, scale_format, row_perm, tail):
+    # whole rounds of 256-row workgroups and a tail of 64- or 128-row ones: one to 59 tile rows in the tail, rounds that are whole to the last
+    # CU and not, a last block of 10 rows, K groups of four, five and unequal lengths
+    import plan_util
+    from gpu_util import run_gemm
+    assert plan_util.launched_tail(N, K, M) == tail
+    p = W.make_problem("tail", K, N, M, 9800 + K + M, fractions={2: 0.3, 3: 0.3, 4: 0.4}, outliers=True, group=group, scale_format=scale_format,
+                       block=(1, max(1, group // 128)), use_row_perm=row_perm, fast_codes=True)
+    first = N - 128 * tail[1]  # first feature of the tail, in reordered row order
+    at = np.unique([0, first - 1, first, first + 127, N - 1, *np.random.default_rng(M).choice(N, 250, replace=False),
+                    *np.random.default_rng(K).choice(np.arange(first, N), 60, replace=False)])
+    y1 = run_gemm(p)
+    _check(p, y1, at)
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
+
+
 @pytest.mark.parametrize("K,N,M,group,row_perm,form", [
     (256, 16512, 2100, 128, True, (8, 1, 1)), (640, 8320, 3001, 64, False, (7, 1, 1)), (384, 2304, 5000, 128, True, (6, 1, 1)),
     (896, 2048, 5800, 256, True, (6, 1, 1)), (256, 1280, 9000, 128, True, (6, 1, 1))])
