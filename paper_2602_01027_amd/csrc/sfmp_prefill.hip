@@ -35,67 +35,58 @@ namespace sfmp {
 // -------------------------------------------------------------------------------------------
 // column gather / column scatter, one row of fp16 through LDS per workgroup
 // -------------------------------------------------------------------------------------------
-// R rows per workgroup: the permutation entries of a unit of 8 columns are loaded once and serve all R rows (they
-// are twice the bytes of the data they steer), and R rows of loads are in flight per workgroup.
-template <int R>
+// A row per workgroup, as many threads as give each the same number of units of 8 columns (see pass_threads).  Several rows per
+// workgroup, which share the permutation entries, and 1024 threads whatever K, were 0.3 to 1.4 us longer (this pass alone: 777 x 4096
+// 3.7 -> 3.5 us, 2048 x 4096 8.5 -> 7.1, 2048 x 28672 53.9 -> 51.9).  Stored past the caches it takes 35 of those 52 us, but the product,
+// which reads it next, becomes as much longer (64 x 4096 -> 14336 even 4 % in all).
 __global__ __launch_bounds__(1024) void gather_cols_kernel(const _Float16* __restrict__ X,
                                                            const int32_t* __restrict__ col_perm,
-                                                           _Float16* __restrict__ Xp, int M, int K) {
+                                                           _Float16* __restrict__ Xp, int K) {
   // Output layout: blocks of 128 rows x 128 columns, each block contiguous (32 KiB), block (mt, tc) at
   // (mt * K/128 + tc) * 16384 elements: the GEMM then reads one contiguous block per step instead of 128
   // row pieces K*2 bytes apart.
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  _Float16* rows = reinterpret_cast<_Float16*>(lds_raw);  // [R][K]
-  const int64_t m0 = (int64_t)blockIdx.x * R;
-  const int units = K / 8;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (m0 + r < M) {
-      const uint4* src = reinterpret_cast<const uint4*>(X + (m0 + r) * K);
-      for (int i = threadIdx.x; i < units; i += 1024) reinterpret_cast<uint4*>(rows + (size_t)r * K)[i] = src[i];
-    }
-  }
+  const _Float16* row = reinterpret_cast<const _Float16*>(lds_raw);
+  const int64_t m = blockIdx.x;
+  const int units = K / 8, threads = (int)blockDim.x;
+  const uint4* src = reinterpret_cast<const uint4*>(X + m * K);
+  for (int i = threadIdx.x; i < units; i += threads) reinterpret_cast<uint4*>(lds_raw)[i] = src[i];
   __syncthreads();
   const int64_t ntc = K / kTile;
-  for (int i = threadIdx.x; i < units; i += 1024) {
+  _Float16* const dst = Xp + (m / kTile) * ntc * (kTile * kTile) + (m % kTile) * kTile;
+  for (int i = threadIdx.x; i < units; i += threads) {
     int4 c0 = int4{8 * i, 8 * i + 1, 8 * i + 2, 8 * i + 3}, c1 = int4{8 * i + 4, 8 * i + 5, 8 * i + 6, 8 * i + 7};
     if (col_perm) {  // (no permutation: the pass only changes the layout)
       c0 = reinterpret_cast<const int4*>(col_perm)[2 * i];
       c1 = reinterpret_cast<const int4*>(col_perm)[2 * i + 1];
     }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t m = m0 + r;
-      if (m < M) {
-        const _Float16* row = rows + (size_t)r * K;
-        union {
-          _Float16 h[8];
-          uint4 u;
-        } v;
-        v.h[0] = row[c0.x];
-        v.h[1] = row[c0.y];
-        v.h[2] = row[c0.z];
-        v.h[3] = row[c0.w];
-        v.h[4] = row[c1.x];
-        v.h[5] = row[c1.y];
-        v.h[6] = row[c1.z];
-        v.h[7] = row[c1.w];
-        _Float16* dst = Xp + (m / kTile) * ntc * (kTile * kTile) + (m % kTile) * kTile;
-        *reinterpret_cast<uint4*>(dst + (int64_t)(i / 16) * (kTile * kTile) + (i % 16) * 8) = v.u;
-      }
-    }
+    union {
+      _Float16 h[8];
+      uint4 u;
+    } v;
+    v.h[0] = row[c0.x];
+    v.h[1] = row[c0.y];
+    v.h[2] = row[c0.z];
+    v.h[3] = row[c0.w];
+    v.h[4] = row[c1.x];
+    v.h[5] = row[c1.y];
+    v.h[6] = row[c1.z];
+    v.h[7] = row[c1.w];
+    *reinterpret_cast<uint4*>(dst + (int64_t)(i / 16) * (kTile * kTile) + (i % 16) * 8) = v.u;
   }
 }
 
-// Y[m, row_perm[i]] = Yt[m, i]
-__global__ __launch_bounds__(256) void scatter_cols_kernel(const _Float16* __restrict__ Yt,
+// Y[m, row_perm[i]] = Yt[m, i].  The result is stored past the caches: nothing of this call reads it, and dirty lines are
+// written back when the kernel ends (2048 x 4096 -> 14336, the whole call 242 -> 237 us; with threads by N besides, 140 x 2048 ->
+// 20480 28.1 -> 26.4 us).
+__global__ __launch_bounds__(1024) void scatter_cols_kernel(const _Float16* __restrict__ Yt,
                                                            const int32_t* __restrict__ row_perm,
                                                            _Float16* __restrict__ Y, int N) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   _Float16* row = reinterpret_cast<_Float16*>(lds_raw);
   const int64_t m = blockIdx.x;
   const uint4* src = reinterpret_cast<const uint4*>(Yt + m * N);
-  for (int i = threadIdx.x; i < N / 8; i += 256) {
+  for (int i = threadIdx.x; i < N / 8; i += (int)blockDim.x) {
     const int4 c0 = reinterpret_cast<const int4*>(row_perm)[2 * i];
     const int4 c1 = reinterpret_cast<const int4*>(row_perm)[2 * i + 1];
     union {
@@ -113,8 +104,9 @@ __global__ __launch_bounds__(256) void scatter_cols_kernel(const _Float16* __res
     row[c1.w] = v.h[7];
   }
   __syncthreads();
-  uint4* dst = reinterpret_cast<uint4*>(Y + m * N);
-  for (int i = threadIdx.x; i < N / 8; i += 256) dst[i] = reinterpret_cast<const uint4*>(row)[i];
+  u32x4* dst = reinterpret_cast<u32x4*>(Y + m * N);
+  for (int i = threadIdx.x; i < N / 8; i += (int)blockDim.x)
+    __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(row)[i], dst + i);
 }
 
 // Y[m, row_perm[i]] (or Y[m, i]) = fp16( sum over the K ranges, in range order, of partial[ks][m][i] ): the second
@@ -1277,6 +1269,13 @@ static int check_launch(const char* what) {
   return SFMP_OK;
 }
 
+// Threads of a workgroup that permutes a row of `columns`: up to 1024, the units of 8 columns evenly among them.  (The scatter
+// pass takes 256 up to 8192 columns: 2000 x 4096 -> 4096 73.3 us with 256 and 74.1 with 512.)
+static unsigned pass_threads(int32_t columns) {
+  const int32_t units = columns / 8, each = (units + 1023) / 1024;
+  return (unsigned)(((units + each - 1) / each + kWave - 1) / kWave * kWave);
+}
+
 int launch_prefill(const GemmArgs& a, void* stream) {
   const sfmp_layout_t* L = a.L;
   const int64_t xperm_bytes = prefill_workspace(L->N, L->K, a.M).xperm_bytes;
@@ -1293,24 +1292,16 @@ int launch_prefill(const GemmArgs& a, void* stream) {
   } else if (a.row_perm) {
     if (int e = allow_full_lds(reinterpret_cast<const void*>(&scatter_cols_kernel), "hipFuncSetAttribute(scatter)")) return e;
   }
-  // activations -> workspace: column permutation applied (if any), 128x128 blocks each contiguous.  Rows per
-  // workgroup: as many as fit in 128 KiB of LDS (8 at most), fewer while that would leave compute units without a
-  // workgroup.
+  // activations -> workspace: column permutation applied (if any), 128x128 blocks each contiguous
   _Float16* Xp = (_Float16*)a.workspace;
   {
-    int R = L->K <= 8192 ? 8 : L->K <= 16384 ? 4 : L->K <= 32768 ? 2 : 1;
-    while (R > 1 && (a.M + R - 1) / R < 256) R /= 2;
-    const void* fn = R == 8   ? reinterpret_cast<const void*>(&gather_cols_kernel<8>)
-                     : R == 4 ? reinterpret_cast<const void*>(&gather_cols_kernel<4>)
-                     : R == 2 ? reinterpret_cast<const void*>(&gather_cols_kernel<2>)
-                              : reinterpret_cast<const void*>(&gather_cols_kernel<1>);
+    const void* fn = reinterpret_cast<const void*>(&gather_cols_kernel);
     if (int e = allow_full_lds(fn, "hipFuncSetAttribute(gather)")) return e;
     const _Float16* Xa = (const _Float16*)a.X;
     const int32_t* cp = a.col_perm;
-    int Ma = a.M, Ka = L->K;
-    void* kargs[] = {&Xa, &cp, &Xp, &Ma, &Ka};
-    hipError_t e = hipLaunchKernel(fn, dim3((unsigned)((a.M + R - 1) / R)), dim3(1024), kargs, (size_t)R * L->K * 2,
-                                   (hipStream_t)stream);
+    int Ka = L->K;
+    void* kargs[] = {&Xa, &cp, &Xp, &Ka};
+    hipError_t e = hipLaunchKernel(fn, dim3((unsigned)a.M), dim3(pass_threads(L->K)), kargs, (size_t)L->K * 2, (hipStream_t)stream);
     if (e != hipSuccess) {
       note_hip_error("sfmp_gemm activation staging launch", hipGetErrorString(e));
       return SFMP_ERR_HIP;
@@ -1369,7 +1360,7 @@ int launch_prefill(const GemmArgs& a, void* stream) {
     }
     if (int e = check_launch("sfmp_gemm split-K reduction launch")) return e;
   } else if (a.row_perm) {
-    hipLaunchKernelGGL(scatter_cols_kernel, dim3((unsigned)a.M), dim3(256), (size_t)L->N * 2, (hipStream_t)stream,
+    hipLaunchKernelGGL(scatter_cols_kernel, dim3((unsigned)a.M), dim3(L->N <= 8192 ? 256 : pass_threads(L->N)), (size_t)L->N * 2, (hipStream_t)stream,
                        (const _Float16*)Yt, a.row_perm, (_Float16*)a.Y, (int)L->N);
     if (int e = check_launch("sfmp_gemm row scatter launch")) return e;
   }

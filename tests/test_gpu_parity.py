@@ -259,6 +259,17 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))  # fixed order of the sums
 
 
+@pytest.mark.parametrize("K,N,M,perms", [(8192, 8192, 140, True), (8320, 8320, 129, True), (8320, 256, 150, False), (128, 16512, 300, True),
+                                         (16512, 128, 140, True), (57344, 128, 129, True), (640, 81920, 130, True)])
+def test_permutation_passes_of_a_prompt(torch_cuda, K, N, M, perms):
+    # a row through LDS: one unit of 8 columns per thread and two to ten, the last of them not there for every thread
+    from gpu_util import run_gemm
+    import plan_util
+    p = W.make_problem("passes", K, N, M, 9400 + K + N, fractions={2: 0.3, 3: 0.3, 4: 0.4}, use_col_perm=perms, use_row_perm=perms, fast_codes=True)
+    assert not plan_util.chunked(N, K, M) and not plan_util.chunks_without_staging(N, K, M)
+    _check(p, run_gemm(p), None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+
+
 @pytest.mark.parametrize("K,N,M,group,scale_format,row_perm,tail", [
     (640, 13184, 2047, 128, "fp16", True, (4, 7)), (640, 13184, 2047, 128, "bf16", True, (4, 7)), (640, 13184, 2000, 64, "fp16", False, (4, 7)),
     (640, 13184, 2000, 64, "bf16", True, (4, 7)), (640, 13696, 2047, 128, "fp16", False, (8, 11)), (640, 13696, 2000, 128, "bf16", True, (8, 11)),
