@@ -805,6 +805,7 @@ template <int MB>
 constexpr int rskinny_slot_bytes() { return kSlotBytes + MB * 256; }
 // resident variant: bytes of the raw copy of the activations in LDS
 __host__ __device__ inline size_t rskinny_raw_bytes(int32_t M, int32_t K) { return ((size_t)M * K * 2 + 15) & ~(size_t)15; }
+constexpr int kInPlaceQuads = 2;  // permuted in place: groups of four columns per thread (K <= 8192)
 
 // RES (resident): when MB x K fp16 fit in LDS beside the rings, every workgroup stages the activations itself,
 // exactly as the GEMV kernel does (raw copy into the idle rings, permute inside LDS) into the same per-tile-column
@@ -814,6 +815,7 @@ __host__ __device__ inline size_t rskinny_raw_bytes(int32_t M, int32_t K) { retu
 // 16, which is what covers the latencies of its loop.  The forms with MB = 4 and with RA hold no sums in registers
 // (they write them to LDS as a slab finishes); there ACC only tells the variants for 16 and for 8 wavefronts apart.
 // G64: group length 64 (two parameter pairs per row and tile column; never together with RES without RA).
+// RES with S = 2: the activations are permuted in place, for which up to 8192 columns fit.
 // RES with RA = 2: the operands are gathered by every workgroup itself, through a transposed copy of the activations in LDS that
 // lies where the second ring slots and the finished sums come later; no staging launch.
 // RA (activations in registers; 0, 2 or 4): when a wavefront has at most RA tile columns (K <= 128 RA NW) it loads
@@ -859,15 +861,16 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   // registers: with the activations in registers and with up to four activation rows
   constexpr bool DS = RA || RS || MB == 4;
   constexpr int kFin = 64 * R;  // sums of a slab
+  constexpr bool kInPlace = RESL && S == 2;  // resident, permuted in place (no room beside them for the raw rows)
   // LDS: red [NW/4][max_slabs][R][64] f32 (in the room of R = 4) | (Xs [ntc][MB][256 B] | SxL | raw activations [M][K] fp16) |
   //      rings [NW][S][kSlot];  with DS: fin [max_slabs][NW][64][R] f32 | ...
   float* red = reinterpret_cast<float*>(lds_raw);
   unsigned char* Xs = lds_raw + (DS ? (size_t)p.max_slabs * NW * kFin * 4 : (size_t)p.max_slabs * 1024 * kRedGroups);
   // (resident) SxL [ntc][4] f32: the sums of the activations of the four rows over a tile column, one for every lane group
-  // of the product (64 bytes a tile column are set aside, as for a product with all 16 rows)
+  // of the product (64 bytes a tile column are set aside: with 16, the rings 48 bytes a tile column earlier, calls took 1 to 1.5 % longer)
   float* SxL = reinterpret_cast<float*>(Xs + (RESL ? (size_t)p.ntc * (MB * 256) : (size_t)0));
-  unsigned char* raw_region = reinterpret_cast<unsigned char*>(SxL) + (RESL ? (size_t)p.ntc * 64 : (size_t)0);
-  unsigned char* rings = raw_region + (RESL ? rskinny_raw_bytes(p.M, p.K) : (size_t)0);
+  unsigned char* raw_region = reinterpret_cast<unsigned char*>(SxL) + (RESL && !kInPlace ? (size_t)p.ntc * 64 : (size_t)0);
+  unsigned char* rings = raw_region + (RESL && !kInPlace ? rskinny_raw_bytes(p.M, p.K) : (size_t)0);
 
   const int tid = threadIdx.x;
   const int lane = tid % kWave;
@@ -938,7 +941,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   };
 
   int issued_early = 0;  // items of the first batch that are already on their way when the loop below starts
-  if constexpr (RESL) {
+  if constexpr (RESL && !kInPlace) {
     // Start of the resident form, ordered as in the GEMV kernel: everything that depends on the arguments alone is
     // requested at once (raw copies of the M rows into their own LDS region, 1 KiB per wavefront and copy; the
     // column permutation into registers; the tile descriptors of the first batch of items), the first items of
@@ -1008,6 +1011,70 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       }
     }
     barrier_lds_only();  // Xs and SxL are complete
+  } else if constexpr (kInPlace) {
+    // The same start without room for the raw rows: everything that depends on the arguments alone is requested at once (four
+    // columns of all rows per thread and pass, their permutation entries, the tile descriptors of the first batch of items),
+    // and the first items of every ring go out as soon as that is there.  The activations are permuted through LDS meanwhile,
+    // in the place where they stay: stored with the four rows of a column together, gathered by columns (8 bytes give all rows)
+    // into registers, and, when every wavefront has done so, stored row by row.  (Their sums are taken per item: no slab count
+    // for which they pay for a pass of their own.)  Bound by L2 -> CU (64 KiB of activations and 32 KiB of entries at K = 8192, about
+    // 1500 cycles) and four barriers; with K <= 4096 the raw copies straight into LDS are 0.1 to 0.6 us shorter.
+    constexpr int Q = kInPlaceQuads;
+    const int quads = p.K / 4;
+    u32x2 x[Q][4];
+    int4 c[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (q * NT < quads) {  // uniform
+        const int i = min(tid + q * NT, quads - 1);
+#pragma unroll
+        for (int m = 0; m < 4; ++m)  // (rows past the last: the last again; their products are not stored)
+          x[q][m] = *reinterpret_cast<const u32x2*>(p.X + (size_t)min(m, p.M - 1) * p.K + 4 * i);
+        c[q] = p.col_perm ? reinterpret_cast<const int4*>(p.col_perm)[i] : int4{4 * i, 4 * i + 1, 4 * i + 2, 4 * i + 3};
+      }
+    }
+    const int Eb0 = min(64, E);
+    describe(0, Eb0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // one trip to memory for all of the above
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (q * NT < quads)
+        asm volatile("" : "+v"(x[q][0]), "+v"(x[q][1]), "+v"(x[q][2]), "+v"(x[q][3]), "+v"(c[q].x), "+v"(c[q].y), "+v"(c[q].z), "+v"(c[q].w));
+    asm volatile("" : "+v"(it_wlo), "+v"(it_whi), "+v"(it_xhi), "+v"(it_soff), "+v"(it_misc));
+    issued_early = min(2, Eb0);
+    for (int e = 0; e < issued_early; ++e) issue_item(e, e);
+    auto lower = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return __builtin_amdgcn_perm(b, a, 0x05040100u); };
+    auto upper = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return __builtin_amdgcn_perm(b, a, 0x07060302u); };
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (tid + q * NT < quads) {
+        u32x4* const to = reinterpret_cast<u32x4*>(Xs) + 2 * (tid + q * NT);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          to[h] = u32x4{lower(x[q][0][h], x[q][1][h]), lower(x[q][2][h], x[q][3][h]), upper(x[q][0][h], x[q][1][h]), upper(x[q][2][h], x[q][3][h])};
+      }
+    barrier_lds_only();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (q * NT < quads) {
+        const u32x2* const columns = reinterpret_cast<const u32x2*>(Xs);
+        x[q][0] = columns[c[q].x], x[q][1] = columns[c[q].y], x[q][2] = columns[c[q].z], x[q][3] = columns[c[q].w];
+      }
+    barrier_lds_only();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (tid + q * NT < quads) {
+        const int i = tid + q * NT, unit = i / 2 % 16;
+        unsigned char* const to = Xs + (size_t)(i / 32) * 1024 + i % 2 * 8;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const int h = m / 2;
+          *reinterpret_cast<u32x2*>(to + m * 256 + (unit ^ m) * 16) =
+              m % 2 ? u32x2{upper(x[q][0][h], x[q][1][h]), upper(x[q][2][h], x[q][3][h])}
+                    : u32x2{lower(x[q][0][h], x[q][1][h]), lower(x[q][2][h], x[q][3][h])};
+        }
+      }
+    barrier_lds_only();  // Xs is complete
   }
 
   half8 ones;
@@ -1209,7 +1276,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     sums_t sx;
     if constexpr (RA == 2 || RS) {
       sx = sx_known;
-    } else if constexpr (RESL) {
+    } else if constexpr (RESL && !kInPlace) {
       sx = SxL[(misc & 0xFFFF) * 4 + kb];
     } else {
       floatx4 all = {0.f, 0.f, 0.f, 0.f};
@@ -1552,6 +1619,7 @@ struct RSkinnyConfig {
   int32_t ra;  // activations in registers (at most 2 or 4 tile columns per wavefront; 0: not): 16-row operand-order staging, small slots
 };
 static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
+constexpr int kSlotsInPlace = 2;  // (and that number of slots tells the two resident forms apart)
 // LDS of the ring-skinny kernel: reduction buffers, (resident: activations in operand layout, their tile-column sums,
 // their raw copy), rings
 static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int32_t M, int32_t K) {
@@ -1563,6 +1631,7 @@ static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int3
   }
   if (c.ra || c.rs)  // fin | rings
     return (int64_t)max_slabs * 1024 * c.nw + (int64_t)c.nw * c.slots * (c.rs ? c.rs : 1) * kSlotBytes64;
+  if (c.resident && c.slots == kSlotsInPlace) return red + (int64_t)c.mb * K * 2 + (int64_t)c.nw * c.slots * kSlotBytes64;
   return c.resident ? red + (int64_t)c.mb * K * 2 + (int64_t)(K / kTile) * 64 + (int64_t)rskinny_raw_bytes(M, K) +
                           (int64_t)c.nw * c.slots * kSlotBytes64
                     : red + (int64_t)c.nw * c.slots * (kSlotBytes64 + c.mb * 256);
@@ -1599,6 +1668,16 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int
     c.resident = true;
     c.slots = kSlotsResident;
     if (rskinny_lds_bytes(c, max_slabs, M, K) > 160 * 1024) c.resident = false;
+  }
+  // Up to four rows of a longer K, permuted in place (two slots, no raw copy) instead of in a launch in front: staged / in place,
+  // back-to-back calls, M = 4 4224 -> 4096 7.7 / 6.1 us, 8192 -> 8192 11.9 / 10.1, 8192 -> 28672 23.2 / 21.6, 8192 -> 1024 8.9 / 7.5, 8192 ->
+  // 57344 (two rounds of workgroups) 51.7 / 46.9, q|k|v of a 70B-shaped layer 15.6 / 12.5; M = 2 8192 -> 8192 11.8 / 10.0.  Not beyond
+  // K = 8192, where the start is the longer one (M = 4 8320 -> 8192 10.5 / 10.9, 14336 -> 4096 9.9 / 11.4).
+  if (!c.resident && !g64 && c.mb == 4 && wide && !overwrites && K > 4096 && K / 4 <= kInPlaceQuads * c.nw * 64) {
+    c.resident = true;
+    c.slots = kSlotsInPlace;
+    if (rskinny_lds_bytes(c, max_slabs, M, K) <= 160 * 1024) return c;
+    c.resident = false;
   }
   if (!c.resident && K / kTile <= 4 * c.nw) {
     // at most two or four tile columns per wavefront: their operands stay in registers (any M up to 16 as 16 rows)
@@ -1680,7 +1759,8 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool
   d.gemv = false;
   d.grid = grid;
   d.max_slabs = (nslab + grid - 1) / grid;
-  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, (grid + kGemvMaxGrid - 1) / kGemvMaxGrid, group == 64, overwrites);
+  const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
+  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, rounds, group == 64, overwrites);
   d.mb = c.mb;
   d.nw = c.nw;
   d.acc = c.acc;
@@ -1689,13 +1769,14 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool
   d.rs = c.rs;
   d.slots = c.slots;
   d.lds_bytes = (int32_t)rskinny_lds_bytes(c, d.max_slabs, M, K);
-  d.workspace_bytes = round_up_256((int64_t)ntc * c.mb * 256);
+  // (whatever the buffers: the form that stages its activations)
+  d.workspace_bytes = round_up_256((int64_t)ntc * rskinny_config(M, K, d.max_slabs, rounds, group == 64, true).mb * 256);
   return d;
 }
 
 DecodePlan decode_plan_of(const GemmArgs& a) {
   const DecodePlan d = make_decode_plan(a.L->N, a.L->K, a.M, a.L->group, false);
-  const bool gathers = !d.gemv && d.resident && d.ra;
+  const bool gathers = !d.gemv && d.resident && (d.ra || d.slots == kSlotsInPlace);
   return gathers && overwrites_activations(&a, 1) ? make_decode_plan(a.L->N, a.L->K, a.M, a.L->group, true) : d;
 }
 
@@ -1888,6 +1969,7 @@ static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M) {
 // The compiled configurations (see rskinny_config and rows_to_four): X(NW, S, MB, RES, ACC, RA, RS, R)
 #define SFMP_RSKINNY_CONFIGS(X)                                                                                    \
   X(16, kSlotsResident, 4, true, 4, 0, 0, 1) X(8, kSlotsResident, 4, true, 16, 0, 0, 1)                            \
+  X(16, kSlotsInPlace, 4, true, 4, 0, 0, 1)                                                                        \
   X(16, kSlotsMb4, 4, false, 4, 0, 0, 1) X(8, kSlotsMb4, 4, false, 16, 0, 0, 1)                                    \
   X(16, kSlotsMb8, 8, false, 4, 0, 0, 2) X(16, kSlotsMb8, 8, false, 8, 0, 0, 2) X(8, kSlotsMb8, 8, false, 16, 0, 0, 2) \
   X(16, kSlotsMb16Wide, 16, false, 4, 0, 0, 4) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0, 4)                        \
@@ -2013,7 +2095,7 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
 
 // One configuration for a whole batched launch: the one that fits the problem with the most slabs per workgroup and
 // the largest K (resident or register activations only when every problem of the batch fits them).
-int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinnyConfig* c, bool* g64) {
+static int batch_config_for(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinnyConfig* c, bool* g64, bool overwrites) {
   int32_t max_slabs = 0, max_k = 0;
   int n64 = 0;
   // one workgroup per CU, or (rounds) two to four per CU one after the other while that brings a workgroup's share
@@ -2044,9 +2126,13 @@ int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinn
   int32_t grid = 0;
   for (int i = 0; i < count; ++i) grid += g[i];
   const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
-  *c = rskinny_config(M, max_k, max_slabs, rounds, n64 != 0, false);
-  if (c->resident && c->ra && overwrites_activations(probs, count)) *c = rskinny_config(M, max_k, max_slabs, rounds, n64 != 0, true);
+  *c = rskinny_config(M, max_k, max_slabs, rounds, n64 != 0, overwrites);
   return SFMP_OK;
+}
+int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinnyConfig* c, bool* g64) {
+  if (int e = batch_config_for(probs, count, M, g, c, g64, false)) return e;
+  const bool gathers = c->resident && (c->ra || c->slots == kSlotsInPlace);
+  return gathers && overwrites_activations(probs, count) ? batch_config_for(probs, count, M, g, c, g64, true) : SFMP_OK;
 }
 
 int64_t batched_workspace_bytes(const GemmArgs* probs, int count, int32_t M) {
@@ -2054,8 +2140,9 @@ int64_t batched_workspace_bytes(const GemmArgs* probs, int count, int32_t M) {
   int32_t g[kGemvMaxBatch];
   RSkinnyConfig c;
   bool g64 = false;
-  // a batch that the launch will refuse anyway gets the size of the largest staging layout
-  const int32_t mb = batch_config(probs, count, M, g, &c, &g64) == SFMP_OK ? c.mb : 16;
+  // the form that stages its activations, whatever the buffers; a batch that the launch will refuse anyway gets the size of
+  // the largest staging layout
+  const int32_t mb = batch_config_for(probs, count, M, g, &c, &g64, true) == SFMP_OK ? c.mb : 16;
   return plan_batch_staging(probs, count, mb).bytes;
 }
 

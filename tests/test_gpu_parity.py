@@ -817,10 +817,10 @@ def test_gemm_batched_streamed_activations_with_different_K(torch_cuda, M, group
 
 @pytest.mark.parametrize("K,N,M,group,scale_format,over,form", [
     (512, 256, 2, 128, "fp16", False, (4, 0, 0)), (4096, 384, 3, 256, "bf16", False, (4, 0, 0)), (128, 131200, 4, 128, "fp16", False, (4, 0, 0)),
-    (8320, 256, 1, 64, "bf16", True, (4, 0, 0)), (8320, 384, 3, 128, "fp16", False, (4, 0, 0)), (8320, 4224, 4, 64, "fp16", False, (4, 0, 0)),
+    (8320, 256, 1, 64, "bf16", True, (4, 0, 0)), (8320, 384, 3, 128, "fp16", True, (4, 0, 0)), (8320, 4224, 4, 64, "fp16", False, (4, 0, 0)),
     (512, 256, 3, 64, "fp16", True, (16, 2, 0)), (2176, 512, 4, 64, "bf16", True, (16, 2, 0)), (4096, 256, 7, 128, "fp16", True, (16, 2, 0)),
     (128, 131200, 2, 64, "fp16", False, (16, 2, 0)), (128, 131200, 6, 128, "bf16", False, (16, 2, 0)),
-    (8192, 256, 3, 128, "fp16", False, (16, 4, 0)), (4224, 512, 4, 64, "bf16", False, (16, 4, 0)), (8192, 384, 5, 128, "fp16", False, (16, 4, 0)),
+    (8192, 256, 3, 128, "fp16", True, (16, 4, 0)), (4224, 512, 4, 64, "bf16", False, (16, 4, 0)), (8192, 384, 5, 128, "fp16", False, (16, 4, 0)),
     (4224, 256, 8, 64, "fp16", False, (16, 4, 0)), (9216, 256, 5, 128, "fp16", False, (8, 0, 0)), (9216, 512, 6, 64, "bf16", False, (8, 0, 0)),
     (12288, 4224, 7, 128, "fp16", False, (8, 0, 2))])
 def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, scale_format, over, form):
@@ -842,6 +842,23 @@ def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, sc
         assert (d.mb, d.ra, d.rs) == form and not (d.resident and d.ra)
     S.sfmp_gemm(X, cp, dp.layout, dp.s2, dp.s3, dp.s4, dp.index, dp.scales, dp.zeros, dp.bitmap, rp, Y, make_workspace(dp.layout, M))
     _check(p, Y.cpu().numpy(), None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+
+
+@pytest.mark.parametrize("K,N,M,group,scale_format,perm", [
+    (4224, 128, 4, 128, "fp16", True), (5504, 4352, 3, 128, "bf16", True), (5120, 16512, 4, 256, "fp16", True), (6144, 512, 4, 512, "bf16", False),
+    (8064, 1024, 3, 128, "fp16", True), (8192, 8192, 4, 128, "fp16", True), (8192, 256, 2, 128, "bf16", False)])
+def test_small_batch_permuted_in_place(torch_cuda, K, N, M, group, scale_format, perm):
+    # up to four rows of 4224 to 8192 columns: second groups of four columns that 32, 256, 352, 512, 992 and all 1024 threads have, one to five slabs per
+    # workgroup; every row of the operand, with rows past the last
+    import plan_util
+    from gpu_util import run_gemm
+    p = W.make_problem("place", K, N, M, 9200 + K + M, fractions={2: 0.3, 3: 0.4, 4: 0.3}, outliers=True, group=group, scale_format=scale_format,
+                       block=(1, max(1, group // 128)), use_col_perm=perm, fast_codes=N * K > 2 ** 22)
+    d = plan_util.decode_plan(N, K, M, group)
+    assert (d.mb, d.resident, d.ra, d.slots) == (4, True, 0, 2) and d.workspace_bytes == K // 128 * 16 * 256
+    y1 = run_gemm(p)
+    _check(p, y1, None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
 
 
 @pytest.mark.parametrize("K,N,M", [(1024, 40960, 3), (1024, 40960, 8), (4224, 36864, 8), (4224, 36864, 16)])
