@@ -814,7 +814,7 @@ constexpr int kInPlaceQuads = 2;  // permuted in place: groups of four columns p
 // the kernel needs about 130 vector registers and runs 8 wavefronts per CU; with 4 or 8 it stays below 128 and runs
 // 16, which is what covers the latencies of its loop.  The forms with MB = 4 and with RA hold no sums in registers
 // (they write them to LDS as a slab finishes); there ACC only tells the variants for 16 and for 8 wavefronts apart.
-// G64: group length 64 (two parameter pairs per row and tile column; never together with RES without RA).
+// G64: group length 64 (two parameter pairs per row and tile column; with RES only in the forms that keep no activation sums).
 // RES with S = 2: the activations are permuted in place, for which up to 8192 columns fit.
 // RES with RA = 2: the operands are gathered by every workgroup itself, through a transposed copy of the activations in LDS that
 // lies where the second ring slots and the finished sums come later; no staging launch.
@@ -845,7 +845,7 @@ template <int NW, int S, int MB, bool RES, int ACC, bool G64, int RA, int RS, in
 __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int bid, const int G, unsigned char* lds_raw) {
   // RES with RA: the operands are gathered by the kernel itself (XT below); RESL: resident in LDS
   constexpr bool XT = RES && RA > 0, RESL = RES && !XT;
-  static_assert(!(RESL && G64), "the resident form keeps one activation sum per tile column");
+  static_assert(!(RESL && S != 2 && G64), "the resident form keeps one activation sum per tile column");
   static_assert(!RS || (RS == 2 && !RES && !RA && S == 3 && NW == 16), "streamed operands: three sets and slots");
   static_assert(R == 4 || (R == 2 && (MB == 8 || (RA && !RES))) || (R == 1 && (MB == 4 || (RA && !RES))), "rows of the operand");
   typedef RowSums<R> Rows;
@@ -1651,9 +1651,10 @@ constexpr int kSlotsStreamedActs = 3;
 constexpr int kSlotsRegisterActs = 2;  // activations in registers: the slots hold a slab and its parameters only
 // max_slabs: the largest number of slabs of a workgroup over the problems of the launch; K: the largest K
 // g64: group length 64, for which the resident form does not exist
-// rounds: workgroups per CU, one after the other; overwrites: outputs lie over activations, so the operands are not gathered in
+// grid: workgroups of the launch; overwrites: outputs lie over activations, so the operands are not gathered in
 // the launch that stores the products
-static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int32_t rounds, bool g64, bool overwrites) {
+static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int32_t grid, bool g64, bool overwrites) {
+  const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
   RSkinnyConfig c;
   c.mb = rskinny_mb(M);
   // 16 wavefronts where the finished sums fit beside the rest in 128 registers and the rings in LDS
@@ -1673,7 +1674,10 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int
   // back-to-back calls, M = 4 4224 -> 4096 7.7 / 6.1 us, 8192 -> 8192 11.9 / 10.1, 8192 -> 28672 23.2 / 21.6, 8192 -> 1024 8.9 / 7.5, 8192 ->
   // 57344 (two rounds of workgroups) 51.7 / 46.9, q|k|v of a 70B-shaped layer 15.6 / 12.5; M = 2 8192 -> 8192 11.8 / 10.0.  Not beyond
   // K = 8192, where the start is the longer one (M = 4 8320 -> 8192 10.5 / 10.9, 14336 -> 4096 9.9 / 11.4).
-  if (!c.resident && !g64 && c.mb == 4 && wide && !overwrites && K > 4096 && K / 4 <= kInPlaceQuads * c.nw * 64) {
+  // At group length 64, which the other resident form does not have, of any K where the workgroups are as many as CUs (gathered
+  // operands / in place: M = 4 4096 -> 4096 6.6 / 5.7 us, 4096 -> 14336 11.0 / 10.2, 2048 -> 40960 16.2 / 11.8; 4224 -> 1024, staged before, 7.9 /
+  // 6.3); on smaller matrices the gathered operands stay, whose launch is near that of an empty kernel.
+  if (!c.resident && c.mb == 4 && wide && !overwrites && (K > 4096 || (g64 && grid >= kGemvMaxGrid)) && K / 4 <= kInPlaceQuads * c.nw * 64) {
     c.resident = true;
     c.slots = kSlotsInPlace;
     if (rskinny_lds_bytes(c, max_slabs, M, K) <= 160 * 1024) return c;
@@ -1759,8 +1763,7 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool
   d.gemv = false;
   d.grid = grid;
   d.max_slabs = (nslab + grid - 1) / grid;
-  const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
-  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, rounds, group == 64, overwrites);
+  const RSkinnyConfig c = rskinny_config(M, K, d.max_slabs, grid, group == 64, overwrites);
   d.mb = c.mb;
   d.nw = c.nw;
   d.acc = c.acc;
@@ -1770,7 +1773,7 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool
   d.slots = c.slots;
   d.lds_bytes = (int32_t)rskinny_lds_bytes(c, d.max_slabs, M, K);
   // (whatever the buffers: the form that stages its activations)
-  d.workspace_bytes = round_up_256((int64_t)ntc * rskinny_config(M, K, d.max_slabs, rounds, group == 64, true).mb * 256);
+  d.workspace_bytes = round_up_256((int64_t)ntc * rskinny_config(M, K, d.max_slabs, grid, group == 64, true).mb * 256);
   return d;
 }
 
@@ -1986,7 +1989,7 @@ static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) 
   const int32_t r = rows_to_four(d.mb, d.resident, d.ra, a.M);
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                             \
   if (r == R_ && d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
-    if constexpr (!RES_ || RA_) {                                                             \
+    if constexpr (!RES_ || RA_ || S_ == kSlotsInPlace) {                                                             \
       if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_, R_>(a, d, stream); \
     }                                                                                         \
     return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(a, d, stream);        \
@@ -2125,8 +2128,7 @@ static int batch_config_for(const GemmArgs* probs, int count, int32_t M, int32_t
   *g64 = n64 != 0;
   int32_t grid = 0;
   for (int i = 0; i < count; ++i) grid += g[i];
-  const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
-  *c = rskinny_config(M, max_k, max_slabs, rounds, n64 != 0, overwrites);
+  *c = rskinny_config(M, max_k, max_slabs, grid, n64 != 0, overwrites);
   return SFMP_OK;
 }
 int batch_config(const GemmArgs* probs, int count, int32_t M, int32_t* g, RSkinnyConfig* c, bool* g64) {
@@ -2158,7 +2160,7 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
   const int32_t r = rows_to_four(c.mb, c.resident, c.ra, M);
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                           \
   if (r == R_ && c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
-    if constexpr (!RES_ || RA_) {                                                           \
+    if constexpr (!RES_ || RA_ || S_ == kSlotsInPlace) {                                                           \
       if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \
     }                                                                                       \
     return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \

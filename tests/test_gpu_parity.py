@@ -820,7 +820,7 @@ def test_gemm_batched_streamed_activations_with_different_K(torch_cuda, M, group
     (8320, 256, 1, 64, "bf16", True, (4, 0, 0)), (8320, 384, 3, 128, "fp16", True, (4, 0, 0)), (8320, 4224, 4, 64, "fp16", False, (4, 0, 0)),
     (512, 256, 3, 64, "fp16", True, (16, 2, 0)), (2176, 512, 4, 64, "bf16", True, (16, 2, 0)), (4096, 256, 7, 128, "fp16", True, (16, 2, 0)),
     (128, 131200, 2, 64, "fp16", False, (16, 2, 0)), (128, 131200, 6, 128, "bf16", False, (16, 2, 0)),
-    (8192, 256, 3, 128, "fp16", True, (16, 4, 0)), (4224, 512, 4, 64, "bf16", False, (16, 4, 0)), (8192, 384, 5, 128, "fp16", False, (16, 4, 0)),
+    (8192, 256, 3, 128, "fp16", True, (16, 4, 0)), (4224, 512, 4, 64, "bf16", True, (16, 4, 0)), (8192, 384, 5, 128, "fp16", False, (16, 4, 0)),
     (4224, 256, 8, 64, "fp16", False, (16, 4, 0)), (9216, 256, 5, 128, "fp16", False, (8, 0, 0)), (9216, 512, 6, 64, "bf16", False, (8, 0, 0)),
     (12288, 4224, 7, 128, "fp16", False, (8, 0, 2))])
 def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, scale_format, over, form):
@@ -846,9 +846,10 @@ def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, sc
 
 @pytest.mark.parametrize("K,N,M,group,scale_format,perm", [
     (4224, 128, 4, 128, "fp16", True), (5504, 4352, 3, 128, "bf16", True), (5120, 16512, 4, 256, "fp16", True), (6144, 512, 4, 512, "bf16", False),
-    (8064, 1024, 3, 128, "fp16", True), (8192, 8192, 4, 128, "fp16", True), (8192, 256, 2, 128, "bf16", False)])
+    (8064, 1024, 3, 128, "fp16", True), (8192, 8192, 4, 128, "fp16", True), (8192, 256, 2, 128, "bf16", False),
+    (128, 4096, 2, 64, "fp16", True), (4096, 4352, 4, 64, "bf16", True), (8192, 512, 3, 64, "fp16", True), (2048, 33024, 4, 64, "fp16", False)])
 def test_small_batch_permuted_in_place(torch_cuda, K, N, M, group, scale_format, perm):
-    # up to four rows of 4224 to 8192 columns: second groups of four columns that 32, 256, 352, 512, 992 and all 1024 threads have, one to five slabs per
+    # up to four rows of 4224 to 8192 columns, at group length 64 of any number up to that: second groups of four columns that 32, 256, 352, 512, 992 and all 1024 threads have, one to five slabs per
     # workgroup; every row of the operand, with rows past the last
     import plan_util
     from gpu_util import run_gemm
