@@ -835,7 +835,8 @@ constexpr int kInPlaceQuads = 2;  // permuted in place: groups of four columns p
 // 25.2 -> 21.5.
 // Resident operands (RES with RA): LDS bytes of the transposed activations (16 or 8 rows of a column together), and where a
 // byte of them lies.
-__host__ __device__ inline int64_t rskinny_xt_bytes(int32_t M, int32_t K) { return (int64_t)K * (M <= 8 ? 16 : 32); }
+// (spread: up to 8 rows, two to every four of the operand, as 16 of which half are not there)
+__host__ __device__ inline int64_t rskinny_xt_bytes(int32_t M, int32_t K, bool spread) { return (int64_t)K * (M <= 8 && !spread ? 16 : 32); }
 // (byte `at` of the plain layout; bits 4-7, the 16-byte unit of 256 bytes, are exchanged by the number of the 256 bytes)
 __device__ __forceinline__ uint32_t xt_offset(uint32_t at) { return at ^ ((at >> 4) & 0xF0u); }
 typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -847,7 +848,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   constexpr bool XT = RES && RA > 0, RESL = RES && !XT;
   static_assert(!(RESL && S != 2 && G64), "the resident form keeps one activation sum per tile column");
   static_assert(!RS || (RS == 2 && !RES && !RA && S == 3 && NW == 16), "streamed operands: three sets and slots");
-  static_assert(R == 4 || (R == 2 && (MB == 8 || (RA && !RES))) || (R == 1 && (MB == 4 || (RA && !RES))), "rows of the operand");
+  static_assert(R == 4 || (R == 2 && (MB == 8 || RA)) || (R == 1 && (MB == 4 || (RA && !RES))), "rows of the operand");
   typedef RowSums<R> Rows;
   typedef typename Rows::type sums_t;
   static_assert((!RA || MB == 16) && (RA == 0 || RA == 2 || RA == 4), "activations in registers: 16 rows");
@@ -921,7 +922,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   // without resident activations MB/4 KiB of staged activations of the item's tile column (scalar address)
   constexpr int kWaveSlots = XT ? 1 : S * (RS ? RS : 1);  // (RS: a slot holds the item of every slab)
   // (XT) the first slots of all wavefronts lie behind the transposed activations, the second ones where a slot lies anyway
-  const uint32_t xt_first = XT ? (uint32_t)max((int)rskinny_xt_bytes(p.M, p.K) - (int)(rings - lds_raw), NW * kSlot) : 0u;
+  const uint32_t xt_first = XT ? (uint32_t)max((int)rskinny_xt_bytes(p.M, p.K, R == 2) - (int)(rings - lds_raw), NW * kSlot) : 0u;
   const uint32_t ring_off = (uint32_t)(uintptr_t)(lptr_t)(rings + (size_t)wave * kWaveSlots * kSlot);
   const unsigned char* ring = rings + (size_t)wave * kWaveSlots * kSlot;
   const uint64_t xb = (uint64_t)p.xblk;
@@ -1117,7 +1118,8 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     }
     const int units = p.K / 4;
     auto stage = [&](auto rtag) __attribute__((always_inline)) {
-      constexpr int RL = decltype(rtag)::value;
+      constexpr int RL = decltype(rtag)::value;      // rows loaded
+      constexpr int RW = R == 2 ? 16 : RL;           // rows of a column in LDS (R = 2: rows 2g, 2g + 1 lie at 4g, 4g + 1)
       u32x2 x[RL];
       if (wave * kWave < units) {
         const _Float16* const from = p.X + 4 * min(tid, units - 1);
@@ -1141,7 +1143,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
       issued_early = min(1, Eb0);
       if (issued_early) issue_item(0, 0);
       if (tid < units) {
-        const uint32_t base = xt_offset((uint32_t)tid * (8 * RL));  // (4 columns: the low bits of the unit are added by XOR)
+        const uint32_t base = xt_offset((uint32_t)tid * (8 * RW));  // (4 columns: the low bits of the unit are added by XOR)
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
           uint32_t v[RL / 2];
@@ -1149,13 +1151,14 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
           for (int m = 0; m < RL / 2; ++m)
             v[m] = __builtin_amdgcn_perm(x[2 * m + 1][kk / 2], x[2 * m][kk / 2], kk % 2 ? 0x07060302u : 0x05040100u);
 #pragma unroll
-          for (int h = 0; h < RL / 8; ++h)
-            *reinterpret_cast<u32x4*>(lds_raw + (base ^ (uint32_t)(kk * 2 * RL + h * 16))) =
-                u32x4{v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]};
+          for (int h = 0; h < RW / 8; ++h)
+            *reinterpret_cast<u32x4*>(lds_raw + (base ^ (uint32_t)(kk * 2 * RW + h * 16))) =
+                R == 2 ? u32x4{v[2 * h], v[2 * h], v[2 * h + 1], v[2 * h + 1]}
+                       : u32x4{v[RL == RW ? 4 * h : 0], v[RL == RW ? 4 * h + 1 : 0], v[RL == RW ? 4 * h + 2 : 0], v[RL == RW ? 4 * h + 3 : 0]};
         }
       }
       barrier_lds_only();
-      const uint32_t in_column = (uint32_t)(RL == 16 ? chunk : chunk % 2) * 8;
+      const uint32_t in_column = (uint32_t)(RW == 16 ? chunk : chunk % 2) * 8;
 #pragma unroll
       for (int t = 0; t < RA; ++t) {
         if (wave + NW * t < p.ntc) {
@@ -1167,7 +1170,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
             } o;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-              const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * RL) + in_column);
+              const unsigned char* at = lds_raw + xt_offset((uint32_t)pk[t][2 * kappa + h] * (2 * RW) + in_column);
               o.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16_lds)(at));
             }
             aset[t][kappa] = o.v;
@@ -1183,9 +1186,9 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
         for (int kappa = 0; kappa < 4; ++kappa) asm volatile("" : "+v"(aset[t][kappa]));
       barrier_lds_only();  // every wavefront has its operands: the second slots and the finished sums may overwrite the rest
     };
-    if (p.M <= 8)
+    if (R == 2 || p.M <= 8)
       stage(std::integral_constant<int, 8>{});
-    else
+    else if constexpr (R == 4)
       stage(std::integral_constant<int, 16>{});
   } else if constexpr (RA > 0) {
 #pragma unroll
@@ -1619,15 +1622,29 @@ struct RSkinnyConfig {
   int32_t ra;  // activations in registers (at most 2 or 4 tile columns per wavefront; 0: not): 16-row operand-order staging, small slots
 };
 static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
+// Activation rows to every four of the operand: as few as the launch's rows (at most M) allow.  The operands that a workgroup
+// gathers itself take at least two: a transposing read takes four consecutive rows of a column from an address of 8 bytes, so
+// that spread rows are stored among as many that are not there, twice the stores of the start.  From three slabs per workgroup on the
+// shorter loop pays for them (four rows / spread, M = 8: 4096 -> 28672 14.2 / 13.7 us, 4096 -> 14336 at group length 64 11.65 / 11.27, 1024 ->
+// 28672 8.1 / 7.8, 512 -> 14336 5.8 / 5.6; with one slab 4096 -> 4096 6.25 / 6.42, with two 4096 -> 8192 7.5 / 7.6).
+constexpr int kXtSpreadSlabs = 3;
+static bool spreads_gathered(int32_t M, int32_t max_slabs) { return M <= 8 && max_slabs >= kXtSpreadSlabs; }
+static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M, int32_t max_slabs) {
+  if (!ra) return mb / 4;
+  if (resident) return spreads_gathered(M, max_slabs) ? 2 : 4;
+  return M <= 4 ? 1 : M <= 8 ? 2 : 4;
+}
+
 constexpr int kSlotsInPlace = 2;  // (and that number of slots tells the two resident forms apart)
 // LDS of the ring-skinny kernel: reduction buffers, (resident: activations in operand layout, their tile-column sums,
 // their raw copy), rings
-static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int32_t M, int32_t K) {
+// (spread: see spreads_gathered, of the launch)
+static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int32_t M, int32_t K, bool spread) {
   const int64_t red = (int64_t)max_slabs * 1024 * (c.nw / 4);
   // (slots sized for group length 64, 128 bytes larger, whatever the layout)
   if (c.ra && c.resident) {  // fin | second slots, beside them the transposed activations | first slots
     const int64_t slots = (int64_t)c.nw * kSlotBytes64, second = (int64_t)max_slabs * 1024 * c.nw + slots;
-    return std::max(second, rskinny_xt_bytes(M, K)) + slots;
+    return std::max(second, rskinny_xt_bytes(M, K, spread)) + slots;
   }
   if (c.ra || c.rs)  // fin | rings
     return (int64_t)max_slabs * 1024 * c.nw + (int64_t)c.nw * c.slots * (c.rs ? c.rs : 1) * kSlotBytes64;
@@ -1655,6 +1672,7 @@ constexpr int kSlotsRegisterActs = 2;  // activations in registers: the slots ho
 // the launch that stores the products
 static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int32_t grid, bool g64, bool overwrites) {
   const int32_t rounds = (grid + kGemvMaxGrid - 1) / kGemvMaxGrid;
+  const bool spread = spreads_gathered(M, max_slabs);
   RSkinnyConfig c;
   c.mb = rskinny_mb(M);
   // 16 wavefronts where the finished sums fit beside the rest in 128 registers and the rings in LDS
@@ -1668,7 +1686,7 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int
   if (!g64 && c.mb == 4 && (int64_t)M * K * 2 <= kResidentMaxRawBytes && K / 8 <= kGemvUnitIters * c.nw * 64) {
     c.resident = true;
     c.slots = kSlotsResident;
-    if (rskinny_lds_bytes(c, max_slabs, M, K) > 160 * 1024) c.resident = false;
+    if (rskinny_lds_bytes(c, max_slabs, M, K, spread) > 160 * 1024) c.resident = false;
   }
   // Up to four rows of a longer K, permuted in place (two slots, no raw copy) instead of in a launch in front: staged / in place,
   // back-to-back calls, M = 4 4224 -> 4096 7.7 / 6.1 us, 8192 -> 8192 11.9 / 10.1, 8192 -> 28672 23.2 / 21.6, 8192 -> 1024 8.9 / 7.5, 8192 ->
@@ -1680,7 +1698,7 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int
   if (!c.resident && c.mb == 4 && wide && !overwrites && (K > 4096 || (g64 && grid >= kGemvMaxGrid)) && K / 4 <= kInPlaceQuads * c.nw * 64) {
     c.resident = true;
     c.slots = kSlotsInPlace;
-    if (rskinny_lds_bytes(c, max_slabs, M, K) <= 160 * 1024) return c;
+    if (rskinny_lds_bytes(c, max_slabs, M, K, spread) <= 160 * 1024) return c;
     c.resident = false;
   }
   if (!c.resident && K / kTile <= 4 * c.nw) {
@@ -1704,7 +1722,7 @@ static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int
     // to 0.99 there, up to 0.94: 68096 outputs of K = 4096, 12 rows 40.5 / 43.3 us; with a shorter K 1.00 to 1.08).
     const bool long_start = M > 8 && rounds > 1 && K > (rounds == 2 ? 3072 : 2048);
     r.resident = r.nw == 16 && r.ra == 2 && !overwrites && !long_start;
-    if (rskinny_lds_bytes(r, max_slabs, M, K) <= 160 * 1024) return r;
+    if (rskinny_lds_bytes(r, max_slabs, M, K, spread) <= 160 * 1024) return r;
   }
   // a longer K with two slabs per workgroup (4096 < N <= 8192 on a full grid): operands streamed through registers.  Not
   // with one slab, where a tile column serves one item only (14336 -> 4096: M = 8 13.0 -> 14.2 us, M = 16 unchanged), and
@@ -1771,7 +1789,7 @@ DecodePlan make_decode_plan(int32_t N, int32_t K, int32_t M, int32_t group, bool
   d.ra = c.ra;
   d.rs = c.rs;
   d.slots = c.slots;
-  d.lds_bytes = (int32_t)rskinny_lds_bytes(c, d.max_slabs, M, K);
+  d.lds_bytes = (int32_t)rskinny_lds_bytes(c, d.max_slabs, M, K, spreads_gathered(M, d.max_slabs));
   // (whatever the buffers: the form that stages its activations)
   d.workspace_bytes = round_up_256((int64_t)ntc * rskinny_config(M, K, d.max_slabs, grid, group == 64, true).mb * 256);
   return d;
@@ -1962,13 +1980,6 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   return after_launch("sfmp_gemm skinny launch");
 }
 
-// Activation rows to every four of the operand: as few as the launch's rows (at most M) allow.  The operands that a workgroup
-// gathers itself have all four: a transposing read takes four consecutive rows of a column from an address of 8 bytes.
-static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M) {
-  if (!ra) return mb / 4;
-  return resident ? 4 : M <= 4 ? 1 : M <= 8 ? 2 : 4;
-}
-
 // The compiled configurations (see rskinny_config and rows_to_four): X(NW, S, MB, RES, ACC, RA, RS, R)
 #define SFMP_RSKINNY_CONFIGS(X)                                                                                    \
   X(16, kSlotsResident, 4, true, 4, 0, 0, 1) X(8, kSlotsResident, 4, true, 16, 0, 0, 1)                            \
@@ -1978,7 +1989,7 @@ static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M) {
   X(16, kSlotsMb16Wide, 16, false, 4, 0, 0, 4) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0, 4)                        \
   X(8, kSlotsMb16, 16, false, 16, 0, 0, 4)                                                                         \
   X(16, kSlotsStreamedActs, 8, false, 4, 0, 2, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2, 4)                 \
-  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 4)                                                                  \
+  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 2) X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 4)                                                             \
   SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 2) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 2)                            \
   SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 4) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 4)
 #define SFMP_RSKINNY_REGISTER_CONFIGS(X, NW, ACC, RA)                                                              \
@@ -1986,7 +1997,7 @@ static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M) {
   X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 4)
 
 static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) {
-  const int32_t r = rows_to_four(d.mb, d.resident, d.ra, a.M);
+  const int32_t r = rows_to_four(d.mb, d.resident, d.ra, a.M, d.max_slabs);
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                             \
   if (r == R_ && d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
     if constexpr (!RES_ || RA_ || S_ == kSlotsInPlace) {                                                             \
@@ -2069,7 +2080,7 @@ static int launch_rskinny_batched_variant(const GemmArgs* probs, int count, int3
     const RSkinnyConfig cfg = {MB, NW, S, ACC, RES, RS, RA};
     if (RS && max_slabs > RS) return SFMP_ERR_SHAPE;
     if (!RA && !RS && MB != 4 && max_slabs > ACC) return SFMP_ERR_SHAPE;  // (those two forms keep no sums in registers)
-    const int64_t need = rskinny_lds_bytes(cfg, max_slabs, probs[i].M, L->K);
+    const int64_t need = rskinny_lds_bytes(cfg, max_slabs, probs[i].M, L->K, R == 2);
     lds = need > lds ? need : lds;
     b.first[i] = first;
     first += g[i];
@@ -2157,7 +2168,9 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
   RSkinnyConfig c;
   bool n64 = false;
   if (int e = batch_config(probs, count, M, g, &c, &n64)) return e;
-  const int32_t r = rows_to_four(c.mb, c.resident, c.ra, M);
+  int32_t max_slabs = 0;
+  for (int i = 0; i < count; ++i) max_slabs = std::max(max_slabs, (8 * (probs[i].L->N / kTile) + g[i] - 1) / g[i]);
+  const int32_t r = rows_to_four(c.mb, c.resident, c.ra, M, max_slabs);
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                           \
   if (r == R_ && c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
     if constexpr (!RES_ || RA_ || S_ == kSlotsInPlace) {                                                           \

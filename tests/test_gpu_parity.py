@@ -699,6 +699,23 @@ def test_small_batch_operands_gathered_without_a_staging_launch(torch_cuda, K, N
     assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
 
 
+@pytest.mark.parametrize("K,N,M,group,scale_format,perm", [
+    (512, 14336, 5, 128, "fp16", True), (128, 12288, 6, 128, "bf16", False), (4096, 12416, 7, 64, "bf16", True), (4096, 28672, 8, 128, "fp16", True),
+    (2176, 36864, 8, 64, "fp16", True)])
+def test_small_batch_gathered_operands_spread(torch_cuda, K, N, M, group, scale_format, perm):
+    # 5 to 8 rows in operands that every workgroup gathers itself, two rows to every four: three to seven slabs per workgroup, one round and
+    # two, one and two tile columns per wavefront, wavefronts without any
+    import plan_util
+    from gpu_util import run_gemm
+    p = W.make_problem("gspread", K, N, M, 9650 + K + M, fractions={2: 0.3, 3: 0.4, 4: 0.3}, outliers=True, group=group, scale_format=scale_format,
+                       use_col_perm=perm, fast_codes=True)
+    d = plan_util.decode_plan(N, K, M, group)
+    assert d.ra == 2 and d.resident and d.max_slabs >= 3 and d.lds_bytes <= 160 * 1024
+    y1 = run_gemm(p)
+    _check(p, y1, np.random.default_rng(M).choice(N, 384, replace=False))
+    assert np.array_equal(y1.view(np.uint16), run_gemm(p).view(np.uint16))
+
+
 @pytest.mark.parametrize("K,N,M,group,shift", [
     (2048, 2048, 5, 128, 0), (4096, 4096, 16, 128, 0), (4096, 14336, 8, 64, 0), (4096, 1024, 16, 128, 4096), (128, 256, 7, 128, 128),
     (512, 512, 64, 128, 0), (2048, 1024, 33, 64, 1024), (4096, 4096, 64, 128, 0), (4096, 512, 128, 64, 0), (1024, 2048, 200, 128, 0)])
