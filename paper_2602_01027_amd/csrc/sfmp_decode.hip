@@ -1653,9 +1653,9 @@ static int64_t rskinny_lds_bytes(const RSkinnyConfig& c, int32_t max_slabs, int3
                           (int64_t)c.nw * c.slots * kSlotBytes64
                     : red + (int64_t)c.nw * c.slots * (kSlotBytes64 + c.mb * 256);
 }
-// The resident variant (activations staged into LDS by every workgroup, no staging kernel) exists for blocks of
+// The resident variant with raw rows (activations staged into LDS by every workgroup, no staging kernel) exists for blocks of
 // 4 rows and M x K activations of at most 32 KiB: measured, the saved launch outweighs 256 workgroups each permuting
-// the activations up to that size (8 to 17 % on K = 4096 with M <= 4) and no longer beyond it.
+// the activations up to that size (8 to 17 % on K = 4096 with M <= 4).  Beyond it: permuted in place (see rskinny_config).
 constexpr int64_t kResidentMaxRawBytes = 32 * 1024;
 // ring slots per wavefront of the four forms (shallow, as in the GEMV kernel; 3 measured best for the resident form)
 constexpr int kSlotsResident = 3, kSlotsMb4 = 2, kSlotsMb8 = 2, kSlotsMb16 = 2;

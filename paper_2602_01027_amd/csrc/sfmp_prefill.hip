@@ -17,6 +17,7 @@
 //     into the B operands of v_mfma_f32_16x16x32_f16; every operand feeds four to eight MFMAs.  Activations, packed
 //     words and parameters go from global memory directly into LDS.  The product leaves through LDS in whole 256-byte
 //     row segments.
+//     prefill_mixed_kernel: whole rounds of its 256-row workgroups, and smaller ones on the last tile rows.
 //     prefill_kernel: 128 x 128 outputs, four wavefronts that do all of this themselves, two workgroups per CU; for the
 //     few numbers of workgroups that suit it better.
 //  3. scatter_cols_kernel (only with a row permutation): the GEMM writes the product in reordered
@@ -659,8 +660,8 @@ __device__ __forceinline__ void load_lanes_to_lds_16(uint64_t vaddr, uint32_t ld
 // and 4500 at the end.  With several full rounds of workgroups the chip's power limit lowers the clock instead (2048 x 28672 -> 8192:
 // pipe 0.73 busy at 1.51 GHz); 2048 x 4096 -> 14336 loses half of its fourth round first (0.55 busy at 1.78 GHz).
 // Whole calls back to back, the kernels before (whose wavefronts did all of this themselves) -> now: 777 x 4096 -> 4096 49.1 -> 37.7 us,
-// 200 x 14336 -> 4096 (group length 64) 47.7 -> 39.3, 64 x 4096 -> 14336 22.6 -> 20.6, 2048 x 4096 -> 14336 266.7 -> 248.6, 2048 x
-// 28672 -> 8192 884.8 -> 818.0.
+// 200 x 14336 -> 4096 (group length 64) 47.7 -> 39.3, 64 x 4096 -> 14336 22.6 -> 20.6, 2048 x 4096 -> 14336 266.7 -> 248.6 (a tail of smaller
+// workgroups since, see PrefillMixed), 2048 x 28672 -> 8192 884.8 -> 818.0.
 // MI = 8 reaches the 168 registers of 12 wavefronts and spills 1 to 11 of them, most with two K groups and at group length 64
 // (there with reloads inside the tile loops; the choice of the form does not know of it).
 // Not better: 32x32x16 instructions (the words of two slabs exchanged between rows of 16 lanes): 2770 cycles where 16x16x32
@@ -1269,11 +1270,13 @@ static int check_launch(const char* what) {
   return SFMP_OK;
 }
 
-// Threads of a workgroup that permutes a row of `columns`: up to 1024, the units of 8 columns evenly among them.  (The scatter
+// Threads of a workgroup that permutes a row of `columns`: up to 1024, the units of 8 columns evenly among them; with fewer rows
+// than two workgroups per CU as many as there are units (57 x 25856 -> 4352 30.8 us with 1024 threads, 31.3 with 832).  (The scatter
 // pass takes 256 up to 8192 columns: 2000 x 4096 -> 4096 73.3 us with 256 and 74.1 with 512.)
-static unsigned pass_threads(int32_t columns) {
-  const int32_t units = columns / 8, each = (units + 1023) / 1024;
-  return (unsigned)(((units + each - 1) / each + kWave - 1) / kWave * kWave);
+static unsigned pass_threads(int32_t columns, int32_t rows) {
+  const int32_t units = columns / 8, each = rows < 512 ? 1 : (units + 1023) / 1024;
+  const int32_t threads = ((units + each - 1) / each + kWave - 1) / kWave * kWave;
+  return (unsigned)(threads < 1024 ? threads : 1024);
 }
 
 int launch_prefill(const GemmArgs& a, void* stream) {
@@ -1301,7 +1304,7 @@ int launch_prefill(const GemmArgs& a, void* stream) {
     const int32_t* cp = a.col_perm;
     int Ka = L->K;
     void* kargs[] = {&Xa, &cp, &Xp, &Ka};
-    hipError_t e = hipLaunchKernel(fn, dim3((unsigned)a.M), dim3(pass_threads(L->K)), kargs, (size_t)L->K * 2, (hipStream_t)stream);
+    hipError_t e = hipLaunchKernel(fn, dim3((unsigned)a.M), dim3(pass_threads(L->K, a.M)), kargs, (size_t)L->K * 2, (hipStream_t)stream);
     if (e != hipSuccess) {
       note_hip_error("sfmp_gemm activation staging launch", hipGetErrorString(e));
       return SFMP_ERR_HIP;
@@ -1360,7 +1363,7 @@ int launch_prefill(const GemmArgs& a, void* stream) {
     }
     if (int e = check_launch("sfmp_gemm split-K reduction launch")) return e;
   } else if (a.row_perm) {
-    hipLaunchKernelGGL(scatter_cols_kernel, dim3((unsigned)a.M), dim3(L->N <= 8192 ? 256 : pass_threads(L->N)), (size_t)L->N * 2, (hipStream_t)stream,
+    hipLaunchKernelGGL(scatter_cols_kernel, dim3((unsigned)a.M), dim3(L->N <= 8192 ? 256 : pass_threads(L->N, a.M)), (size_t)L->N * 2, (hipStream_t)stream,
                        (const _Float16*)Yt, a.row_perm, (_Float16*)a.Y, (int)L->N);
     if (int e = check_launch("sfmp_gemm row scatter launch")) return e;
   }
