@@ -47,6 +47,7 @@ struct PrefillTail {
   int32_t mi, tile_rows;
 };
 PrefillTail choose_prefill_tail(int32_t N, int32_t K, int32_t M);
+bool stores_past_caches(int32_t N, int32_t M);  // the un-permute pass of a matrix-core call
 double matrix_core_time_us(int32_t N, int32_t K, int32_t M);  // estimated time of that call
 
 constexpr int32_t kDecodeMaxM = 16;

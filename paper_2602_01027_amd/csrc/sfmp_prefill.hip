@@ -77,9 +77,8 @@ __global__ __launch_bounds__(1024) void gather_cols_kernel(const _Float16* __res
   }
 }
 
-// Y[m, row_perm[i]] = Yt[m, i].  The result is stored past the caches: nothing of this call reads it, and dirty lines are
-// written back when the kernel ends (2048 x 4096 -> 14336, the whole call 242 -> 237 us; with threads by N besides, 140 x 2048 ->
-// 20480 28.1 -> 26.4 us).
+// Y[m, row_perm[i]] = Yt[m, i].  PAST: the result is stored past the caches (see stores_past_caches).
+template <bool PAST>
 __global__ __launch_bounds__(1024) void scatter_cols_kernel(const _Float16* __restrict__ Yt,
                                                            const int32_t* __restrict__ row_perm,
                                                            _Float16* __restrict__ Y, int N) {
@@ -106,8 +105,13 @@ __global__ __launch_bounds__(1024) void scatter_cols_kernel(const _Float16* __re
   }
   __syncthreads();
   u32x4* dst = reinterpret_cast<u32x4*>(Y + m * N);
-  for (int i = threadIdx.x; i < N / 8; i += (int)blockDim.x)
-    __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(row)[i], dst + i);
+  for (int i = threadIdx.x; i < N / 8; i += (int)blockDim.x) {
+    const u32x4 v = reinterpret_cast<const u32x4*>(row)[i];
+    if constexpr (PAST)
+      __builtin_nontemporal_store(v, dst + i);
+    else
+      dst[i] = v;
+  }
 }
 
 // Y[m, row_perm[i]] (or Y[m, i]) = fp16( sum over the K ranges, in range order, of partial[ks][m][i] ): the second
@@ -1279,6 +1283,15 @@ static unsigned pass_threads(int32_t columns, int32_t rows) {
   return (unsigned)(threads < 1024 ? threads : 1024);
 }
 
+// Does the un-permute pass store its result past the caches?  A call alone is 0 to 2 us shorter for it at any size, but whatever
+// reads the result next then takes it from memory: it counts what the two take together.  That is shorter once the result and the
+// product before the un-permute, which this pass reads, do not fit in the 256 MiB of the memory-side cache together.  The call
+// followed by an addition to another matrix / by a multiplication in place, past the caches -> through them: 777 x 2048 -> 14336 (22 MB)
+// 77.6 -> 77.3 / 75.9 -> 75.3 us, 2048 x 4096 -> 4096 followed by a product with its result 108.0 -> 106.6, 2048 x 4096 -> 14336 (59 MB) 275.7 -> 274.4 /
+// 267.4 -> 265.3, 2048 x 512 -> 28672 (117 MB) 211 -> 216 / 186 -> 183; 16384 x 1024 -> 4096 (134 MB) 294 -> 309 / 266 -> 279, 4096 x 1024 ->
+// 28672 (235 MB) 467 -> 491 / 440 -> 449, the call alone 335 -> 373.
+bool stores_past_caches(int32_t N, int32_t M) { return 2 * ((int64_t)M * N * 2) >= (int64_t)256 << 20; }
+
 int launch_prefill(const GemmArgs& a, void* stream) {
   const sfmp_layout_t* L = a.L;
   const int64_t xperm_bytes = prefill_workspace(L->N, L->K, a.M).xperm_bytes;
@@ -1292,8 +1305,11 @@ int launch_prefill(const GemmArgs& a, void* stream) {
                                              : reinterpret_cast<const void*>(&reduce_split_kernel<8>);
   if (form.ksplit > 1) {
     if (int e = allow_full_lds(reduce_fn, "hipFuncSetAttribute(reduce)")) return e;
-  } else if (a.row_perm) {
-    if (int e = allow_full_lds(reinterpret_cast<const void*>(&scatter_cols_kernel), "hipFuncSetAttribute(scatter)")) return e;
+  }
+  const bool past = stores_past_caches(L->N, a.M);
+  const void* scatter_fn = past ? reinterpret_cast<const void*>(&scatter_cols_kernel<true>) : reinterpret_cast<const void*>(&scatter_cols_kernel<false>);
+  if (form.ksplit == 1 && a.row_perm) {
+    if (int e = allow_full_lds(scatter_fn, "hipFuncSetAttribute(scatter)")) return e;
   }
   // activations -> workspace: column permutation applied (if any), 128x128 blocks each contiguous
   _Float16* Xp = (_Float16*)a.workspace;
@@ -1363,8 +1379,11 @@ int launch_prefill(const GemmArgs& a, void* stream) {
     }
     if (int e = check_launch("sfmp_gemm split-K reduction launch")) return e;
   } else if (a.row_perm) {
-    hipLaunchKernelGGL(scatter_cols_kernel, dim3((unsigned)a.M), dim3(L->N <= 8192 ? 256 : pass_threads(L->N, a.M)), (size_t)L->N * 2, (hipStream_t)stream,
-                       (const _Float16*)Yt, a.row_perm, (_Float16*)a.Y, (int)L->N);
+    const dim3 grid((unsigned)a.M), threads(L->N <= 8192 ? 256 : pass_threads(L->N, a.M));
+    if (past)
+      hipLaunchKernelGGL(scatter_cols_kernel<true>, grid, threads, (size_t)L->N * 2, s, (const _Float16*)Yt, a.row_perm, (_Float16*)a.Y, (int)L->N);
+    else
+      hipLaunchKernelGGL(scatter_cols_kernel<false>, grid, threads, (size_t)L->N * 2, s, (const _Float16*)Yt, a.row_perm, (_Float16*)a.Y, (int)L->N);
     if (int e = check_launch("sfmp_gemm row scatter launch")) return e;
   }
   return SFMP_OK;

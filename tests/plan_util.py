@@ -103,3 +103,8 @@ def launched_tail(N, K, M):
     """(16-row blocks of a wavefront, tile rows) of the tail of a matrix-core call in two forms; (0, 0): one form."""
     t = _call("_ZN4sfmp19choose_prefill_tailEiii", _PrefillTail, N, K, M)
     return t.mi, t.tile_rows
+
+
+def stores_past_caches(N, M):
+    """Does the un-permute pass of a matrix-core call store its result past the caches?"""
+    return _call("_ZN4sfmp18stores_past_cachesEii", C.c_bool, N, M)

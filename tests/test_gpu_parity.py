@@ -270,6 +270,16 @@ def test_permutation_passes_of_a_prompt(torch_cuda, K, N, M, perms):
     _check(p, run_gemm(p), None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
 
 
+@pytest.mark.parametrize("M,past", [(4095, False), (4096, True)])
+def test_un_permuted_result_through_and_past_the_caches(torch_cuda, M, past):
+    # one row on either side of 128 MiB of results
+    import plan_util
+    from gpu_util import run_gemm
+    assert plan_util.stores_past_caches(16384, M) == past
+    p = W.make_problem("stores", 128, 16384, M, 9450, fractions={2: 0.3, 3: 0.3, 4: 0.4}, fast_codes=True)
+    _check(p, run_gemm(p), np.random.default_rng(M).choice(p.N, 384, replace=False), m_rows=np.r_[:64, 2000:2064, M - 64:M])
+
+
 @pytest.mark.parametrize("K,N,M,group,scale_format,row_perm,tail", [
     (640, 13184, 2047, 128, "fp16", True, (4, 7)), (640, 13184, 2047, 128, "bf16", True, (4, 7)), (640, 13184, 2000, 64, "fp16", False, (4, 7)),
     (640, 13184, 2000, 64, "bf16", True, (4, 7)), (640, 13696, 2047, 128, "fp16", False, (8, 11)), (640, 13696, 2000, 128, "bf16", True, (8, 11)),

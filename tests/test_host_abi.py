@@ -492,3 +492,11 @@ def test_activations_are_gathered_where_the_start_is_paid_for_seldom(N, K, M, ga
 def test_small_batches_that_stream_their_activations(N, K, M, group, streamed):
     import plan_util
     assert plan_util.decode_plan(N, K, M, group).rs == (2 if streamed else 0)
+
+
+@pytest.mark.parametrize("N,M,past", [
+    (14336, 2048, False), (4096, 777, False), (8192, 150, False), (28672, 2048, False),  # shorter alone, longer with the reader of the result
+    (4096, 16383, False), (4096, 16384, True), (28672, 4096, True)])
+def test_result_of_a_prompt_goes_past_the_caches_only_where_they_could_not_hold_it(N, M, past):
+    import plan_util
+    assert plan_util.stores_past_caches(N, M) == past
