@@ -47,7 +47,9 @@ struct PrefillTail {
   int32_t mi, tile_rows;
 };
 PrefillTail choose_prefill_tail(int32_t N, int32_t K, int32_t M);
-bool stores_past_caches(int32_t N, int32_t M);  // the un-permute pass of a matrix-core call
+// the un-permute pass of a matrix-core call
+bool stores_past_caches(int32_t N, int32_t M);
+int32_t scatter_threads(int32_t N, int32_t M);
 double matrix_core_time_us(int32_t N, int32_t K, int32_t M);  // estimated time of that call
 
 constexpr int32_t kDecodeMaxM = 16;

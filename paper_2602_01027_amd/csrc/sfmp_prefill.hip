@@ -1275,13 +1275,19 @@ static int check_launch(const char* what) {
 }
 
 // Threads of a workgroup that permutes a row of `columns`: up to 1024, the units of 8 columns evenly among them; with fewer rows
-// than two workgroups per CU as many as there are units (57 x 25856 -> 4352 30.8 us with 1024 threads, 31.3 with 832).  (The scatter
-// pass takes 256 up to 8192 columns: 2000 x 4096 -> 4096 73.3 us with 256 and 74.1 with 512.)
+// than two workgroups per CU as many as there are units (57 x 25856 -> 4352 30.8 us with 1024 threads, 31.3 with 832; staging passes of 150 rows
+// of 8320 to 28672 columns 0.1 us shorter, 300 to 2048 rows within 1 % either way but 1000 x 8320, 29.2 and 29.9).
 static unsigned pass_threads(int32_t columns, int32_t rows) {
   const int32_t units = columns / 8, each = rows < 512 ? 1 : (units + 1023) / 1024;
   const int32_t threads = ((units + each - 1) / each + kWave - 1) / kWave * kWave;
   return (unsigned)(threads < 1024 ? threads : 1024);
 }
+
+// Of the un-permute pass: 256 from 512 rows on up to 10240 columns.  256 -> pass_threads, calls with K = 512 of 1024 to 28672 columns: up to
+// 420 rows never longer and shorter from 3072 columns on (150 x 8192 12.6 -> 12.3 us, 300 x 14336 19.4 -> 19.0, 200 x 28672 25.1 -> 22.9); from 520
+// rows on longer by up to 3 % between 6144 and 10240 columns (520 x 6144 16.8 -> 17.2, 520 x 10240 22.5 -> 23.2, 777 x 6144 20.3 -> 20.7), within
+// noise up to 20480 and shorter beyond (1024 x 28672 73.8 -> 71.3, 2048 x 28672 154.8 -> 149.5).
+int32_t scatter_threads(int32_t N, int32_t M) { return M >= 512 && N <= 10240 ? 256 : (int32_t)pass_threads(N, M); }
 
 // Does the un-permute pass store its result past the caches?  A call alone is 0 to 2 us shorter for it at any size, but whatever
 // reads the result next then takes it from memory: it counts what the two take together.  That is shorter once the result and the
@@ -1379,7 +1385,7 @@ int launch_prefill(const GemmArgs& a, void* stream) {
     }
     if (int e = check_launch("sfmp_gemm split-K reduction launch")) return e;
   } else if (a.row_perm) {
-    const dim3 grid((unsigned)a.M), threads(L->N <= 8192 ? 256 : pass_threads(L->N, a.M));
+    const dim3 grid((unsigned)a.M), threads((unsigned)scatter_threads(L->N, a.M));
     if (past)
       hipLaunchKernelGGL(scatter_cols_kernel<true>, grid, threads, (size_t)L->N * 2, s, (const _Float16*)Yt, a.row_perm, (_Float16*)a.Y, (int)L->N);
     else

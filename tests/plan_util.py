@@ -108,3 +108,8 @@ def launched_tail(N, K, M):
 def stores_past_caches(N, M):
     """Does the un-permute pass of a matrix-core call store its result past the caches?"""
     return _call("_ZN4sfmp18stores_past_cachesEii", C.c_bool, N, M)
+
+
+def scatter_threads(N, M):
+    """Threads of a workgroup (one row) of that pass."""
+    return _call("_ZN4sfmp15scatter_threadsEii", C.c_int32, N, M)

@@ -260,9 +260,11 @@ def test_matrix_core_call_in_every_form(torch_cuda, K, N, M, group, scale_format
 
 
 @pytest.mark.parametrize("K,N,M,perms", [(8192, 8192, 140, True), (8320, 8320, 129, True), (8320, 256, 150, False), (128, 16512, 300, True),
-                                         (16512, 128, 140, True), (57344, 128, 129, True), (640, 81920, 130, True)])
+                                         (16512, 128, 140, True), (57344, 128, 129, True), (640, 81920, 130, True),
+                                         (128, 10240, 511, True), (128, 10240, 512, True), (128, 10368, 512, True), (128, 128, 300, True)])
 def test_permutation_passes_of_a_prompt(torch_cuda, K, N, M, perms):
-    # a row through LDS: one unit of 8 columns per thread and two to ten, the last of them not there for every thread
+    # a row through LDS: one unit of 8 columns per thread and two to ten, the last of them not there for every thread; either side of the
+    # lines at 512 rows and 10240 columns
     from gpu_util import run_gemm
     import plan_util
     p = W.make_problem("passes", K, N, M, 9400 + K + N, fractions={2: 0.3, 3: 0.3, 4: 0.4}, use_col_perm=perms, use_row_perm=perms, fast_codes=True)

@@ -500,3 +500,11 @@ def test_small_batches_that_stream_their_activations(N, K, M, group, streamed):
 def test_result_of_a_prompt_goes_past_the_caches_only_where_they_could_not_hold_it(N, M, past):
     import plan_util
     assert plan_util.stores_past_caches(N, M) == past
+
+
+@pytest.mark.parametrize("N,M,threads", [
+    (10240, 777, 256), (10240, 512, 256), (6144, 520, 256), (128, 2048, 256),  # longer with more threads
+    (10368, 512, 704), (10240, 511, 1024), (8192, 150, 1024), (4096, 300, 512), (128, 130, 64), (28672, 2048, 896), (81920, 130, 1024)])
+def test_threads_of_the_un_permute_pass(N, M, threads):
+    import plan_util
+    assert plan_util.scatter_threads(N, M) == threads
