@@ -1236,22 +1236,37 @@ static double rounds_time_us(int32_t N, int32_t K, int32_t M, const PrefillForm&
   return 10.1 + steps * (0.402 + 0.119 * f.mi + (double)(rounds - 1) * (0.541 + 0.137 * f.mi)) + 1.84 * mk + 1.29 * mn;
 }
 
+// Rounds that `pieces` workgroups behind `large` ones take when the large ones fill up to `whole` rounds.  Workgroup b runs on XCD b % 8,
+// whose 32 CUs share what falls to it and nothing else: a CU without a large workgroup in the last whole round takes `early` pieces
+// meanwhile, of its own XCD only.  (Counted over the chip, 256 pieces beside a few early ones on some of the XCDs passed for one round:
+// 1524 x 1792 -> 6784 64.9 us with a tail, 58.9 without; 1354 x 6016 -> 6912 156 and 145.)
+static int64_t tail_rounds(int64_t large, int64_t pieces, int64_t whole, int64_t early) {
+  int64_t rounds = 0;
+  for (int64_t xcd = 0; xcd < 8; ++xcd) {
+    const int64_t here = (large + 7 - xcd) / 8, left = (large + pieces + 7 - xcd) / 8 - here - early * (32 * whole - here);
+    if (left > 0 && (left + 31) / 32 > rounds) rounds = (left + 31) / 32;
+  }
+  return rounds;
+}
+
 // Whole rounds of 256-row workgroups and a tail of smaller ones (see PrefillMixed).  Up to four whole rounds and 2048 rows, where
 // its time was fitted (1000 calls of each tail, 3.3 and 4.0 % rms), and where that is below 0.945 of the form's own: of these calls
 // 13 % take it, which are 5.8 % faster in the geometric mean (up to 14 %), and 0.3 % are more than 2 % slower (with 0.97 for 0.945 20 %,
-// 4.1 % faster, and 1.5 % slower).  2048 x 4096 -> 14336, three and a half rounds, 255.3 -> 245.7 us (252.4 -> 248.1 on another
+// 4.1 % faster, and 1.5 % slower).  300 other calls that take it, in every format: 6.0 % faster with fp16 and 7.0 % with bf16 parameters, 6.7 and
+// 5.8 % at group length 64 (where the merged kernel spills more); 5 to 7 % of them, 0.8 % of all, more than 2 % slower, up to 9 %, nearly
+// all with a single whole round of a long K.  2048 x 4096 -> 14336, three and a half rounds, 255.3 -> 245.7 us (252.4 -> 248.1 on another
 // machine); 1970 x 13184 -> 4736 302 -> 265; 1442 x 6912 -> 12928 293 -> 270; 510 x 5504 -> 19840 134 -> 118.
 PrefillTail choose_prefill_tail(int32_t N, int32_t K, int32_t M) {
   PrefillTail best = {0, 0};
   const int64_t ntr = N / kTile, ntc = K / kTile, blocks = (M + 255) / 256, full = blocks * ntr / 256;
   if (M <= 256 || M > 2048 || full == 0 || full > 4 || blocks * ntr % 256 == 0 || ntc < 4) return best;
-  // the last tile rows, those that do not fit in the whole rounds; CUs without a workgroup in the last whole round take pieces then
-  const int64_t rows = ntr - 256 * full / blocks, idle = 256 * full - blocks * (ntr - rows), steps = (ntc + 1) / 2;
+  // the last tile rows, those that do not fit in the whole rounds
+  const int64_t rows = ntr - 256 * full / blocks, steps = (ntc + 1) / 2;
   const double mn = (double)M * N * 1e-6, mk = (double)M * K * 1e-6;
   double least = 0.945 * rounds_time_us(N, K, M, choose_prefill_form(N, K, M));
   for (int32_t mi = 4; mi <= 8; mi += 4) {
-    const int64_t early = idle * (mi == 4 ? 2 : 1), pieces = (M + 16 * mi - 1) / (16 * mi) * rows;
-    const double rounds = (double)(pieces > early ? (pieces - early + 255) / 256 : 0);
+    const int64_t pieces = (M + 16 * mi - 1) / (16 * mi) * rows;
+    const double rounds = (double)tail_rounds(blocks * (ntr - rows), pieces, full, mi == 4 ? 2 : 1);
     const double t = mi == 4 ? 10.55 + (double)ntc * (1.436 + 1.669 * (double)(full - 1)) + rounds * (1.125 * (double)steps + 1.82) + 1.51 * mk + 1.33 * mn
                              : 10.19 + (double)ntc * (1.249 + 1.655 * (double)(full - 1)) + rounds * (1.812 * (double)steps + 3.55) + 1.95 * mk + 1.33 * mn;
     if (t < least) least = t, best = PrefillTail{mi, (int32_t)rows};

@@ -508,3 +508,11 @@ def test_result_of_a_prompt_goes_past_the_caches_only_where_they_could_not_hold_
 def test_threads_of_the_un_permute_pass(N, M, threads):
     import plan_util
     assert plan_util.scatter_threads(N, M) == threads
+
+
+@pytest.mark.parametrize("N,K,M,tail", [
+    (6784, 1792, 1524, (0, 0)), (6912, 6016, 1354, (0, 0)),  # 33 pieces for an XCD whose 32 CUs all have a large workgroup: two rounds
+    (14336, 4096, 2048, (8, 16)), (13184, 640, 2047, (4, 7)), (5632, 9088, 1681, (4, 8))])
+def test_tail_of_a_prompt_counts_its_rounds_per_xcd(N, K, M, tail):
+    import plan_util
+    assert plan_util.launched_tail(N, K, M) == tail
