@@ -1116,6 +1116,7 @@ static void launch_fed(PrefillParams p, int M, bool g64, bool bf16, hipStream_t 
 template <int MI>
 static void launch_mixed(PrefillParams p, int M, int tail_rows, bool g64, bool bf16, hipStream_t stream) {
   PrefillMixed m;
+  p.ksplit = 1, p.partial = nullptr;  // (both sizes go over the whole K and leave no partial products)
   p.ntr -= tail_rows;
   p.n_mtiles = (M + 255) / 256;
   p.items = order_of(p.ntr, p.n_mtiles, 1);
@@ -1263,7 +1264,9 @@ PrefillTail choose_prefill_tail(int32_t N, int32_t K, int32_t M) {
   // the last tile rows, those that do not fit in the whole rounds
   const int64_t rows = ntr - 256 * full / blocks, steps = (ntc + 1) / 2;
   const double mn = (double)M * N * 1e-6, mk = (double)M * K * 1e-6;
-  double least = 0.945 * rounds_time_us(N, K, M, choose_prefill_form(N, K, M));
+  const PrefillForm one = choose_prefill_form(N, K, M);
+  if (one.ksplit != 1) return best;  // (never: K ranges are for 256 workgroups and fewer, of at most 128 rows)
+  double least = 0.945 * rounds_time_us(N, K, M, one);
   for (int32_t mi = 4; mi <= 8; mi += 4) {
     const int64_t pieces = (M + 16 * mi - 1) / (16 * mi) * rows;
     const double rounds = (double)tail_rounds(blocks * (ntr - rows), pieces, full, mi == 4 ? 2 : 1);

@@ -516,3 +516,18 @@ def test_threads_of_the_un_permute_pass(N, M, threads):
 def test_tail_of_a_prompt_counts_its_rounds_per_xcd(N, K, M, tail):
     import plan_util
     assert plan_util.launched_tail(N, K, M) == tail
+
+
+def test_prompts_with_a_tail_have_no_k_ranges():
+    # the workgroups of both sizes go over the whole K: partial products of the form in one size would never be summed
+    import plan_util
+    rng = np.random.default_rng(14)
+    tails = 0
+    for _ in range(6000):
+        K, N = (int(128 * np.ceil(2 ** rng.uniform(2, 7.8))) for _ in range(2))
+        M = int(rng.integers(257, 2049))
+        mi, tile_rows = plan_util.launched_tail(N, K, M)
+        if mi:
+            tails += 1
+            assert 0 < tile_rows < N // 128 and plan_util.launched_form(N, K, M)[2] == 1, (N, K, M)
+    assert tails > 100
