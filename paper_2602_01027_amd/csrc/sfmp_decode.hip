@@ -848,7 +848,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
   constexpr bool XT = RES && RA > 0, RESL = RES && !XT;
   static_assert(!(RESL && S != 2 && G64), "the resident form keeps one activation sum per tile column");
   static_assert(!RS || (RS == 2 && !RES && !RA && S == 3 && NW == 16), "streamed operands: three sets and slots");
-  static_assert(R == 4 || (R == 2 && (MB == 8 || RA)) || (R == 1 && (MB == 4 || (RA && !RES))), "rows of the operand");
+  static_assert(R == 4 || (R == 2 && (MB == 8 || RA)) || (R == 1 && (MB == 4 || (RA && !RES && NW == 8 && G64))), "rows of the operand");
   typedef RowSums<R> Rows;
   typedef typename Rows::type sums_t;
   static_assert((!RA || MB == 16) && (RA == 0 || RA == 2 || RA == 4), "activations in registers: 16 rows");
@@ -1629,10 +1629,13 @@ static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
 // 28672 8.1 / 7.8, 512 -> 14336 5.8 / 5.6; with one slab 4096 -> 4096 6.25 / 6.42, with two 4096 -> 8192 7.5 / 7.6).
 constexpr int kXtSpreadSlabs = 3;
 static bool spreads_gathered(int32_t M, int32_t max_slabs) { return M <= 8 && max_slabs >= kXtSpreadSlabs; }
-static int32_t rows_to_four(int32_t mb, bool resident, int32_t ra, int32_t M, int32_t max_slabs) {
+// With activations in registers, staged, one row to every four only with 8 wavefronts at group length 64 (more than 131072 features; two rows /
+// one: 2 x 128 -> 131200 28.2 / 26.4 us, 4 x 3456 -> 131200 97.8 / 92.3): no other call of up to four rows comes here but one whose output lies
+// over its activations.
+static int32_t rows_to_four(int32_t mb, int32_t nw, bool resident, int32_t ra, bool g64, int32_t M, int32_t max_slabs) {
   if (!ra) return mb / 4;
   if (resident) return spreads_gathered(M, max_slabs) ? 2 : 4;
-  return M <= 4 ? 1 : M <= 8 ? 2 : 4;
+  return M <= 4 && nw == 8 && g64 ? 1 : M <= 8 ? 2 : 4;
 }
 
 constexpr int kSlotsInPlace = 2;  // (and that number of slots tells the two resident forms apart)
@@ -1991,19 +1994,24 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   X(16, kSlotsStreamedActs, 8, false, 4, 0, 2, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2, 4)                 \
   X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 2) X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 4)                                                             \
   SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 2) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 2)                            \
+  X(8, kSlotsRegisterActs, 16, false, 16, 2, 0, 1) X(8, kSlotsRegisterActs, 16, false, 16, 4, 0, 1)                \
   SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 4) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 4)
 #define SFMP_RSKINNY_REGISTER_CONFIGS(X, NW, ACC, RA)                                                              \
-  X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 1) X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 2)          \
-  X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 4)
+  X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 2) X(NW, kSlotsRegisterActs, 16, false, ACC, RA, 0, 4)
+
+// which group lengths a configuration is compiled for: 64 (not the resident form with raw rows), and the others
+constexpr bool for_group_64(bool res, int32_t ra, int32_t slots) { return !res || ra || slots == kSlotsInPlace; }
+constexpr bool for_other_groups(int32_t ra, int32_t r) { return !ra || r != 1; }
 
 static int launch_rskinny(const GemmArgs& a, const DecodePlan& d, void* stream) {
-  const int32_t r = rows_to_four(d.mb, d.resident, d.ra, a.M, d.max_slabs);
+  const int32_t r = rows_to_four(d.mb, d.nw, d.resident, d.ra, a.L->group == 64, a.M, d.max_slabs);
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                             \
   if (r == R_ && d.nw == NW_ && d.mb == MB_ && d.resident == RES_ && d.acc == ACC_ && d.slots == S_ && d.ra == RA_ && d.rs == RS_) { \
-    if constexpr (!RES_ || RA_ || S_ == kSlotsInPlace) {                                                             \
+    if constexpr (for_group_64(RES_, RA_, S_)) {                                                   \
       if (a.L->group == 64) return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_, R_>(a, d, stream); \
-    }                                                                                         \
-    return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(a, d, stream);        \
+    }                                                                                              \
+    if constexpr (for_other_groups(RA_, R_))                                                       \
+      return launch_rskinny_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(a, d, stream);  \
   }
   SFMP_RSKINNY_CONFIGS(SFMP_X)
 #undef SFMP_X
@@ -2170,13 +2178,14 @@ int launch_decode_batched(const GemmArgs* probs, int count, int32_t M, void* wor
   if (int e = batch_config(probs, count, M, g, &c, &n64)) return e;
   int32_t max_slabs = 0;
   for (int i = 0; i < count; ++i) max_slabs = std::max(max_slabs, (8 * (probs[i].L->N / kTile) + g[i] - 1) / g[i]);
-  const int32_t r = rows_to_four(c.mb, c.resident, c.ra, M, max_slabs);
+  const int32_t r = rows_to_four(c.mb, c.nw, c.resident, c.ra, n64, M, max_slabs);
 #define SFMP_X(NW_, S_, MB_, RES_, ACC_, RA_, RS_, R_)                                           \
   if (r == R_ && c.nw == NW_ && c.mb == MB_ && c.resident == RES_ && c.acc == ACC_ && c.slots == S_ && c.ra == RA_ && c.rs == RS_) { \
-    if constexpr (!RES_ || RA_ || S_ == kSlotsInPlace) {                                                           \
+    if constexpr (for_group_64(RES_, RA_, S_)) {                                            \
       if (n64) return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, true, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \
     }                                                                                       \
-    return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \
+    if constexpr (for_other_groups(RA_, R_))                                                \
+      return launch_rskinny_batched_variant<NW_, S_, MB_, RES_, ACC_, false, RA_, RS_, R_>(probs, count, M, g, workspace, stream); \
   }
   SFMP_RSKINNY_CONFIGS(SFMP_X)
 #undef SFMP_X
