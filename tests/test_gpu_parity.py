@@ -651,16 +651,22 @@ def test_gemm_batched_shared_activations(torch_cuda, M):
         assert np.array_equal(run_gemm(p, dp, cp, rp).view(np.uint16), y.view(np.uint16))
 
 
-@pytest.mark.parametrize("M,group", [(2, 128), (5, 128), (16, 128), (3, 64), (16, 64)])
-def test_gemm_batched_five_slabs_per_workgroup_short_K(torch_cuda, M, group):
-    # two problems of 640 slabs on 128 workgroups each: five slabs per workgroup, with K = 2560 (20 tile columns:
-    # wavefronts 0-3 have two, the others one) and K = 1024 (8 tile columns: half of the wavefronts have none); the
-    # form of the small-batch kernel that keeps the activations in registers and every wavefront's sums in LDS
+@pytest.mark.parametrize("N,M,group,form,slabs", [
+    (10240, 2, 128, (4, 0, True, 3), [4, 8]), (10240, 5, 128, (8, 0, False, 2), [4, 8]), (10240, 16, 128, (16, 0, False, 1), [4, 8]),
+    (10240, 3, 64, (4, 0, True, 2), [4, 8]), (10240, 16, 64, (16, 0, False, 1), [4, 8]), (6400, 2, 128, (4, 0, True, 3), [3, 5]),
+    (6400, 5, 128, (16, 2, True, 2), [3, 5]), (6400, 16, 128, (16, 2, True, 2), [3, 5]), (6400, 3, 64, (4, 0, True, 2), [3, 5]),
+    (6400, 16, 64, (16, 2, True, 2), [3, 5])])
+def test_gemm_batched_several_slabs_per_workgroup_short_K(torch_cuda, N, M, group, form, slabs):
+    # two problems on shares of 256 workgroups by their bytes, up to eight and five slabs per workgroup, with K = 2560 (20 tile
+    # columns: wavefronts 0-3 have two, the others one) and K = 1024 (8 tile columns: half of the wavefronts have none): resident
+    # with raw rows, permuted in place, through the ring slots (eight slabs leave no room for gathered operands), gathered by the
+    # kernel with two rows to every four and with four
     import paper_2602_01027_amd as S
+    import plan_util
     from gpu_util import device_problem, run_gemm
     torch = torch_cuda
-    probs = [W.make_problem("a", 2560, 10240, M, 8400, fractions={2: 0.5, 3: 0.5}, outliers=True, group=group),
-             W.make_problem("b", 1024, 10240, M, 8401, fractions={2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, group=group)]
+    probs = [W.make_problem("a", 2560, N, M, 8400, fractions={2: 0.5, 3: 0.5}, outliers=True, group=group),
+             W.make_problem("b", 1024, N, M, 8401, fractions={2: 1 / 3, 3: 1 / 3, 4: 1 / 3}, group=group)]
     batch, keep = [], []
     for p in probs:
         dp, cp, rp = device_problem(p)
@@ -668,6 +674,8 @@ def test_gemm_batched_five_slabs_per_workgroup_short_K(torch_cuda, M, group):
         Y = torch.full((M, p.N), float("nan"), dtype=torch.float16, device="cuda:0")
         batch.append((X, cp, dp, rp, Y))
         keep.append((dp, cp, rp))
+    c, grids = plan_util.batched_config([dp.layout for dp, _, _ in keep], M)
+    assert (c.mb, c.ra, c.resident, c.slots) == form and [-(-N // 16 // g) for g in grids] == slabs
     ws = torch.empty(S.sfmp_gemm_batched_workspace(batch, M), dtype=torch.uint8, device="cuda:0").fill_(0xFF)
     S.sfmp_gemm_batched(batch, M, ws)
     torch.cuda.synchronize()
@@ -677,12 +685,15 @@ def test_gemm_batched_five_slabs_per_workgroup_short_K(torch_cuda, M, group):
         assert np.array_equal(run_gemm(p, dp, cp, rp).view(np.uint16), y.view(np.uint16))
 
 
-@pytest.mark.parametrize("K,N,M,group", [(5120, 1024, 6, 128), (8192, 2048, 16, 128), (8192, 1024, 9, 128), (6144, 1024, 3, 64),
+@pytest.mark.parametrize("K,N,M,group", [(5120, 1024, 6, 128), (8192, 2048, 16, 128), (8192, 1024, 9, 128), (6144, 1024, 5, 64),
                                          (8192, 1024, 16, 64), (8192, 1280, 16, 256)])
 def test_small_batch_three_and_four_tile_columns_per_wavefront(torch_cuda, K, N, M, group):
-    # 4096 < K <= 8192: the activations of a wavefront's three or four tile columns are held in registers (K = 5120:
-    # wavefronts 0-7 have three tile columns, the others two; K = 6144 at group length 64: no resident form at M = 3)
+    # 4096 < K <= 8192 and more than four rows: the activations of a wavefront's three or four tile columns are held in
+    # registers (K = 5120: wavefronts 0-7 have three tile columns, the others two)
+    import plan_util
     from gpu_util import run_gemm
+    d = plan_util.decode_plan(N, K, M, group)
+    assert (d.mb, d.ra, d.resident) == (16, 4, False)
     p = W.make_problem("ra4", K, N, M, 8600 + M + K // 128, fractions={2: 0.4, 3: 0.3, 4: 0.3}, outliers=True, group=group)
     _check(p, run_gemm(p))
 
@@ -747,24 +758,29 @@ def test_output_over_the_activations(torch_cuda, K, N, M, group, shift):
     _check(p, Y.cpu().numpy(), None if N <= 1024 else np.random.default_rng(M).choice(N, 384, replace=False))
 
 
-def test_batched_output_over_the_activations_of_another_problem(torch_cuda):
+@pytest.mark.parametrize("M,K,form", [(8, 2048, (16, 2)), (4, 6144, (16, 4))])
+def test_batched_output_over_the_activations_of_another_problem(torch_cuda, M, K, form):
     # q|k|v of one input, the last output over that input; and two chained buffers: the first output over the second's input
+    # (M = 4: instead of the form that permutes the activations in place)
     import paper_2602_01027_amd as S
+    import plan_util
     from gpu_util import device_problem
     torch = torch_cuda
-    M, K = 8, 2048
     probs = [W.make_problem("over.b", K, N, M, 9990, fractions={2: 0.3, 3: 0.4, 4: 0.3}) for N in (1024, 512, 2048)]
     packed = [device_problem(p) for p in probs]
     for over in ("the input they share", "the second one's input"):
         X = [torch.from_numpy(probs[0].X).to("cuda:0")] * 3
         Y = [torch.full((M, p.N), float("nan"), dtype=torch.float16, device="cuda:0") for p in probs]
         if over == "the input they share":
-            Y[2] = X[0].view(M, probs[2].N)
+            Y[2] = X[0].view(-1)[:M * probs[2].N].view(M, probs[2].N)
         else:
             X[1] = torch.from_numpy(probs[1].X).to("cuda:0")
             Y[0] = X[1].view(-1)[:M * probs[0].N].view(M, probs[0].N)
         inputs = [x.cpu().numpy() for x in X]
         batch = [(x, cp, dp, rp, y) for x, (dp, cp, rp), y in zip(X, packed, Y)]
+        layouts = [dp.layout for dp, _, _ in packed]
+        c = plan_util.batched_config(layouts, M, [x.data_ptr() for x in X], [y.data_ptr() for y in Y])[0]
+        assert (c.mb, c.ra, c.resident) == (*form, False) and plan_util.batched_config(layouts, M)[0].resident
         ws = torch.empty(S.sfmp_gemm_batched_workspace(batch, M), dtype=torch.uint8, device="cuda:0").fill_(0xFF)
         S.sfmp_gemm_batched(batch, M, ws)
         torch.cuda.synchronize()
@@ -848,13 +864,14 @@ def test_gemm_batched_streamed_activations_with_different_K(torch_cuda, M, group
     (512, 256, 2, 128, "fp16", False, (4, 0, 0)), (4096, 384, 3, 256, "bf16", False, (4, 0, 0)), (128, 131200, 4, 128, "fp16", False, (4, 0, 0)),
     (8320, 256, 1, 64, "bf16", True, (4, 0, 0)), (8320, 384, 3, 128, "fp16", True, (4, 0, 0)), (8320, 4224, 4, 64, "fp16", False, (4, 0, 0)),
     (512, 256, 3, 64, "fp16", True, (16, 2, 0)), (2176, 512, 4, 64, "bf16", True, (16, 2, 0)), (4096, 256, 7, 128, "fp16", True, (16, 2, 0)),
-    (128, 131200, 2, 64, "fp16", False, (16, 2, 0)), (128, 131200, 6, 128, "bf16", False, (16, 2, 0)),
+    (128, 131200, 2, 64, "fp16", False, (16, 2, 0)), (2176, 131200, 4, 64, "bf16", False, (16, 4, 0)), (128, 131200, 6, 128, "bf16", False, (16, 2, 0)),
     (8192, 256, 3, 128, "fp16", True, (16, 4, 0)), (4224, 512, 4, 64, "bf16", True, (16, 4, 0)), (8192, 384, 5, 128, "fp16", False, (16, 4, 0)),
     (4224, 256, 8, 64, "fp16", False, (16, 4, 0)), (9216, 256, 5, 128, "fp16", False, (8, 0, 0)), (9216, 512, 6, 64, "bf16", False, (8, 0, 0)),
     (12288, 4224, 7, 128, "fp16", False, (8, 0, 2))])
 def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, scale_format, over, form):
     # one activation row to every four of the matrix-instruction operand (M <= 4) or two (M <= 8), in every form that has them:
-    # resident, through the ring slots, in registers (staged: the output lies over the activations, or 8 wavefronts), streamed
+    # resident, through the ring slots, in registers (staged: the output lies over the activations, with two rows to every four for
+    # M <= 4 as well, or 8 wavefronts), streamed
     import paper_2602_01027_amd as S
     import plan_util
     from gpu_util import device_problem, make_workspace
@@ -876,7 +893,7 @@ def test_small_batch_rows_spread_over_the_operand(torch_cuda, K, N, M, group, sc
 @pytest.mark.parametrize("K,N,M,group,scale_format,perm", [
     (4224, 128, 4, 128, "fp16", True), (5504, 4352, 3, 128, "bf16", True), (5120, 16512, 4, 256, "fp16", True), (6144, 512, 4, 512, "bf16", False),
     (8064, 1024, 3, 128, "fp16", True), (8192, 8192, 4, 128, "fp16", True), (8192, 256, 2, 128, "bf16", False),
-    (128, 4096, 2, 64, "fp16", True), (4096, 4352, 4, 64, "bf16", True), (8192, 512, 3, 64, "fp16", True), (2048, 33024, 4, 64, "fp16", False)])
+    (128, 4096, 2, 64, "fp16", True), (4096, 4352, 4, 64, "bf16", True), (6144, 1024, 3, 64, "fp16", True), (8192, 512, 3, 64, "fp16", True), (2048, 33024, 4, 64, "fp16", False)])
 def test_small_batch_permuted_in_place(torch_cuda, K, N, M, group, scale_format, perm):
     # up to four rows of 4224 to 8192 columns, at group length 64 of any number up to that: second groups of four columns that 32, 256, 352, 512, 992 and all 1024 threads have, one to five slabs per
     # workgroup; every row of the operand, with rows past the last
@@ -894,9 +911,12 @@ def test_small_batch_permuted_in_place(torch_cuda, K, N, M, group, scale_format,
 @pytest.mark.parametrize("K,N,M", [(1024, 40960, 3), (1024, 40960, 8), (4224, 36864, 8), (4224, 36864, 16)])
 def test_small_batch_more_than_2048_slabs(torch_cuda, K, N, M):
     # more than 8 slabs per workgroup on 256 workgroups: the launch takes 512 workgroups (two per CU in turn, 5 slabs
-    # each) and keeps 16 wavefronts; K = 1024 with the activations resident in LDS (M = 3) or in registers, K = 4224
-    # (33 tile columns) with the activations travelling through the ring slots
+    # each) and keeps 16 wavefronts; K = 1024 with the activations resident in LDS (M = 3) or gathered by every workgroup,
+    # K = 4224 (33 tile columns) with up to three tile columns per wavefront staged and held in registers
+    import plan_util
     from gpu_util import run_gemm
+    d = plan_util.decode_plan(N, K, M)
+    assert (d.mb, d.ra, d.resident, d.nw) == ((4, 0, True, 16) if M == 3 else (16, 2, True, 16) if K == 1024 else (16, 4, False, 16))
     p = W.make_problem("wide", K, N, M, 8500 + M + K, fractions={2: 0.5, 3: 0.25, 4: 0.25})
     _check(p, run_gemm(p))
 
