@@ -1019,7 +1019,7 @@ __device__ __forceinline__ void rskinny_body(const RSkinnyParams& p, const int b
     // in the place where they stay: stored with the four rows of a column together, gathered by columns (8 bytes give all rows)
     // into registers, and, when every wavefront has done so, stored row by row.  (Their sums are taken per item: no slab count
     // for which they pay for a pass of their own.)  Bound by L2 -> CU (64 KiB of activations and 32 KiB of entries at K = 8192, about
-    // 1500 cycles) and four barriers; with K <= 4096 the raw copies straight into LDS are 0.1 to 0.6 us shorter.
+    // 1500 cycles) and three barriers; with K <= 4096 the raw copies straight into LDS are 0.1 to 0.6 us shorter.
     constexpr int Q = kInPlaceQuads;
     const int quads = p.K / 4;
     u32x2 x[Q][4];
@@ -1625,7 +1625,7 @@ static int32_t rskinny_mb(int32_t M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
 // Activation rows to every four of the operand: as few as the launch's rows (at most M) allow.  The operands that a workgroup
 // gathers itself take at least two: a transposing read takes four consecutive rows of a column from an address of 8 bytes, so
 // that spread rows are stored among as many that are not there, twice the stores of the start.  From three slabs per workgroup on the
-// shorter loop pays for them (four rows / spread, M = 8: 4096 -> 28672 14.2 / 13.7 us, 4096 -> 14336 at group length 64 11.65 / 11.27, 1024 ->
+// shorter loop pays for them (four rows / spread, M = 8: 4096 -> 28672 15.2 / 14.3 us, 4096 -> 14336 at group length 64 11.65 / 11.27, 1024 ->
 // 28672 8.1 / 7.8, 512 -> 14336 5.8 / 5.6; with one slab 4096 -> 4096 6.25 / 6.42, with two 4096 -> 8192 7.5 / 7.6).
 constexpr int kXtSpreadSlabs = 3;
 static bool spreads_gathered(int32_t M, int32_t max_slabs) { return M <= 8 && max_slabs >= kXtSpreadSlabs; }
@@ -1670,7 +1670,7 @@ constexpr int kSkinnyMaxRounds = 4;  // workgroups per CU, one after the other, 
 constexpr int kSlotsStreamedActs = 3;
 constexpr int kSlotsRegisterActs = 2;  // activations in registers: the slots hold a slab and its parameters only
 // max_slabs: the largest number of slabs of a workgroup over the problems of the launch; K: the largest K
-// g64: group length 64, for which the resident form does not exist
+// g64: group length 64, for which the resident form with raw rows does not exist
 // grid: workgroups of the launch; overwrites: outputs lie over activations, so the operands are not gathered in
 // the launch that stores the products
 static RSkinnyConfig rskinny_config(int32_t M, int32_t K, int32_t max_slabs, int32_t grid, bool g64, bool overwrites) {
@@ -1992,7 +1992,7 @@ static int launch_rskinny_variant(const GemmArgs& a, const DecodePlan& d, void* 
   X(16, kSlotsMb16Wide, 16, false, 4, 0, 0, 4) X(16, kSlotsMb16Wide, 16, false, 8, 0, 0, 4)                        \
   X(8, kSlotsMb16, 16, false, 16, 0, 0, 4)                                                                         \
   X(16, kSlotsStreamedActs, 8, false, 4, 0, 2, 2) X(16, kSlotsStreamedActs, 16, false, 4, 0, 2, 4)                 \
-  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 2) X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 4)                                                             \
+  X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 2) X(16, kSlotsRegisterActs, 16, true, 4, 2, 0, 4)                  \
   SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 2) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 2)                            \
   X(8, kSlotsRegisterActs, 16, false, 16, 2, 0, 1) X(8, kSlotsRegisterActs, 16, false, 16, 4, 0, 1)                \
   SFMP_RSKINNY_REGISTER_CONFIGS(X, 16, 4, 4) SFMP_RSKINNY_REGISTER_CONFIGS(X, 8, 16, 4)

@@ -666,8 +666,9 @@ __device__ __forceinline__ void load_lanes_to_lds_16(uint64_t vaddr, uint32_t ld
 // Whole calls back to back, the kernels before (whose wavefronts did all of this themselves) -> now: 777 x 4096 -> 4096 49.1 -> 37.7 us,
 // 200 x 14336 -> 4096 (group length 64) 47.7 -> 39.3, 64 x 4096 -> 14336 22.6 -> 20.6, 2048 x 4096 -> 14336 266.7 -> 248.6 (a tail of smaller
 // workgroups since, see PrefillMixed), 2048 x 28672 -> 8192 884.8 -> 818.0.
-// MI = 8 reaches the 168 registers of 12 wavefronts and spills 1 to 11 of them, most with two K groups and at group length 64
-// (there with reloads inside the tile loops; the choice of the form does not know of it).
+// MI = 8 reaches the 168 registers of 12 wavefronts.  prefill_fed_kernel<8, 1> spills 1 of them, 3 and 9 at group length 64 (fp16 and bf16
+// parameters; there with reloads inside the tile loops), <8, 2> 7 and 2, 9 and 11; prefill_mixed_kernel<8>, which is both, 10 and 3, 14 and 20,
+// <4> as many as <8, 1>.  The choice of the form does not know of it: calls with a tail gain as much at group length 64 (see choose_prefill_tail).
 // Not better: 32x32x16 instructions (the words of two slabs exchanged between rows of 16 lanes): 2770 cycles where 16x16x32
 // takes 2550, and 290 us instead of 253 on 2048 x 4096 -> 14336, where the clock falls further; the order of every phase fixed
 // by hand (spills at 168 registers).
