@@ -574,7 +574,7 @@ def main():
             torch.cuda.empty_cache()
         result["roofline_prefill"] = {
             "bound": "mfma",
-            "kernel": "sfmp::prefill_fed_kernel (fp16 MFMA, weights dequantised in registers) + activation staging and "
+            "kernel": "sfmp::prefill_fed_kernel, prefill_mixed_kernel on 4096->14336 (fp16 MFMA, weights dequantised in registers) + activation staging and "
                       "row un-permute passes",
             "achieved": round(tot_fl / tot_t / 1e6, 1),
             "peak": MFMA_F16_PEAK_TFLOPS,
